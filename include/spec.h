@@ -296,10 +296,9 @@ int spec_accept_rows_static(const float* p_logits_dev, int n_rows, const float* 
  * decode kernels); -1 (default) = dense when the shapes allow it and the prompt has more than 64 tokens.
  * Both fill the caches with the same K / V up to bf16 rounding of differently ordered sums.
  * SPEC_OPT_FUSE_SINGLE: 1 (default) = forwards over a single token (every draft step, autoregressive and pre-verify
- * target forwards) run seven kernels per layer: the QKV, gate/up and down projections form their input in their
- * prologue (residual add + norm input, SiLU * mul); 0 = the ten-kernel chain that forwards over several tokens use.
- * Same operations, sums in the same order up to the grouping of the sums of squares (results agree to fp32
- * rounding, not bit for bit).
+ * target forwards) add the O and down projections to the residual stream in those projections' epilogues; 0 = as K
+ * slices that a kernel of its own adds.  Same operations, other orders of the sums (results agree to fp32 rounding,
+ * not bit for bit).
  * SPEC_OPT_TARGET_TAIL_LAYERS: while the two models overlap with one projection workgroup per CU and stream (PEARL
  * loops from gamma 6 on, or SPEC_OPT_GEMM_WGS_PER_CU = 1), the last n layers of a target forward (rounded to whole
  * launch chunks of the forward) and its LM head launch with two: the chain that would end later gets the larger share

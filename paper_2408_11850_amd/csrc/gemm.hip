@@ -18,7 +18,6 @@
 #include "spec_internal.h"
 
 #define GEMM_WAVES 8
-static_assert(GEMM_WAVES == GEMM_WAVES_PER_GROUP, "consumers of the fused projections count 8 S sums of squares");
 #define GEMM_THREADS (GEMM_WAVES * 64)
 #ifndef GEMM_RP
 #define GEMM_RP 4   // panels per reduction round
@@ -95,74 +94,12 @@ __device__ __forceinline__ void mma_chunk(f32x4 (&acc)[MT], const u32x4 (&a)[8],
 // WPE = waves per SIMD the register budget is sized for.  The 16-row variant is held to 128 VGPRs (WPE 4) so
 // that two workgroups share a CU: 16 waves per CU hide the HBM latency far better than 8 (measured 6.9 vs
 // 5.9 TB/s on the gate/up matrix), and the second slot can also go to the other stream's kernel.
-// ---- prologues of the single-token projections (PRO != PRO_NONE, M = 1) ------------------------------------
-// A wave forms the activation values of its own K range (at most 256 columns): lane l the four columns
-// k0 + 4 l .. + 3, all loads of a lane independent of each other.  The bf16 results go through LDS into operand
-// order.  Every sum runs in the order the stand-alone kernels use (K slices ascending), so the values are the ones
-// the three-kernel chain would produce.
-__device__ __forceinline__ unsigned pack_bf16x2(float a, float b) {
-  const bf16 x = __float2bfloat16(a), y = __float2bfloat16(b);
-  return (unsigned)__builtin_bit_cast(unsigned short, x) | ((unsigned)__builtin_bit_cast(unsigned short, y) << 16);
-}
-
-// h_in + sum of the K slices (ascending), four independent loads in flight
-__device__ __forceinline__ f32x4 sum_slices(f32x4 t, const f32x4* __restrict__ P4, size_t sstride4, int S) {
-  int s = 0;
-  for (; s + 4 <= S; s += 4) {
-    const f32x4 p0 = P4[(size_t)(s + 0) * sstride4], p1 = P4[(size_t)(s + 1) * sstride4];
-    const f32x4 p2 = P4[(size_t)(s + 2) * sstride4], p3 = P4[(size_t)(s + 3) * sstride4];
-    t += p0; t += p1; t += p2; t += p3;
-  }
-  for (; s < S; ++s) t += P4[(size_t)s * sstride4];
-  return t;
-}
-
-template <int PRO>
-__device__ __forceinline__ void prologue_values(const GemmPro& pro, int K, int k, bool valid, bool first_group, int ws,
-                                                int lane, uint2* __restrict__ dst) {
-  f32x4 r = {0.f, 0.f, 0.f, 0.f};
-  if (PRO == PRO_ADDNORM) {
-    // residual add, sums of squares, x' = bf16(h * gain) (the consumers of this projection apply 1 / rms)
-    f32x4 t = {0.f, 0.f, 0.f, 0.f};
-    if (valid) {
-      t = *reinterpret_cast<const f32x4*>(pro.h_in + k);
-      if (pro.part) t = sum_slices(t, reinterpret_cast<const f32x4*>(pro.part) + (k >> 2), (size_t)(K >> 2), pro.S);
-      const bf16* g = pro.gain + k;
-      r = f32x4{t.x * __bfloat162float(g[0]), t.y * __bfloat162float(g[1]), t.z * __bfloat162float(g[2]),
-                t.w * __bfloat162float(g[3])};
-    }
-    if (first_group) {
-      if (valid) *reinterpret_cast<f32x4*>(pro.h_out + k) = t;
-      float ss = t.x * t.x + t.y * t.y + t.z * t.z + t.w * t.w;
-#pragma unroll
-      for (int o = 32; o > 0; o >>= 1) ss += __shfl_xor(ss, o);
-      if (lane == 0) pro.ssq_out[ws] = ss;
-    }
-  } else if (PRO == PRO_SWIGLU) {
-    if (valid) {
-      const int gc = (k >> 4) * 32 + (k & 15);          // gate panel of 16 columns, then the up panel
-      const f32x4 zero = {0.f, 0.f, 0.f, 0.f};
-      const f32x4* P4 = reinterpret_cast<const f32x4*>(pro.part + gc);
-      const f32x4 g = sum_slices(zero, P4, (size_t)(K >> 1), pro.S);
-      const f32x4 u = sum_slices(zero, P4 + 4, (size_t)(K >> 1), pro.S);
-      const float inv = pro.rs.inv(0);
-#pragma unroll
-      for (int i = 0; i < 4; ++i) {
-        const float gv = g[i] * inv, uv = u[i] * inv;
-        r[i] = gv / (1.0f + __expf(-gv)) * uv;
-      }
-    }
-  }
-  dst[0] = make_uint2(pack_bf16x2(r.x, r.y), pack_bf16x2(r.z, r.w));
-}
-
-template <int MT, int SPWMAX, int TAG, int WPE, int PRO>
+template <int MT, int SPWMAX, int TAG, int WPE>
 __global__ __launch_bounds__(GEMM_THREADS, WPE) void gemm_partial_kernel(const bf16* __restrict__ X,
                                                                     const u32x4* __restrict__ Wp,
                                                                     float* __restrict__ P, int M, int N, int K,
                                                                     int NT, int steps, int S, int spw, int Gs,
-                                                                    GemmPro pro) {
-  static_assert(PRO == PRO_NONE || MT == 1, "the fused prologues exist for single-token forwards only");
+                                                                    unsigned long long* stamp) {
   constexpr int NCH = SPWMAX / 8;            // chunks per panel
   constexpr int UNITS = GEMM_RP * NCH;       // chunks per reduction round (even)
   constexpr int NBUF = (MT == 1) ? 2 : 1;    // LDS reduction buffers: two let a round end with a single barrier
@@ -173,8 +110,8 @@ __global__ __launch_bounds__(GEMM_THREADS, WPE) void gemm_partial_kernel(const b
   const int p1 = (int)((long long)(idx + 1) * NT / Gs);
   const int w = threadIdx.x >> 6, lane = threadIdx.x & 63;
   const int c = lane & 15, kb = lane >> 4;
-  if (pro.stamp && threadIdx.x == 0)
-    atomicMax(pro.stamp + 2 * (blockIdx.x % STAMP_WAYS), ~(unsigned long long)wall_clock64());
+  if (stamp && threadIdx.x == 0)
+    atomicMax(stamp + 2 * (blockIdx.x % STAMP_WAYS), ~(unsigned long long)wall_clock64());
   // the K steps are dealt evenly to the S * 8 waves that share a panel: floor / ceil of steps / (8 S) each
   const int ws = s * GEMM_WAVES + w, nws = S * GEMM_WAVES;
   const int step0 = (int)((long long)ws * steps / nws);
@@ -185,8 +122,7 @@ __global__ __launch_bounds__(GEMM_THREADS, WPE) void gemm_partial_kernel(const b
   // Two-deep software pipeline over the chunk sequence (panel-major, NCH chunks per panel): chunks q and
   // q+1 are in flight; once chunk q is consumed its buffer is refilled with chunk q+2.  The sequence runs on
   // across reduction rounds, so the loads never drain at a round's barrier.  The first two chunks are requested
-  // before anything else: whatever the activations cost (a plain load, or a fused prologue with dependent loads
-  // of its own) then runs under the start of the weight stream.
+  // before anything else.
   u32x4 a[2][8];
 #pragma unroll
   for (int q = 0; q < 2; ++q)
@@ -194,33 +130,16 @@ __global__ __launch_bounds__(GEMM_THREADS, WPE) void gemm_partial_kernel(const b
 
   // activation fragments of this wave's K range, kept for the whole kernel
   bf16x8 b[MT][SPWMAX];
-  if (PRO == PRO_NONE) {
 #pragma unroll
-    for (int mt = 0; mt < MT; ++mt)
-#pragma unroll
-      for (int j = 0; j < SPWMAX; ++j) {
-        const int m = mt * 16 + c;
-        const int k = (step0 + j) * 32 + kb * 8;
-        u32x4 v = {0u, 0u, 0u, 0u};
-        if (j < nst && m < M && k < K) v = *reinterpret_cast<const u32x4*>(X + (size_t)m * K + k);
-        b[mt][j] = __builtin_bit_cast(bf16x8, v);
-      }
-  } else {
-    // the wave's (at most) 256 columns: formed four per lane, handed over in operand order through LDS (the
-    // reduction buffer is not in use yet)
-    unsigned short* stage = reinterpret_cast<unsigned short*>(&red[0][0][0][0][0]) + w * (SPWMAX * 32);
-    const int kk = step0 * 32 + 4 * lane;
-    const bool valid = 4 * lane < nst * 32 && kk < K;
-    prologue_values<PRO>(pro, K, kk, valid, idx == 0, ws, lane, reinterpret_cast<uint2*>(stage) + lane);
-    __syncthreads();
+  for (int mt = 0; mt < MT; ++mt)
 #pragma unroll
     for (int j = 0; j < SPWMAX; ++j) {
+      const int m = mt * 16 + c;
+      const int k = (step0 + j) * 32 + kb * 8;
       u32x4 v = {0u, 0u, 0u, 0u};
-      if (j < nst && c == 0) v = *reinterpret_cast<const u32x4*>(stage + j * 32 + kb * 8);
-      b[0][j] = __builtin_bit_cast(bf16x8, v);
+      if (j < nst && m < M && k < K) v = *reinterpret_cast<const u32x4*>(X + (size_t)m * K + k);
+      b[mt][j] = __builtin_bit_cast(bf16x8, v);
     }
-    __syncthreads();   // the staging area is the reduction buffer of the first round
-  }
 
   int rb = 0;
   for (int pr = p0; pr < p1; pr += GEMM_RP) {
@@ -260,51 +179,32 @@ __global__ __launch_bounds__(GEMM_THREADS, WPE) void gemm_partial_kernel(const b
     if (NBUF == 2) rb ^= 1;
     else __syncthreads();
   }
-  if (pro.stamp && threadIdx.x == 0)
-    atomicMax(pro.stamp + 2 * (blockIdx.x % STAMP_WAYS) + 1, (unsigned long long)wall_clock64());
+  if (stamp && threadIdx.x == 0)
+    atomicMax(stamp + 2 * (blockIdx.x % STAMP_WAYS) + 1, (unsigned long long)wall_clock64());
 }
 
-template <int TAG, int PRO>
+template <int TAG>
 static void launch_tagged(const GemmPlan& p, const bf16* x, const void* wp, float* partials, hipStream_t st,
-                          const GemmPro& pro) {
+                          unsigned long long* stamp) {
   dim3 grid(p.Gs * p.S), block(GEMM_THREADS);
   if (p.MT == 1)
-    gemm_partial_kernel<1, 8, TAG, 4, PRO><<<grid, block, 0, st>>>(x, (const u32x4*)wp, partials, p.M, p.N, p.K, p.NT,
-                                                                     p.steps, p.S, p.spw, p.Gs, pro);
-  else if (PRO == PRO_NONE)
-    gemm_partial_kernel<2, 8, TAG, 2, PRO_NONE><<<grid, block, 0, st>>>(x, (const u32x4*)wp, partials, p.M, p.N, p.K,
-                                                                          p.NT, p.steps, p.S, p.spw, p.Gs, pro);
+    gemm_partial_kernel<1, 8, TAG, 4><<<grid, block, 0, st>>>(x, (const u32x4*)wp, partials, p.M, p.N, p.K, p.NT,
+                                                                p.steps, p.S, p.spw, p.Gs, stamp);
+  else
+    gemm_partial_kernel<2, 8, TAG, 2><<<grid, block, 0, st>>>(x, (const u32x4*)wp, partials, p.M, p.N, p.K, p.NT,
+                                                                p.steps, p.S, p.spw, p.Gs, stamp);
 }
 
 hipError_t launch_gemm_partials(const GemmPlan& p, const bf16* x, const void* wp, float* partials, hipStream_t st,
                                 int tag, unsigned long long* stamp) {
-  GemmPro none;
-  memset(&none, 0, sizeof(none));
-  none.stamp = stamp;
-  if (tag == 0) launch_tagged<0, PRO_NONE>(p, x, wp, partials, st, none);
-  else if (tag == 1) launch_tagged<1, PRO_NONE>(p, x, wp, partials, st, none);
-  else launch_tagged<2, PRO_NONE>(p, x, wp, partials, st, none);
+  if (tag == 0) launch_tagged<0>(p, x, wp, partials, st, stamp);
+  else if (tag == 1) launch_tagged<1>(p, x, wp, partials, st, stamp);
+  else launch_tagged<2>(p, x, wp, partials, st, stamp);
   return hipGetLastError();
 }
 
-template <int TAG>
-static void launch_fused_tagged(const GemmPlan& p, const GemmPro& pro, const void* wp, float* partials, hipStream_t st) {
-  if (pro.kind == PRO_ADDNORM) launch_tagged<TAG, PRO_ADDNORM>(p, nullptr, wp, partials, st, pro);
-  else launch_tagged<TAG, PRO_SWIGLU>(p, nullptr, wp, partials, st, pro);
-}
-
-hipError_t launch_gemm_fused(const GemmPlan& p, const GemmPro& pro, const void* wp, float* partials, hipStream_t st,
-                             int tag) {
-  if (p.M != 1 || p.MT != 1 || pro.kind < PRO_ADDNORM || pro.kind > PRO_SWIGLU || (p.K & 3)) return hipErrorInvalidValue;
-  if (tag == 0) launch_fused_tagged<0>(p, pro, wp, partials, st);
-  else launch_fused_tagged<1>(p, pro, wp, partials, st);
-  return hipGetLastError();
-}
-
-// y[i] = sum_s partials[s][i], slices added in ascending order; with a row scale, row i / N of the sum is
-// multiplied by it (N % 4 == 0)
-__global__ void reduce_partials_kernel(float* __restrict__ y, const float* __restrict__ P, int S, size_t n4, RowScale rs,
-                                       int N4) {
+// y[i] = sum_s partials[s][i], slices added in ascending order
+__global__ void reduce_partials_kernel(float* __restrict__ y, const float* __restrict__ P, int S, size_t n4) {
   size_t i = (size_t)blockIdx.x * blockDim.x + threadIdx.x;
   if (i >= n4) return;
   const f32x4* p = reinterpret_cast<const f32x4*>(P);
@@ -312,7 +212,6 @@ __global__ void reduce_partials_kernel(float* __restrict__ y, const float* __res
   f32x4 v[4];
 #pragma unroll
   for (int k = 0; k < 4; ++k) v[k] = (k < S) ? p[(size_t)k * n4 + i] : f32x4{0.f, 0.f, 0.f, 0.f};
-  const float inv = rs.ssq ? rs.inv((int)(i / (size_t)N4)) : 1.0f;
   f32x4 t = v[0];
 #pragma unroll
   for (int k = 1; k < 4; ++k)
@@ -324,15 +223,12 @@ __global__ void reduce_partials_kernel(float* __restrict__ y, const float* __res
     for (int k = 0; k < 4; ++k)
       if (s0 + k < S) t += v[k];
   }
-  if (rs.ssq) t *= inv;
   reinterpret_cast<f32x4*>(y)[i] = t;
 }
 
-hipError_t launch_reduce_partials(float* y, const float* partials, int S, size_t n, hipStream_t st, RowScale rs, int N) {
+hipError_t launch_reduce_partials(float* y, const float* partials, int S, size_t n, hipStream_t st) {
   size_t n4 = n / 4;   // n = M*N with N % 16 == 0
-  if (rs.ssq && N < 4) return hipErrorInvalidValue;
-  reduce_partials_kernel<<<dim3((unsigned)((n4 + 255) / 256)), dim3(256), 0, st>>>(y, partials, S, n4, rs,
-                                                                                   rs.ssq ? N / 4 : 1);
+  reduce_partials_kernel<<<dim3((unsigned)((n4 + 255) / 256)), dim3(256), 0, st>>>(y, partials, S, n4);
   return hipGetLastError();
 }
 

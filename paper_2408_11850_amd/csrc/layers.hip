@@ -169,7 +169,7 @@ __global__ __launch_bounds__(ADDSQ_THREADS) void add_sumsq_kernel(float* __restr
 hipError_t launch_add_sumsq(float* h, const float* partials, int S, const bf16* gain, bf16* a, float* ssq, int M,
                             int d, int* W_out, hipStream_t st) {
   const int W = ((d >> 2) + ADDSQ_THREADS - 1) / ADDSQ_THREADS;
-  if ((d & 3) || W > ADDSQ_MAX_PIECES) return hipErrorInvalidValue;
+  if ((d & 3) || d > SPEC_D_MODEL_MAX) return hipErrorInvalidValue;
   add_sumsq_kernel<<<dim3(W, M), ADDSQ_THREADS, 0, st>>>(h, partials, S, gain, a, ssq, M, d, W);
   *W_out = W;
   return hipGetLastError();
@@ -194,55 +194,20 @@ hipError_t launch_rope_table(float2* tab, const int* len_ptr, int M, int dh, flo
   return hipGetLastError();
 }
 
-__global__ void rope_append_kernel(const float* __restrict__ P, int S, bf16* __restrict__ q, bf16* __restrict__ pool,
+__global__ void rope_append_kernel(const float* __restrict__ y, bf16* __restrict__ q, bf16* __restrict__ pool,
                                    const int* __restrict__ block_table, const int* __restrict__ len_ptr, KvGeom g,
-                                   int layer, int M, int Hq, float theta, const float2* __restrict__ tab, RowScale rs) {
+                                   int layer, int Hq, const float2* __restrict__ tab) {
   const int i = blockIdx.x, head = blockIdx.y * ROPE_HPB + (threadIdx.x >> 6);
   const int dh = g.head_dim, half = dh >> 1, Hkv = g.n_kv_heads;
   const int N = (Hq + 2 * Hkv) * dh;
   const int e = threadIdx.x & 63;
   if (e >= half || head >= Hq + 2 * Hkv) return;
   const int pos = len_ptr[0] + i;
-  // The kernel is one chain of latencies, so every load goes out before anything waits: the first four K slices,
-  // the row's sums of squares, the position; the fp64 angle is worked out while they are in flight.  Slices are
-  // added in ascending order whatever the grouping.
-  const float* base = P + (size_t)i * N + (size_t)head * dh;
-  const size_t sstride = (size_t)M * N;
-  float a0[4], a1[4];
-#pragma unroll
-  for (int k = 0; k < 4; ++k) {
-    a0[k] = (k < S) ? base[k * sstride + e] : 0.f;
-    a1[k] = (k < S) ? base[k * sstride + e + half] : 0.f;
-  }
-  const float inv = rs.inv(i);
-  float cs = 1.f, sn = 0.f;
+  const float* base = y + (size_t)i * N + (size_t)head * dh;
+  float x0 = base[e], x1 = base[e + half];
   if (head < Hq + Hkv) {   // rotation of pair (e, e + dh/2) by pos * theta^(-2e/dh)
-    if (tab) {
-      const float2 t = tab[(size_t)i * half + e];
-      cs = t.x; sn = t.y;
-    } else {
-      const double ang = (double)pos * pow((double)theta, -2.0 * (double)e / (double)dh);
-      cs = (float)cos(ang); sn = (float)sin(ang);
-    }
-  }
-  float x0 = 0.f, x1 = 0.f;
-#pragma unroll
-  for (int k = 0; k < 4; ++k)
-    if (k < S) { x0 += a0[k]; x1 += a1[k]; }
-  for (int s0 = 4; s0 < S; s0 += 4) {
-#pragma unroll
-    for (int k = 0; k < 4; ++k) {
-      a0[k] = (s0 + k < S) ? base[(s0 + k) * sstride + e] : 0.f;
-      a1[k] = (s0 + k < S) ? base[(s0 + k) * sstride + e + half] : 0.f;
-    }
-#pragma unroll
-    for (int k = 0; k < 4; ++k)
-      if (s0 + k < S) { x0 += a0[k]; x1 += a1[k]; }
-  }
-  x0 *= inv;
-  x1 *= inv;
-  if (head < Hq + Hkv) {
-    const float y0 = x0 * cs - x1 * sn, y1 = x0 * sn + x1 * cs;
+    const float2 t = tab[(size_t)i * half + e];
+    const float y0 = x0 * t.x - x1 * t.y, y1 = x0 * t.y + x1 * t.x;
     x0 = y0; x1 = y1;
   }
   if (head < Hq) {
@@ -269,53 +234,9 @@ __global__ void rope_append_kernel(const float* __restrict__ P, int S, bf16* __r
     blk[((size_t)chunk * dh + e + half) * 32 + slot] = __float2bfloat16(x1);
   }
 }
-hipError_t launch_rope_append(const float* partials, int S, bf16* q, bf16* pool, const int* block_table,
-                              const int* len_ptr, KvGeom g, int layer, int M, int Hq, float theta, hipStream_t st,
-                              const float2* tab, RowScale rs) {
+hipError_t launch_rope_append(const float* y, bf16* q, bf16* pool, const int* block_table, const int* len_ptr, KvGeom g,
+                              int layer, int M, int Hq, hipStream_t st, const float2* tab) {
   dim3 grid(M, (Hq + 2 * g.n_kv_heads + ROPE_HPB - 1) / ROPE_HPB), block(64 * ROPE_HPB);
-  rope_append_kernel<<<grid, block, 0, st>>>(partials, S, q, pool, block_table, len_ptr, g, layer, M, Hq, theta, tab,
-                                             rs);
-  return hipGetLastError();
-}
-
-// z[m][f] = silu(gate) * up, gate/up panels interleaved in the fused projection output (width 2F)
-__global__ void silu_mul_kernel(const float* __restrict__ P, int S, bf16* __restrict__ z, int M, int F, RowScale rs) {
-  const int m = blockIdx.y;
-  const int f = blockIdx.x * blockDim.x + threadIdx.x;
-  if (f >= F) return;
-  const int gc = (f >> 4) * 32 + (f & 15);
-  // all loads of the first four K slices and of the row's sums of squares go out together (one round trip);
-  // slices are added in ascending order whatever the grouping
-  const float* base = P + (size_t)m * (2 * (size_t)F) + gc;
-  const size_t sstride = (size_t)M * (2 * (size_t)F);
-  float g4[4], u4[4];
-#pragma unroll
-  for (int k = 0; k < 4; ++k) {
-    g4[k] = (k < S) ? base[k * sstride] : 0.f;
-    u4[k] = (k < S) ? base[k * sstride + 16] : 0.f;
-  }
-  const float inv = rs.inv(m);
-  float gv = 0.f, uv = 0.f;
-#pragma unroll
-  for (int k = 0; k < 4; ++k)
-    if (k < S) { gv += g4[k]; uv += u4[k]; }
-  for (int s0 = 4; s0 < S; s0 += 4) {
-#pragma unroll
-    for (int k = 0; k < 4; ++k) {
-      g4[k] = (s0 + k < S) ? base[(s0 + k) * sstride] : 0.f;
-      u4[k] = (s0 + k < S) ? base[(s0 + k) * sstride + 16] : 0.f;
-    }
-#pragma unroll
-    for (int k = 0; k < 4; ++k)
-      if (s0 + k < S) { gv += g4[k]; uv += u4[k]; }
-  }
-  gv *= inv;
-  uv *= inv;
-  const float sg = gv / (1.0f + __expf(-gv));
-  z[(size_t)m * F + f] = __float2bfloat16(sg * uv);
-}
-hipError_t launch_silu_mul(const float* partials, int S, bf16* z, int M, int F, hipStream_t st, RowScale rs) {
-  dim3 grid((F + 255) / 256, M), block(256);
-  silu_mul_kernel<<<grid, block, 0, st>>>(partials, S, z, M, F, rs);
+  rope_append_kernel<<<grid, block, 0, st>>>(y, q, pool, block_table, len_ptr, g, layer, Hq, tab);
   return hipGetLastError();
 }

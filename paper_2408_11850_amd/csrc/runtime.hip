@@ -53,9 +53,8 @@ struct ModelRt {
   int* len_dev = nullptr;
   int* tok_in = nullptr;
   float* h = nullptr;
-  float* h2 = nullptr;            // second residual buffer of the single-token path (its projections read one, write the other)
-  float* partials2 = nullptr;     // and second buffer of K-slice sums
-  float2* rope_tab = nullptr;     // (cos, sin) of the new position of a single-token forward
+  float* qkv = nullptr;           // fused QKV projection of a forward
+  float2* rope_tab = nullptr;     // (cos, sin) of the new positions of a forward
   float* ssq = nullptr;           // sums of squares of the rows of h, SSQ_STRIDE floats per row
   bf16 *a = nullptr, *qbuf = nullptr, *attn_out = nullptr, *z = nullptr;
   float *partials = nullptr, *opart = nullptr, *mlpart = nullptr, *logits = nullptr;
@@ -111,7 +110,7 @@ struct spec_ctx {
   int tail_layers = 0;            // what the next target forward uses
   hipEvent_t ev_t0[2] = {}, ev_tend[2] = {}, ev_dend[2] = {};   // start of a PEARL step, ends of its target / draft chain (timed), two sets in turn
   bool bal_valid[2] = {false, false};   // set holds a step's three events
-  bool fuse_single = true;        // single-token forwards through the projections with fused prologues
+  bool fuse_single = true;        // single-token forwards: residual add in the O and down projections' epilogues
   int prefill_opt = -1;           // -1 automatic, 0 = 32-token verify forwards, 1 = dense path
   int fail_prefill_after = 0;     // test hook: > 0 = the next spec_prefill gives up after that many forwards
   ProfStamps prof;
@@ -127,7 +126,7 @@ int check_desc(const spec_model_desc& d, const char* name) {
   if (d.head_dim != 64 && d.head_dim != 128) FAIL(SPEC_E_INVAL, "%s: head_dim must be 64 or 128", name);
   if (d.n_heads % d.n_kv_heads) FAIL(SPEC_E_INVAL, "%s: n_heads must be a multiple of n_kv_heads", name);
   if (d.d_model % 16 || d.d_ffn % 16 || d.vocab % 16) FAIL(SPEC_E_INVAL, "%s: d_model, d_ffn, vocab must be multiples of 16", name);
-  if (d.d_model > 1024 * ADDSQ_MAX_PIECES) FAIL(SPEC_E_INVAL, "%s: d_model above %d", name, 1024 * ADDSQ_MAX_PIECES);
+  if (d.d_model > SPEC_D_MODEL_MAX) FAIL(SPEC_E_INVAL, "%s: d_model above %d", name, SPEC_D_MODEL_MAX);
   if (!(d.rope_theta > 1.0f) || !(d.rms_eps >= 0.0f)) FAIL(SPEC_E_INVAL, "%s: bad rope_theta / rms_eps", name);
   return SPEC_OK;
 }
@@ -183,16 +182,14 @@ int init_model(ModelRt& m, const spec_model_desc& d, const spec_weights& w, cons
   if ((rc = dev_alloc(&m.attn_out, (size_t)MX * d.n_heads * d.head_dim))) return rc;
   if ((rc = dev_alloc(&m.z, (size_t)MX * d.d_ffn))) return rc;
   size_t pb = 0;
-  const int shapes[5][2] = {{qkvN, d.d_model}, {d.d_model, d.n_heads * d.head_dim}, {2 * d.d_ffn, d.d_model},
-                            {d.d_model, d.d_ffn}, {d.vocab, d.d_model}};
+  const int shapes[2][2] = {{d.d_model, d.n_heads * d.head_dim}, {d.d_model, d.d_ffn}};   // run_resid by K slices
   for (int mm : {1, 16, MX})
     for (auto& s : shapes) {
       size_t b = gemm_plan(mm, s[0], s[1]).partial_bytes();
       if (b > pb) pb = b;
     }
   if ((rc = dev_alloc(&m.partials, pb / sizeof(float)))) return rc;
-  if ((rc = dev_alloc(&m.partials2, pb / sizeof(float)))) return rc;
-  if ((rc = dev_alloc(&m.h2, (size_t)MX * d.d_model))) return rc;
+  if ((rc = dev_alloc(&m.qkv, (size_t)MX * qkvN))) return rc;
   if ((rc = dev_alloc(&m.rope_tab, (size_t)MX * (d.head_dim / 2)))) return rc;
   const size_t aw = attention_workspace_floats(d.n_heads, d.n_kv_heads, d.head_dim, m.n_pages * SPEC_PAGE_TOKENS);
   if ((rc = dev_alloc(&m.opart, aw))) return rc;
@@ -210,7 +207,7 @@ void free_model(ModelRt& m) {
             (void)hipGraphExecDestroy(g);
             g = nullptr;
           }
-  void* ptrs[] = {m.h2, m.partials2, m.rope_tab,
+  void* ptrs[] = {m.qkv, m.rope_tab,
                   m.pool, m.block_table_dev, m.len_dev, m.tok_in, m.h, m.ssq, m.a, m.qbuf, m.attn_out, m.z, m.partials,
                   m.opart, m.logits, m.pf_tok, m.pf_h, m.pf_a, m.pf_q, m.pf_attn, m.pf_z, m.pf_rope};
   for (void* p : ptrs)
@@ -265,145 +262,87 @@ int prof_slot(spec_ctx* c, double bytes, unsigned long long** slot) {
   return SPEC_OK;
 }
 
-int run_gemm(spec_ctx* c, int which, ModelRt& m, int M, int N, int K, const bf16* x, const void* w, GemmPlan* plan_out) {
-  GemmPlan p = gemm_plan(M, N, K, c->wgs);
-  const bool prof = (c->profile_flags & 1) && which == SPEC_TARGET;
-  unsigned long long* slot = nullptr;
+// a whole-K projection of model `which`
+int run_proj(spec_ctx* c, int which, ModelRt& m, const ProjPlan& p, int epi, ProjArgs a) {
   int rc;
-  if (prof && (rc = prof_slot(c, (double)p.weight_bytes(), &slot))) return rc;
-  HIPCHK(launch_gemm_partials(p, x, w, m.partials, m.stream, which, slot));
-  *plan_out = p;
+  if ((c->profile_flags & 1) && which == SPEC_TARGET && (rc = prof_slot(c, (double)p.weight_bytes(), &a.stamp))) return rc;
+  HIPCHK(launch_proj(p, epi, a, m.stream, which));
   return SPEC_OK;
+}
+
+// h += x W^T, x' = bf16(h * gain) for the next projection and the sums of squares of h, *W_out pieces per row: one
+// whole-K launch, or K slices and the kernel that adds them.
+int run_resid(spec_ctx* c, int which, ModelRt& m, int M, int K, const bf16* x, const void* w, const void* gain, int* W_out) {
+  const int N = m.d.d_model;
+  int rc;
+  if (proj_whole_k(M, N, K) && (M > 1 || c->fuse_single)) {
+    const ProjPlan p = proj_plan(M, N, K, PROJ_RESID, c->wgs);
+    ProjArgs a = {};
+    a.x = x; a.w = w; a.h = m.h; a.gain = (const bf16*)gain; a.xo = m.a; a.ssq_out = m.ssq;
+    *W_out = p.pieces();
+    return run_proj(c, which, m, p, PROJ_RESID, a);
+  }
+  const GemmPlan p = gemm_plan(M, N, K, c->wgs);
+  unsigned long long* slot = nullptr;
+  if ((c->profile_flags & 1) && which == SPEC_TARGET && (rc = prof_slot(c, (double)p.weight_bytes(), &slot))) return rc;
+  HIPCHK(launch_gemm_partials(p, x, w, m.partials, m.stream, which, slot));
+  HIPCHK(launch_add_sumsq(m.h, m.partials, p.S, (const bf16*)gain, m.a, m.ssq, M, N, W_out, m.stream));
+  return SPEC_OK;
+}
+
+// pieces per row of the sums of squares that run_resid leaves for a projection over K columns
+int resid_pieces(const spec_ctx* c, const ModelRt& m, int M, int K) {
+  const int N = m.d.d_model;
+  if (proj_whole_k(M, N, K) && (M > 1 || c->fuse_single)) return proj_plan(M, N, K, PROJ_RESID, c->wgs).pieces();
+  return (N + 1023) / 1024;
 }
 
 // The kernel chain of one forward over the M tokens in m.tok_in.  Nothing here depends on host state other
 // than M, logit_rows and the launch mode: positions come from *len_dev, pages from the device block table,
 // so the chain can be captured once into a HIP graph and replayed.
 // Layers [l0, l1) of the chain: the embedding goes with layer 0, the LM head and the length update with the last layer.
+// State between layers: the residual stream in h, x' = bf16(h * gain) of the next norm in a, its sums of squares in ssq.
 int enqueue_forward(spec_ctx* c, int which, int M, int logit_rows, int l0, int l1) {
   ModelRt& m = c->m[which];
   const spec_model_desc& d = m.d;
   hipStream_t st = m.stream;
   int rc;
-  if (l0 == 0) HIPCHK(launch_embed(m.h, (const bf16*)m.tok_embed, m.tok_in, M, d.d_model, d.vocab, st));
   const int qkvN = (d.n_heads + 2 * d.n_kv_heads) * d.head_dim;
   const int HD = d.n_heads * d.head_dim;
-  GemmPlan p;
-  // a chain that starts behind layer 0 first adds the K slices the previous layer's down projection left
-  const float* prev = l0 > 0 ? m.partials : nullptr;
-  int prevS = l0 > 0 ? gemm_plan(M, d.d_model, d.d_ffn, c->wgs).S : 0;
-  // Every RMSNorm is split in three: a residual add spread over several workgroups per row, which leaves the
-  // rows' sums of squares and x' = bf16(h * gain); the projection of x'; and the factor 1/rms, applied to the
-  // projection's output rows by the kernel that adds its K slices.
-  RowScale rs{m.ssq, 0, d.d_model, d.rms_eps};
+  int W = l0 > 0 ? resid_pieces(c, m, M, d.d_ffn) : 0;
+  if (l0 == 0) {
+    HIPCHK(launch_embed(m.h, (const bf16*)m.tok_embed, m.tok_in, M, d.d_model, d.vocab, st));
+    HIPCHK(launch_rope_table(m.rope_tab, m.len_dev, M, d.head_dim, d.rope_theta, st));
+    HIPCHK(launch_add_sumsq(m.h, nullptr, 0, (const bf16*)m.attn_norm[0], m.a, m.ssq, M, d.d_model, &W, st));
+  }
+  ProjArgs normed = {};      // a projection of the normalised residual stream
+  normed.x = m.a;
+  normed.ssq = m.ssq;
+  normed.eps = d.rms_eps;
   for (int l = l0; l < l1; ++l) {
-    HIPCHK(launch_add_sumsq(m.h, prev, prevS, (const bf16*)m.attn_norm[l], m.a, m.ssq, M, d.d_model, &rs.W, st));
-    if ((rc = run_gemm(c, which, m, M, qkvN, d.d_model, m.a, m.wqkv[l], &p))) return rc;
-    HIPCHK(launch_rope_append(m.partials, p.S, m.qbuf, m.pool, m.block_table_dev, m.len_dev, m.geom, l, M, d.n_heads,
-                              d.rope_theta, st, nullptr, rs));
+    ProjArgs pa = normed;
+    pa.w = m.wqkv[l]; pa.y = m.qkv; pa.ssq_w = W;
+    if ((rc = run_proj(c, which, m, proj_plan(M, qkvN, d.d_model, PROJ_STORE, c->wgs), PROJ_STORE, pa))) return rc;
+    HIPCHK(launch_rope_append(m.qkv, m.qbuf, m.pool, m.block_table_dev, m.len_dev, m.geom, l, M, d.n_heads, st, m.rope_tab));
     HIPCHK(launch_attention(m.qbuf, m.pool, m.block_table_dev, m.len_dev, m.geom, l, M, d.n_heads, m.split_tokens,
                             m.opart, m.mlpart, m.attn_out, st));
-    if ((rc = run_gemm(c, which, m, M, d.d_model, HD, m.attn_out, m.wo[l], &p))) return rc;
-    HIPCHK(launch_add_sumsq(m.h, m.partials, p.S, (const bf16*)m.ffn_norm[l], m.a, m.ssq, M, d.d_model, &rs.W, st));
-    if ((rc = run_gemm(c, which, m, M, 2 * d.d_ffn, d.d_model, m.a, m.wgu[l], &p))) return rc;
-    HIPCHK(launch_silu_mul(m.partials, p.S, m.z, M, d.d_ffn, st, rs));
-    if ((rc = run_gemm(c, which, m, M, d.d_model, d.d_ffn, m.z, m.wdown[l], &p))) return rc;
-    prev = m.partials;
-    prevS = p.S;
+    if ((rc = run_resid(c, which, m, M, HD, m.attn_out, m.wo[l], m.ffn_norm[l], &W))) return rc;
+    pa = normed;
+    pa.w = m.wgu[l]; pa.xo = m.z; pa.ssq_w = W;
+    if ((rc = run_proj(c, which, m, proj_plan(M, 2 * d.d_ffn, d.d_model, PROJ_SWIGLU, c->wgs), PROJ_SWIGLU, pa))) return rc;
+    const void* next = l + 1 < d.n_layers ? m.attn_norm[l + 1] : m.final_norm;
+    if ((rc = run_resid(c, which, m, M, d.d_ffn, m.z, m.wdown[l], next, &W))) return rc;
   }
   if (l1 < d.n_layers) return SPEC_OK;
   if (logit_rows > 0) {
-    HIPCHK(launch_add_sumsq(m.h, prev, prevS, (const bf16*)m.final_norm, m.a, m.ssq, M, d.d_model, &rs.W, st));
     const int rows = logit_rows >= M ? M : 1;
-    const bf16* x = m.a + (size_t)(M - rows) * d.d_model;
-    if ((rc = run_gemm(c, which, m, rows, d.vocab, d.d_model, x, m.lm_head, &p))) return rc;
-    RowScale rl = rs;
-    rl.ssq = m.ssq + (size_t)(M - rows) * SSQ_STRIDE;
-    HIPCHK(launch_reduce_partials(m.logits, m.partials, p.S, (size_t)rows * d.vocab, st, rl, d.vocab));
+    ProjArgs pa = normed;
+    pa.x = m.a + (size_t)(M - rows) * d.d_model;
+    pa.ssq = m.ssq + (size_t)(M - rows) * SSQ_STRIDE;
+    pa.w = m.lm_head; pa.y = m.logits; pa.ssq_w = W;
+    if ((rc = run_proj(c, which, m, proj_plan(rows, d.vocab, d.d_model, PROJ_STORE, c->wgs), PROJ_STORE, pa))) return rc;
   }
   HIPCHK(launch_add_int(m.len_dev, M, st));
-  return SPEC_OK;
-}
-
-// a plain projection into a given buffer of K-slice sums
-int run_gemm_into(spec_ctx* c, int which, ModelRt& m, const GemmPlan& p, const bf16* x, const void* w, float* out) {
-  const bool prof = (c->profile_flags & 1) && which == SPEC_TARGET;
-  unsigned long long* slot = nullptr;
-  int rc;
-  if (prof && (rc = prof_slot(c, (double)p.weight_bytes(), &slot))) return rc;
-  HIPCHK(launch_gemm_partials(p, x, w, out, m.stream, which, slot));
-  return SPEC_OK;
-}
-
-int run_gemm_fused(spec_ctx* c, int which, ModelRt& m, const GemmPlan& p, GemmPro pro, const void* w, float* out) {
-  const bool prof = (c->profile_flags & 1) && which == SPEC_TARGET;
-  int rc;
-  if (prof && (rc = prof_slot(c, (double)p.weight_bytes(), &pro.stamp))) return rc;
-  HIPCHK(launch_gemm_fused(p, pro, w, out, m.stream, which));
-  return SPEC_OK;
-}
-
-bool single_token_path(const spec_ctx* c, const ModelRt& m, int M) {
-  return c->fuse_single && M == 1;
-}
-
-// The same layers for a single token (every draft step, autoregressive and pre-verify target forwards) in seven
-// kernels per layer instead of ten: the QKV, gate/up and down projections (and the LM head) form their own input in
-// their prologue (residual add + gain + sums of squares; SiLU(gate) * up).  Those projections read the residual
-// stream and the K-slice sums from one buffer and write the other.  Entry state of a layer: residual in h,
-// pending K-slice sums of the previous down projection in partials2.  Measured on the 70B/7B shapes: draft forward
-// 3.46 -> 3.26 ms, single-token target forward 23.30 -> 22.97 ms.
-int enqueue_forward_single(spec_ctx* c, int which, int logit_rows, int l0, int l1) {
-  ModelRt& m = c->m[which];
-  const spec_model_desc& d = m.d;
-  hipStream_t st = m.stream;
-  int rc;
-  if (l0 == 0) {
-    HIPCHK(launch_embed(m.h, (const bf16*)m.tok_embed, m.tok_in, 1, d.d_model, d.vocab, st));
-    HIPCHK(launch_rope_table(m.rope_tab, m.len_dev, 1, d.head_dim, d.rope_theta, st));
-  }
-  const int qkvN = (d.n_heads + 2 * d.n_kv_heads) * d.head_dim;
-  const int HD = d.n_heads * d.head_dim;
-  const float* prev = l0 > 0 ? m.partials2 : nullptr;
-  int prevS = l0 > 0 ? gemm_plan(1, d.d_model, d.d_ffn, c->wgs).S : 0;
-  GemmPro pro;
-  for (int l = l0; l < l1; ++l) {
-    const GemmPlan pq = gemm_plan(1, qkvN, d.d_model, c->wgs);
-    memset(&pro, 0, sizeof(pro));
-    pro.kind = PRO_ADDNORM; pro.h_in = m.h; pro.h_out = m.h2; pro.gain = (const bf16*)m.attn_norm[l]; pro.ssq_out = m.ssq;
-    pro.part = prev; pro.S = prevS;
-    if ((rc = run_gemm_fused(c, which, m, pq, pro, m.wqkv[l], m.partials))) return rc;
-    RowScale rs{m.ssq, GEMM_WAVES_PER_GROUP * pq.S, d.d_model, d.rms_eps};
-    const GemmPlan po = gemm_plan(1, d.d_model, HD, c->wgs);
-    HIPCHK(launch_rope_append(m.partials, pq.S, m.qbuf, m.pool, m.block_table_dev, m.len_dev, m.geom, l, 1, d.n_heads,
-                              d.rope_theta, st, m.rope_tab, rs));
-    HIPCHK(launch_attention(m.qbuf, m.pool, m.block_table_dev, m.len_dev, m.geom, l, 1, d.n_heads, m.split_tokens,
-                            m.opart, m.mlpart, m.attn_out, st));
-    if ((rc = run_gemm_into(c, which, m, po, m.attn_out, m.wo[l], m.partials2))) return rc;
-    const GemmPlan pg = gemm_plan(1, 2 * d.d_ffn, d.d_model, c->wgs);
-    memset(&pro, 0, sizeof(pro));
-    pro.kind = PRO_ADDNORM; pro.h_in = m.h2; pro.h_out = m.h; pro.gain = (const bf16*)m.ffn_norm[l]; pro.ssq_out = m.ssq;
-    pro.part = m.partials2; pro.S = po.S;
-    if ((rc = run_gemm_fused(c, which, m, pg, pro, m.wgu[l], m.partials))) return rc;
-    const GemmPlan pd = gemm_plan(1, d.d_model, d.d_ffn, c->wgs);
-    memset(&pro, 0, sizeof(pro));
-    pro.kind = PRO_SWIGLU; pro.part = m.partials; pro.S = pg.S;
-    pro.rs = RowScale{m.ssq, GEMM_WAVES_PER_GROUP * pg.S, d.d_model, d.rms_eps};
-    if ((rc = run_gemm_fused(c, which, m, pd, pro, m.wdown[l], m.partials2))) return rc;
-    prev = m.partials2;
-    prevS = pd.S;
-  }
-  if (l1 < d.n_layers) return SPEC_OK;
-  if (logit_rows > 0) {
-    const GemmPlan pl = gemm_plan(1, d.vocab, d.d_model, c->wgs);
-    memset(&pro, 0, sizeof(pro));
-    pro.kind = PRO_ADDNORM; pro.h_in = m.h; pro.h_out = m.h2; pro.gain = (const bf16*)m.final_norm; pro.ssq_out = m.ssq;
-    pro.part = prev; pro.S = prevS;
-    if ((rc = run_gemm_fused(c, which, m, pl, pro, m.lm_head, m.partials))) return rc;
-    RowScale rl{m.ssq, GEMM_WAVES_PER_GROUP * pl.S, d.d_model, d.rms_eps};
-    HIPCHK(launch_reduce_partials(m.logits, m.partials, pl.S, (size_t)d.vocab, st, rl, d.vocab));
-  }
-  HIPCHK(launch_add_int(m.len_dev, 1, st));
   return SPEC_OK;
 }
 
@@ -461,8 +400,7 @@ int forward(spec_ctx* c, int which, const TokenSrc& src, int logit_rows) {
           rc = SPEC_E_HIP;
           break;
         }
-        rc = single_token_path(c, m, M) ? enqueue_forward_single(c, which, logit_rows, un.l0, un.l1)
-                                        : enqueue_forward(c, which, M, logit_rows, un.l0, un.l1);
+        rc = enqueue_forward(c, which, M, logit_rows, un.l0, un.l1);
         hipGraph_t g = nullptr;
         e = hipStreamEndCapture(st, &g);   // always leave capture mode, also after a failed launch
         if (rc || e != hipSuccess) {
@@ -488,8 +426,7 @@ int forward(spec_ctx* c, int which, const TokenSrc& src, int logit_rows) {
         rc = SPEC_E_HIP;
       }
     } else {
-      rc = single_token_path(c, m, M) ? enqueue_forward_single(c, which, logit_rows, un.l0, un.l1)
-                                      : enqueue_forward(c, which, M, logit_rows, un.l0, un.l1);
+      rc = enqueue_forward(c, which, M, logit_rows, un.l0, un.l1);
     }
   }
   c->wgs = wgs_saved;
@@ -1363,8 +1300,16 @@ extern "C" int spec_gemm_partials(const void* x, const void* w, int M, int N, in
 }
 extern "C" int spec_gemm(float* y, const void* x, const void* w, int M, int N, int K, void* work, void* stream) {
   if (!y) FAIL(SPEC_E_INVAL, "null pointer");
-  int rc = spec_gemm_partials(x, w, M, N, K, work, stream);
+  if (!x || !w || !work) FAIL(SPEC_E_INVAL, "null pointer");
+  int rc = check_gemm_args(M, N, K);
   if (rc) return rc;
+  if (proj_whole_k(M, N, K)) {
+    ProjArgs a = {};
+    a.x = (const bf16*)x; a.w = w; a.y = y;
+    HIPCHK(launch_proj(proj_plan(M, N, K, PROJ_STORE, 2), PROJ_STORE, a, (hipStream_t)stream, 2));
+    return SPEC_OK;
+  }
+  if ((rc = spec_gemm_partials(x, w, M, N, K, work, stream))) return rc;
   GemmPlan p = gemm_plan(M, N, K);
   HIPCHK(launch_reduce_partials(y, (const float*)work, p.S, (size_t)M * N, (hipStream_t)stream));
   return SPEC_OK;

@@ -38,82 +38,60 @@ struct GemmPlan {
 // wgs_per_cu: 2 = fill both workgroup slots of every CU (a stream running alone), 1 = leave one slot to
 // the other stream's kernels.  The K split (S, spw) does not depend on it.
 GemmPlan gemm_plan(int M, int N, int K, int wgs_per_cu = 2);
-// stamp: optional pair of device words that receives the launch's time stamps (see GemmPro::stamp)
+// stamp: optional device words that receive the launch's time stamps (see STAMP_WAYS)
 hipError_t launch_gemm_partials(const GemmPlan& p, const bf16* x, const void* wp, float* partials, hipStream_t st,
                                 int tag, unsigned long long* stamp = nullptr);
 
-// The RMSNorm of the decode path is split in three: the residual-add kernel stores x' = bf16(h * gain) and the
-// rows' sums of squares (W pieces per row); the projection runs on x' unchanged; whoever adds the projection's K
-// slices multiplies the sum by inv_m = 1 / sqrt(sum_w ssq[m][w] / d + eps) (the projection is linear in its rows
-// and bf16 keeps the same relative precision at any scale).  ssq == nullptr: no scaling.
-#define SSQ_STRIDE 128                     // floats per row of sums of squares
-static_assert(SSQ_STRIDE % 4 == 0, "RowScale::inv reads the pieces as 16-byte vectors");
-struct RowScale {
-  const float* ssq;    // [rows][SSQ_STRIDE], W pieces in use (whatever lies behind them is ignored)
-  int W, d;
-  float eps;
-#ifdef __HIPCC__
-  // the row's pieces come in independent 16-byte loads, four in flight (one round trip for up to 16 pieces), and
-  // are added in ascending order
-  __device__ __forceinline__ float inv(int m) const {
-    if (!ssq) return 1.0f;
-    const f32x4* p = reinterpret_cast<const f32x4*>(ssq + (size_t)m * SSQ_STRIDE);
-    const int nv = (W + 3) >> 2;
-    float tot = 0.f;
-    for (int k0 = 0; k0 < nv; k0 += 4) {
-      f32x4 v[4];
-#pragma unroll
-      for (int k = 0; k < 4; ++k) v[k] = (k0 + k < nv) ? p[k0 + k] : f32x4{0.f, 0.f, 0.f, 0.f};
-#pragma unroll
-      for (int k = 0; k < 4; ++k) {
-        const int i0 = (k0 + k) * 4;
-        tot += (i0 + 0 < W) ? v[k].x : 0.f; tot += (i0 + 1 < W) ? v[k].y : 0.f;
-        tot += (i0 + 2 < W) ? v[k].z : 0.f; tot += (i0 + 3 < W) ? v[k].w : 0.f;
-      }
-    }
-    return 1.0f / sqrtf(tot / (float)d + eps);
-  }
-#endif
-};
+// The RMSNorm of the decode path is split in three: whoever updates the residual stream h stores x' = bf16(h * gain)
+// and pieces of the rows' sums of squares; the projection runs on x' unchanged; its epilogue multiplies the sums by
+// inv_m = 1 / sqrt(sum_w ssq[m][w] / d + eps) (the projection is linear in its rows and bf16 keeps the same relative
+// precision at any scale).
+#define SSQ_STRIDE 1024                    // floats per row of sums of squares: at most one piece per 16 columns
+#define SPEC_D_MODEL_MAX (16 * SSQ_STRIDE)
 
-// ---------------------------------------------------------------------------------------
-// Single-token forwards (M = 1: every draft step, autoregressive and pre-verify target forwards) fold the residual
-// add + RMSNorm input and the SiLU * mul into the prologue of the projection that consumes them: a wave forms the
-// activation fragments of its own K range itself, after its first weight loads are on their way, so the dependent
-// loads hide behind the start of the weight stream and three kernel boundaries per layer disappear.
-// ---------------------------------------------------------------------------------------
-enum { PRO_NONE = 0, PRO_ADDNORM = 1, PRO_SWIGLU = 2 };
+// Optional time stamps of a projection launch: STAMP_WAYS pairs (workgroup b uses pair b % STAMP_WAYS, so that the
+// atomics of a launch do not queue on one address: one pair cost 3.5 us per launch), stamp[2 i] = max over its workgroups
+// of ~(start), stamp[2 i + 1] = max of their end, in ticks of the constant-rate wall clock; all start at 0.  The kernel's
+// own duration, first workgroup in to last workgroup out, without the dispatch overhead that events around a launch
+// include.
 #define STAMP_WAYS 16
-#define GEMM_WAVES_PER_GROUP 8   // waves of a projection workgroup: a PRO_ADDNORM launch leaves 8 S sums of squares
-struct GemmPro {
-  int kind;
-  // Optional time stamps of the launch (any kind): STAMP_WAYS pairs (workgroup b uses pair b % STAMP_WAYS, so that
-  // the atomics of a launch do not queue on one address: one pair cost 3.5 us per launch), stamp[2 i] = max over its
-  // workgroups of ~(start), stamp[2 i + 1] = max of their end, in ticks of the constant-rate wall clock; all start at
-  // 0.  The kernel's own duration, first workgroup in to last workgroup out, without the dispatch overhead that
-  // events around a launch include.
-  unsigned long long* stamp;
-  // PRO_ADDNORM: x' = bf16((h_in + sum_s part[s]) * gain); the workgroups of the first panel range also store the new
-  // residual stream to h_out (another buffer than h_in: the other workgroups still read h_in) and one sum of
-  // squares per wave to ssq[0 .. 8 S)
-  const float* h_in;
-  float* h_out;
-  const bf16* gain;
-  float* ssq_out;
-  // PRO_ADDNORM, PRO_SWIGLU: K-slice partial sums of the producing projection, [S][width]
-  const float* part;
-  int S;
-  // PRO_SWIGLU: z = bf16(silu(g * inv) * (u * inv)), gate / up panels interleaved in `part` (width 2 K)
-  RowScale rs;
+
+// ---------------------------------------------------------------------------------------
+// Whole-K projection (proj.hip): the K axis inside one workgroup, the element-wise work behind it in the epilogue.
+// ---------------------------------------------------------------------------------------
+enum { PROJ_STORE = 0, PROJ_RESID = 1, PROJ_SWIGLU = 2 };
+struct ProjPlan {
+  int M, N, K;
+  int steps;   // K rounded up to 32, divided by 32
+  int NT;      // N / 16 panels
+  int mode;    // how tokens and outputs fill the MFMA operands (see proj.hip)
+  int units;   // pieces of work: panel pairs (SWIGLU), panels or half panels
+  int RP;      // panels a wave streams at a time
+  int G;       // workgroups
+  int pieces() const { return units; }   // RESID: sums of squares per row
+  size_t weight_bytes() const { return (size_t)NT * steps * 1024; }
 };
-// the same projection for M = 1 with the activation formed in the prologue (pro.kind != PRO_NONE)
-hipError_t launch_gemm_fused(const GemmPlan& p, const GemmPro& pro, const void* wp, float* partials, hipStream_t st,
-                             int tag);
+ProjPlan proj_plan(int M, int N, int K, int epi, int wgs_per_cu);
+bool proj_whole_k(int M, int N, int K);   // whether this kernel is the faster one (else K slices, gemm.hip)
+struct ProjArgs {
+  const bf16* x;               // [M][K]
+  const void* w;               // packed panels
+  unsigned long long* stamp;   // see STAMP_WAYS
+  const float* ssq;            // STORE, SWIGLU: sums of squares of the rows behind x (null: no scaling) ...
+  int ssq_w;                   // ... pieces per row
+  float eps;
+  float* y;                    // STORE: [M][N]
+  float* h;                    // RESID: residual stream [M][N], updated in place
+  const bf16* gain;            // RESID: gain of the following norm [N]
+  bf16* xo;                    // RESID: bf16(h * gain) [M][N];  SWIGLU: z [M][N / 2]
+  float* ssq_out;              // RESID: sums of squares of h, one piece per 16 columns
+  int M, N, K, steps;          // set by launch_proj ...
+  int per, rem;                // ... units per workgroup; the first `rem` take one more
+};
+hipError_t launch_proj(const ProjPlan& p, int epi, ProjArgs a, hipStream_t st, int tag);
 
-
-// n = M * N elements; rs scales row i / N (N given) of the sum
-hipError_t launch_reduce_partials(float* y, const float* partials, int S, size_t n, hipStream_t st,
-                                  RowScale rs = RowScale{nullptr, 0, 0, 0.f}, int N = 0);
+// y = the sum of the K slices, n = M * N elements
+hipError_t launch_reduce_partials(float* y, const float* partials, int S, size_t n, hipStream_t st);
 hipError_t launch_pack_weight(void* dst, const void* src, int N, int K, int panel_start, int panel_step, hipStream_t st);
 hipError_t launch_read_probe(const void* src, size_t bytes, void* out, hipStream_t st);
 
@@ -152,22 +130,16 @@ hipError_t launch_addnorm(float* h, const float* partials, int S, const bf16* ga
 // h += sum_s partials[s] (if partials), a = bf16(h * gain) (not normalised), ssq[m][w] = sum of h^2 over the w-th
 // piece of 1024 columns of row m (row stride SSQ_STRIDE; pieces beyond W
 // are never written); returns the number of pieces W through *W_out
-#define ADDSQ_MAX_PIECES 16
-static_assert(ADDSQ_MAX_PIECES <= SSQ_STRIDE, "a row of sums of squares holds every piece");
 hipError_t launch_add_sumsq(float* h, const float* partials, int S, const bf16* gain, bf16* a, float* ssq, int M,
                             int d, int* W_out, hipStream_t st);
-// tab: optional [M][dh/2] (cos, sin) table from launch_rope_table for the same len; nullptr = compute in place
-hipError_t launch_rope_append(const float* partials, int S, bf16* q, bf16* pool, const int* block_table,
-                              const int* len_ptr, KvGeom g, int layer, int M, int Hq, float theta, hipStream_t st,
-                              const float2* tab = nullptr, RowScale rs = RowScale{nullptr, 0, 0, 0.f});
+// y: the fused QKV projection [M][(Hq + 2 Hkv) dh]; tab: [M][dh/2] (cos, sin) table from launch_rope_table for the same len
+hipError_t launch_rope_append(const float* y, bf16* q, bf16* pool, const int* block_table,
+                              const int* len_ptr, KvGeom g, int layer, int M, int Hq, hipStream_t st, const float2* tab);
 hipError_t launch_rope_table(float2* tab, const int* len_ptr, int M, int dh, float theta, hipStream_t st);
 hipError_t launch_attention(const bf16* q, const bf16* pool, const int* block_table, const int* len_ptr, KvGeom g,
                             int layer, int M, int Hq, int split_tokens, float* opart, float* mlpart, bf16* out,
                             hipStream_t st);
 size_t attention_workspace_floats(int Hq, int Hkv, int dh, int max_seq);
-hipError_t launch_silu_mul(const float* partials, int S, bf16* z, int M, int F, hipStream_t st,
-                           RowScale rs = RowScale{nullptr, 0, 0, 0.f});
-
 // prompt-sized (matrix-core bound) kernels: epilogue 0 = store fp32, 1 = add into fp32, 2 = silu(gate)*up -> bf16
 #define SPEC_PREFILL_BLOCK_MAX 4096   // most prompt tokens one dense pass takes
 hipError_t launch_dense_gemm(const bf16* x, const void* wp, int M, int N, int K, int epi, float* y, bf16* z,

@@ -12,118 +12,310 @@
 
 #define NEG_BIG (-1.0e30f)
 
+// Where a forward's new tokens come from: the fused QKV projection y [M][(Hq + 2 Hkv) dh] (fp32) and the (cos, sin)
+// table [M][dh / 2] of their positions.
+struct AttnNew {
+  const float* y;
+  const float2* tab;
+};
+
+// Row `tok` (valid), head slot `head` of the QKV projection, rotated and rounded: K step j of lane group g4 holds columns
+// 32 j + 8 g4 .. + 7, and a lane's columns of step j pair up with its columns of step j + dh / 64.
 template <int DH>
-__global__ __launch_bounds__(256) void attn_split_kernel(const bf16* __restrict__ q, const bf16* __restrict__ pool,
+__device__ __forceinline__ void attn_rotated(bf16x8 (&f)[DH / 32], const AttnNew& nw, int N, bool valid, int tok, int head, int g4) {
+#pragma unroll
+  for (int j = 0; j < DH / 64; ++j) {
+    f32x4 x[2][2] = {}, t[4] = {};
+    if (valid) {
+      const float* src = nw.y + (size_t)tok * N + (size_t)head * DH + j * 32 + g4 * 8;
+      const f32x4* ts = reinterpret_cast<const f32x4*>(nw.tab + (size_t)tok * (DH / 2) + j * 32 + g4 * 8);
+#pragma unroll
+      for (int h = 0; h < 2; ++h) {
+        x[0][h] = reinterpret_cast<const f32x4*>(src)[h];
+        x[1][h] = reinterpret_cast<const f32x4*>(src + DH / 2)[h];
+        t[h * 2] = ts[h * 2];
+        t[h * 2 + 1] = ts[h * 2 + 1];
+      }
+    }
+#pragma unroll
+    for (int i = 0; i < 8; ++i) {
+      const float x0 = x[0][i >> 2][i & 3], x1 = x[1][i >> 2][i & 3];
+      const float cs = t[i >> 1][(i & 1) * 2], sn = t[i >> 1][(i & 1) * 2 + 1];
+      f[j][i] = (__bf16)(x0 * cs - x1 * sn);
+      f[j + DH / 64][i] = (__bf16)(x0 * sn + x1 * cs);
+    }
+  }
+}
+
+// One wave's 16 query rows: rotated q fragments, running maximum / sum per row and the output accumulator.
+template <int DH>
+struct AttnRows {
+  bf16x8 qf[DH / 32];
+  f32x4 o[DH / 16];
+  float m, l;
+  __device__ __forceinline__ void clear() {
+    m = NEG_BIG;
+    l = 0.f;
+#pragma unroll
+    for (int dt = 0; dt < DH / 16; ++dt) o[dt] = f32x4{0.f, 0.f, 0.f, 0.f};
+  }
+};
+
+template <int DH>
+struct AttnChunk {                      // K / V fragments of 32 positions
+  u32x4 k[2][DH / 32], v[DH / 16];
+  __device__ __forceinline__ void load(const bf16* pool, int page, const KvGeom& g, int layer, int kvh, int ch, int lane) {
+    const int c = lane & 15, g4 = lane >> 4, half = ch & 1;
+    const u32x4* kblk = reinterpret_cast<const u32x4*>(pool + g.offset(page, layer, 0, kvh)) + (size_t)half * (DH / 16) * 64 + lane;
+    const bf16* vblk = pool + g.offset(page, layer, 1, kvh) + (size_t)half * DH * 32;
+#pragma unroll
+    for (int t = 0; t < 2; ++t)
+#pragma unroll
+      for (int j = 0; j < DH / 32; ++j) k[t][j] = kblk[(size_t)(t * (DH / 32) + j) * 64];
+#pragma unroll
+    for (int dt = 0; dt < DH / 16; ++dt) v[dt] = *reinterpret_cast<const u32x4*>(vblk + ((size_t)(dt * 16 + c) * 32 + g4 * 8));
+  }
+  // The new tokens as one chunk (positions beyond M hold zeros), straight from the QKV projection, k rotated.  Loads are
+  // unconditional (rows beyond M read the last one); the second 16 positions are skipped as a whole where there are none.
+  __device__ __forceinline__ void fresh(const AttnNew& nw, const KvGeom& g, int M, int Hq, int kvh, int lane) {
+    const int c = lane & 15, g4 = lane >> 4, N = (Hq + 2 * g.n_kv_heads) * DH;
+#pragma unroll
+    for (int dt = 0; dt < DH / 16; ++dt) v[dt] = u32x4{0u, 0u, 0u, 0u};
+#pragma unroll
+    for (int t = 0; t < 2; ++t) {
+#pragma unroll
+      for (int j = 0; j < DH / 32; ++j) k[t][j] = u32x4{0u, 0u, 0u, 0u};
+      if (t * 16 >= M) continue;                      // uniform
+      // v: lane (c, g4) holds columns 16 dt + c of positions 16 t + 4 g4 .. + 3
+      float x[4][DH / 16];
+#pragma unroll
+      for (int e = 0; e < 4; ++e) {
+        const float* src = nw.y + (size_t)min(t * 16 + g4 * 4 + e, M - 1) * N + (size_t)(Hq + g.n_kv_heads + kvh) * DH + c;
+#pragma unroll
+        for (int dt = 0; dt < DH / 16; ++dt) x[e][dt] = src[dt * 16];
+      }
+      // k: lane (c, g4) holds columns 32 j + 8 g4 .. + 7 of position 16 t + c
+      const int i = t * 16 + c;
+      bf16x8 f[DH / 32];
+      attn_rotated<DH>(f, nw, N, true, min(i, M - 1), Hq + kvh, g4);
+#pragma unroll
+      for (int j = 0; j < DH / 32; ++j)
+        if (i < M) k[t][j] = __builtin_bit_cast(u32x4, f[j]);
+#pragma unroll
+      for (int dt = 0; dt < DH / 16; ++dt) {
+        bf16x8 h = __builtin_bit_cast(bf16x8, v[dt]);
+#pragma unroll
+        for (int e = 0; e < 4; ++e) h[t * 4 + e] = (__bf16)(t * 16 + g4 * 4 + e < M ? x[e][dt] : 0.f);
+        v[dt] = __builtin_bit_cast(u32x4, h);
+      }
+    }
+  }
+  // appends the chunk that fresh() made to the pages of positions len .. len + M - 1 (at most two)
+  __device__ __forceinline__ void append(bf16* pool, const int* block_table, const KvGeom& g, int layer, int M, int kvh,
+                                         int len, int lane) const {
+    const int c = lane & 15, g4 = lane >> 4;
+    const int first = len / SPEC_PAGE_TOKENS, page0 = block_table[first], page1 = block_table[(len + M - 1) / SPEC_PAGE_TOKENS];
+#pragma unroll
+    for (int t = 0; t < 2; ++t) {
+      if (t * 16 >= M) continue;
+      const int i = t * 16 + c, pos = len + i, rr = pos % SPEC_PAGE_TOKENS;
+      if (i < M) {
+        u32x4* dst = reinterpret_cast<u32x4*>(pool + g.offset(pos / SPEC_PAGE_TOKENS == first ? page0 : page1, layer, 0, kvh)) +
+                     (size_t)(rr >> 4) * (DH / 32) * 64 + g4 * 16 + (rr & 15);
+#pragma unroll
+        for (int j = 0; j < DH / 32; ++j) dst[j * 64] = k[t][j];
+      }
+#pragma unroll
+      for (int e = 0; e < 4; ++e) {
+        const int iv = t * 16 + g4 * 4 + e, pv = len + iv, rv = pv % SPEC_PAGE_TOKENS, r32 = rv & 31;
+        if (iv < M) {
+          __bf16* dst = reinterpret_cast<__bf16*>(pool + g.offset(pv / SPEC_PAGE_TOKENS == first ? page0 : page1, layer, 1, kvh)) +
+                        ((size_t)(rv >> 5) * DH + c) * 32 + ((r32 & 15) >> 2) * 8 + (r32 >> 4) * 4 + (r32 & 3);
+#pragma unroll
+          for (int dt = 0; dt < DH / 16; ++dt) dst[(size_t)dt * 16 * 32] = __builtin_bit_cast(bf16x8, v[dt])[t * 4 + e];
+        }
+      }
+    }
+  }
+};
+static_assert(SPEC_PAGE_TOKENS == 64, "two chunks of 32 positions per page");
+
+// online softmax over a chunk whose first position is pos0; positions beyond `limit` are masked
+template <int DH>
+__device__ __forceinline__ void attn_chunk(AttnRows<DH>& r, const AttnChunk<DH>& kv, int pos0, int limit, float scale, int g4) {
+  f32x4 s[2];
+#pragma unroll
+  for (int t = 0; t < 2; ++t) {
+    s[t] = f32x4{0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+    for (int j = 0; j < DH / 32; ++j)
+      s[t] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, kv.k[t][j]), r.qf[j], s[t], 0, 0, 0);
+  }
+  // s[t][i] = score of position pos0 + 16 t + 4 g4 + i for query row c
+  float mx = NEG_BIG;
+#pragma unroll
+  for (int t = 0; t < 2; ++t)
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+      const int pos = pos0 + t * 16 + g4 * 4 + i;
+      const float v = (pos <= limit) ? s[t][i] * scale : NEG_BIG;
+      s[t][i] = v;
+      mx = fmaxf(mx, v);
+    }
+  mx = fmaxf(mx, __shfl_xor(mx, 16));
+  mx = fmaxf(mx, __shfl_xor(mx, 32));
+  const float m_new = fmaxf(r.m, mx);
+  const float corr = __expf(r.m - m_new);
+  float psum = 0.f;
+  bf16x8 pf;
+#pragma unroll
+  for (int t = 0; t < 2; ++t)
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+      const float p = (s[t][i] > 0.5f * NEG_BIG) ? __expf(s[t][i] - m_new) : 0.f;
+      psum += p;
+      pf[t * 4 + i] = (__bf16)p;
+    }
+  r.l = r.l * corr + psum;
+  r.m = m_new;
+#pragma unroll
+  for (int dt = 0; dt < DH / 16; ++dt) {
+    r.o[dt] *= corr;
+    r.o[dt] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, kv.v[dt]), pf, r.o[dt], 0, 0, 0);
+  }
+}
+
+// the query row of lane c of row tile `rtile` of a KV head
+struct AttnRow {
+  bool valid;
+  int tok, head;
+  __device__ __forceinline__ AttnRow(int Rr, int R, int G, int kvh) {
+    valid = Rr < R;
+    tok = valid ? Rr / G : 0;
+    head = kvh * G + (valid ? Rr % G : 0);
+  }
+};
+
+// Splits 0 .. nsplit - 2 take the cache's chunks s, s + (nsplit - 1), ..., the last split the new tokens.  A wave's first
+// chunk does not depend on the length, so its page lookup and K / V loads go out at once (of a chunk beyond the length
+// too: a page of the pool, all masked) and the chain is page id -> K / V -> result.
+template <int DH>
+__global__ __launch_bounds__(256) void attn_split_kernel(AttnNew nw, bf16* __restrict__ pool,
                                                          const int* __restrict__ block_table,
                                                          const int* __restrict__ len_ptr, KvGeom g, int layer, int M,
                                                          int Hq, int nsplit, int Rpad, float scale,
                                                          float* __restrict__ opart, float* __restrict__ mlpart) {
-  const int kvh = blockIdx.y, split = blockIdx.z;
-  const int w = threadIdx.x >> 6, lane = threadIdx.x & 63;
+  const int kvh = blockIdx.y, split = blockIdx.z, S = nsplit - 1;
+  const int w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), lane = threadIdx.x & 63;
   const int Hkv = g.n_kv_heads, G = Hq / Hkv, R = M * G;
   const int rtile = blockIdx.x * (blockDim.x >> 6) + w;
   if (rtile * 16 >= R) return;
   const int c = lane & 15, g4 = lane >> 4;
-  const int len = len_ptr[0];
-  const int T = len + M;
-  const int nchunks = (T + 31) >> 5;
-  const int cps = (nchunks + nsplit - 1) / nsplit;
-  const int c0 = split * cps;
-  const int c1 = (c0 + cps < nchunks) ? c0 + cps : nchunks;
-
   const int Rr = rtile * 16 + c;
-  const bool valid = Rr < R;
-  const int tok = valid ? Rr / G : 0;
-  const int head = kvh * G + (valid ? Rr % G : 0);
-  const int limit = valid ? len + tok : -1;   // last visible position
-
-  bf16x8 qf[DH / 32];
+  const AttnRow row(Rr, R, G, kvh);
+  AttnRows<DH> r;
+  r.clear();
+  AttnChunk<DH> kv[2];
+  if (split == S) {
+    attn_rotated<DH>(r.qf, nw, (Hq + 2 * Hkv) * DH, row.valid, row.tok, row.head, g4);
+    kv[0].fresh(nw, g, M, Hq, kvh, lane);
+    attn_chunk(r, kv[0], 0, row.valid ? row.tok : -1, scale, g4);
+  } else {
+    // two chunks in flight: while one is multiplied the loads of the next are on their way
+    kv[0].load(pool, block_table[split >> 1], g, layer, kvh, split, lane);
+    const int len = len_ptr[0], nchunks = (len + 31) >> 5, limit = row.valid ? len - 1 : -1;
+    attn_rotated<DH>(r.qf, nw, (Hq + 2 * Hkv) * DH, row.valid, row.tok, row.head, g4);
+    int ch = split;
+    for (; ch + S < nchunks; ch += 2 * S) {
+      kv[1].load(pool, block_table[(ch + S) >> 1], g, layer, kvh, ch + S, lane);
+      attn_chunk(r, kv[0], ch << 5, limit, scale, g4);
+      if (ch + 2 * S < nchunks) kv[0].load(pool, block_table[(ch + 2 * S) >> 1], g, layer, kvh, ch + 2 * S, lane);
+      attn_chunk(r, kv[1], (ch + S) << 5, limit, scale, g4);
+    }
+    if (ch < nchunks) attn_chunk(r, kv[0], ch << 5, limit, scale, g4);
+  }
+  r.l += __shfl_xor(r.l, 16);
+  r.l += __shfl_xor(r.l, 32);
+  if (row.valid) {
+    const size_t at = ((size_t)kvh * Rpad + Rr) * nsplit + split;   // the splits of a query row lie side by side
 #pragma unroll
-  for (int j = 0; j < DH / 32; ++j) {
-    u32x4 v = {0u, 0u, 0u, 0u};
-    if (valid) v = *reinterpret_cast<const u32x4*>(q + ((size_t)tok * Hq + head) * DH + j * 32 + g4 * 8);
-    qf[j] = __builtin_bit_cast(bf16x8, v);
-  }
-
-  float m_run = NEG_BIG, l_run = 0.f;
-  f32x4 o[DH / 16];
-#pragma unroll
-  for (int dt = 0; dt < DH / 16; ++dt) o[dt] = f32x4{0.f, 0.f, 0.f, 0.f};
-
-  // K / V fragments of two chunks: while one chunk is multiplied the loads of the next are already in flight
-  // (a wave owns only a handful of chunks, so its run time is a chain of load latencies unless they overlap).
-  u32x4 ka[2][2][DH / 32], va[2][DH / 16];
-#define ATT_LOAD(B, CH)                                                                                       \
-  {                                                                                                           \
-    const int pos0_ = (CH) << 5;                                                                              \
-    const int page_ = block_table[pos0_ / SPEC_PAGE_TOKENS];                                                  \
-    const int inpage_ = pos0_ % SPEC_PAGE_TOKENS;                                                             \
-    const u32x4* kblk_ = reinterpret_cast<const u32x4*>(pool + g.offset(page_, layer, 0, kvh)) +              \
-                         (size_t)(inpage_ >> 4) * (DH / 32) * 64 + lane;                                      \
-    const bf16* vblk_ = pool + g.offset(page_, layer, 1, kvh) + (size_t)(inpage_ >> 5) * DH * 32;             \
-    _Pragma("unroll") for (int t = 0; t < 2; ++t)                                                             \
-      _Pragma("unroll") for (int j = 0; j < DH / 32; ++j) ka[B][t][j] = kblk_[(size_t)(t * (DH / 32) + j) * 64]; \
-    _Pragma("unroll") for (int dt = 0; dt < DH / 16; ++dt)                                                    \
-      va[B][dt] = *reinterpret_cast<const u32x4*>(vblk_ + ((size_t)(dt * 16 + c) * 32 + g4 * 8));             \
-  }
-#define ATT_COMPUTE(B, CH)                                                                                    \
-  {                                                                                                           \
-    const int pos0 = (CH) << 5;                                                                               \
-    f32x4 s[2];                                                                                               \
-    _Pragma("unroll") for (int t = 0; t < 2; ++t) {                                                           \
-      s[t] = f32x4{0.f, 0.f, 0.f, 0.f};                                                                       \
-      _Pragma("unroll") for (int j = 0; j < DH / 32; ++j)                                                     \
-        s[t] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, ka[B][t][j]), qf[j], s[t], 0, 0, 0); \
-    }                                                                                                         \
-    /* s[t][r] = score of position pos0 + 16 t + 4 g4 + r for query row c */                                  \
-    float mx = NEG_BIG;                                                                                       \
-    _Pragma("unroll") for (int t = 0; t < 2; ++t)                                                             \
-      _Pragma("unroll") for (int r = 0; r < 4; ++r) {                                                         \
-        const int pos = pos0 + t * 16 + g4 * 4 + r;                                                           \
-        const float v = (pos <= limit) ? s[t][r] * scale : NEG_BIG;                                           \
-        s[t][r] = v;                                                                                          \
-        mx = fmaxf(mx, v);                                                                                    \
-      }                                                                                                       \
-    mx = fmaxf(mx, __shfl_xor(mx, 16));                                                                       \
-    mx = fmaxf(mx, __shfl_xor(mx, 32));                                                                       \
-    const float m_new = fmaxf(m_run, mx);                                                                     \
-    const float corr = __expf(m_run - m_new);                                                                 \
-    float psum = 0.f;                                                                                         \
-    bf16x8 pf;                                                                                                \
-    _Pragma("unroll") for (int t = 0; t < 2; ++t)                                                             \
-      _Pragma("unroll") for (int r = 0; r < 4; ++r) {                                                         \
-        const float p = (s[t][r] > 0.5f * NEG_BIG) ? __expf(s[t][r] - m_new) : 0.f;                           \
-        psum += p;                                                                                            \
-        pf[t * 4 + r] = (__bf16)p;                                                                            \
-      }                                                                                                       \
-    l_run = l_run * corr + psum;                                                                              \
-    m_run = m_new;                                                                                            \
-    _Pragma("unroll") for (int dt = 0; dt < DH / 16; ++dt) {                                                  \
-      o[dt] *= corr;                                                                                          \
-      o[dt] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, va[B][dt]), pf, o[dt], 0, 0, 0); \
-    }                                                                                                         \
-  }
-  if (c0 < c1) ATT_LOAD(0, c0)
-  int ch = c0;
-  for (; ch + 2 <= c1; ch += 2) {
-    ATT_LOAD(1, ch + 1)
-    ATT_COMPUTE(0, ch)
-    if (ch + 2 < c1) ATT_LOAD(0, ch + 2)
-    ATT_COMPUTE(1, ch + 1)
-  }
-  if (ch < c1) ATT_COMPUTE(0, ch)
-#undef ATT_LOAD
-#undef ATT_COMPUTE
-  l_run += __shfl_xor(l_run, 16);
-  l_run += __shfl_xor(l_run, 32);
-  if (valid) {
-    const size_t row = ((size_t)kvh * Rpad + Rr) * nsplit + split;   // the splits of a query row lie side by side
-#pragma unroll
-    for (int dt = 0; dt < DH / 16; ++dt)
-      *reinterpret_cast<f32x4*>(opart + row * DH + dt * 16 + g4 * 4) = o[dt];
+    for (int dt = 0; dt < DH / 16; ++dt) *reinterpret_cast<f32x4*>(opart + at * DH + dt * 16 + g4 * 4) = r.o[dt];
     if (g4 == 0) {
-      mlpart[row * 2] = m_run;
-      mlpart[row * 2 + 1] = l_run;
+      mlpart[at * 2] = r.m;
+      mlpart[at * 2 + 1] = r.l;
+    }
+  }
+  if (split == S && rtile == 0) kv[0].append(pool, block_table, g, layer, M, kvh, len_ptr[0], lane);
+}
+
+// Short caches: one workgroup per KV head and row tile takes the whole range, wave w < 7 the chunks w, w + 7, .. and the
+// eighth wave the new tokens; the waves' parts are merged through LDS, so there is no merge kernel.
+#define SHORT_WAVES 8
+#define SHORT_CHUNK_WAVES (SHORT_WAVES - 1)
+#define SHORT_TOKENS 1024
+template <int DH>
+__global__ __launch_bounds__(SHORT_WAVES * 64, 2) void attn_short_kernel(AttnNew nw, bf16* __restrict__ pool,
+                                                                      const int* __restrict__ block_table,
+                                                                      const int* __restrict__ len_ptr, KvGeom g, int layer,
+                                                                      int M, int Hq, float scale, int last_chunk,
+                                                                      bf16* __restrict__ out) {
+  constexpr int S = SHORT_CHUNK_WAVES;
+  __shared__ f32x4 osh[SHORT_WAVES][16][DH / 4 + 1];     // [row][4 columns], a row padded by 16 bytes
+  __shared__ float msh[SHORT_WAVES][16], lsh[SHORT_WAVES][16];
+  const int rtile = blockIdx.x, kvh = blockIdx.y;
+  const int w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), lane = threadIdx.x & 63;
+  const int c = lane & 15, g4 = lane >> 4;
+  const int Hkv = g.n_kv_heads, G = Hq / Hkv, R = M * G;
+  const AttnRow row(rtile * 16 + c, R, G, kvh);
+  AttnRows<DH> r;
+  r.clear();
+  AttnChunk<DH> kv[2];
+  if (w == S) {
+    attn_rotated<DH>(r.qf, nw, (Hq + 2 * Hkv) * DH, row.valid, row.tok, row.head, g4);
+    kv[0].fresh(nw, g, M, Hq, kvh, lane);
+    attn_chunk(r, kv[0], 0, row.valid ? row.tok : -1, scale, g4);
+  } else {
+    const int ch0 = min(w, last_chunk);      // the table has entries up to last_chunk / 2
+    kv[0].load(pool, block_table[ch0 >> 1], g, layer, kvh, ch0, lane);
+    const int len = len_ptr[0], nchunks = (len + 31) >> 5, limit = row.valid ? len - 1 : -1;
+    if (w + S < nchunks) kv[1].load(pool, block_table[(w + S) >> 1], g, layer, kvh, w + S, lane);
+    attn_rotated<DH>(r.qf, nw, (Hq + 2 * Hkv) * DH, row.valid, row.tok, row.head, g4);
+    for (int ch = w; ch < nchunks; ch += 2 * S) {
+      attn_chunk(r, kv[0], ch << 5, limit, scale, g4);
+      if (ch + 2 * S < nchunks) kv[0].load(pool, block_table[(ch + 2 * S) >> 1], g, layer, kvh, ch + 2 * S, lane);
+      if (ch + S < nchunks) {
+        attn_chunk(r, kv[1], (ch + S) << 5, limit, scale, g4);
+        if (ch + 3 * S < nchunks) kv[1].load(pool, block_table[(ch + 3 * S) >> 1], g, layer, kvh, ch + 3 * S, lane);
+      }
+    }
+  }
+  r.l += __shfl_xor(r.l, 16);
+  r.l += __shfl_xor(r.l, 32);
+#pragma unroll
+  for (int dt = 0; dt < DH / 16; ++dt) osh[w][c][dt * 4 + g4] = r.o[dt];
+  if (g4 == 0) msh[w][c] = r.m, lsh[w][c] = r.l;
+  __syncthreads();
+  // the page stores come last: nobody in this launch reads them, and the other waves merge meanwhile
+  if (w == S && rtile == 0) kv[0].append(pool, block_table, g, layer, M, kvh, len_ptr[0], lane);
+  const int rr = threadIdx.x / (DH / 4), q = threadIdx.x % (DH / 4);
+  if (rr < 16) {
+    const AttnRow me(rtile * 16 + rr, R, G, kvh);
+    if (me.valid) {
+      float m = msh[0][rr];
+#pragma unroll
+      for (int k = 1; k < SHORT_WAVES; ++k) m = fmaxf(m, msh[k][rr]);
+      f32x4 num = {0.f, 0.f, 0.f, 0.f};
+      float den = 0.f;
+#pragma unroll
+      for (int k = 0; k < SHORT_WAVES; ++k) {
+        const float e = __expf(msh[k][rr] - m);      // a wave without a chunk holds (NEG_BIG, 0, 0)
+        num += e * osh[k][rr][q];
+        den += e * lsh[k][rr];
+      }
+      bf16 o[4];
+#pragma unroll
+      for (int i = 0; i < 4; ++i) o[i] = __float2bfloat16(num[i] / den);
+      *reinterpret_cast<uint2*>(out + ((size_t)me.tok * Hq + me.head) * DH + q * 4) = *reinterpret_cast<const uint2*>(o);
     }
   }
 }
@@ -185,7 +377,7 @@ static int attn_nsplit(int Hkv, int nrt, int T) {
   int ns = (3 * spec_num_cu() + Hkv * nrt - 1) / (Hkv * nrt);   // about three waves per compute unit ...
   if (ns > (nchunks + 1) / 2) ns = (nchunks + 1) / 2;           // ... but at least two chunks per split
   if (ns < 1) ns = 1;
-  return ns;
+  return ns + 1;                                                // and the new tokens' own
 }
 
 size_t attention_workspace_floats(int Hq, int Hkv, int dh, int max_seq) {
@@ -196,22 +388,33 @@ size_t attention_workspace_floats(int Hq, int Hkv, int dh, int max_seq) {
   return (size_t)ns_max * Hkv * Rpad * (dh + 2);
 }
 
-hipError_t launch_attention(const bf16* q, const bf16* pool, const int* block_table, const int* len_ptr, KvGeom g,
-                            int layer, int M, int Hq, int split_tokens, float* opart, float* mlpart, bf16* out,
+hipError_t launch_attention(const float* y, const float2* tab, bf16* pool, const int* block_table, const int* len_ptr,
+                            KvGeom g, int layer, int M, int Hq, int split_tokens, float* opart, float* mlpart, bf16* out,
                             hipStream_t st) {
   const int Hkv = g.n_kv_heads, G = Hq / Hkv, R = M * G, dh = g.head_dim;
   const int nrt = (R + 15) / 16;
   const int Rpad = ((SPEC_MAX_TOKENS * G + 15) / 16) * 16;
-  // the split count is sized for the longest context, not the current one, so that the launch is replayable
+  const float scale = 1.0f / sqrtf((float)dh);
+  const AttnNew nw = {y, tab};
+  // the kernel and the split count are chosen for the longest context, not the current one, so that the launch is replayable
+  if (split_tokens <= SHORT_TOKENS) {
+    dim3 grid(nrt, Hkv), block(SHORT_WAVES * 64);
+    if (dh == 128)
+      attn_short_kernel<128><<<grid, block, 0, st>>>(nw, pool, block_table, len_ptr, g, layer, M, Hq, scale,
+                                                   split_tokens / 32 - 1, out);
+    else
+      attn_short_kernel<64><<<grid, block, 0, st>>>(nw, pool, block_table, len_ptr, g, layer, M, Hq, scale,
+                                                   split_tokens / 32 - 1, out);
+    return hipGetLastError();
+  }
   const int nsplit = attn_nsplit(Hkv, nrt, split_tokens);
   const int wpb = nrt < 4 ? nrt : 4;
   dim3 grid((nrt + wpb - 1) / wpb, Hkv, nsplit), block(64 * wpb);
-  const float scale = 1.0f / sqrtf((float)dh);
   if (dh == 128)
-    attn_split_kernel<128><<<grid, block, 0, st>>>(q, pool, block_table, len_ptr, g, layer, M, Hq, nsplit, Rpad, scale,
+    attn_split_kernel<128><<<grid, block, 0, st>>>(nw, pool, block_table, len_ptr, g, layer, M, Hq, nsplit, Rpad, scale,
                                                    opart, mlpart);
   else
-    attn_split_kernel<64><<<grid, block, 0, st>>>(q, pool, block_table, len_ptr, g, layer, M, Hq, nsplit, Rpad, scale,
+    attn_split_kernel<64><<<grid, block, 0, st>>>(nw, pool, block_table, len_ptr, g, layer, M, Hq, nsplit, Rpad, scale,
                                                   opart, mlpart);
   hipError_t e = hipGetLastError();
   if (e != hipSuccess) return e;

@@ -175,13 +175,8 @@ hipError_t launch_add_sumsq(float* h, const float* partials, int S, const bf16* 
   return hipGetLastError();
 }
 
-// One 64-thread slice of a workgroup per (token, head) of the fused QKV output (ROPE_HPB heads per workgroup);
-// thread e of the slice handles the pair (e, e + dh/2).
-// q heads: rotate, store bf16 [M][Hq][dh].  k heads: rotate, store into the page in K-operand order.
-// v heads: store into the page in V-operand order.  Position of token i is len + i.
-#define ROPE_HPB 4
-// (cos, sin) of the rotation angle of pair e at position len + i, for all tokens of a prompt block: the same
-// expression as in rope_append_kernel, evaluated once per block instead of once per layer and head.
+// (cos, sin) of the rotation angle pos * theta^(-2e/dh) of pair e at position len + i, in fp64, once per forward or
+// prompt block instead of once per layer and head.
 __global__ void rope_table_kernel(float2* __restrict__ tab, const int* __restrict__ len_ptr, int dh, float theta) {
   const int i = blockIdx.x, e = threadIdx.x, half = dh >> 1;
   if (e >= half) return;
@@ -191,52 +186,5 @@ __global__ void rope_table_kernel(float2* __restrict__ tab, const int* __restric
 }
 hipError_t launch_rope_table(float2* tab, const int* len_ptr, int M, int dh, float theta, hipStream_t st) {
   rope_table_kernel<<<M, 64, 0, st>>>(tab, len_ptr, dh, theta);
-  return hipGetLastError();
-}
-
-__global__ void rope_append_kernel(const float* __restrict__ y, bf16* __restrict__ q, bf16* __restrict__ pool,
-                                   const int* __restrict__ block_table, const int* __restrict__ len_ptr, KvGeom g,
-                                   int layer, int Hq, const float2* __restrict__ tab) {
-  const int i = blockIdx.x, head = blockIdx.y * ROPE_HPB + (threadIdx.x >> 6);
-  const int dh = g.head_dim, half = dh >> 1, Hkv = g.n_kv_heads;
-  const int N = (Hq + 2 * Hkv) * dh;
-  const int e = threadIdx.x & 63;
-  if (e >= half || head >= Hq + 2 * Hkv) return;
-  const int pos = len_ptr[0] + i;
-  const float* base = y + (size_t)i * N + (size_t)head * dh;
-  float x0 = base[e], x1 = base[e + half];
-  if (head < Hq + Hkv) {   // rotation of pair (e, e + dh/2) by pos * theta^(-2e/dh)
-    const float2 t = tab[(size_t)i * half + e];
-    const float y0 = x0 * t.x - x1 * t.y, y1 = x0 * t.y + x1 * t.x;
-    x0 = y0; x1 = y1;
-  }
-  if (head < Hq) {
-    bf16* dst = q + ((size_t)i * Hq + head) * dh;
-    dst[e] = __float2bfloat16(x0);
-    dst[e + half] = __float2bfloat16(x1);
-    return;
-  }
-  const int page = block_table[pos / SPEC_PAGE_TOKENS];
-  const int r = pos % SPEC_PAGE_TOKENS;
-  if (head < Hq + Hkv) {
-    bf16* blk = pool + g.offset(page, layer, 0, head - Hq);
-    const int tile = r >> 4, rr = r & 15, nsteps = dh >> 5;
-    for (int t = 0; t < 2; ++t) {
-      const int ee = t ? e + half : e;
-      const size_t off = ((size_t)((tile * nsteps + (ee >> 5)) * 64 + ((ee & 31) >> 3) * 16 + rr)) * 8 + (ee & 7);
-      blk[off] = __float2bfloat16(t ? x1 : x0);
-    }
-  } else {
-    bf16* blk = pool + g.offset(page, layer, 1, head - Hq - Hkv);
-    const int chunk = r >> 5, r32 = r & 31;
-    const int slot = ((r32 & 15) >> 2) * 8 + (r32 >> 4) * 4 + (r32 & 3);
-    blk[((size_t)chunk * dh + e) * 32 + slot] = __float2bfloat16(x0);
-    blk[((size_t)chunk * dh + e + half) * 32 + slot] = __float2bfloat16(x1);
-  }
-}
-hipError_t launch_rope_append(const float* y, bf16* q, bf16* pool, const int* block_table, const int* len_ptr, KvGeom g,
-                              int layer, int M, int Hq, hipStream_t st, const float2* tab) {
-  dim3 grid(M, (Hq + 2 * g.n_kv_heads + ROPE_HPB - 1) / ROPE_HPB), block(64 * ROPE_HPB);
-  rope_append_kernel<<<grid, block, 0, st>>>(y, q, pool, block_table, len_ptr, g, layer, Hq, tab);
   return hipGetLastError();
 }

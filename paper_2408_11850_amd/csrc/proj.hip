@@ -131,19 +131,35 @@ __global__ __launch_bounds__(PROJ_THREADS, RP * MT > 4 ? 2 : 4) void proj_kernel
     return proj_rsrc(reinterpret_cast<const char*>(a.w) + (panel * a.steps + s0 * Q) * 1024 + half, bytes);
   };
   __amdgpu_buffer_rsrc_t wr = group_rsrc(p0);
+  // 1 / rms of every row from its sums of squares (ssq_w pieces, added in a fixed order).  A wave's first row is
+  // requested ahead of the ring, so that it is not waited for behind the weights, and summed once the ring is on its way.
+  const bool scaled = EPI != PROJ_RESID && a.ssq;
+  f32x4 sq[2] = {};
+  const int row_bytes = (a.ssq_w + 3) / 4 * 16;   // whole vectors; what lies behind the pieces is masked below
+  if (EPI != PROJ_RESID) {
+    const __amdgpu_buffer_rsrc_t sr = proj_rsrc(a.ssq + (size_t)w * SSQ_STRIDE, scaled && w < a.M ? row_bytes : 0);
 #pragma unroll
-  for (int d = 0; d < D; ++d) PROJ_LOAD(d, wr, d)
+    for (int i = 0; i < 2; ++i) sq[i] = __builtin_bit_cast(f32x4, __builtin_amdgcn_raw_buffer_load_b128(sr, lane * 16 + i * 1024, 0, 0));
+    __builtin_amdgcn_sched_barrier(0);
+  }
+#pragma unroll
+  for (int d = 0; d < D; ++d) {
+    PROJ_LOAD(d, wr, d)
+    __builtin_amdgcn_sched_barrier(0);
+  }
 
-  if (EPI != PROJ_RESID && a.ssq) {
-    // 1 / rms of every row from its sums of squares (ssq_w pieces, added in a fixed order); the loads arrive with the
-    // first weights
+  if (scaled) {
     for (int m = w; m < a.M; m += PROJ_WAVES) {
       const float* row = a.ssq + (size_t)m * SSQ_STRIDE;
-      float t = 0.f;
-      for (int i = lane; i < a.ssq_w; i += 64) t += row[i];
+      float s = 0.f;
+      for (int i = lane * 4, k = 0; i < a.ssq_w; i += 256, ++k) {
+        f32x4 t = m == w && k == 0 ? sq[0] : m == w && k == 1 ? sq[1] : *reinterpret_cast<const f32x4*>(row + i);
 #pragma unroll
-      for (int o = 32; o > 0; o >>= 1) t += __shfl_xor(t, o);
-      if (lane == 0) inv_sh[m] = 1.0f / sqrtf(t / (float)a.K + a.eps);
+        for (int r = 0; r < 4; ++r) s += i + r < a.ssq_w ? t[r] : 0.f;
+      }
+#pragma unroll
+      for (int o = 32; o > 0; o >>= 1) s += __shfl_xor(s, o);
+      if (lane == 0) inv_sh[m] = 1.0f / sqrtf(s / (float)a.K + a.eps);
     }
   }
 

@@ -56,7 +56,7 @@ struct ModelRt {
   float* qkv = nullptr;           // fused QKV projection of a forward
   float2* rope_tab = nullptr;     // (cos, sin) of the new positions of a forward
   float* ssq = nullptr;           // sums of squares of the rows of h, SSQ_STRIDE floats per row
-  bf16 *a = nullptr, *qbuf = nullptr, *attn_out = nullptr, *z = nullptr;
+  bf16 *a = nullptr, *attn_out = nullptr, *z = nullptr;
   float *partials = nullptr, *opart = nullptr, *mlpart = nullptr, *logits = nullptr;
   long long n_forwards = 0;
   int split_tokens = 0;           // context length the attention split count is sized for (fixed per context)
@@ -178,7 +178,6 @@ int init_model(ModelRt& m, const spec_model_desc& d, const spec_weights& w, cons
   if ((rc = dev_alloc(&m.ssq, (size_t)MX * SSQ_STRIDE))) return rc;
   HIPCHK(hipMemset(m.ssq, 0, (size_t)MX * SSQ_STRIDE * sizeof(float)));
   if ((rc = dev_alloc(&m.a, (size_t)MX * amax))) return rc;
-  if ((rc = dev_alloc(&m.qbuf, (size_t)MX * d.n_heads * d.head_dim))) return rc;
   if ((rc = dev_alloc(&m.attn_out, (size_t)MX * d.n_heads * d.head_dim))) return rc;
   if ((rc = dev_alloc(&m.z, (size_t)MX * d.d_ffn))) return rc;
   size_t pb = 0;
@@ -208,7 +207,7 @@ void free_model(ModelRt& m) {
             g = nullptr;
           }
   void* ptrs[] = {m.qkv, m.rope_tab,
-                  m.pool, m.block_table_dev, m.len_dev, m.tok_in, m.h, m.ssq, m.a, m.qbuf, m.attn_out, m.z, m.partials,
+                  m.pool, m.block_table_dev, m.len_dev, m.tok_in, m.h, m.ssq, m.a, m.attn_out, m.z, m.partials,
                   m.opart, m.logits, m.pf_tok, m.pf_h, m.pf_a, m.pf_q, m.pf_attn, m.pf_z, m.pf_rope};
   for (void* p : ptrs)
     if (p) (void)hipFree(p);
@@ -323,9 +322,8 @@ int enqueue_forward(spec_ctx* c, int which, int M, int logit_rows, int l0, int l
     ProjArgs pa = normed;
     pa.w = m.wqkv[l]; pa.y = m.qkv; pa.ssq_w = W;
     if ((rc = run_proj(c, which, m, proj_plan(M, qkvN, d.d_model, PROJ_STORE, c->wgs), PROJ_STORE, pa))) return rc;
-    HIPCHK(launch_rope_append(m.qkv, m.qbuf, m.pool, m.block_table_dev, m.len_dev, m.geom, l, M, d.n_heads, st, m.rope_tab));
-    HIPCHK(launch_attention(m.qbuf, m.pool, m.block_table_dev, m.len_dev, m.geom, l, M, d.n_heads, m.split_tokens,
-                            m.opart, m.mlpart, m.attn_out, st));
+    HIPCHK(launch_attention(m.qkv, m.rope_tab, m.pool, m.block_table_dev, m.len_dev, m.geom, l, M, d.n_heads,
+                            m.split_tokens, m.opart, m.mlpart, m.attn_out, st));
     if ((rc = run_resid(c, which, m, M, HD, m.attn_out, m.wo[l], m.ffn_norm[l], &W))) return rc;
     pa = normed;
     pa.w = m.wgu[l]; pa.xo = m.z; pa.ssq_w = W;

@@ -132,12 +132,11 @@ hipError_t launch_addnorm(float* h, const float* partials, int S, const bf16* ga
 // are never written); returns the number of pieces W through *W_out
 hipError_t launch_add_sumsq(float* h, const float* partials, int S, const bf16* gain, bf16* a, float* ssq, int M,
                             int d, int* W_out, hipStream_t st);
-// y: the fused QKV projection [M][(Hq + 2 Hkv) dh]; tab: [M][dh/2] (cos, sin) table from launch_rope_table for the same len
-hipError_t launch_rope_append(const float* y, bf16* q, bf16* pool, const int* block_table,
-                              const int* len_ptr, KvGeom g, int layer, int M, int Hq, hipStream_t st, const float2* tab);
 hipError_t launch_rope_table(float2* tab, const int* len_ptr, int M, int dh, float theta, hipStream_t st);
-hipError_t launch_attention(const bf16* q, const bf16* pool, const int* block_table, const int* len_ptr, KvGeom g,
-                            int layer, int M, int Hq, int split_tokens, float* opart, float* mlpart, bf16* out,
+// y: the fused QKV projection [M][(Hq + 2 Hkv) dh] of M new tokens; tab: their [M][dh/2] (cos, sin) from launch_rope_table.
+// Rotates q and k, appends k and v to the pages and attends over the cache and the new tokens.
+hipError_t launch_attention(const float* y, const float2* tab, bf16* pool, const int* block_table, const int* len_ptr,
+                            KvGeom g, int layer, int M, int Hq, int split_tokens, float* opart, float* mlpart, bf16* out,
                             hipStream_t st);
 size_t attention_workspace_floats(int Hq, int Hkv, int dh, int max_seq);
 // prompt-sized (matrix-core bound) kernels: epilogue 0 = store fp32, 1 = add into fp32, 2 = silu(gate)*up -> bf16

@@ -540,7 +540,7 @@ extern "C" int spec_init(const spec_config* cfg, const spec_model_desc* target, 
   if (!rc) rc = init_model(c->m[SPEC_DRAFT], *draft, *dw, *cfg, (hipStream_t)cfg->stream_draft);
   if (!rc) rc = dev_alloc(&c->qcache, (size_t)c->ring_n * target->vocab);
   if (!rc) rc = dev_alloc(&c->ring, (size_t)SPEC_RING_MAX);
-  if (!rc) rc = dev_alloc(&c->accept_scratch, (size_t)256 + target->vocab);
+  if (!rc) rc = dev_alloc(&c->accept_scratch, accept_scratch_floats(target->vocab));
   if (!rc) rc = dev_alloc(&c->res_dev, (size_t)1);
   if (!rc) {
     hipError_t e = hipMemset(c->ring, 0, SPEC_RING_MAX * sizeof(int));
@@ -1355,7 +1355,7 @@ extern "C" int spec_accept_rows(const float* p_logits, int n_rows, const float* 
   float* scratch = nullptr;
   AcceptResult* res = nullptr;
   hipStream_t st = (hipStream_t)stream;
-  if (hipMalloc((void**)&scratch, (256 + (size_t)vocab) * sizeof(float)) != hipSuccess ||
+  if (hipMalloc((void**)&scratch, accept_scratch_floats(vocab) * sizeof(float)) != hipSuccess ||
       hipMalloc((void**)&res, sizeof(AcceptResult)) != hipSuccess) {
     if (scratch) (void)hipFree(scratch);
     FAIL(SPEC_E_NOMEM, "hipMalloc failed");

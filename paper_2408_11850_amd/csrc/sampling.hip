@@ -5,9 +5,12 @@
 // one-hot at the arg-max (lowest id on ties) for greedy decoding.  A draw is an inverse-CDF walk in
 // ascending token id with one uniform u: the first k whose running sum (fp64) exceeds u * total.
 // The acceptance test is evaluated without a division, in fp64: accept iff r * q[x] <= p[x].
-// One workgroup of 1024 threads handles one vocabulary row.  With a single compute unit per row the kernels are
-// bound by its vector ALU and by the latency of dependent passes, so rows of up to 32768 ids are held in
-// registers and read once (the reg_* functions); longer rows take the generic multi-pass kernels.
+//
+// What bounds them is one compute unit's vector ALU and the latency of dependent passes, so
+//   * up to 32768 ids one workgroup of 1024 threads holds a row in registers and reads it once (the reg_* functions);
+//   * longer rows are cut into pieces of 8192 ids, one workgroup each; what the pieces have to know of each other (row
+//     maximum, sums) goes through a kernel boundary (accept) or is worked out by every workgroup again (sample);
+//   * wave reductions and scans run on DPP row shifts and broadcasts, not on LDS permutes.
 #include <cstring>
 
 #include "spec_internal.h"
@@ -17,162 +20,127 @@
 
 struct MaxIdx { float v; int i; };
 
-__device__ __forceinline__ MaxIdx better(MaxIdx a, MaxIdx b) {
+// ---- wave reductions and scans on DPP ------------------------------------------------------------
+// A lane receives x of the lane that CTRL names (row_shr:n inside rows of 16 lanes; row_bcast:15 / :31 = the last lane
+// of the row(s) before, into the rows of mask RM), or `none` where there is none.
+template <int CTRL, int RM>
+__device__ __forceinline__ int dpp_i(int none, int x) {
+  return __builtin_amdgcn_update_dpp(none, x, CTRL, RM, 0xf, false);
+}
+template <int CTRL, int RM>
+__device__ __forceinline__ float dpp_f(float none, float x) {
+  return __int_as_float(dpp_i<CTRL, RM>(__float_as_int(none), __float_as_int(x)));
+}
+template <int CTRL, int RM>
+__device__ __forceinline__ double dpp_d(double x) {
+  return __hiloint2double(dpp_i<CTRL, RM>(0, __double2hiint(x)), dpp_i<CTRL, RM>(0, __double2loint(x)));
+}
+// inclusive sum over the lanes 0 .. this one; lane 63 holds the total
+__device__ __forceinline__ double wave_scan_d(double x) {
+  x += dpp_d<0x111, 0xf>(x);
+  x += dpp_d<0x112, 0xf>(x);
+  x += dpp_d<0x114, 0xf>(x);
+  x += dpp_d<0x118, 0xf>(x);
+  x += dpp_d<0x142, 0xa>(x);
+  x += dpp_d<0x143, 0xc>(x);
+  return x;
+}
+__device__ __forceinline__ double lane_d(double x, int lane) {
+  return __hiloint2double(__builtin_amdgcn_readlane(__double2hiint(x), lane), __builtin_amdgcn_readlane(__double2loint(x), lane));
+}
+__device__ __forceinline__ MaxIdx better(MaxIdx a, float v, int i) {
   // larger value wins; on equal values the lower index wins
-  if (b.v > a.v || (b.v == a.v && b.i < a.i)) return b;
+  const bool take = (v > a.v) | ((v == a.v) & (i < a.i));
+  a.v = take ? v : a.v;
+  a.i = take ? i : a.i;
   return a;
 }
+// larger value, then lower index, over the wave; to every lane
+__device__ __forceinline__ MaxIdx wave_argmax(MaxIdx m) {
+  float v = m.v;
+  v = fmaxf(v, dpp_f<0x111, 0xf>(-INFINITY, v));
+  v = fmaxf(v, dpp_f<0x112, 0xf>(-INFINITY, v));
+  v = fmaxf(v, dpp_f<0x114, 0xf>(-INFINITY, v));
+  v = fmaxf(v, dpp_f<0x118, 0xf>(-INFINITY, v));
+  v = fmaxf(v, dpp_f<0x142, 0xa>(-INFINITY, v));
+  v = fmaxf(v, dpp_f<0x143, 0xc>(-INFINITY, v));
+  MaxIdx r;
+  r.v = __int_as_float(__builtin_amdgcn_readlane(__float_as_int(v), 63));
+  int i = m.v == r.v ? m.i : 0x7fffffff;
+  i = min(i, dpp_i<0x111, 0xf>(0x7fffffff, i));
+  i = min(i, dpp_i<0x112, 0xf>(0x7fffffff, i));
+  i = min(i, dpp_i<0x114, 0xf>(0x7fffffff, i));
+  i = min(i, dpp_i<0x118, 0xf>(0x7fffffff, i));
+  i = min(i, dpp_i<0x142, 0xa>(0x7fffffff, i));
+  i = min(i, dpp_i<0x143, 0xc>(0x7fffffff, i));
+  r.i = __builtin_amdgcn_readlane(i, 63);
+  return r;
+}
 
-__device__ MaxIdx block_argmax(MaxIdx m, MaxIdx* sh) {
-#pragma unroll
-  for (int o = 32; o > 0; o >>= 1) {
-    MaxIdx t;
-    t.v = __shfl_xor(m.v, o);
-    t.i = __shfl_xor(m.i, o);
-    m = better(m, t);
-  }
-  const int w = threadIdx.x >> 6;
-  if ((threadIdx.x & 63) == 0) sh[w] = m;
+__device__ __forceinline__ MaxIdx block_argmax(MaxIdx m, MaxIdx* sh) {
+  const int lane = threadIdx.x & 63;
+  m = wave_argmax(m);
+  if (lane == 0) sh[threadIdx.x >> 6] = m;
   __syncthreads();
-  MaxIdx r = sh[0];
-  for (int i = 1; i < SAMP_WAVES; ++i) r = better(r, sh[i]);
+  MaxIdx r;
+  r.v = -INFINITY; r.i = 0x7fffffff;
+  if (lane < SAMP_WAVES) r = sh[lane];
+  r = wave_argmax(r);
   __syncthreads();
   return r;
 }
 
-__device__ double block_sum_d(double v, double* sh) {
-#pragma unroll
-  for (int o = 32; o > 0; o >>= 1) v += __shfl_xor(v, o);
-  const int w = threadIdx.x >> 6;
-  if ((threadIdx.x & 63) == 0) sh[w] = v;
+__device__ __forceinline__ double block_sum_d(double v, double* sh) {
+  const int lane = threadIdx.x & 63;
+  v = wave_scan_d(v);
+  if (lane == 63) sh[threadIdx.x >> 6] = v;
   __syncthreads();
-  double r = 0.0;
-  for (int i = 0; i < SAMP_WAVES; ++i) r += sh[i];
+  const double r = lane_d(wave_scan_d(lane < SAMP_WAVES ? sh[lane] : 0.0), 63);
   __syncthreads();
   return r;
 }
 
-// Row statistics: arg-max of the logits and sum_j exp(mult*(l_j - max)).
-__device__ void row_stats(const float* __restrict__ logits, int V, float mult, MaxIdx* shm, double* shd,
-                          MaxIdx& top, float& sum) {
-  MaxIdx m;
-  m.v = -INFINITY; m.i = 0x7fffffff;
-  for (int j = threadIdx.x; j < V; j += SAMP_THREADS) {
-    MaxIdx t; t.v = logits[j]; t.i = j;
-    m = better(m, t);
-  }
-  top = block_argmax(m, shm);
-  float acc = 0.f;
-  const float zmax = top.v * mult;
-  for (int j = threadIdx.x; j < V; j += SAMP_THREADS) acc += expf(logits[j] * mult - zmax);
-  sum = (float)block_sum_d((double)acc, shd);
-}
-
-// Inverse-CDF draw from the non-negative weights w[0..V) (device memory, fp32) with uniform u.
-// Thread t owns the contiguous ids [t*C, (t+1)*C).  Returns the token to every thread.
-__device__ int block_inverse_cdf(const float* __restrict__ w, int V, float u, double* shd, int* shi, double* total_out) {
-  const int C = (V + SAMP_THREADS - 1) / SAMP_THREADS;
-  const int b = threadIdx.x * C;
-  int e = b + C;
-  if (e > V) e = V;
-  double local = 0.0;
-  for (int j = b; j < e; ++j) local += (double)w[j];
-  // inclusive scan over threads: wave scan, then scan of the wave totals
-  double incl = local;
+// Four consecutive values, at any 4-byte alignment (rows of a vocabulary that is no multiple of four), `fill` beyond V.
+typedef float f32x4u __attribute__((ext_vector_type(4), aligned(4)));
+__device__ __forceinline__ f32x4 load4(const float* __restrict__ row, int j, int V, float fill) {
+  f32x4 v = {fill, fill, fill, fill};
+  if (j + 4 <= V) {
+    v = *reinterpret_cast<const f32x4u*>(row + j);
+  } else {
 #pragma unroll
-  for (int o = 1; o < 64; o <<= 1) {
-    double t = __shfl_up(incl, o);
-    if ((threadIdx.x & 63) >= o) incl += t;
-  }
-  const int wv = threadIdx.x >> 6;
-  if ((threadIdx.x & 63) == 63) shd[wv] = incl;
-  if (threadIdx.x == 0) shi[0] = 0x7fffffff;
-  __syncthreads();
-  double base = 0.0, total = 0.0;
-  for (int i = 0; i < SAMP_WAVES; ++i) {
-    if (i < wv) base += shd[i];
-    total += shd[i];
-  }
-  incl += base;
-  const double target = (double)u * total;
-  if (incl > target && local > 0.0) atomicMin(&shi[0], (int)threadIdx.x);
-  __syncthreads();
-  const int owner = shi[0];
-  __syncthreads();
-  if ((int)threadIdx.x == owner) {
-    double run = incl - local;
-    int k = -1, lastpos = -1;
-    for (int j = b; j < e; ++j) {
-      const double wj = (double)w[j];
-      run += wj;
-      if (wj > 0.0) lastpos = j;
-      if (run > target && wj > 0.0) { k = j; break; }
-    }
-    shi[1] = k >= 0 ? k : lastpos;
-  }
-  __syncthreads();
-  int tok = shi[1];
-  if (owner == 0x7fffffff) tok = -1;   // no mass at all
-  if (total_out) *total_out = total;
-  __syncthreads();
-  return tok;
-}
-
-// ---- draft: q = softmax(mult*logits), x = invCDF(q, u) -------------------------------------
-__global__ __launch_bounds__(SAMP_THREADS) void sample_row_kernel(const float* __restrict__ logits, int V, float mult,
-                                                                  int greedy, float u, float* __restrict__ q_out,
-                                                                  int* __restrict__ tok_out) {
-  __shared__ MaxIdx shm[SAMP_WAVES];
-  __shared__ double shd[SAMP_WAVES];
-  __shared__ int shi[2];
-  MaxIdx top;
-  float sum;
-  if (greedy) {
-    MaxIdx m;
-    m.v = -INFINITY; m.i = 0x7fffffff;
-    for (int j = threadIdx.x; j < V; j += SAMP_THREADS) {
-      MaxIdx t; t.v = logits[j]; t.i = j;
-      m = better(m, t);
-    }
-    top = block_argmax(m, shm);
-    for (int j = threadIdx.x; j < V; j += SAMP_THREADS) q_out[j] = (j == top.i) ? 1.0f : 0.0f;
-    if (threadIdx.x == 0) tok_out[0] = top.i;
-    return;
-  }
-  row_stats(logits, V, mult, shm, shd, top, sum);
-  const float zmax = top.v * mult;
-  for (int j = threadIdx.x; j < V; j += SAMP_THREADS) q_out[j] = expf(logits[j] * mult - zmax) / sum;
-  __threadfence_block();
-  __syncthreads();
-  const int tok = block_inverse_cdf(q_out, V, u, shd, shi, nullptr);
-  if (threadIdx.x == 0) tok_out[0] = tok;
-}
-
-// The same draw for vocabularies of up to 32768 ids with the row held in registers: wave w owns the ids
-// [w R 64, (w+1) R 64) (R = rows of 64 ids per wave), lane l of it the ids w R 64 + 64 k + l, so every load and
-// store is a coalesced 256-byte run and the logits are read once.  The inverse-CDF walk is three nested searches
-// in ascending id order, all sums in fp64: wave (scan of the 16 wave totals), row of 64 ids (scan of the wave's
-// row totals), lane (scan of the row).  The row totals come from one transposing butterfly (32 exchanges for 32
-// rows instead of 6 per row): each exchange halves the rows a lane still carries.
-#define SAMP_ROWS_MAX 32
-__device__ __forceinline__ double scan_up_d(double v, int lane, int width) {
-#pragma unroll
-  for (int o = 1; o < 64; o <<= 1) {
-    const double t = __shfl_up(v, o);
-    if (o < width && lane >= o) v += t;
+    for (int i = 0; i < 4; ++i)
+      if (j + i < V) v[i] = row[j + i];
   }
   return v;
 }
-struct RegGeom {          // which ids a thread owns: row0 + 64 k + lane, k < R
-  int R, w, lane, row0, j0;
+__device__ __forceinline__ void store4(float* __restrict__ row, int j, int V, f32x4 v) {
+  if ((V & 3) == 0) {
+    if (j < V) *reinterpret_cast<f32x4u*>(row + j) = v;
+  } else if (j + 4 <= V) {
+    *reinterpret_cast<f32x4u*>(row + j) = v;
+  } else {
+#pragma unroll
+    for (int i = 0; i < 4; ++i)
+      if (j + i < V) row[j + i] = v[i];
+  }
+}
+
+// ---- a row, or a piece of one, in the registers of a workgroup ------------------------------------
+// Wave w owns the ids [w R 256, (w + 1) R 256), lane l of it the four ids w R 256 + 256 k + 4 l .. + 3 of every k < R.
+#define SAMP_CHUNKS_MAX 8
+#define SAMP_REG_VOCAB_MAX (SAMP_CHUNKS_MAX * 4 * SAMP_THREADS)
+#define SAMP_PIECE 8192
+#define SAMP_PIECE_CHUNKS (SAMP_PIECE / (4 * SAMP_THREADS))
+struct RegGeom {
+  int R, w, lane, j0;
+  __device__ __forceinline__ int id(int k) const { return j0 + 256 * k; }
 };
 __device__ __forceinline__ RegGeom reg_geom(int V) {
   RegGeom g;
-  g.R = (V + SAMP_THREADS - 1) / SAMP_THREADS;
-  g.w = threadIdx.x >> 6;
+  g.R = (V + 4 * SAMP_THREADS - 1) / (4 * SAMP_THREADS);
+  g.w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   g.lane = threadIdx.x & 63;
-  g.row0 = g.w * g.R * 64;
-  g.j0 = g.row0 + g.lane;
+  g.j0 = g.w * g.R * 256 + g.lane * 4;
   return g;
 }
 // probability of a logit given the row's statistics: hardware exp2 (1 ulp) of a product rounded once, times the
@@ -180,153 +148,300 @@ __device__ __forceinline__ RegGeom reg_geom(int V) {
 // logits carry.  Every kernel of the register path forms p and q with this one expression.
 __device__ __forceinline__ float reg_prob(float l, float mult, float zmax, float inv) { return __expf(l * mult - zmax) * inv; }
 
-// Loads the row once; returns the arg-max, sum_j exp(mult l_j - zmax) and e[k] = exp(mult l - zmax) (0 outside V).
-__device__ __forceinline__ void reg_softmax(const float* __restrict__ row, int V, float mult, const RegGeom& g,
-                                            float (&e)[SAMP_ROWS_MAX], MaxIdx& top, float& sum, MaxIdx* shm,
-                                            double* shd) {
+// A thread's chunks of a row, `fill` beyond V.  Where no vector straddles the end the loads are unconditional (lanes
+// beyond the end read the last vector): behind branches each would be waited for before the next goes out.
+template <int CH>
+__device__ __forceinline__ void reg_fetch(const float* __restrict__ row, int V, const RegGeom& g, float fill, f32x4 (&e)[CH]) {
+  if ((V & 3) == 0) {
+#pragma unroll
+    for (int k = 0; k < CH; ++k) e[k] = *reinterpret_cast<const f32x4u*>(row + min(g.id(k), V - 4));
+#pragma unroll
+    for (int k = 0; k < CH; ++k)
+      if (k >= g.R || g.id(k) >= V) e[k] = f32x4{fill, fill, fill, fill};
+  } else {
+#pragma unroll
+    for (int k = 0; k < CH; ++k) {
+      e[k] = f32x4{fill, fill, fill, fill};
+      if (k < g.R) e[k] = load4(row, g.id(k), V, fill);
+    }
+  }
+}
+template <int CH>
+__device__ __forceinline__ MaxIdx reg_load(const float* __restrict__ row, int V, const RegGeom& g, f32x4 (&e)[CH]) {
   MaxIdx m;
   m.v = -INFINITY; m.i = 0x7fffffff;
+  reg_fetch(row, V, g, __builtin_nanf(""), e);     // which wins no comparison
 #pragma unroll
-  for (int k = 0; k < SAMP_ROWS_MAX; ++k) {
-    const int j = g.j0 + 64 * k;
-    const bool in = k < g.R && j < V;
-    e[k] = in ? row[j] : -INFINITY;
-    if (in && e[k] > m.v) { m.v = e[k]; m.i = j; }   // ids ascend with k: a strict test keeps the lowest id on ties
-  }
-  top = block_argmax(m, shm);
+  for (int k = 0; k < CH; ++k)
+#pragma unroll
+    for (int i = 0; i < 4; ++i) m = better(m, e[k][i], g.id(k) + i);
+  return m;
+}
+
+// Loads the row once; returns the arg-max, sum_j exp(mult l_j - zmax) and e[k] = exp(mult l - zmax) (0 outside V).
+__device__ __forceinline__ void reg_softmax(const float* __restrict__ row, int V, float mult, const RegGeom& g,
+                                            f32x4 (&e)[SAMP_CHUNKS_MAX], MaxIdx& top, float& sum, MaxIdx* shm, double* shd) {
+  top = block_argmax(reg_load(row, V, g, e), shm);
   const float zmax = top.v * mult;
   float acc = 0.f;
 #pragma unroll
-  for (int k = 0; k < SAMP_ROWS_MAX; ++k) {
-    const int j = g.j0 + 64 * k;
-    e[k] = (k < g.R && j < V) ? __expf(e[k] * mult - zmax) : 0.f;
-    acc += e[k];
+  for (int k = 0; k < SAMP_CHUNKS_MAX; ++k) {
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+      const float x = __expf(e[k][i] * mult - zmax);
+      e[k][i] = ((k < g.R) & (g.id(k) + i < V)) ? x : 0.f;
+    }
+    acc += (e[k][0] + e[k][1]) + (e[k][2] + e[k][3]);
   }
   sum = (float)block_sum_d((double)acc, shd);
 }
 
-// Inverse-CDF draw over the non-negative weights e[] (0 outside V).  Returns the id to every thread, -1 if the
-// weights have no mass; *total_out = their fp64 sum.  rt: [SAMP_WAVES][SAMP_ROWS_MAX + 1] doubles, shi: 1 int.
+__device__ __forceinline__ double sum4_d(f32x4 v) { return ((double)v[0] + (double)v[1]) + ((double)v[2] + (double)v[3]); }
+
+// One wave's part of the walk: the first id of its chunks whose running sum, from `base` on, exceeds target; the last
+// id with mass if rounding lets the search run off its end, or if `clamp` asks for that one.  The wave has mass.
+template <int CH>
+__device__ __forceinline__ int wave_walk(const f32x4 (&e)[CH], int j0, int lane, double base, double target, bool clamp) {
+  int lastpos = -1;
+#pragma unroll
+  for (int k = 0; k < CH; ++k)
+#pragma unroll
+    for (int i = 0; i < 4; ++i)
+      lastpos = e[k][i] > 0.f ? j0 + 256 * k + i : lastpos;
+#pragma unroll
+  for (int o = 32; o > 0; o >>= 1) lastpos = max(lastpos, __shfl_xor(lastpos, o));
+  int tok = -1;
+#pragma unroll
+  for (int k = 0; k < CH; ++k) {
+    if (tok >= 0 || clamp) continue;             // uniform over the wave
+    f32x4 v = e[k];
+    asm volatile("" : "+v"(v));                  // keeps the fp64 values of reg_draw's sums from being held for here
+    const double s = sum4_d(v);
+    const double incl = wave_scan_d(s);
+    const double tot = lane_d(incl, 63);
+    if (tot > 0.0 && base + tot > target) {
+      const unsigned long long pos = __ballot(s > 0.0), hit = __ballot(s > 0.0 && base + incl > target);
+      const int l = hit ? __ffsll((long long)hit) - 1 : 63 - __clzll((long long)pos);
+      double run = base + (incl - s);
+      int mine = -1, lastm = -1;
+#pragma unroll
+      for (int i = 0; i < 4; ++i) {
+        run += (double)v[i];
+        const bool mass = v[i] > 0.f;
+        lastm = mass ? j0 + 256 * k + i : lastm;
+        mine = (mass & (mine < 0) & (run > target)) ? lastm : mine;
+      }
+      tok = __builtin_amdgcn_readlane(mine >= 0 ? mine : lastm, l);
+    }
+    base += tot;
+  }
+  return tok >= 0 ? tok : lastpos;
+}
+
+// Inverse-CDF draw over the non-negative weights e[] (0 outside V): first the wave (scan of the 16 wave totals), then
+// its chunks of 256 ids, the lane, the id, all sums in fp64.  Returns the id to every thread, -1 if the weights have no
+// mass; *total_out = their sum.  `before` and `target` serve a caller whose weights are a piece of a longer row: the
+// sum ahead of the piece and the value to exceed (target < 0: u times the total).  shd: SAMP_WAVES doubles, shi: 1 int.
 // Every thread of the workgroup must call it (two barriers inside).
-__device__ __forceinline__ int reg_draw(const float (&e)[SAMP_ROWS_MAX], const RegGeom& g, float u,
-                                        double (*rt)[SAMP_ROWS_MAX + 1], int* shi, double* total_out) {
-  const int lane = g.lane, w = g.w;
-  // transposing butterfly: after the exchange over lane bit b a lane carries half of its rows, summed over both
-  // partners; after bits 5..1 it carries row (lane >> 1), after bit 0 both lanes of a pair hold that row's total
-  double a[SAMP_ROWS_MAX / 2];
-  {
-    const bool hi = (lane & 32) != 0;
+template <int CH>
+__device__ __forceinline__ int reg_draw(const f32x4 (&e)[CH], const RegGeom& g, float u, double before, double target,
+                                        double* shd, int* shi, double* total_out) {
+  double mine = 0.0;
 #pragma unroll
-    for (int i = 0; i < SAMP_ROWS_MAX / 2; ++i) {
-      const float x = e[i], y = e[i + SAMP_ROWS_MAX / 2];
-      asm volatile("" ::"v"(x), "v"(y));        // a second use keeps the choice a select of values, not of indices
-      const double send = (double)(hi ? x : y);
-      const double keep = (double)(hi ? y : x);
-      a[i] = keep + __shfl_xor(send, 32);
-    }
-  }
-#pragma unroll
-  for (int half = SAMP_ROWS_MAX / 4, off = 16; half >= 1; half >>= 1, off >>= 1) {
-    const bool hi = (lane & off) != 0;
-#pragma unroll
-    for (int i = 0; i < half; ++i) {
-      const double x = a[i], y = a[i + half];
-      asm volatile("" ::"v"(x), "v"(y));
-      const double send = hi ? x : y;
-      const double keep = hi ? y : x;
-      a[i] = keep + __shfl_xor(send, off);
-    }
-  }
-  a[0] += __shfl_xor(a[0], 1);
-  if ((lane & 1) == 0) rt[w][lane >> 1] = a[0];
+  for (int k = 0; k < CH; ++k) mine += sum4_d(e[k]);
+  const double winc = wave_scan_d(mine);
+  if (g.lane == 63) shd[g.w] = winc;
   __syncthreads();
-  // every wave: the 16 wave totals (lane i < 16 sums wave i's rows in order), their scan, the owner wave
-  double wt = 0.0;
-  if (lane < SAMP_WAVES) {
-    for (int k = 0; k < SAMP_ROWS_MAX; ++k) wt += rt[lane][k];
-  }
-  const double wincl = scan_up_d(wt, lane, SAMP_WAVES);
-  const double total = __shfl(wincl, SAMP_WAVES - 1);
+  const double wt = g.lane < SAMP_WAVES ? shd[g.lane] : 0.0;
+  const double wincl = wave_scan_d(wt);
+  const double total = lane_d(wincl, SAMP_WAVES - 1);
   if (total_out) *total_out = total;
-  const double target = (double)u * total;
-  const unsigned long long wmass = __ballot(lane < SAMP_WAVES && wt > 0.0);
-  const unsigned long long whit = __ballot(lane < SAMP_WAVES && wt > 0.0 && wincl > target);
+  if (target < 0.0) target = (double)u * total;
+  const unsigned long long wmass = __ballot(g.lane < SAMP_WAVES && wt > 0.0);
+  const unsigned long long whit = __ballot(g.lane < SAMP_WAVES && wt > 0.0 && before + wincl > target);
   // rounding can leave the target at or beyond the total: then the draw is the last id with mass
   const bool clamp = whit == 0;
   const int owner = !wmass ? -1 : (clamp ? 63 - __clzll((long long)wmass) : __ffsll((long long)whit) - 1);
   if (threadIdx.x == 0 && owner < 0) shi[0] = -1;      // no mass at all
-  if (w == owner) {
-    double wexcl = __shfl_up(wincl, 1);
-    if (lane == 0) wexcl = 0.0;
-    const double base = __shfl(wexcl, owner);
-    // the last id of this wave with mass (the fallback wherever rounding lets a search run off its end)
-    int lastpos = -1;
-#pragma unroll
-    for (int k = 0; k < SAMP_ROWS_MAX; ++k)
-      if (e[k] > 0.f) lastpos = g.j0 + 64 * k;
-#pragma unroll
-    for (int o = 32; o > 0; o >>= 1) lastpos = max(lastpos, __shfl_xor(lastpos, o));
-    // row search: lane k < 32 holds row k's total
-    const double rtk = lane < SAMP_ROWS_MAX ? rt[w][lane] : 0.0;
-    const double rincl = scan_up_d(rtk, lane, SAMP_ROWS_MAX);
-    const unsigned long long rhit = __ballot(lane < SAMP_ROWS_MAX && rtk > 0.0 && base + rincl > target);
-    int tok = lastpos;
-    if (!clamp && rhit) {
-      const int row = __ffsll((long long)rhit) - 1;
-      double rexcl = __shfl_up(rincl, 1);
-      if (lane == 0) rexcl = 0.0;
-      const double rbase = base + __shfl(rexcl, row);
-      float qf = 0.f;
-#pragma unroll
-      for (int k = 0; k < SAMP_ROWS_MAX; ++k) qf = (k == row) ? e[k] : qf;
-      const double qk = (double)qf;
-      const double incl = scan_up_d(qk, lane, 64);
-      const unsigned long long pos = __ballot(qk > 0.0);
-      const unsigned long long hit = __ballot(qk > 0.0 && rbase + incl > target);
-      const int l = hit ? __ffsll((long long)hit) - 1 : 63 - __clzll((long long)pos);   // pos != 0: the row has mass
-      tok = g.row0 + 64 * row + l;
-    }
-    if (lane == 0) shi[0] = tok;
+  if (g.w == owner) {
+    const double base = before + (owner > 0 ? lane_d(wincl, owner > 0 ? owner - 1 : 0) : 0.0);
+    const int tok = wave_walk(e, g.j0, g.lane, base, target, clamp);
+    if (g.lane == 0) shi[0] = tok;
   }
   __syncthreads();
   return shi[0];
 }
 
+// ---- draft: q = softmax(mult*logits), x = invCDF(q, u) -------------------------------------
 __global__ __launch_bounds__(SAMP_THREADS) void sample_row_reg_kernel(const float* __restrict__ logits, int V, float mult,
-                                                                      float u, float* __restrict__ q_out,
+                                                                      int greedy, float u, float* __restrict__ q_out,
                                                                       int* __restrict__ tok_out) {
   __shared__ MaxIdx shm[SAMP_WAVES];
   __shared__ double shd[SAMP_WAVES];
-  __shared__ double rt[SAMP_WAVES][SAMP_ROWS_MAX + 1];   // row totals, one padded line per wave
   __shared__ int shi[1];
   const RegGeom g = reg_geom(V);
-  float e[SAMP_ROWS_MAX];
+  f32x4 e[SAMP_CHUNKS_MAX];
   MaxIdx top;
+  if (greedy) {
+    top = block_argmax(reg_load(logits, V, g, e), shm);
+#pragma unroll
+    for (int k = 0; k < SAMP_CHUNKS_MAX; ++k) {
+      f32x4 o;
+#pragma unroll
+      for (int i = 0; i < 4; ++i) o[i] = g.id(k) + i == top.i ? 1.0f : 0.0f;
+      if (k < g.R) store4(q_out, g.id(k), V, o);
+    }
+    if (threadIdx.x == 0) tok_out[0] = top.i;
+    return;
+  }
   float sum;
   reg_softmax(logits, V, mult, g, e, top, sum, shm, shd);
   const float inv = 1.0f / sum;
 #pragma unroll
-  for (int k = 0; k < SAMP_ROWS_MAX; ++k) {
-    const int j = g.j0 + 64 * k;
-    e[k] = e[k] * inv;
-    if (k < g.R && j < V) q_out[j] = e[k];
+  for (int k = 0; k < SAMP_CHUNKS_MAX; ++k) {
+#pragma unroll
+    for (int i = 0; i < 4; ++i) e[k][i] *= inv;
+    if (k < g.R) store4(q_out, g.id(k), V, e[k]);
   }
-  const int tok = reg_draw(e, g, u, rt, shi, nullptr);
+  const int tok = reg_draw(e, g, u, 0.0, -1.0, shd, shi, nullptr);
+  if (threadIdx.x == 0) tok_out[0] = tok;
+}
+
+// Rows beyond the registers of a workgroup: workgroup p works out the whole row's maximum and sum again (the row comes
+// from L2) and writes its piece of q (greedy: of the one-hot); the draw is a launch of its own.
+__global__ __launch_bounds__(SAMP_THREADS) void sample_piece_kernel(const float* __restrict__ logits, int V, float mult,
+                                                                    int greedy, float* __restrict__ q_out,
+                                                                    int* __restrict__ tok_out) {
+  __shared__ MaxIdx shm[SAMP_WAVES];
+  __shared__ double shd[SAMP_WAVES];
+  MaxIdx m;
+  m.v = -INFINITY; m.i = 0x7fffffff;
+#pragma unroll 4
+  for (int j = 4 * threadIdx.x; j < V; j += 4 * SAMP_THREADS) {
+    const f32x4 v = load4(logits, j, V, -INFINITY);
+#pragma unroll
+    for (int i = 0; i < 4; ++i)
+      if (j + i < V) m = better(m, v[i], j + i);
+  }
+  const MaxIdx top = block_argmax(m, shm);
+  const int first = blockIdx.x * SAMP_PIECE, end = min(first + SAMP_PIECE, V);
+  if (greedy) {
+    for (int j = first + 4 * threadIdx.x; j < end; j += 4 * SAMP_THREADS) {
+      f32x4 o;
+#pragma unroll
+      for (int i = 0; i < 4; ++i) o[i] = j + i == top.i ? 1.0f : 0.0f;
+      store4(q_out, j, V, o);
+    }
+    if (blockIdx.x == 0 && threadIdx.x == 0) tok_out[0] = top.i;
+    return;
+  }
+  const float zmax = top.v * mult;
+  float acc = 0.f;
+#pragma unroll 4
+  for (int j = 4 * threadIdx.x; j < V; j += 4 * SAMP_THREADS) {
+    const f32x4 v = load4(logits, j, V, -INFINITY);
+    f32x4 x;
+#pragma unroll
+    for (int i = 0; i < 4; ++i) x[i] = j + i < V ? expf(v[i] * mult - zmax) : 0.f;
+    acc += (x[0] + x[1]) + (x[2] + x[3]);
+  }
+  const float sum = (float)block_sum_d((double)acc, shd);
+  for (int j = first + 4 * threadIdx.x; j < end; j += 4 * SAMP_THREADS) {
+    f32x4 v = load4(logits, j, V, -INFINITY);
+#pragma unroll
+    for (int i = 0; i < 4; ++i) v[i] = expf(v[i] * mult - zmax) / sum;
+    store4(q_out, j, V, v);
+  }
+}
+
+// Inverse-CDF draw from the non-negative weights w[0 .. V) in memory by one workgroup: 16 ranges, one per wave, whose
+// sums find the owner; its range again in 16, and so on until a range fits the registers of the workgroup.  Returns
+// the id to every thread, -1 if there is no mass.  The barriers inside also separate it from what wrote w.
+__device__ int block_draw(const float* __restrict__ w, int V, float u, double* shd, int* shi) {
+  __threadfence_block();
+  __syncthreads();
+  const int lane = threadIdx.x & 63, wv = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  int first = 0, n = V;
+  double before = 0.0, target = -1.0;
+  while (n > SAMP_PIECE) {
+    const int per = ((n + SAMP_WAVES - 1) / SAMP_WAVES + 255) / 256 * 256;
+    const int b = first + wv * per, e = min(b + per, first + n);
+    double mine = 0.0;
+#pragma unroll 4
+    for (int j = b + 4 * lane; j < e; j += 256) mine += sum4_d(load4(w, j, e, 0.f));
+    mine = wave_scan_d(mine);
+    if (lane == 63) shd[wv] = mine;
+    __syncthreads();
+    const double wt = lane < SAMP_WAVES ? shd[lane] : 0.0;
+    __syncthreads();
+    const double wincl = wave_scan_d(wt);
+    const double total = lane_d(wincl, SAMP_WAVES - 1);
+    if (target < 0.0) target = (double)u * total;
+    const unsigned long long wmass = __ballot(lane < SAMP_WAVES && wt > 0.0);
+    const unsigned long long whit = __ballot(lane < SAMP_WAVES && wt > 0.0 && before + wincl > target);
+    if (!wmass) return -1;
+    const int owner = whit ? __ffsll((long long)whit) - 1 : 63 - __clzll((long long)wmass);
+    if (owner > 0) before += lane_d(wincl, owner - 1);
+    const int nb = first + owner * per;
+    n = min(per, first + n - nb);
+    first = nb;
+  }
+  const RegGeom g = reg_geom(n);
+  f32x4 e[SAMP_PIECE_CHUNKS];
+  reg_fetch(w + first, n, g, 0.f, e);
+  const int tok = reg_draw(e, g, u, before, target, shd, shi, nullptr);
+  return tok < 0 ? -1 : first + tok;
+}
+
+__global__ __launch_bounds__(SAMP_THREADS) void draw_kernel(const float* __restrict__ w, int V, float u, int* __restrict__ tok_out) {
+  __shared__ double shd[SAMP_WAVES];
+  __shared__ int shi[1];
+  const int tok = block_draw(w, V, u, shd, shi);
   if (threadIdx.x == 0) tok_out[0] = tok;
 }
 
 hipError_t launch_sample_row(const float* logits, int V, float mult, int greedy, float u, float* q_out, int* tok_out,
                              hipStream_t st) {
-  if (!greedy && V <= SAMP_ROWS_MAX * SAMP_THREADS) {
-    sample_row_reg_kernel<<<1, SAMP_THREADS, 0, st>>>(logits, V, mult, u, q_out, tok_out);
-  } else {
-    sample_row_kernel<<<1, SAMP_THREADS, 0, st>>>(logits, V, mult, greedy, u, q_out, tok_out);
+  if (V <= SAMP_REG_VOCAB_MAX) {
+    sample_row_reg_kernel<<<1, SAMP_THREADS, 0, st>>>(logits, V, mult, greedy, u, q_out, tok_out);
+    return hipGetLastError();
   }
+  sample_piece_kernel<<<(V + SAMP_PIECE - 1) / SAMP_PIECE, SAMP_THREADS, 0, st>>>(logits, V, mult, greedy, q_out, tok_out);
+  hipError_t e = hipGetLastError();
+  if (e != hipSuccess || greedy) return e;
+  draw_kernel<<<1, SAMP_THREADS, 0, st>>>(q_out, V, u, tok_out);
   return hipGetLastError();
 }
 
 // ---- target: per-row test, then first rejection + resampling ---------------------------------
-// stats layout per row i: [0] = max logit, [1] = sum exp, [2] = arg-max (as int bits), [3] = accept flag
+// Scratch of an acceptance: [0, 256) four statistics per row: max logit, sum exp, arg-max (as int bits), accept flag;
+// then, for vocabularies beyond SAMP_REG_VOCAB_MAX, three floats per (row, piece): max logit, sum exp relative to it,
+// arg-max; the pieces' weight sums (doubles); and the row of V weights a draw walks over.
+__host__ __device__ static constexpr int accept_pieces(int V) { return V <= SAMP_REG_VOCAB_MAX ? 0 : (V + SAMP_PIECE - 1) / SAMP_PIECE; }
+__host__ __device__ static constexpr size_t accept_sums_at(int V) { return 256 + (size_t)accept_pieces(V) * SPEC_MAX_TOKENS * 3; }
+__host__ __device__ static constexpr size_t accept_weights_at(int V) { return accept_sums_at(V) + (size_t)accept_pieces(V) * 2; }
+static constexpr size_t accept_scratch_floats_of(int V) { return accept_weights_at(V) + (size_t)V; }
+size_t accept_scratch_floats(int V) { return accept_scratch_floats_of(V); }
+
+// what row i's test needs from its statistics, by one thread
+__device__ __forceinline__ int accept_test(const float* __restrict__ row, int i, int V, float mult, int greedy, float top,
+                                           float sum, int amax, const float* __restrict__ qcache,
+                                           const int* __restrict__ ring, const int* __restrict__ x_direct,
+                                           const AcceptArgs& a) {
+  if (i >= a.n_test) return 0;
+  const int x = x_direct ? x_direct[i] : ring[a.slot[i]];
+  const float* qrow = x_direct ? qcache + (size_t)i * V : qcache + (size_t)a.slot[i] * V;
+  int acc;
+  if (greedy) {
+    acc = x == amax;
+  } else {
+    const float px = V <= SAMP_REG_VOCAB_MAX ? reg_prob(row[x], mult, top * mult, 1.0f / sum) : expf(row[x] * mult - top * mult) / sum;
+    acc = (double)a.r[i] * (double)qrow[x] <= (double)px;
+  }
+  if (a.force_mask >= 0) acc = (int)((a.force_mask >> i) & 1);
+  return acc;
+}
+
 __global__ __launch_bounds__(SAMP_THREADS) void accept_rows_kernel(const float* __restrict__ logits, int V, float mult,
                                                                    int greedy, const float* __restrict__ qcache,
                                                                    const int* __restrict__ ring,
@@ -336,122 +451,241 @@ __global__ __launch_bounds__(SAMP_THREADS) void accept_rows_kernel(const float* 
   __shared__ double shd[SAMP_WAVES];
   const int i = blockIdx.x;
   const float* row = logits + (size_t)i * V;
-  const bool reg = V <= SAMP_ROWS_MAX * SAMP_THREADS;   // the row fits the registers of the workgroup
+  const RegGeom g = reg_geom(V);
+  f32x4 e[SAMP_CHUNKS_MAX];
   MaxIdx top;
   float sum = 1.f;
-  if (greedy) {
-    MaxIdx m;
-    m.v = -INFINITY; m.i = 0x7fffffff;
-    for (int j = threadIdx.x; j < V; j += SAMP_THREADS) {
-      MaxIdx t; t.v = row[j]; t.i = j;
-      m = better(m, t);
-    }
-    top = block_argmax(m, shm);
-  } else if (reg) {
-    float e[SAMP_ROWS_MAX];
-    reg_softmax(row, V, mult, reg_geom(V), e, top, sum, shm, shd);
-  } else {
-    row_stats(row, V, mult, shm, shd, top, sum);
-  }
+  if (greedy) top = block_argmax(reg_load(row, V, g, e), shm);
+  else reg_softmax(row, V, mult, g, e, top, sum, shm, shd);
   if (threadIdx.x == 0) {
-    int acc = 0;
-    if (i < a.n_test) {
-      const int x = x_direct ? x_direct[i] : ring[a.slot[i]];
-      const float* qrow = x_direct ? qcache + (size_t)i * V : qcache + (size_t)a.slot[i] * V;
-      if (greedy) {
-        acc = (x == top.i);
-      } else {
-        const float px = reg ? reg_prob(row[x], mult, top.v * mult, 1.0f / sum) : expf(row[x] * mult - top.v * mult) / sum;
-        acc = ((double)a.r[i] * (double)qrow[x] <= (double)px);
-      }
-      if (a.force_mask >= 0) acc = (int)((a.force_mask >> i) & 1);
-    }
     stats[i * 4 + 0] = top.v;
     stats[i * 4 + 1] = sum;
     stats[i * 4 + 2] = __int_as_float(top.i);
-    stats[i * 4 + 3] = __int_as_float(acc);
+    stats[i * 4 + 3] = __int_as_float(accept_test(row, i, V, mult, greedy, top.v, sum, top.i, qcache, ring, x_direct, a));
   }
 }
 
-// One workgroup: n = first rejection; draw from norm(max(0, p_n - q_n)) (from p_n if that has no
-// mass), or the bonus / autoregressive token from the row after the last test.  `wbuf` is a
-// scratch row of V floats holding the weights the draw walks over.
-__global__ __launch_bounds__(SAMP_THREADS) void accept_finish_kernel(const float* __restrict__ logits, int V,
-                                                                     float mult, int greedy,
-                                                                     const float* __restrict__ qcache,
-                                                                     const int* __restrict__ ring,
-                                                                     const int* __restrict__ x_direct, AcceptArgs a,
-                                                                     const float* __restrict__ stats,
-                                                                     float* __restrict__ wbuf,
-                                                                     AcceptResult* __restrict__ res,
-                                                                     int* __restrict__ out2) {
+// long rows: statistics of one piece of one row
+__global__ __launch_bounds__(SAMP_THREADS) void accept_piece_kernel(const float* __restrict__ logits, int V, float mult,
+                                                                    int greedy, float* __restrict__ scratch) {
+  __shared__ MaxIdx shm[SAMP_WAVES];
   __shared__ double shd[SAMP_WAVES];
-  __shared__ int shi[2];
-  __shared__ double rt[SAMP_WAVES][SAMP_ROWS_MAX + 1];
+  const int p = blockIdx.x, i = blockIdx.y, first = p * SAMP_PIECE, n = min(SAMP_PIECE, V - first);
+  const RegGeom g = reg_geom(SAMP_PIECE);
+  f32x4 e[SAMP_PIECE_CHUNKS];
+  const MaxIdx top = block_argmax(reg_load(logits + (size_t)i * V + first, n, g, e), shm);
+  float sum = 0.f;
+  if (!greedy) {
+    const float zmax = top.v * mult;
+    float acc = 0.f;
+#pragma unroll
+    for (int k = 0; k < SAMP_PIECE_CHUNKS; ++k) {
+#pragma unroll
+      for (int j = 0; j < 4; ++j) e[k][j] = g.id(k) + j < n && top.v > -INFINITY ? expf(e[k][j] * mult - zmax) : 0.f;
+      acc += (e[k][0] + e[k][1]) + (e[k][2] + e[k][3]);
+    }
+    sum = (float)block_sum_d((double)acc, shd);
+  }
+  if (threadIdx.x == 0) {
+    float* s = scratch + 256 + ((size_t)i * accept_pieces(V) + p) * 3;
+    s[0] = top.v;
+    s[1] = sum;
+    s[2] = __int_as_float(top.i == 0x7fffffff ? top.i : first + top.i);
+  }
+}
+
+// long rows: every row's statistics from its pieces', by the whole workgroup, into `st` (LDS, four floats per row)
+__device__ void accept_combine(const float* __restrict__ logits, int V, float mult, int greedy,
+                               const float* __restrict__ qcache, const int* __restrict__ ring,
+                               const int* __restrict__ x_direct, const AcceptArgs& a, const float* __restrict__ scratch,
+                               float* st) {
+  const int lane = threadIdx.x & 63, P = accept_pieces(V);
+  for (int i = threadIdx.x >> 6; i < a.n_rows; i += SAMP_WAVES) {
+    const float* s = scratch + 256 + (size_t)i * P * 3;
+    MaxIdx m;
+    m.v = -INFINITY; m.i = 0x7fffffff;
+    for (int p = lane; p < P; p += 64) m = better(m, s[p * 3], __float_as_int(s[p * 3 + 2]));
+    const MaxIdx top = wave_argmax(m);
+    float sum = 1.f;
+    if (!greedy) {
+      const double zmax = (double)(top.v * mult);
+      double t = 0.0;
+      for (int p = lane; p < P; p += 64)
+        if (s[p * 3 + 1] != 0.f) t += (double)s[p * 3 + 1] * exp((double)(s[p * 3] * mult) - zmax);
+      sum = (float)lane_d(wave_scan_d(t), 63);
+    }
+    if (lane == 0) {
+      st[i * 4 + 0] = top.v;
+      st[i * 4 + 1] = sum;
+      st[i * 4 + 2] = __int_as_float(top.i);
+      st[i * 4 + 3] = __int_as_float(accept_test(logits + (size_t)i * V, i, V, mult, greedy, top.v, sum, top.i, qcache, ring, x_direct, a));
+    }
+  }
+  __syncthreads();
+}
+
+// n = first rejection.  *off_path: a guided test ended at a draft that left the guessed path (row n >= 1 is the
+// target's distribution after x_1..x_n only if those are the guesses).
+__device__ __forceinline__ int accept_count(const AcceptArgs& a, const int* __restrict__ ring, const float* stats, bool* off_path) {
   int n = 0;
-  bool off_path = false;   // guided tests: row n is the target's distribution after x_1..x_n only if those are the guesses
+  *off_path = false;
   while (n < a.n_test) {
     if (a.guided && n >= 1 && ring[a.slot[n - 1]] != a.guess[n - 1]) {
-      off_path = true;
+      *off_path = true;
       break;
     }
     if (__float_as_int(stats[n * 4 + 3]) == 0) break;
     ++n;
   }
+  return n;
+}
+
+// long rows: the weights of the draw, norm(max(0, p_n - q_n)) after a rejection, p_n for the row after the last test
+__global__ __launch_bounds__(SAMP_THREADS) void accept_weights_kernel(const float* __restrict__ logits, int V, float mult,
+                                                                      const float* __restrict__ qcache,
+                                                                      const int* __restrict__ ring,
+                                                                      const int* __restrict__ x_direct, AcceptArgs a,
+                                                                      float* __restrict__ scratch) {
+  __shared__ double shd[SAMP_WAVES];
+  __shared__ float st[4 * SPEC_MAX_TOKENS];
+  accept_combine(logits, V, mult, 0, qcache, ring, x_direct, a, scratch, st);
+  bool off_path;
+  const int n = accept_count(a, ring, st, &off_path);
+  const bool rejected = !off_path && n < a.n_test;
+  if (!rejected && (a.guided || n >= a.n_rows)) return;
+  const int p = blockIdx.x, first = p * SAMP_PIECE, m = min(SAMP_PIECE, V - first);
+  const float* row = logits + (size_t)n * V + first;
+  const float* qrow = nullptr;
+  if (rejected) qrow = (x_direct ? qcache + (size_t)n * V : qcache + (size_t)a.slot[n] * V) + first;
+  const float zmax = st[n * 4] * mult, sum = st[n * 4 + 1];
+  float* wbuf = scratch + accept_weights_at(V) + first;
+  const RegGeom g = reg_geom(SAMP_PIECE);
+  f32x4 e[SAMP_PIECE_CHUNKS], q[SAMP_PIECE_CHUNKS];
+  reg_fetch(row, m, g, 0.f, e);
+  if (qrow) reg_fetch(qrow, m, g, 0.f, q);
+  double mine = 0.0;
+#pragma unroll
+  for (int k = 0; k < SAMP_PIECE_CHUNKS; ++k) {
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+      const float pv = expf(e[k][i] * mult - zmax) / sum;
+      e[k][i] = g.id(k) + i < m ? (qrow ? (float)fmax((double)pv - (double)q[k][i], 0.0) : pv) : 0.f;
+    }
+    store4(wbuf, g.id(k), m, e[k]);
+    mine += sum4_d(e[k]);
+  }
+  const double t = block_sum_d(mine, shd);
+  if (threadIdx.x == 0) reinterpret_cast<double*>(scratch + accept_sums_at(V))[p] = t;
+}
+
+// The draw over row n in registers: residual weights max(0, p - q), or p itself (qrow == nullptr; also where the
+// residual has no mass in floating point).
+__device__ __forceinline__ int accept_draw(const float* __restrict__ row, const float* __restrict__ qrow, int V, float mult,
+                                           float zmax, float sum, float u, double* shd, int* shi) {
+  const float inv = 1.0f / sum;
+  int token = -1;
+#pragma unroll 1
+  for (int attempt = 0; attempt < 2; ++attempt) {
+    RegGeom g = reg_geom(V);
+    asm volatile("" : "+v"(g.j0));     // keeps the addresses of both rows from being worked out for both attempts
+    f32x4 e[SAMP_CHUNKS_MAX];
+    reg_fetch(row, V, g, 0.f, e);
+#pragma unroll
+    for (int h = 0; h < 4; ++h) {      // q in parts: registers
+      constexpr int H = SAMP_CHUNKS_MAX / 4;
+      RegGeom gh = g;
+      gh.j0 = g.id(h * H);
+      gh.R = g.R - h * H;
+      f32x4 q[H];
+      if (qrow) reg_fetch(qrow, V, gh, 0.f, q);
+      __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+      for (int k = 0; k < H; ++k)
+#pragma unroll
+        for (int i = 0; i < 4; ++i) {
+          const float p = reg_prob(e[h * H + k][i], mult, zmax, inv);
+          const float w = qrow ? (float)fmax((double)p - (double)q[k][i], 0.0) : p;
+          e[h * H + k][i] = ((k < gh.R) & (gh.id(k) + i < V)) ? w : 0.f;
+        }
+    }
+    double total = 0.0;
+    token = reg_draw(e, g, u, 0.0, -1.0, shd, shi, &total);
+    if (!qrow || total > 0.0) break;
+    qrow = nullptr;
+    __syncthreads();
+  }
+  return token;
+}
+
+// The same for a long row: the piece the draw falls into (accept_weights_kernel left the weights and their sums), then
+// the walk inside it.
+__device__ __forceinline__ int accept_draw_long(const float* __restrict__ row, bool rejected, int V, float mult, float zmax,
+                                                float sum, float u, float* __restrict__ scratch, double* shd, int* shi) {
+  float* wbuf = scratch + accept_weights_at(V);
+  const double* sums = reinterpret_cast<const double*>(scratch + accept_sums_at(V));
+  const int P = accept_pieces(V), lane = threadIdx.x & 63;
+  double total = 0.0;
+  for (int p0 = 0; p0 < P; p0 += 64) total += lane_d(wave_scan_d(p0 + lane < P ? sums[p0 + lane] : 0.0), 63);
+  if (rejected && !(total > 0.0)) {   // no residual mass in floating point: draw from p itself
+    for (int j = threadIdx.x; j < V; j += SAMP_THREADS) wbuf[j] = expf(row[j] * mult - zmax) / sum;
+    return block_draw(wbuf, V, u, shd, shi);
+  }
+  const double target = (double)u * total;
+  double before = 0.0, ahead = 0.0;
+  int piece = -1, last = -1;
+  for (int p0 = 0; p0 < P && piece < 0; p0 += 64) {
+    const double s = p0 + lane < P ? sums[p0 + lane] : 0.0;
+    const double incl = wave_scan_d(s);
+    const unsigned long long mass = __ballot(s > 0.0), hit = __ballot(s > 0.0 && before + incl > target);
+    const int l = hit ? __ffsll((long long)hit) - 1 : (mass ? 63 - __clzll((long long)mass) : -1);
+    if (l >= 0) {
+      last = p0 + l;
+      ahead = before + (lane_d(incl, l) - lane_d(s, l));
+      if (hit) piece = last;
+    }
+    before += lane_d(incl, 63);
+  }
+  if (piece < 0) piece = last;      // rounding: the last piece with mass
+  if (piece < 0) return -1;
+  const int first = piece * SAMP_PIECE, m = min(SAMP_PIECE, V - first);
+  const RegGeom g = reg_geom(SAMP_PIECE);
+  f32x4 e[SAMP_PIECE_CHUNKS];
+  reg_fetch(wbuf + first, m, g, 0.f, e);
+  const int t = reg_draw(e, g, u, ahead, target, shd, shi, nullptr);
+  return t < 0 ? -1 : first + t;
+}
+
+// One workgroup: n = first rejection; draw from norm(max(0, p_n - q_n)) (from p_n if that has no
+// mass), or the bonus / autoregressive token from the row after the last test.
+template <bool LONG>
+__global__ __launch_bounds__(SAMP_THREADS) void accept_finish_kernel(const float* __restrict__ logits, int V,
+                                                                     float mult, int greedy,
+                                                                     const float* __restrict__ qcache,
+                                                                     const int* __restrict__ ring,
+                                                                     const int* __restrict__ x_direct, AcceptArgs a,
+                                                                     float* __restrict__ scratch,
+                                                                     AcceptResult* __restrict__ res,
+                                                                     int* __restrict__ out2) {
+  __shared__ double shd[SAMP_WAVES];
+  __shared__ int shi[1];
+  __shared__ float st[4 * SPEC_MAX_TOKENS];
+  if (LONG) accept_combine(logits, V, mult, greedy, qcache, ring, x_direct, a, scratch, st);
+  const float* stats = LONG ? st : scratch;
+  bool off_path;
+  const int n = accept_count(a, ring, stats, &off_path);
   const bool rejected = !off_path && n < a.n_test;
   int token = -1;
   if (rejected || (!a.guided && n < a.n_rows)) {   // a row to draw from exists: the rejecting row, or the bonus row
     const float* row = logits + (size_t)n * V;
-    const float vmax = stats[n * 4 + 0], sum = stats[n * 4 + 1];
-    const int amax = __float_as_int(stats[n * 4 + 2]);
+    const float zmax = stats[n * 4 + 0] * mult, sum = stats[n * 4 + 1];
     if (greedy) {
-      token = amax;   // residual of two one-hots, or the one-hot itself, is the target's arg-max
+      token = __float_as_int(stats[n * 4 + 2]);   // residual of two one-hots, or the one-hot itself, is the target's arg-max
+    } else if (LONG) {
+      token = accept_draw_long(row, rejected, V, mult, zmax, sum, a.u_resample, scratch, shd, shi);
     } else {
       const float* qrow = nullptr;
       if (rejected) qrow = x_direct ? qcache + (size_t)n * V : qcache + (size_t)a.slot[n] * V;
-      const float zmax = vmax * mult;
-      if (V <= SAMP_ROWS_MAX * SAMP_THREADS) {
-        // the row in registers: residual weights (or p itself for the bonus / autoregressive token), one draw
-        const RegGeom g = reg_geom(V);
-        const float inv = 1.0f / sum;
-        float e[SAMP_ROWS_MAX];
-#pragma unroll
-        for (int k = 0; k < SAMP_ROWS_MAX; ++k) {
-          const int j = g.j0 + 64 * k;
-          float wj = 0.f;
-          if (k < g.R && j < V) {
-            const float p = reg_prob(row[j], mult, zmax, inv);
-            wj = qrow ? (float)fmax((double)p - (double)qrow[j], 0.0) : p;
-          }
-          e[k] = wj;
-        }
-        double total = 0.0;
-        token = reg_draw(e, g, a.u_resample, rt, shi, &total);
-        if (rejected && !(total > 0.0)) {   // no residual mass in floating point: draw from p itself
-#pragma unroll
-          for (int k = 0; k < SAMP_ROWS_MAX; ++k) {
-            const int j = g.j0 + 64 * k;
-            e[k] = (k < g.R && j < V) ? reg_prob(row[j], mult, zmax, inv) : 0.f;
-          }
-          token = reg_draw(e, g, a.u_resample, rt, shi, nullptr);
-        }
-      } else {
-      for (int j = threadIdx.x; j < V; j += SAMP_THREADS) {
-        const float p = expf(row[j] * mult - zmax) / sum;
-        wbuf[j] = qrow ? (float)fmax((double)p - (double)qrow[j], 0.0) : p;
-      }
-      __threadfence_block();
-      __syncthreads();
-      double total = 0.0;
-      token = block_inverse_cdf(wbuf, V, a.u_resample, shd, shi, &total);
-      if (rejected && !(total > 0.0)) {   // no residual mass in floating point: draw from p itself
-        __syncthreads();
-        for (int j = threadIdx.x; j < V; j += SAMP_THREADS) wbuf[j] = expf(row[j] * mult - zmax) / sum;
-        __threadfence_block();
-        __syncthreads();
-        token = block_inverse_cdf(wbuf, V, a.u_resample, shd, shi, nullptr);
-      }
-      }
+      token = accept_draw(row, qrow, V, mult, zmax, sum, a.u_resample, shd, shi);
     }
   }
   if (threadIdx.x == 0) {
@@ -468,16 +702,26 @@ __global__ __launch_bounds__(SAMP_THREADS) void accept_finish_kernel(const float
 }
 
 hipError_t launch_accept(const float* logits, int V, float mult, int greedy, const float* qcache, const int* ring,
-                         const int* x_direct, AcceptArgs a, float* stats_scratch, AcceptResult* result_dev,
+                         const int* x_direct, AcceptArgs a, float* scratch, AcceptResult* result_dev,
                          hipStream_t st, int* out2) {
-  // stats_scratch: 4 floats per row, followed (at a 256-float offset) by one scratch row of V floats
   if (a.guided && !ring) return hipErrorInvalidValue;   // guided tests compare ring tokens with the guesses
-  accept_rows_kernel<<<a.n_rows, SAMP_THREADS, 0, st>>>(logits, V, mult, greedy, qcache, ring, x_direct, a,
-                                                        stats_scratch);
+  const int P = accept_pieces(V);
+  if (!P) {
+    accept_rows_kernel<<<a.n_rows, SAMP_THREADS, 0, st>>>(logits, V, mult, greedy, qcache, ring, x_direct, a, scratch);
+  } else {
+    accept_piece_kernel<<<dim3(P, a.n_rows), SAMP_THREADS, 0, st>>>(logits, V, mult, greedy, scratch);
+    hipError_t e = hipGetLastError();
+    if (e != hipSuccess) return e;
+    if (!greedy) accept_weights_kernel<<<P, SAMP_THREADS, 0, st>>>(logits, V, mult, qcache, ring, x_direct, a, scratch);
+  }
   hipError_t e = hipGetLastError();
   if (e != hipSuccess) return e;
-  accept_finish_kernel<<<1, SAMP_THREADS, 0, st>>>(logits, V, mult, greedy, qcache, ring, x_direct, a, stats_scratch,
-                                                   stats_scratch + 256, result_dev, out2);
+  if (P)
+    accept_finish_kernel<true><<<1, SAMP_THREADS, 0, st>>>(logits, V, mult, greedy, qcache, ring, x_direct, a, scratch,
+                                                           result_dev, out2);
+  else
+    accept_finish_kernel<false><<<1, SAMP_THREADS, 0, st>>>(logits, V, mult, greedy, qcache, ring, x_direct, a, scratch,
+                                                            result_dev, out2);
   return hipGetLastError();
 }
 
@@ -488,8 +732,8 @@ hipError_t launch_accept(const float* logits, int V, float mult, int greedy, con
 // process ends; its address on a device is looked up once, with that device current.  All calls on one GPU share
 // the array, so calls that overlap on one GPU (two streams, two threads) race; nothing in it has to start at zero
 // (every word a call reads was written by that call before).
-#define ACCEPT_STATIC_STATS_FLOATS 256
-#define ACCEPT_STATIC_BYTES ((ACCEPT_STATIC_STATS_FLOATS + SPEC_STATIC_VOCAB_MAX) * 4 + 512)
+#define ACCEPT_STATIC_FLOATS accept_scratch_floats_of(SPEC_STATIC_VOCAB_MAX)
+#define ACCEPT_STATIC_BYTES (ACCEPT_STATIC_FLOATS * 4 + 512)
 static __device__ __align__(256) unsigned char scratch[ACCEPT_STATIC_BYTES];
 
 #include <mutex>
@@ -539,7 +783,7 @@ extern "C" int spec_accept_rows_static(const float* p_logits, int n_rows, const 
     spec_set_error("bad temperature / logit_scale / uniform");
     return SPEC_E_INVAL;
   }
-  static_assert(4 * SPEC_MAX_TOKENS <= ACCEPT_STATIC_STATS_FLOATS, "four statistics per row");
+  static_assert(4 * SPEC_MAX_TOKENS <= 256, "four statistics per row");
   static_assert(sizeof(AcceptResult) <= 512, "the result record sits in the last 512 bytes");
   unsigned char* base = (unsigned char*)static_scratch_ptr();
   if (!base) return SPEC_E_HIP;
@@ -557,8 +801,8 @@ extern "C" int spec_accept_rows_static(const float* p_logits, int n_rows, const 
     a.r[i] = r[i];
   }
   const bool greedy = temperature == 0.0f;
-  float* stats = (float*)base;
-  AcceptResult* res = (AcceptResult*)(base + (size_t)(ACCEPT_STATIC_STATS_FLOATS + SPEC_STATIC_VOCAB_MAX) * 4);
+  float* stats = (float*)base;   // all of the scratch
+  AcceptResult* res = (AcceptResult*)(base + ACCEPT_STATIC_FLOATS * 4);
   hipError_t e = launch_accept(p_logits, vocab, greedy ? 1.0f : logit_scale / temperature, greedy ? 1 : 0, q_rows,
                                nullptr, x, a, stats, res, (hipStream_t)stream, result_dev);
   if (e != hipSuccess) {

@@ -170,8 +170,9 @@ struct AcceptResult {       // device -> pinned host
 };
 hipError_t launch_sample_row(const float* logits, int V, float mult, int greedy, float u, float* q_out, int* tok_out,
                              hipStream_t st);
+size_t accept_scratch_floats(int V);   // scratch of one acceptance (rows <= SPEC_MAX_TOKENS)
 hipError_t launch_accept(const float* logits, int V, float mult, int greedy, const float* qcache, const int* ring,
-                         const int* x_direct, AcceptArgs a, float* stats_scratch, AcceptResult* result_dev,
+                         const int* x_direct, AcceptArgs a, float* scratch, AcceptResult* result_dev,
                          hipStream_t st, int* out2 = nullptr);
 
 void spec_set_error(const char* fmt, ...);

@@ -3,23 +3,9 @@
 // partials of the preceding projection and add the slices in ascending order.
 #include "spec_internal.h"
 
-__global__ void gather_tokens_kernel(int* tok_out, const int* ring, TokenSrc src) {
-  int i = threadIdx.x;
-  if (i < src.n) tok_out[i] = src.imm[i] >= 0 ? src.imm[i] : ring[src.slot[i]];
-}
-hipError_t launch_gather_tokens(int* tok_out, const int* ring, TokenSrc src, hipStream_t st) {
-  gather_tokens_kernel<<<1, 64, 0, st>>>(tok_out, ring, src);
-  return hipGetLastError();
-}
-
 __global__ void set_int_kernel(int* dst, int v) { dst[0] = v; }
-__global__ void add_int_kernel(int* dst, int d) { dst[0] += d; }
 hipError_t launch_set_int(int* dst, int value, hipStream_t st) {
   set_int_kernel<<<1, 1, 0, st>>>(dst, value);
-  return hipGetLastError();
-}
-hipError_t launch_add_int(int* dst, int delta, hipStream_t st) {
-  add_int_kernel<<<1, 1, 0, st>>>(dst, delta);
   return hipGetLastError();
 }
 __global__ void set_pages_kernel(int* bt, PageUpdate u) {
@@ -175,16 +161,66 @@ hipError_t launch_add_sumsq(float* h, const float* partials, int S, const bf16* 
   return hipGetLastError();
 }
 
-// (cos, sin) of the rotation angle pos * theta^(-2e/dh) of pair e at position len + i, in fp64, once per forward or
-// prompt block instead of once per layer and head.
+// (cos, sin) of the rotation angle pos * theta^(-2e/dh) of pair e, in fp64, once per forward or prompt block instead of
+// once per layer and head.
+__device__ __forceinline__ float2 rope_angle(int pos, int e, int dh, float theta) {
+  const double ang = (double)pos * pow((double)theta, -2.0 * (double)e / (double)dh);
+  return make_float2((float)cos(ang), (float)sin(ang));
+}
 __global__ void rope_table_kernel(float2* __restrict__ tab, const int* __restrict__ len_ptr, int dh, float theta) {
   const int i = blockIdx.x, e = threadIdx.x, half = dh >> 1;
-  if (e >= half) return;
-  const int pos = len_ptr[0] + i;
-  const double ang = (double)pos * pow((double)theta, -2.0 * (double)e / (double)dh);
-  tab[(size_t)i * half + e] = make_float2((float)cos(ang), (float)sin(ang));
+  if (e < half) tab[(size_t)i * half + e] = rope_angle(len_ptr[0] + i, e, dh, theta);
 }
 hipError_t launch_rope_table(float2* tab, const int* len_ptr, int M, int dh, float theta, hipStream_t st) {
   rope_table_kernel<<<M, 64, 0, st>>>(tab, len_ptr, dh, theta);
+  return hipGetLastError();
+}
+
+// First launch of a forward, outside its captured part: everything the chain reads that changes from call to call comes in
+// as arguments.  Workgroup (x, i): 1024 columns of token i's embedding as residual stream, x' = bf16(h * gain) of the first
+// norm and the piece's sum of squares (a token outside the vocabulary reads row 0; ids are validated on the host).  The last
+// x: the rotation angles of position len + i; for i = 0 also the length and the new entries of the page table.
+#define BEGIN_THREADS 256
+__global__ __launch_bounds__(BEGIN_THREADS) void begin_kernel(BeginArgs a, TokenSrc src, PageUpdate pages) {
+  __shared__ float sh[BEGIN_THREADS / 64];
+  const int i = blockIdx.y, t = threadIdx.x;
+  if (blockIdx.x == gridDim.x - 1) {
+    const int half = a.dh >> 1;
+    if (t < half) a.tab[(size_t)i * half + t] = rope_angle(a.len + i, t, a.dh, a.theta);
+    if (i == 0) {
+      if (t == 0) a.len_dev[0] = a.len;
+      if (t < pages.count) a.block_table[pages.first + t] = pages.page[t];
+    }
+    return;
+  }
+  int tok = src.imm[i] >= 0 ? src.imm[i] : a.ring[src.slot[i]];
+  if (tok < 0 || tok >= a.vocab) tok = 0;
+  const int col = (blockIdx.x * BEGIN_THREADS + t) * 4;
+  float ss = 0.f;
+  if (col < a.d) {
+    const uint2 ev = *reinterpret_cast<const uint2*>(a.embed + (size_t)tok * a.d + col);
+    const uint2 gv = *reinterpret_cast<const uint2*>(a.gain + col);
+    const bf16 *e = reinterpret_cast<const bf16*>(&ev), *g = reinterpret_cast<const bf16*>(&gv);
+    f32x4 h;
+    bf16 o[4];
+#pragma unroll
+    for (int r = 0; r < 4; ++r) {
+      h[r] = __bfloat162float(e[r]);
+      o[r] = __float2bfloat16(h[r] * __bfloat162float(g[r]));
+      ss += h[r] * h[r];
+    }
+    *reinterpret_cast<f32x4*>(a.h + (size_t)i * a.d + col) = h;
+    *reinterpret_cast<uint2*>(a.xo + (size_t)i * a.d + col) = *reinterpret_cast<const uint2*>(o);
+  }
+#pragma unroll
+  for (int o = 32; o > 0; o >>= 1) ss += __shfl_xor(ss, o);
+  if ((t & 63) == 0) sh[t >> 6] = ss;
+  __syncthreads();
+  if (t == 0) a.ssq[(size_t)i * SSQ_STRIDE + blockIdx.x] = (sh[0] + sh[1]) + (sh[2] + sh[3]);
+}
+hipError_t launch_begin(const BeginArgs& a, const TokenSrc& src, const PageUpdate& pages, int* W_out, hipStream_t st) {
+  *W_out = (a.d + 4 * BEGIN_THREADS - 1) / (4 * BEGIN_THREADS);
+  if (src.n < 1 || src.n > SPEC_MAX_TOKENS || (a.d & 3) || (a.dh >> 1) > BEGIN_THREADS || pages.count > 8) return hipErrorInvalidValue;
+  begin_kernel<<<dim3(*W_out + 1, src.n), BEGIN_THREADS, 0, st>>>(a, src, pages);
   return hipGetLastError();
 }

@@ -49,9 +49,8 @@ struct ModelRt {
   int* block_table_dev = nullptr;
   std::vector<int> block_table;   // pages of the sequence, in order
   std::vector<int> free_pages;
-  int len = 0;                    // host mirror of *len_dev
+  int len = 0;                    // tokens in the cache; every forward sets *len_dev to it
   int* len_dev = nullptr;
-  int* tok_in = nullptr;
   float* h = nullptr;
   float* qkv = nullptr;           // fused QKV projection of a forward
   float2* rope_tab = nullptr;     // (cos, sin) of the new positions of a forward
@@ -173,7 +172,6 @@ int init_model(ModelRt& m, const spec_model_desc& d, const spec_weights& w, cons
   const int qkvN = (d.n_heads + 2 * d.n_kv_heads) * d.head_dim;
   const int kmax = d.d_model > d.d_ffn ? d.d_model : d.d_ffn;
   const int amax = kmax > d.n_heads * d.head_dim ? kmax : d.n_heads * d.head_dim;
-  if ((rc = dev_alloc(&m.tok_in, (size_t)MX))) return rc;
   if ((rc = dev_alloc(&m.h, (size_t)MX * d.d_model))) return rc;
   if ((rc = dev_alloc(&m.ssq, (size_t)MX * SSQ_STRIDE))) return rc;
   HIPCHK(hipMemset(m.ssq, 0, (size_t)MX * SSQ_STRIDE * sizeof(float)));
@@ -207,34 +205,33 @@ void free_model(ModelRt& m) {
             g = nullptr;
           }
   void* ptrs[] = {m.qkv, m.rope_tab,
-                  m.pool, m.block_table_dev, m.len_dev, m.tok_in, m.h, m.ssq, m.a, m.attn_out, m.z, m.partials,
+                  m.pool, m.block_table_dev, m.len_dev, m.h, m.ssq, m.a, m.attn_out, m.z, m.partials,
                   m.opart, m.logits, m.pf_tok, m.pf_h, m.pf_a, m.pf_q, m.pf_attn, m.pf_z, m.pf_rope};
   for (void* p : ptrs)
     if (p) (void)hipFree(p);
 }
 
-// make sure pages exist for positions [0, new_len)
-int ensure_pages(ModelRt& m, int new_len) {
+// Make sure pages exist for positions [0, new_len).  The last update of the device's page table is left in *last (count
+// 0: none) for the caller's next launch to carry; any before it (more than 8 new pages) go out here.
+int ensure_pages(ModelRt& m, int new_len, PageUpdate* last) {
+  last->first = last->count = 0;
   const int need = (new_len + SPEC_PAGE_TOKENS - 1) / SPEC_PAGE_TOKENS;
   const int have = (int)m.block_table.size();
   if (need <= have) return SPEC_OK;
   if ((size_t)(need - have) > m.free_pages.size())
     FAIL(SPEC_E_NOMEM, "KV cache full: %d tokens need %d pages, %d in use, %zu free", new_len, need, have,
          m.free_pages.size());
-  int first = have;
   while ((int)m.block_table.size() < need) {
-    PageUpdate u;
-    u.first = (int)m.block_table.size();
-    u.count = 0;
-    while (u.count < 8 && (int)m.block_table.size() < need) {
+    if (last->count) HIPCHK(launch_set_pages(m.block_table_dev, *last, m.stream));
+    last->first = (int)m.block_table.size();
+    last->count = 0;
+    while (last->count < 8 && (int)m.block_table.size() < need) {
       const int pg = m.free_pages.back();
       m.free_pages.pop_back();
       m.block_table.push_back(pg);
-      u.page[u.count++] = pg;
+      last->page[last->count++] = pg;
     }
-    HIPCHK(launch_set_pages(m.block_table_dev, u, m.stream));
   }
-  (void)first;
   return SPEC_OK;
 }
 
@@ -296,24 +293,20 @@ int resid_pieces(const spec_ctx* c, const ModelRt& m, int M, int K) {
   return (N + 1023) / 1024;
 }
 
-// The kernel chain of one forward over the M tokens in m.tok_in.  Nothing here depends on host state other
+// The kernel chain of one forward behind its first launch.  Nothing here depends on host state other
 // than M, logit_rows and the launch mode: positions come from *len_dev, pages from the device block table,
 // so the chain can be captured once into a HIP graph and replayed.
-// Layers [l0, l1) of the chain: the embedding goes with layer 0, the LM head and the length update with the last layer.
+// Layers [l0, l1) of the chain; the LM head goes with the last one.
+// W0: pieces of sums of squares per row that the first launch leaves.
 // State between layers: the residual stream in h, x' = bf16(h * gain) of the next norm in a, its sums of squares in ssq.
-int enqueue_forward(spec_ctx* c, int which, int M, int logit_rows, int l0, int l1) {
+int enqueue_forward(spec_ctx* c, int which, int M, int logit_rows, int W0, int l0, int l1) {
   ModelRt& m = c->m[which];
   const spec_model_desc& d = m.d;
   hipStream_t st = m.stream;
   int rc;
   const int qkvN = (d.n_heads + 2 * d.n_kv_heads) * d.head_dim;
   const int HD = d.n_heads * d.head_dim;
-  int W = l0 > 0 ? resid_pieces(c, m, M, d.d_ffn) : 0;
-  if (l0 == 0) {
-    HIPCHK(launch_embed(m.h, (const bf16*)m.tok_embed, m.tok_in, M, d.d_model, d.vocab, st));
-    HIPCHK(launch_rope_table(m.rope_tab, m.len_dev, M, d.head_dim, d.rope_theta, st));
-    HIPCHK(launch_add_sumsq(m.h, nullptr, 0, (const bf16*)m.attn_norm[0], m.a, m.ssq, M, d.d_model, &W, st));
-  }
+  int W = l0 > 0 ? resid_pieces(c, m, M, d.d_ffn) : W0;
   ProjArgs normed = {};      // a projection of the normalised residual stream
   normed.x = m.a;
   normed.ssq = m.ssq;
@@ -340,7 +333,6 @@ int enqueue_forward(spec_ctx* c, int which, int M, int logit_rows, int l0, int l
     pa.w = m.lm_head; pa.y = m.logits; pa.ssq_w = W;
     if ((rc = run_proj(c, which, m, proj_plan(rows, d.vocab, d.d_model, PROJ_STORE, c->wgs), PROJ_STORE, pa))) return rc;
   }
-  HIPCHK(launch_add_int(m.len_dev, M, st));
   return SPEC_OK;
 }
 
@@ -358,9 +350,14 @@ int forward(spec_ctx* c, int which, const TokenSrc& src, int logit_rows) {
   const int M = src.n;
   if (M < 1 || M > SPEC_MAX_TOKENS) FAIL(SPEC_E_INVAL, "forward over %d tokens (1..%d allowed)", M, SPEC_MAX_TOKENS);
   int rc;
-  if ((rc = ensure_pages(m, m.len + M))) return rc;
+  PageUpdate pages;
+  if ((rc = ensure_pages(m, m.len + M, &pages))) return rc;
   hipStream_t st = m.stream;
-  HIPCHK(launch_gather_tokens(m.tok_in, c->ring, src, st));
+  const spec_model_desc& d = m.d;
+  BeginArgs ba = {(const bf16*)m.tok_embed, (const bf16*)m.attn_norm[0], c->ring, m.h, m.a, m.ssq, m.rope_tab, m.len_dev,
+                  m.block_table_dev, d.d_model, d.vocab, d.head_dim, m.len, d.rope_theta};
+  int W0 = 0;
+  HIPCHK(launch_begin(ba, src, pages, &W0, st));
   const int L = m.d.n_layers;
   // Cut of the layers into launch units.  Two graphs per forward: launching ~10 nodes per layer costs the host
   // about 0.45 us per node (0.45 ms for the 80-layer target), during which the stream would sit idle; a short graph
@@ -398,7 +395,7 @@ int forward(spec_ctx* c, int which, const TokenSrc& src, int logit_rows) {
           rc = SPEC_E_HIP;
           break;
         }
-        rc = enqueue_forward(c, which, M, logit_rows, un.l0, un.l1);
+        rc = enqueue_forward(c, which, M, logit_rows, W0, un.l0, un.l1);
         hipGraph_t g = nullptr;
         e = hipStreamEndCapture(st, &g);   // always leave capture mode, also after a failed launch
         if (rc || e != hipSuccess) {
@@ -424,7 +421,7 @@ int forward(spec_ctx* c, int which, const TokenSrc& src, int logit_rows) {
         rc = SPEC_E_HIP;
       }
     } else {
-      rc = enqueue_forward(c, which, M, logit_rows, un.l0, un.l1);
+      rc = enqueue_forward(c, which, M, logit_rows, W0, un.l0, un.l1);
     }
   }
   c->wgs = wgs_saved;
@@ -465,7 +462,10 @@ int prefill_dense_block(spec_ctx* c, int which, const int32_t* tok, int C) {
   const spec_model_desc& d = m.d;
   hipStream_t st = m.stream;
   int rc;
-  if ((rc = ensure_pages(m, m.len + C))) return rc;
+  PageUpdate pages;
+  if ((rc = ensure_pages(m, m.len + C, &pages))) return rc;
+  if (pages.count) HIPCHK(launch_set_pages(m.block_table_dev, pages, st));
+  HIPCHK(launch_set_int(m.len_dev, m.len, st));
   HIPCHK(hipMemcpyAsync(m.pf_tok, tok, (size_t)C * sizeof(int), hipMemcpyHostToDevice, st));
   HIPCHK(launch_embed(m.pf_h, (const bf16*)m.tok_embed, m.pf_tok, C, d.d_model, d.vocab, st));
   HIPCHK(launch_rope_table(m.pf_rope, m.len_dev, C, d.head_dim, d.rope_theta, st));
@@ -482,7 +482,6 @@ int prefill_dense_block(spec_ctx* c, int which, const int32_t* tok, int C) {
     HIPCHK(launch_dense_gemm(m.pf_a, m.wgu[l], C, 2 * d.d_ffn, d.d_model, 2, nullptr, m.pf_z, st));
     HIPCHK(launch_dense_gemm(m.pf_z, m.wdown[l], C, d.d_model, d.d_ffn, 1, m.pf_h, nullptr, st));
   }
-  HIPCHK(launch_add_int(m.len_dev, C, st));
   m.len += C;
   m.n_forwards++;
   return SPEC_OK;
@@ -499,7 +498,6 @@ int rollback_model(spec_ctx* c, int which, int new_len) {
   if (new_len < 0 || new_len > m.len) FAIL(SPEC_E_INVAL, "rollback to %d outside [0, %d]", new_len, m.len);
   if (new_len == m.len) return SPEC_OK;
   m.len = new_len;
-  HIPCHK(launch_set_int(m.len_dev, new_len, m.stream));
   const int keep = (new_len + SPEC_PAGE_TOKENS - 1) / SPEC_PAGE_TOKENS;
   while ((int)m.block_table.size() > keep) {
     m.free_pages.push_back(m.block_table.back());
@@ -728,8 +726,7 @@ extern "C" int spec_verify(spec_ctx* c, const int32_t* tokens, int n_tokens, flo
   c->last_verify_rows = n_tokens;
   c->n_guess = -1;
   if (logits_out) {
-    HIPCHK(hipStreamSynchronize(m.stream));
-    HIPCHK(hipMemcpy(logits_out, m.logits, (size_t)n_tokens * m.d.vocab * sizeof(float), hipMemcpyDeviceToHost));
+    HIPCHK(hipMemcpyWithStream(logits_out, m.logits, (size_t)n_tokens * m.d.vocab * sizeof(float), hipMemcpyDeviceToHost, m.stream));
   }
   return SPEC_OK;
 }
@@ -779,8 +776,7 @@ extern "C" int spec_verify_guess(spec_ctx* c, const int32_t* guess, int n_guess,
   for (int i = 0; i < ng; ++i) c->guess[i] = g[i];
   if (n_fed) *n_fed = ng;
   if (logits_out) {
-    HIPCHK(hipStreamSynchronize(m.stream));
-    HIPCHK(hipMemcpy(logits_out, m.logits, (size_t)(ng + 1) * m.d.vocab * sizeof(float), hipMemcpyDeviceToHost));
+    HIPCHK(hipMemcpyWithStream(logits_out, m.logits, (size_t)(ng + 1) * m.d.vocab * sizeof(float), hipMemcpyDeviceToHost, m.stream));
   }
   return SPEC_OK;
 }

@@ -119,9 +119,20 @@ struct PageUpdate {         // by-value kernel argument: new block-table entries
   int page[8];
 };
 
-hipError_t launch_gather_tokens(int* tok_out, const int* ring, TokenSrc src, hipStream_t st);
+// the first launch of a forward (see begin_kernel); *W_out = pieces of sums of squares per row
+struct BeginArgs {
+  const bf16 *embed, *gain;   // embedding matrix, gain of the first norm
+  const int* ring;            // draft tokens
+  float* h;                   // residual stream
+  bf16* xo;
+  float* ssq;
+  float2* tab;
+  int *len_dev, *block_table;
+  int d, vocab, dh, len;
+  float theta;
+};
+hipError_t launch_begin(const BeginArgs& a, const TokenSrc& src, const PageUpdate& pages, int* W_out, hipStream_t st);
 hipError_t launch_set_int(int* dst, int value, hipStream_t st);
-hipError_t launch_add_int(int* dst, int delta, hipStream_t st);
 hipError_t launch_set_pages(int* block_table, PageUpdate u, hipStream_t st);
 hipError_t launch_embed(float* h, const bf16* embed, const int* tok, int M, int d, int vocab, hipStream_t st);
 // h += sum_s partials[s] (if partials), a = rmsnorm(h) * gain

@@ -58,6 +58,100 @@ typedef __attribute__((address_space(3))) u32x4 dg_lds_u32x4;
 // k, v into the paged cache in operand order.  For the rotation a wave must hold columns e and e + dh/2 of a
 // head: with head_dim 64 its 64 columns are one head; with head_dim 128 the two waves of a head take the
 // 16-column panels {0, 1, 4, 5} and {2, 3, 6, 7}.  Either way accumulator tiles nt and nt + 2 pair up.
+// A wave's 64 outputs (group wn of them) x 16 MTN tokens from m0 on.
+template <int EPI, int MTN>
+__device__ __forceinline__ void dense_epilogue(const f32x4 (&acc)[4][MTN], int m0, int wn, int c, int kb, float* __restrict__ Y,
+                                               bf16* __restrict__ Z, int M, int N, const DenseRope& ra) {
+  // acc[nt][mt][r] = Y[m0 + 16 mt + c][n0 + 16 nt + 4 kb + r]
+  const int n0 = wn * 64;
+  if (EPI == DG_EPI_ROPE128 || EPI == DG_EPI_ROPE64) {
+    constexpr int DH = EPI == DG_EPI_ROPE128 ? 128 : 64;
+    const int Hkv = ra.g.n_kv_heads;
+    const int head = DH == 128 ? wn >> 1 : wn;
+    if (head >= ra.Hq + 2 * Hkv) return;
+    const int len = ra.len_ptr[0];
+    const int ebase = (DH == 128 ? (wn & 1) * 32 : 0) + kb * 4;     // + 16 nt + r: column inside the head, < dh/2
+#pragma unroll
+    for (int mt = 0; mt < MTN; ++mt) {
+      const int m = m0 + mt * 16 + c;
+      if (m >= M) continue;
+      const int pos = len + m;
+#pragma unroll
+      for (int nt = 0; nt < 2; ++nt) {
+        const int e0 = ebase + nt * 16;
+        f32x4 x0 = acc[nt][mt], x1 = acc[nt + 2][mt];               // columns e0 + r and e0 + r + dh/2
+        if (head < ra.Hq + Hkv) {
+#pragma unroll
+          for (int r = 0; r < 4; ++r) {
+            const float2 cs = ra.tab[(size_t)m * (DH / 2) + e0 + r];
+            const float y0 = x0[r] * cs.x - x1[r] * cs.y, y1 = x0[r] * cs.y + x1[r] * cs.x;
+            x0[r] = y0; x1[r] = y1;
+          }
+        }
+        bf16 o0[4], o1[4];
+#pragma unroll
+        for (int r = 0; r < 4; ++r) o0[r] = __float2bfloat16(x0[r]), o1[r] = __float2bfloat16(x1[r]);
+        if (head < ra.Hq) {
+          bf16* dst = ra.q + ((size_t)m * ra.Hq + head) * DH + e0;
+          *reinterpret_cast<uint2*>(dst) = *reinterpret_cast<const uint2*>(o0);
+          *reinterpret_cast<uint2*>(dst + DH / 2) = *reinterpret_cast<const uint2*>(o1);
+          continue;
+        }
+        const int page = ra.block_table[pos / SPEC_PAGE_TOKENS];
+        const int rr = pos % SPEC_PAGE_TOKENS;
+        if (head < ra.Hq + Hkv) {       // K block: [16-token tile][dh/32 steps][64 lanes][8]
+          bf16* blk = ra.pool + ra.g.offset(page, ra.layer, 0, head - ra.Hq);
+#pragma unroll
+          for (int t = 0; t < 2; ++t) {
+            const int e = e0 + t * (DH / 2);
+            const size_t off = ((size_t)(((rr >> 4) * (DH / 32) + (e >> 5)) * 64 + ((e & 31) >> 3) * 16 + (rr & 15))) * 8 + (e & 7);
+            *reinterpret_cast<uint2*>(blk + off) = *reinterpret_cast<const uint2*>(t ? o1 : o0);
+          }
+        } else {                        // V block: [32-token chunk][dh][32 slots]
+          bf16* blk = ra.pool + ra.g.offset(page, ra.layer, 1, head - ra.Hq - Hkv);
+          const int r32 = rr & 31;
+          const int slot = ((r32 & 15) >> 2) * 8 + (r32 >> 4) * 4 + (r32 & 3);
+          bf16* base = blk + ((size_t)(rr >> 5) * DH + e0) * 32 + slot;
+#pragma unroll
+          for (int r = 0; r < 4; ++r) {
+            base[(size_t)r * 32] = o0[r];
+            base[(size_t)(r + DH / 2) * 32] = o1[r];
+          }
+        }
+      }
+    }
+    return;
+  }
+#pragma unroll
+  for (int mt = 0; mt < MTN; ++mt) {
+    const int m = m0 + mt * 16 + c;
+    if (m >= M) continue;
+    if (EPI == DG_EPI_SWIGLU) {
+      const int F = N >> 1;
+#pragma unroll
+      for (int nt = 0; nt < 4; nt += 2) {
+        const int n = n0 + nt * 16;
+        if (n + 32 > N) continue;
+        const int f = (n >> 1) + kb * 4;
+        const f32x4 g = acc[nt][mt], u = acc[nt + 1][mt];
+        bf16 out[4];
+#pragma unroll
+        for (int q = 0; q < 4; ++q) out[q] = __float2bfloat16(g[q] / (1.0f + __expf(-g[q])) * u[q]);
+        *reinterpret_cast<uint2*>(Z + (size_t)m * F + f) = *reinterpret_cast<const uint2*>(out);
+      }
+    } else {
+#pragma unroll
+      for (int nt = 0; nt < 4; ++nt) {
+        const int n = n0 + nt * 16 + kb * 4;
+        if (n >= N) continue;
+        f32x4* dst = reinterpret_cast<f32x4*>(Y + (size_t)m * N + n);
+        if (EPI == DG_EPI_RESID) *dst = *dst + acc[nt][mt];
+        else *dst = acc[nt][mt];
+      }
+    }
+  }
+}
+
 template <int EPI>
 __global__ __launch_bounds__(DG_THREADS, 1) void dense_gemm_kernel(const bf16* __restrict__ X,
                                                                    const u32x4* __restrict__ Wp,
@@ -208,125 +302,166 @@ __global__ __launch_bounds__(DG_THREADS, 1) void dense_gemm_kernel(const bf16* _
                  "+a"(acc[nt][10]), "+a"(acc[nt][11]), "+a"(acc[nt][12]), "+a"(acc[nt][13]), "+a"(acc[nt][14]),
                  "+a"(acc[nt][15]));
 
-  // acc[nt][mt][r] = Y[m0 + 16 mt + c][n0 + 16 nt + 4 kb + r]
-  const int m0 = tm * DG_BM, n0 = tn * DG_BN + w * 64;
-  if (EPI == DG_EPI_ROPE128 || EPI == DG_EPI_ROPE64) {
-    constexpr int DH = EPI == DG_EPI_ROPE128 ? 128 : 64;
-    const int Hkv = ra.g.n_kv_heads;
-    const int head = tn * (DG_BN / DH) + (DH == 128 ? (w >> 1) : w);
-    if (head >= ra.Hq + 2 * Hkv) return;
-    const int len = ra.len_ptr[0];
-    const int ebase = (DH == 128 ? (w & 1) * 32 : 0) + kb * 4;     // + 16 nt + r: column inside the head, < dh/2
+  dense_epilogue<EPI, 16>(acc, tm * DG_BM, tn * 4 + w, c, kb, Y, Z, M, N, ra);
+}
+
+// Grids that 256 x 256 tiles do not fill: workgroup = 4 waves = 128 tokens x 128 outputs, a wave owns 64 x 64 (4 x 4 MFMA
+// tiles).  Both operands go global -> LDS with LDS-direct loads, each byte once per workgroup (a CU pulls about 25 bytes
+// per clock whatever serves them: with every fragment loaded straight into the registers of the two waves that need it,
+// a K step took 0.6 us instead of 0.33).  A stage is two K steps: 16 KiB of X in the layout of the large tile, 16 KiB of
+// W lane-linear; ring of 4 stages.  Bound by LDS: 16 KiB in and 32 KiB out per K step, 0.33 us of it (the MFMAs: 0.11).
+// Sums run over K in the same order as in the large tile: same bits.
+#define DS_STAGES 4
+#define DS_X_BYTES 16384
+#define DS_STAGE_BYTES (2 * DS_X_BYTES)
+template <int EPI>
+__global__ __launch_bounds__(DG_THREADS, 2) void dense_small_kernel(const bf16* __restrict__ X, const u32x4* __restrict__ Wp,
+                                                                    float* __restrict__ Y, bf16* __restrict__ Z, int M, int N,
+                                                                    int K, int NT, int steps, int TM, int tiles, int chunk,
+                                                                    DenseRope ra) {
+  extern __shared__ u32x4 lds[];          // DS_STAGES * DS_STAGE_BYTES
+  const int w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), lane = threadIdx.x & 63;
+  // XCD x takes the tiles [x chunk, (x + 1) chunk), token tiles fastest: its workgroups share weight columns in its L2
+  const int j = blockIdx.x >> 3, tile = (blockIdx.x & 7) * chunk + j;
+  if (tile >= tiles) return;
+  const int tn = tile / TM, tm = tile % TM;
+  const int c = lane & 15, kb = lane >> 4;
+  // per stage a wave loads token tiles 2 w and 2 w + 1 (rows 0-7 and 8-15 of each, 64 k) and panels 2 w and 2 w + 1 (two K
+  // steps of each); rows and panels past the end are clamped, computed and never stored
+  const char* wbase[2];
+  unsigned xoff[4];
 #pragma unroll
-    for (int mt = 0; mt < 16; ++mt) {
-      const int m = m0 + mt * 16 + c;
-      if (m >= M) continue;
-      const int pos = len + m;
-#pragma unroll
-      for (int nt = 0; nt < 2; ++nt) {
-        const int e0 = ebase + nt * 16;
-        f32x4 x0 = acc[nt][mt], x1 = acc[nt + 2][mt];               // columns e0 + r and e0 + r + dh/2
-        if (head < ra.Hq + Hkv) {
-#pragma unroll
-          for (int r = 0; r < 4; ++r) {
-            const float2 cs = ra.tab[(size_t)m * (DH / 2) + e0 + r];
-            const float y0 = x0[r] * cs.x - x1[r] * cs.y, y1 = x0[r] * cs.y + x1[r] * cs.x;
-            x0[r] = y0; x1[r] = y1;
-          }
-        }
-        bf16 o0[4], o1[4];
-#pragma unroll
-        for (int r = 0; r < 4; ++r) o0[r] = __float2bfloat16(x0[r]), o1[r] = __float2bfloat16(x1[r]);
-        if (head < ra.Hq) {
-          bf16* dst = ra.q + ((size_t)m * ra.Hq + head) * DH + e0;
-          *reinterpret_cast<uint2*>(dst) = *reinterpret_cast<const uint2*>(o0);
-          *reinterpret_cast<uint2*>(dst + DH / 2) = *reinterpret_cast<const uint2*>(o1);
-          continue;
-        }
-        const int page = ra.block_table[pos / SPEC_PAGE_TOKENS];
-        const int rr = pos % SPEC_PAGE_TOKENS;
-        if (head < ra.Hq + Hkv) {       // K block: [16-token tile][dh/32 steps][64 lanes][8]
-          bf16* blk = ra.pool + ra.g.offset(page, ra.layer, 0, head - ra.Hq);
-#pragma unroll
-          for (int t = 0; t < 2; ++t) {
-            const int e = e0 + t * (DH / 2);
-            const size_t off = ((size_t)(((rr >> 4) * (DH / 32) + (e >> 5)) * 64 + ((e & 31) >> 3) * 16 + (rr & 15))) * 8 + (e & 7);
-            *reinterpret_cast<uint2*>(blk + off) = *reinterpret_cast<const uint2*>(t ? o1 : o0);
-          }
-        } else {                        // V block: [32-token chunk][dh][32 slots]
-          bf16* blk = ra.pool + ra.g.offset(page, ra.layer, 1, head - ra.Hq - Hkv);
-          const int r32 = rr & 31;
-          const int slot = ((r32 & 15) >> 2) * 8 + (r32 >> 4) * 4 + (r32 & 3);
-          bf16* base = blk + ((size_t)(rr >> 5) * DH + e0) * 32 + slot;
-#pragma unroll
-          for (int r = 0; r < 4; ++r) {
-            base[(size_t)r * 32] = o0[r];
-            base[(size_t)(r + DH / 2) * 32] = o1[r];
-          }
-        }
-      }
-    }
-    return;
+  for (int i = 0; i < 2; ++i) {
+    int panel = tn * 8 + w * 2 + i;
+    if (panel > NT - 1) panel = NT - 1;
+    wbase[i] = reinterpret_cast<const char*>(Wp + (size_t)panel * steps * 64) + lane * 16;
   }
 #pragma unroll
-  for (int mt = 0; mt < 16; ++mt) {
-    const int m = m0 + mt * 16 + c;
-    if (m >= M) continue;
-    if (EPI == DG_EPI_SWIGLU) {
-      const int F = N >> 1;
-#pragma unroll
-      for (int nt = 0; nt < 4; nt += 2) {
-        const int n = n0 + nt * 16;
-        if (n + 32 > N) continue;
-        const int f = (n >> 1) + kb * 4;
-        const f32x4 g = acc[nt][mt], u = acc[nt + 1][mt];
-        bf16 out[4];
-#pragma unroll
-        for (int q = 0; q < 4; ++q) out[q] = __float2bfloat16(g[q] / (1.0f + __expf(-g[q])) * u[q]);
-        *reinterpret_cast<uint2*>(Z + (size_t)m * F + f) = *reinterpret_cast<const uint2*>(out);
-      }
-    } else {
-#pragma unroll
-      for (int nt = 0; nt < 4; ++nt) {
-        const int n = n0 + nt * 16 + kb * 4;
-        if (n >= N) continue;
-        f32x4* dst = reinterpret_cast<f32x4*>(Y + (size_t)m * N + n);
-        if (EPI == DG_EPI_RESID) *dst = *dst + acc[nt][mt];
-        else *dst = acc[nt][mt];
-      }
-    }
+  for (int i = 0; i < 4; ++i) {
+    int m = tm * 128 + (w * 2 + i / 2) * 16 + (i & 1) * 8 + (lane & 7);
+    if (m > M - 1) m = M - 1;
+    xoff[i] = (unsigned)m * (unsigned)K * 2u + (lane >> 3) * 16;     // < 2^32: checked by the launcher
   }
+  const char* xbase = reinterpret_cast<const char*>(X);
+  const unsigned xfix = (lane >> 5) * 64;   // lanes of the second K step of a stage: fall back to the first one
+  const int stages = (steps + 1) >> 1;
+  auto issue = [&](int st) {                // past the end: the last stage again, into a slot that nobody reads
+    u32x4* slot = lds + (st % DS_STAGES) * (DS_STAGE_BYTES / 16);
+    if (st > stages - 1) st = stages - 1;
+    const bool whole = st * 2 + 1 < steps;  // odd K-step count: never read past a row's or a panel's end
+    const unsigned fix = whole ? 0u : xfix;
+#pragma unroll
+    for (int i = 0; i < 4; ++i)
+      __builtin_amdgcn_global_load_lds(xbase + (size_t)st * 128 + (xoff[i] - fix),
+                                       slot + ((w * 2 + i / 2) * DG_TILE_BYTES + (i & 1) * DG_HALF_BYTES) / 16, 16, 0, 0);
+#pragma unroll
+    for (int i = 0; i < 4; ++i)
+      __builtin_amdgcn_global_load_lds(wbase[i / 2] + (size_t)st * 2048 + ((i & 1) && whole ? 1024 : 0),
+                                       slot + (DS_X_BYTES + (w * 2 + i / 2) * 2048 + (i & 1) * 1024) / 16, 16, 0, 0);
+  };
+  // fragment addresses inside a stage: token tile (w >> 1) * 4 + mt, and panel nt of this wave's four
+  const unsigned lds0 = (unsigned)(size_t)(dg_lds_u32x4*)lds;
+  const unsigned xrd = lds0 + (w >> 1) * 4 * DG_TILE_BYTES + (c >> 3) * DG_HALF_BYTES + kb * 128 + (c & 7) * 16;
+  const unsigned wrd = lds0 + DS_X_BYTES + (w & 1) * (EPI == DG_EPI_ROPE128 ? 2 : 4) * 2048 + lane * 16;
+  f32x4 acc[4][4];
+#pragma unroll
+  for (int a = 0; a < 4; ++a)
+#pragma unroll
+    for (int b = 0; b < 4; ++b) acc[a][b] = f32x4{0.f, 0.f, 0.f, 0.f};
+  u32x4 fw[2][4], fx[2][4];                 // fragments of the current and the next K step
+#define DS_READ(B, ST, H)                                                                                    \
+  {                                                                                                          \
+    const unsigned so_ = ((ST) % DS_STAGES) * DS_STAGE_BYTES;                                                \
+    _Pragma("unroll") for (int i = 0; i < 4; ++i)                                                            \
+      asm volatile("ds_read_b128 %0, %1 offset:%2" : "=v"(fx[B][i]) : "v"(xrd + so_), "n"(i * DG_TILE_BYTES + (H) * 512)); \
+    _Pragma("unroll") for (int i = 0; i < 4; ++i)                                                            \
+      asm volatile("ds_read_b128 %0, %1 offset:%2" : "=v"(fw[B][i]) : "v"(wrd + so_),                        \
+                   "n"((EPI == DG_EPI_ROPE128 ? (i & 1) + (i >> 1) * 4 : i) * 2048 + (H) * 1024));           \
+  }
+#define DS_WAIT(B)                                                                                           \
+  asm volatile("s_waitcnt lgkmcnt(0)" : "+v"(fx[B][0]), "+v"(fx[B][1]), "+v"(fx[B][2]), "+v"(fx[B][3]),      \
+               "+v"(fw[B][0]), "+v"(fw[B][1]), "+v"(fw[B][2]), "+v"(fw[B][3])::"memory");
+#define DS_MMA(B)                                                                                            \
+  __builtin_amdgcn_sched_barrier(0);                                                                         \
+  _Pragma("unroll") for (int mt = 0; mt < 4; ++mt)                                                           \
+    _Pragma("unroll") for (int nt = 0; nt < 4; ++nt)                                                         \
+      acc[nt][mt] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, fw[B][nt]),           \
+                                                            __builtin_bit_cast(bf16x8, fx[B][mt]), acc[nt][mt], 0, 0, 0); \
+  __builtin_amdgcn_sched_barrier(0);
+  issue(0);
+  issue(1);
+  issue(2);
+  asm volatile("s_waitcnt vmcnt(16)\n\ts_barrier" ::: "memory");     // stage 0 is in LDS for everybody
+  DS_READ(0, 0, 0)
+  DS_WAIT(0)
+  const int pairs = steps >> 1;
+  for (int st = 0; st < pairs; ++st) {
+    // Stage st + 1 has landed for this wave (8 loads of st + 2 may be in flight), then for everybody, and everybody is past
+    // reading stage st - 1, whose slot is refilled now.
+    asm volatile("s_waitcnt vmcnt(8)\n\ts_barrier" ::: "memory");
+    issue(st + 3);
+    DS_READ(1, st, 1)
+    DS_MMA(0)
+    DS_WAIT(1)
+    DS_READ(0, st + 1, 0)
+    DS_MMA(1)
+    DS_WAIT(0)
+  }
+  if (steps & 1) {
+    DS_MMA(0)
+  }
+#undef DS_READ
+#undef DS_WAIT
+#undef DS_MMA
+  asm volatile("s_waitcnt vmcnt(0)" ::: "memory");   // the redundant tail loads must not outlive the workgroup's LDS
+  dense_epilogue<EPI, 4>(acc, tm * 128 + (w >> 1) * 64, tn * 2 + (w & 1), c, kb, Y, Z, M, N, ra);
+}
+
+// Tile by the time a launch takes, in rounds of one workgroup per CU (measured, K in steps of 32; us = 9 + 0.65 steps per
+// round of 256 x 256 tiles, 3 + 0.335 steps per round of 128 x 128): 511 x 6144 x 2048 50.5 | 27.1, 1023 x 4096 x 4096 90 |
+// 51, 1023 x 4096 x 11008 220 | 121 (one round either way), 2047 x 4096 x 4096 94 | 91 (1 | 2), 1023 x 8192 x 8192 170 | 184
+// (1 | 2), 511 x 22016 x 4096 100 | 133 (1 | 3), 1023 x 22016 x 4096 192 | 292 (2 | 6).
+static bool dense_small_tiles(int M, int NT, int steps) {
+  const int ncu = spec_num_cu();
+  const int large = (M + DG_BM - 1) / DG_BM * ((NT + 15) / 16), small = (M + 127) / 128 * ((NT + 7) / 8);
+  return (long long)((small + ncu - 1) / ncu) * (300 + 33.5 * steps) < (long long)((large + ncu - 1) / ncu) * (900 + 65.0 * steps);
+}
+
+template <int EPI>
+static hipError_t dense_launch_epi(const bf16* x, const u32x4* w, int M, int N, int K, float* y, bf16* z, const DenseRope& ra,
+                                   hipStream_t st) {
+  const int NT = N / 16, steps = K / 32;
+  const bool small = dense_small_tiles(M, NT, steps);
+  const size_t lds_bytes = small ? (size_t)DS_STAGES * DS_STAGE_BYTES : (size_t)DG_STAGES * DG_STAGE_BYTES;
+  static bool attr_set[2] = {false, false};      // more than the default dynamic LDS
+  if (!attr_set[small]) {
+    const void* f = small ? (const void*)dense_small_kernel<EPI> : (const void*)dense_gemm_kernel<EPI>;
+    hipError_t e = hipFuncSetAttribute(f, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds_bytes);
+    if (e != hipSuccess) return e;
+    attr_set[small] = true;
+  }
+  if (small) {
+    const int TM = (M + 127) / 128, tiles = TM * ((NT + 7) / 8), chunk = (tiles + 7) / 8;
+    dense_small_kernel<EPI><<<8 * chunk, DG_THREADS, lds_bytes, st>>>(x, w, y, z, M, N, K, NT, steps, TM, tiles, chunk, ra);
+  } else {
+    const int TM = (M + DG_BM - 1) / DG_BM, TN = (NT + 15) / 16;
+    const int cx = (TN + 7) / 8, groups = (cx + 3) / 4;
+    dense_gemm_kernel<EPI><<<8 * groups * TM * 4, DG_THREADS, lds_bytes, st>>>(x, w, y, z, M, N, K, NT, steps, TM, cx, ra);
+  }
+  return hipGetLastError();
 }
 
 static hipError_t dense_gemm_launch(const bf16* x, const void* wp, int M, int N, int K, int epi, float* y, bf16* z,
                                     const DenseRope& ra, hipStream_t st) {
   if ((double)M * K * 2.0 >= 4294967296.0) return hipErrorInvalidValue;   // per-lane activation offsets are 32-bit
-  const int NT = N / 16, steps = K / 32;
-  const int TM = (M + DG_BM - 1) / DG_BM, TN = (NT + 15) / 16;
-  const int cx = (TN + 7) / 8;
-  const int groups = (cx + 3) / 4;
-  dim3 grid(8 * groups * TM * 4), block(DG_THREADS);
-  static bool attr_set = false;
-  const size_t lds_bytes = (size_t)DG_STAGES * DG_STAGE_BYTES;   // 96 KiB: above the default dynamic-LDS limit
-  if (!attr_set) {
-    const void* fns[5] = {(const void*)dense_gemm_kernel<DG_EPI_STORE>, (const void*)dense_gemm_kernel<DG_EPI_RESID>,
-                          (const void*)dense_gemm_kernel<DG_EPI_SWIGLU>, (const void*)dense_gemm_kernel<DG_EPI_ROPE128>,
-                          (const void*)dense_gemm_kernel<DG_EPI_ROPE64>};
-    for (const void* f : fns) {
-      hipError_t e = hipFuncSetAttribute(f, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds_bytes);
-      if (e != hipSuccess) return e;
-    }
-    attr_set = true;
-  }
   const u32x4* w4 = (const u32x4*)wp;
   switch (epi) {
-    case DG_EPI_STORE: dense_gemm_kernel<DG_EPI_STORE><<<grid, block, lds_bytes, st>>>(x, w4, y, z, M, N, K, NT, steps, TM, cx, ra); break;
-    case DG_EPI_RESID: dense_gemm_kernel<DG_EPI_RESID><<<grid, block, lds_bytes, st>>>(x, w4, y, z, M, N, K, NT, steps, TM, cx, ra); break;
-    case DG_EPI_SWIGLU: dense_gemm_kernel<DG_EPI_SWIGLU><<<grid, block, lds_bytes, st>>>(x, w4, y, z, M, N, K, NT, steps, TM, cx, ra); break;
-    case DG_EPI_ROPE128: dense_gemm_kernel<DG_EPI_ROPE128><<<grid, block, lds_bytes, st>>>(x, w4, y, z, M, N, K, NT, steps, TM, cx, ra); break;
-    default: dense_gemm_kernel<DG_EPI_ROPE64><<<grid, block, lds_bytes, st>>>(x, w4, y, z, M, N, K, NT, steps, TM, cx, ra); break;
+    case DG_EPI_STORE: return dense_launch_epi<DG_EPI_STORE>(x, w4, M, N, K, y, z, ra, st);
+    case DG_EPI_RESID: return dense_launch_epi<DG_EPI_RESID>(x, w4, M, N, K, y, z, ra, st);
+    case DG_EPI_SWIGLU: return dense_launch_epi<DG_EPI_SWIGLU>(x, w4, M, N, K, y, z, ra, st);
+    case DG_EPI_ROPE128: return dense_launch_epi<DG_EPI_ROPE128>(x, w4, M, N, K, y, z, ra, st);
+    default: return dense_launch_epi<DG_EPI_ROPE64>(x, w4, M, N, K, y, z, ra, st);
   }
-  return hipGetLastError();
 }
 
 hipError_t launch_dense_gemm(const bf16* x, const void* wp, int M, int N, int K, int epi, float* y, bf16* z,

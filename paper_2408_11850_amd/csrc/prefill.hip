@@ -61,7 +61,7 @@ typedef __attribute__((address_space(3))) u32x4 dg_lds_u32x4;
 // A wave's 64 outputs (group wn of them) x 16 MTN tokens from m0 on.
 template <int EPI, int MTN>
 __device__ __forceinline__ void dense_epilogue(const f32x4 (&acc)[4][MTN], int m0, int wn, int c, int kb, float* __restrict__ Y,
-                                               bf16* __restrict__ Z, int M, int N, const DenseRope& ra) {
+                                               bf16* __restrict__ Z, int M, int N, int ldz, const DenseRope& ra) {
   // acc[nt][mt][r] = Y[m0 + 16 mt + c][n0 + 16 nt + 4 kb + r]
   const int n0 = wn * 64;
   if (EPI == DG_EPI_ROPE128 || EPI == DG_EPI_ROPE64) {
@@ -127,7 +127,6 @@ __device__ __forceinline__ void dense_epilogue(const f32x4 (&acc)[4][MTN], int m
     const int m = m0 + mt * 16 + c;
     if (m >= M) continue;
     if (EPI == DG_EPI_SWIGLU) {
-      const int F = N >> 1;
 #pragma unroll
       for (int nt = 0; nt < 4; nt += 2) {
         const int n = n0 + nt * 16;
@@ -137,7 +136,7 @@ __device__ __forceinline__ void dense_epilogue(const f32x4 (&acc)[4][MTN], int m
         bf16 out[4];
 #pragma unroll
         for (int q = 0; q < 4; ++q) out[q] = __float2bfloat16(g[q] / (1.0f + __expf(-g[q])) * u[q]);
-        *reinterpret_cast<uint2*>(Z + (size_t)m * F + f) = *reinterpret_cast<const uint2*>(out);
+        *reinterpret_cast<uint2*>(Z + (size_t)m * ldz + f) = *reinterpret_cast<const uint2*>(out);
       }
     } else {
 #pragma unroll
@@ -156,7 +155,7 @@ template <int EPI>
 __global__ __launch_bounds__(DG_THREADS, 1) void dense_gemm_kernel(const bf16* __restrict__ X,
                                                                    const u32x4* __restrict__ Wp,
                                                                    float* __restrict__ Y, bf16* __restrict__ Z, int M,
-                                                                   int N, int K, int NT, int steps, int TM, int cx,
+                                                                   int N, int K, int ldz, int NT, int steps, int TM, int cx,
                                                                    DenseRope ra) {
   extern __shared__ u32x4 lds[];          // DG_STAGES * DG_STAGE_BYTES
   const int w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), lane = threadIdx.x & 63;   // w: wave-uniform
@@ -302,7 +301,7 @@ __global__ __launch_bounds__(DG_THREADS, 1) void dense_gemm_kernel(const bf16* _
                  "+a"(acc[nt][10]), "+a"(acc[nt][11]), "+a"(acc[nt][12]), "+a"(acc[nt][13]), "+a"(acc[nt][14]),
                  "+a"(acc[nt][15]));
 
-  dense_epilogue<EPI, 16>(acc, tm * DG_BM, tn * 4 + w, c, kb, Y, Z, M, N, ra);
+  dense_epilogue<EPI, 16>(acc, tm * DG_BM, tn * 4 + w, c, kb, Y, Z, M, N, ldz, ra);
 }
 
 // Grids that 256 x 256 tiles do not fill: workgroup = 4 waves = 128 tokens x 128 outputs, a wave owns 64 x 64 (4 x 4 MFMA
@@ -317,7 +316,7 @@ __global__ __launch_bounds__(DG_THREADS, 1) void dense_gemm_kernel(const bf16* _
 template <int EPI>
 __global__ __launch_bounds__(DG_THREADS, 2) void dense_small_kernel(const bf16* __restrict__ X, const u32x4* __restrict__ Wp,
                                                                     float* __restrict__ Y, bf16* __restrict__ Z, int M, int N,
-                                                                    int K, int NT, int steps, int TM, int tiles, int chunk,
+                                                                    int K, int ldz, int NT, int steps, int TM, int tiles, int chunk,
                                                                     DenseRope ra) {
   extern __shared__ u32x4 lds[];          // DS_STAGES * DS_STAGE_BYTES
   const int w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), lane = threadIdx.x & 63;
@@ -414,7 +413,7 @@ __global__ __launch_bounds__(DG_THREADS, 2) void dense_small_kernel(const bf16* 
 #undef DS_WAIT
 #undef DS_MMA
   asm volatile("s_waitcnt vmcnt(0)" ::: "memory");   // the redundant tail loads must not outlive the workgroup's LDS
-  dense_epilogue<EPI, 4>(acc, tm * 128 + (w >> 1) * 64, tn * 2 + (w & 1), c, kb, Y, Z, M, N, ra);
+  dense_epilogue<EPI, 4>(acc, tm * 128 + (w >> 1) * 64, tn * 2 + (w & 1), c, kb, Y, Z, M, N, ldz, ra);
 }
 
 // Tile by the time a launch takes, in rounds of one workgroup per CU (measured, K in steps of 32; us = 9 + 0.65 steps per
@@ -428,8 +427,8 @@ static bool dense_small_tiles(int M, int NT, int steps) {
 }
 
 template <int EPI>
-static hipError_t dense_launch_epi(const bf16* x, const u32x4* w, int M, int N, int K, float* y, bf16* z, const DenseRope& ra,
-                                   hipStream_t st) {
+static hipError_t dense_launch_epi(const bf16* x, const u32x4* w, int M, int N, int K, float* y, bf16* z, int ldz,
+                                   const DenseRope& ra, hipStream_t st) {
   const int NT = N / 16, steps = K / 32;
   const bool small = dense_small_tiles(M, NT, steps);
   const size_t lds_bytes = small ? (size_t)DS_STAGES * DS_STAGE_BYTES : (size_t)DG_STAGES * DG_STAGE_BYTES;
@@ -442,32 +441,32 @@ static hipError_t dense_launch_epi(const bf16* x, const u32x4* w, int M, int N, 
   }
   if (small) {
     const int TM = (M + 127) / 128, tiles = TM * ((NT + 7) / 8), chunk = (tiles + 7) / 8;
-    dense_small_kernel<EPI><<<8 * chunk, DG_THREADS, lds_bytes, st>>>(x, w, y, z, M, N, K, NT, steps, TM, tiles, chunk, ra);
+    dense_small_kernel<EPI><<<8 * chunk, DG_THREADS, lds_bytes, st>>>(x, w, y, z, M, N, K, ldz, NT, steps, TM, tiles, chunk, ra);
   } else {
     const int TM = (M + DG_BM - 1) / DG_BM, TN = (NT + 15) / 16;
     const int cx = (TN + 7) / 8, groups = (cx + 3) / 4;
-    dense_gemm_kernel<EPI><<<8 * groups * TM * 4, DG_THREADS, lds_bytes, st>>>(x, w, y, z, M, N, K, NT, steps, TM, cx, ra);
+    dense_gemm_kernel<EPI><<<8 * groups * TM * 4, DG_THREADS, lds_bytes, st>>>(x, w, y, z, M, N, K, ldz, NT, steps, TM, cx, ra);
   }
   return hipGetLastError();
 }
 
 static hipError_t dense_gemm_launch(const bf16* x, const void* wp, int M, int N, int K, int epi, float* y, bf16* z,
-                                    const DenseRope& ra, hipStream_t st) {
+                                    int ldz, const DenseRope& ra, hipStream_t st) {
   if ((double)M * K * 2.0 >= 4294967296.0) return hipErrorInvalidValue;   // per-lane activation offsets are 32-bit
   const u32x4* w4 = (const u32x4*)wp;
   switch (epi) {
-    case DG_EPI_STORE: return dense_launch_epi<DG_EPI_STORE>(x, w4, M, N, K, y, z, ra, st);
-    case DG_EPI_RESID: return dense_launch_epi<DG_EPI_RESID>(x, w4, M, N, K, y, z, ra, st);
-    case DG_EPI_SWIGLU: return dense_launch_epi<DG_EPI_SWIGLU>(x, w4, M, N, K, y, z, ra, st);
-    case DG_EPI_ROPE128: return dense_launch_epi<DG_EPI_ROPE128>(x, w4, M, N, K, y, z, ra, st);
-    default: return dense_launch_epi<DG_EPI_ROPE64>(x, w4, M, N, K, y, z, ra, st);
+    case DG_EPI_STORE: return dense_launch_epi<DG_EPI_STORE>(x, w4, M, N, K, y, z, ldz, ra, st);
+    case DG_EPI_RESID: return dense_launch_epi<DG_EPI_RESID>(x, w4, M, N, K, y, z, ldz, ra, st);
+    case DG_EPI_SWIGLU: return dense_launch_epi<DG_EPI_SWIGLU>(x, w4, M, N, K, y, z, ldz, ra, st);
+    case DG_EPI_ROPE128: return dense_launch_epi<DG_EPI_ROPE128>(x, w4, M, N, K, y, z, ldz, ra, st);
+    default: return dense_launch_epi<DG_EPI_ROPE64>(x, w4, M, N, K, y, z, ldz, ra, st);
   }
 }
 
 hipError_t launch_dense_gemm(const bf16* x, const void* wp, int M, int N, int K, int epi, float* y, bf16* z,
-                             hipStream_t st) {
+                             hipStream_t st, int ldz) {
   DenseRope none = {};
-  return dense_gemm_launch(x, wp, M, N, K, epi, y, z, none, st);
+  return dense_gemm_launch(x, wp, M, N, K, epi, y, z, ldz ? ldz : N / 2, none, st);
 }
 
 // The fused QKV projection of a prompt block: q (rotated, bf16) to `q`, k (rotated) and v into the pages of
@@ -476,7 +475,7 @@ hipError_t launch_dense_qkv_rope(const bf16* x, const void* wp, int M, int K, bf
                                  const int* len_ptr, const float2* tab, KvGeom g, int layer, int Hq, hipStream_t st) {
   DenseRope ra = {q, pool, block_table, len_ptr, tab, g, layer, Hq};
   const int N = (Hq + 2 * g.n_kv_heads) * g.head_dim;
-  return dense_gemm_launch(x, wp, M, N, K, g.head_dim == 128 ? DG_EPI_ROPE128 : DG_EPI_ROPE64, nullptr, nullptr, ra, st);
+  return dense_gemm_launch(x, wp, M, N, K, g.head_dim == 128 ? DG_EPI_ROPE128 : DG_EPI_ROPE64, nullptr, nullptr, 0, ra, st);
 }
 
 // ---------------------------------------------------------------------------------------------------------

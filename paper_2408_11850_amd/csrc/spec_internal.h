@@ -153,7 +153,7 @@ size_t attention_workspace_floats(int Hq, int Hkv, int dh, int max_seq);
 // prompt-sized (matrix-core bound) kernels: epilogue 0 = store fp32, 1 = add into fp32, 2 = silu(gate)*up -> bf16
 #define SPEC_PREFILL_BLOCK_MAX 4096   // most prompt tokens one dense pass takes
 hipError_t launch_dense_gemm(const bf16* x, const void* wp, int M, int N, int K, int epi, float* y, bf16* z,
-                             hipStream_t st);
+                             hipStream_t st, int ldz = 0);   // ldz: row stride of z, 0 = N / 2
 // fused QKV projection of a prompt block with RoPE and the paged K / V append in its epilogue
 hipError_t launch_dense_qkv_rope(const bf16* x, const void* wp, int M, int K, bf16* q, bf16* pool, const int* block_table,
                                  const int* len_ptr, const float2* tab, KvGeom g, int layer, int Hq, hipStream_t st);

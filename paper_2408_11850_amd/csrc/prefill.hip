@@ -488,20 +488,18 @@ hipError_t launch_dense_qkv_rope(const bf16* x, const void* wp, int M, int K, bf
 // per query row in the base-2 domain, O^T += V^T P^T.  Chunks beyond the last position a workgroup's rows may
 // see are never touched (causal skip), and the workgroups with the longest ranges are scheduled first.
 // ---------------------------------------------------------------------------------------------------------
-#define PA_WAVES 8
 #define PA_QT 2                                  // 16-row tiles per wave
-#define PA_ROWS (PA_WAVES * PA_QT * 16)          // rows per workgroup
 #define PA_STAGES 2
 #define PA_NEG_BIG (-1.0e30f)
 
 // Brings chunk `ch` (64 positions = page block_table[ch]) of one KV head into an LDS stage.  Block b of a chunk:
 // b < KB -> K block b (lane-linear in the page), else V block b - KB, whose lane (c, g4) sits at byte
 // c*64 + g4*16 of the block.
-template <int DH>
+template <int DH, int WAVES>
 __device__ __forceinline__ void pa_issue(const bf16* __restrict__ pool, const int* __restrict__ block_table,
                                          const KvGeom& g, int layer, int kvh, int ch, u32x4* lds_stage, int w,
                                          int lane) {
-  constexpr int KB = 4 * (DH / 32), VB = 2 * (DH / 16), LPW = (KB + VB) / PA_WAVES;
+  constexpr int KB = 4 * (DH / 32), VB = 2 * (DH / 16), LPW = (KB + VB) / WAVES;
   const int c = lane & 15, g4 = lane >> 4;
   const int page = block_table[ch];
   const u32x4* kblk = reinterpret_cast<const u32x4*>(pool + g.offset(page, layer, 0, kvh)) + lane;
@@ -515,13 +513,14 @@ __device__ __forceinline__ void pa_issue(const bf16* __restrict__ pool, const in
   }
 }
 
-template <int DH>
-__global__ __launch_bounds__(PA_WAVES * 64, 2) void prefill_attn_kernel(const bf16* __restrict__ q,
+template <int DH, int WAVES>
+__global__ __launch_bounds__(WAVES * 64, 2) void prefill_attn_kernel(const bf16* __restrict__ q,
                                                                         const bf16* __restrict__ pool,
                                                                         const int* __restrict__ block_table,
                                                                         const int* __restrict__ len_ptr, KvGeom g,
                                                                         int layer, int M, int Hq, float scale_log2e,
                                                                         bf16* __restrict__ out) {
+  constexpr int PA_ROWS = WAVES * PA_QT * 16;    // rows per workgroup
   constexpr int KS = DH / 32;                    // K steps per 16-position tile
   constexpr int KB = 4 * KS;                     // K blocks (1 KiB) per chunk
   constexpr int VB = 2 * (DH / 16);              // V blocks per chunk
@@ -570,11 +569,11 @@ __global__ __launch_bounds__(PA_WAVES * 64, 2) void prefill_attn_kernel(const bf
     for (int dt = 0; dt < DH / 16; ++dt) o[t][dt] = f32x4{0.f, 0.f, 0.f, 0.f};
   }
 
-  pa_issue<DH>(pool, block_table, g, layer, kvh, 0, &lds[0][0][0], w, lane);
+  pa_issue<DH, WAVES>(pool, block_table, g, layer, kvh, 0, &lds[0][0][0], w, lane);
   for (int ch = 0; ch < nch; ++ch) {
     // chunk ch has landed for this wave, then for everybody; all waves are done with the other stage
     asm volatile("s_waitcnt vmcnt(0)\n\ts_barrier" ::: "memory");
-    pa_issue<DH>(pool, block_table, g, layer, kvh, ch + 1 < nch ? ch + 1 : nch - 1, &lds[(ch + 1) % PA_STAGES][0][0], w,
+    pa_issue<DH, WAVES>(pool, block_table, g, layer, kvh, ch + 1 < nch ? ch + 1 : nch - 1, &lds[(ch + 1) % PA_STAGES][0][0], w,
                  lane);
     const int pos0 = ch << 6;
     if (pos0 > wave_limit) continue;           // nothing visible for this wave's rows (uniform per wave)
@@ -663,11 +662,19 @@ __global__ __launch_bounds__(PA_WAVES * 64, 2) void prefill_attn_kernel(const bf
 hipError_t launch_prefill_attention(const bf16* q, const bf16* pool, const int* block_table, const int* len_ptr,
                                     KvGeom g, int layer, int M, int Hq, bf16* out, hipStream_t st) {
   const int Hkv = g.n_kv_heads, G = Hq / Hkv, R = M * G, dh = g.head_dim;
-  dim3 grid((R + PA_ROWS - 1) / PA_ROWS, Hkv), block(PA_WAVES * 64);
   const float scale_log2e = 1.4426950408889634f / sqrtf((float)dh);
-  if (dh == 128)
-    prefill_attn_kernel<128><<<grid, block, 0, st>>>(q, pool, block_table, len_ptr, g, layer, M, Hq, scale_log2e, out);
-  else
-    prefill_attn_kernel<64><<<grid, block, 0, st>>>(q, pool, block_table, len_ptr, g, layer, M, Hq, scale_log2e, out);
+  // 8 waves = 256 rows per workgroup read K and V half as often; 4 waves = 128 rows where the grid is short of two
+  // workgroups per CU (1023 tokens, 32 heads: 41.7 us with 128 workgroups, 31.8 with 256)
+  const bool small = (long long)((R + 255) / 256) * Hkv < 2 * spec_num_cu();
+  const dim3 grid((R + (small ? 127 : 255)) / (small ? 128 : 256), Hkv), block(small ? 256 : 512);
+#define PA_GO(DH, WAVES) prefill_attn_kernel<DH, WAVES><<<grid, block, 0, st>>>(q, pool, block_table, len_ptr, g, layer, M, Hq, scale_log2e, out)
+  if (dh == 128) {
+    if (small) PA_GO(128, 4);
+    else PA_GO(128, 8);
+  } else {
+    if (small) PA_GO(64, 4);
+    else PA_GO(64, 8);
+  }
+#undef PA_GO
   return hipGetLastError();
 }

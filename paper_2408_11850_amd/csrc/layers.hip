@@ -17,67 +17,44 @@ hipError_t launch_set_pages(int* block_table, PageUpdate u, hipStream_t st) {
   return hipGetLastError();
 }
 
-// h[m][:] = float(E[tok[m]][:]); an id outside the vocabulary reads row 0 (ids are validated on the host)
+// h[m][:] = float(E[tok[m]][:]); an id outside the vocabulary reads row 0 (ids are validated on the host); d % 4 == 0
 __global__ void embed_kernel(float* __restrict__ h, const bf16* __restrict__ E, const int* __restrict__ tok, int d,
                              int vocab) {
   const int m = blockIdx.x;
   int t = tok[m];
   if (t < 0 || t >= vocab) t = 0;
-  const bf16* row = E + (size_t)t * d;
-  for (int i = threadIdx.x; i < d; i += blockDim.x) h[(size_t)m * d + i] = __bfloat162float(row[i]);
+  const uint2* row = reinterpret_cast<const uint2*>(E + (size_t)t * d);
+  for (int i = threadIdx.x; i < d >> 2; i += blockDim.x) {
+    const uint2 ev = row[i];
+    const bf16* e = reinterpret_cast<const bf16*>(&ev);
+    reinterpret_cast<f32x4*>(h + (size_t)m * d)[i] =
+        f32x4{__bfloat162float(e[0]), __bfloat162float(e[1]), __bfloat162float(e[2]), __bfloat162float(e[3])};
+  }
 }
 hipError_t launch_embed(float* h, const bf16* embed, const int* tok, int M, int d, int vocab, hipStream_t st) {
   embed_kernel<<<M, 256, 0, st>>>(h, embed, tok, d, vocab);
   return hipGetLastError();
 }
 
-__device__ __forceinline__ float block_sum(float v, float* sh) {
-#pragma unroll
-  for (int o = 32; o > 0; o >>= 1) v += __shfl_xor(v, o);
-  const int w = threadIdx.x >> 6;
-  if ((threadIdx.x & 63) == 0) sh[w] = v;
-  __syncthreads();
-  float t = 0.f;
-  const int nw = blockDim.x >> 6;
-  for (int i = 0; i < nw; ++i) t += sh[i];
-  __syncthreads();
-  return t;
-}
-
-// h[m] += sum_s P[s][m] ; a[m] = h[m] * rsqrt(mean(h[m]^2) + eps) * gain.
-// One workgroup of 1024 threads per row; a thread keeps its (at most 4) float4 pieces of the row in
-// registers, and the S slice loads of a piece are independent, so the row is read in a few round trips.
-#define ADDNORM_THREADS 1024
-#define ADDNORM_PIECES 4      // d_model <= 4 * 4 * 1024
-__global__ __launch_bounds__(ADDNORM_THREADS) void addnorm_kernel(float* __restrict__ h, const float* __restrict__ P,
-                                                                  int S, const bf16* __restrict__ gain,
-                                                                  bf16* __restrict__ a, int M, int d, float eps) {
-  __shared__ float sh[ADDNORM_THREADS / 64];
+// a[m] = h[m] * rsqrt(mean(h[m]^2) + eps) * gain, for a prompt block.  One workgroup of 1024 threads per row; a thread keeps
+// its (at most 4) float4 pieces of the row in registers.  Bound by HBM: the row once in, half of it out.
+#define NORM_THREADS 1024
+#define NORM_PIECES 4      // d_model <= 4 * 4 * 1024
+static_assert(SPEC_D_MODEL_MAX <= 4 * NORM_PIECES * NORM_THREADS, "a row fits the registers of a workgroup");
+__global__ __launch_bounds__(NORM_THREADS) void norm_kernel(const float* __restrict__ h, const bf16* __restrict__ gain,
+                                                            bf16* __restrict__ a, int d, float eps) {
+  __shared__ float sh[NORM_THREADS / 64];
   const int m = blockIdx.x;
   const int d4 = d >> 2;
-  f32x4* hr = reinterpret_cast<f32x4*>(h + (size_t)m * d);
-  const f32x4* P4 = reinterpret_cast<const f32x4*>(P);
-  f32x4 v[ADDNORM_PIECES];
+  const f32x4* hr = reinterpret_cast<const f32x4*>(h + (size_t)m * d);
+  f32x4 v[NORM_PIECES];
   float ss = 0.f;
 #pragma unroll
-  for (int it = 0; it < ADDNORM_PIECES; ++it) {
-    const int i = threadIdx.x + it * ADDNORM_THREADS;
+  for (int it = 0; it < NORM_PIECES; ++it) {
+    const int i = threadIdx.x + it * NORM_THREADS;
     v[it] = f32x4{0.f, 0.f, 0.f, 0.f};
-    if (i < d4) {
-      f32x4 t = hr[i];
-      if (P) {
-        int s = 0;
-        for (; s + 4 <= S; s += 4) {   // four independent loads in flight, added in ascending slice order
-          const f32x4 p0 = P4[((size_t)(s + 0) * M + m) * d4 + i], p1 = P4[((size_t)(s + 1) * M + m) * d4 + i];
-          const f32x4 p2 = P4[((size_t)(s + 2) * M + m) * d4 + i], p3 = P4[((size_t)(s + 3) * M + m) * d4 + i];
-          t += p0; t += p1; t += p2; t += p3;
-        }
-        for (; s < S; ++s) t += P4[((size_t)s * M + m) * d4 + i];
-      }
-      hr[i] = t;
-      v[it] = t;
-      ss += t.x * t.x + t.y * t.y + t.z * t.z + t.w * t.w;
-    }
+    if (i < d4) v[it] = hr[i];
+    ss += v[it].x * v[it].x + v[it].y * v[it].y + v[it].z * v[it].z + v[it].w * v[it].w;
   }
 #pragma unroll
   for (int o = 32; o > 0; o >>= 1) ss += __shfl_xor(ss, o);
@@ -85,29 +62,29 @@ __global__ __launch_bounds__(ADDNORM_THREADS) void addnorm_kernel(float* __restr
   __syncthreads();
   float tot = 0.f;
 #pragma unroll
-  for (int i = 0; i < ADDNORM_THREADS / 64; ++i) tot += sh[i];
+  for (int i = 0; i < NORM_THREADS / 64; ++i) tot += sh[i];
   const float inv = 1.0f / sqrtf(tot / (float)d + eps);
 #pragma unroll
-  for (int it = 0; it < ADDNORM_PIECES; ++it) {
-    const int i = threadIdx.x + it * ADDNORM_THREADS;
+  for (int it = 0; it < NORM_PIECES; ++it) {
+    const int i = threadIdx.x + it * NORM_THREADS;
     if (i < d4) {
-      const bf16* g = gain + (size_t)i * 4;
-      bf16* dst = a + (size_t)m * d + (size_t)i * 4;
-      dst[0] = __float2bfloat16(v[it].x * inv * __bfloat162float(g[0]));
-      dst[1] = __float2bfloat16(v[it].y * inv * __bfloat162float(g[1]));
-      dst[2] = __float2bfloat16(v[it].z * inv * __bfloat162float(g[2]));
-      dst[3] = __float2bfloat16(v[it].w * inv * __bfloat162float(g[3]));
+      const uint2 gv = reinterpret_cast<const uint2*>(gain)[i];
+      const bf16* g = reinterpret_cast<const bf16*>(&gv);
+      bf16 o[4];
+#pragma unroll
+      for (int r = 0; r < 4; ++r) o[r] = __float2bfloat16(v[it][r] * inv * __bfloat162float(g[r]));
+      reinterpret_cast<uint2*>(a + (size_t)m * d)[i] = *reinterpret_cast<const uint2*>(o);
     }
   }
 }
-hipError_t launch_addnorm(float* h, const float* partials, int S, const bf16* gain, bf16* a, int M, int d, float eps,
-                          hipStream_t st) {
-  addnorm_kernel<<<M, ADDNORM_THREADS, 0, st>>>(h, partials, S, gain, a, M, d, eps);
+hipError_t launch_norm(const float* h, const bf16* gain, bf16* a, int M, int d, float eps, hipStream_t st) {
+  if ((d & 3) || d > SPEC_D_MODEL_MAX) return hipErrorInvalidValue;
+  norm_kernel<<<M, NORM_THREADS, 0, st>>>(h, gain, a, d, eps);
   return hipGetLastError();
 }
 
 // The residual add alone, spread over d/1024 workgroups per row (one compute unit cannot pull the S slices of a
-// long row fast enough): h += sum_s P[s] in the same order as addnorm_kernel, and the sum of squares of each
+// long row fast enough): h += sum_s P[s] in ascending order, and the sum of squares of each
 // 1024-column piece, plus x' = bf16(h * gain) for the next projection (whose consumers apply 1/rms).
 #define ADDSQ_THREADS 256
 __global__ __launch_bounds__(ADDSQ_THREADS) void add_sumsq_kernel(float* __restrict__ h, const float* __restrict__ P,

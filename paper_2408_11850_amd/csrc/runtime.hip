@@ -480,13 +480,13 @@ int prefill_dense_block(spec_ctx* c, int which, const int32_t* tok, int C) {
   const int qkvN = (d.n_heads + 2 * d.n_kv_heads) * d.head_dim;
   const int HD = d.n_heads * d.head_dim;
   for (int l = 0; l < d.n_layers; ++l) {
-    HIPCHK(launch_addnorm(m.pf_h, nullptr, 0, (const bf16*)m.attn_norm[l], m.pf_a, C, d.d_model, d.rms_eps, st));
+    HIPCHK(launch_norm(m.pf_h, (const bf16*)m.attn_norm[l], m.pf_a, C, d.d_model, d.rms_eps, st));
     HIPCHK(launch_dense_qkv_rope(m.pf_a, m.wqkv[l], C, d.d_model, m.pf_q, m.pool, m.block_table_dev, m.len_dev,
                                  m.pf_rope, m.geom, l, d.n_heads, st));
     HIPCHK(launch_prefill_attention(m.pf_q, m.pool, m.block_table_dev, m.len_dev, m.geom, l, C, d.n_heads, m.pf_attn,
                                     st));
     HIPCHK(launch_dense_gemm(m.pf_attn, m.wo[l], C, d.d_model, HD, 1, m.pf_h, nullptr, st));
-    HIPCHK(launch_addnorm(m.pf_h, nullptr, 0, (const bf16*)m.ffn_norm[l], m.pf_a, C, d.d_model, d.rms_eps, st));
+    HIPCHK(launch_norm(m.pf_h, (const bf16*)m.ffn_norm[l], m.pf_a, C, d.d_model, d.rms_eps, st));
     HIPCHK(launch_dense_gemm(m.pf_a, m.wgu[l], C, 2 * d.d_ffn, d.d_model, 2, nullptr, m.pf_z, st, dense_ffn(d)));
     HIPCHK(launch_dense_gemm(m.pf_z, m.wdown[l], C, d.d_model, dense_ffn(d), 1, m.pf_h, nullptr, st));
   }

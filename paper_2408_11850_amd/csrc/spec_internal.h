@@ -135,9 +135,8 @@ hipError_t launch_begin(const BeginArgs& a, const TokenSrc& src, const PageUpdat
 hipError_t launch_set_int(int* dst, int value, hipStream_t st);
 hipError_t launch_set_pages(int* block_table, PageUpdate u, hipStream_t st);
 hipError_t launch_embed(float* h, const bf16* embed, const int* tok, int M, int d, int vocab, hipStream_t st);
-// h += sum_s partials[s] (if partials), a = rmsnorm(h) * gain
-hipError_t launch_addnorm(float* h, const float* partials, int S, const bf16* gain, bf16* a, int M, int d,
-                          float eps, hipStream_t st);
+// a = rmsnorm(h) * gain
+hipError_t launch_norm(const float* h, const bf16* gain, bf16* a, int M, int d, float eps, hipStream_t st);
 // h += sum_s partials[s] (if partials), a = bf16(h * gain) (not normalised), ssq[m][w] = sum of h^2 over the w-th
 // piece of 1024 columns of row m (row stride SSQ_STRIDE; pieces beyond W
 // are never written); returns the number of pieces W through *W_out

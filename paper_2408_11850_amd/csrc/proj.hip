@@ -302,11 +302,16 @@ __global__ __launch_bounds__(PROJ_THREADS, RP * MT > 4 ? 2 : 4) void proj_kernel
 //   that shows where a workgroup has a single long group           2048 x 5632, M = 17   9.8 | 12.4
 //                                                                  7168 x 19200, M = 32 66.0 | 70.5
 //   (but 7168 x 19200, M = 17 62.6 | 53.1;  4096 x 4096, M = 32 13.3 | 13.2)
+//   long K and uneven shares of panels                             6352 x 16824, M = 16 39.9 | 45.0
+//                                                                  29216 x 10440, M = 6 97.6 | 100.8
+//   (even: 7168 x 19200, M = 12 49.7 | 48.0;  40624 x 5160, M = 1 67.8 | 66.4)
 bool proj_whole_k(int M, int N, int K) {
   if (K > 4 * N) return false;
-  if (M <= 16 || K <= 4096) return true;
   const int NT = N / 16, ncu = spec_num_cu();
-  return NT > (M > 24 ? 2 * ncu : ncu / 2);
+  if (K <= 4096 || (M <= 8 && NT <= 6 * ncu)) return true;
+  if (M > 16 && NT <= (M > 24 ? 2 * ncu : ncu / 2)) return false;
+  // share of the CUs' time in use if every CU takes as many panels as the busiest
+  return NT <= ncu || NT * 10 >= (NT + ncu - 1) / ncu * ncu * (M <= 8 ? 9 : 8);
 }
 
 // Layout, panels at a time (RP) and workgroups.  The layout and RP set the order of the sums and depend on the shape

@@ -79,6 +79,10 @@ __global__ __launch_bounds__(PROJ_THREADS, RP * MT > 4 ? 2 : 4) void proj_kernel
   constexpr int NBUF = RP * MT <= 4 ? 2 : 1;            // two reduction buffers while they fit: one barrier per group
   __shared__ f32x4 red[NBUF][PROJ_WAVES][RP][MT][64];
   __shared__ float inv_sh[SPEC_MAX_TOKENS];
+  // The draft's waves issue first.  Beside a target whose long ranges keep a CU's memory queue full, the draft's short
+  // kernels waited for their turn at every load: a draft forward inside a step of two overlapped chains took 10.5 ms
+  // (3.1 alone) and the step 42.1 ms; with priority 5.2 and 40.7 (70B / 7B shapes, windows of 7).
+  if (TAG == 1) __builtin_amdgcn_s_setprio(3);
   const int w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), lane = threadIdx.x & 63;
   const int c = lane & 15, kb = lane >> 4;
   if (a.stamp && threadIdx.x == 0)

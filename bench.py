@@ -508,7 +508,7 @@ def main():
                                f"{cfg.n_prompt}, temperature {cfg.temperature}, gamma {gamma} (c={tp / tq:.2f})",
                    "gamma": gamma, "c": tp / tq, "gamma_both_streams_busy": g_con, "c_both_streams_busy": tp_c / tq_c,
                    "n_prompt": cfg.n_prompt, "two_streams": True},
-        "roofline": {"bound": "hbm", "kernel": "gemm_partial_kernel<1, 8, 0, 4> (target projections)",
+        "roofline": {"bound": "hbm", "kernel": "proj_kernel (target projections, all epilogues)",
                      "achieved": gemm_alone, "peak": HBM_PEAK_GBS, "unit": "GB/s", "frac": gemm_alone / HBM_PEAK_GBS,
                      "traffic": traffic, "launches": int(n_a), "avg_launch_us": ms_a / max(n_a, 1) * 1e3,
                      "avg_bytes_per_launch": bytes_a / max(n_a, 1), "read_ceiling_GBps": read_ceiling,

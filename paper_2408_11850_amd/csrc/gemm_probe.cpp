@@ -1,4 +1,4 @@
-// Stand-alone driver for profiling the projection kernel without Python: runs spec_gemm_partials on the
+// Stand-alone driver for profiling the projection kernel without Python: runs spec_gemm on the
 // five projection shapes of a model (default: the 70B-shape target) at a given token count, plus the
 // streaming-read probe and the weight-packing copy kernel as calibration launches of known size.
 // Weights are a constant byte pattern (traffic and timing do not depend on the values).
@@ -114,8 +114,9 @@ int main(int argc, char** argv) {
                           {"down", d, F}, {"lm_head", V, d}};
   hipStream_t st;
   CK(hipStreamCreate(&st));
-  size_t max_w = 0, max_work = 0, max_x = 0;
+  size_t max_w = 0, max_work = 0, max_x = 0, max_y = 0;
   for (const Shape& s : shapes) {
+    if ((size_t)M * s.N * 4 > max_y) max_y = (size_t)M * s.N * 4;
     size_t b = spec_packed_bytes(s.N, s.K);
     if (b > max_w) max_w = b;
     size_t w = spec_gemm_workspace_bytes(M, s.N, s.K);
@@ -123,11 +124,12 @@ int main(int argc, char** argv) {
     if ((size_t)M * s.K * 2 > max_x) max_x = (size_t)M * s.K * 2;
   }
   // two weight buffers used alternately, so that a launch never finds its matrix in a cache
-  void *w[2], *x, *work, *out, *rowmajor;
+  void *w[2], *x, *y, *work, *out, *rowmajor;
   CK(hipMalloc(&w[0], max_w));
   CK(hipMalloc(&w[1], max_w));
   CK(hipMalloc(&rowmajor, max_w));
   CK(hipMalloc(&x, max_x));
+  CK(hipMalloc(&y, max_y));
   CK(hipMalloc(&work, max_work));
   CK(hipMalloc(&out, 256));
   CK(hipMemset(w[0], 0x3c, max_w));
@@ -142,9 +144,9 @@ int main(int argc, char** argv) {
   printf("projection probe: M=%d, %d launches per shape\n", M, iters);
   for (const Shape& s : shapes) {
     const size_t bytes = spec_packed_bytes(s.N, s.K);
-    SK(spec_gemm_partials(x, w[0], M, s.N, s.K, work, st));   // warm-up
+    SK(spec_gemm((float*)y, x, w[0], M, s.N, s.K, work, st));   // warm-up
     CK(hipEventRecord(e0, st));
-    for (int i = 0; i < iters; ++i) SK(spec_gemm_partials(x, w[(i + 1) & 1], M, s.N, s.K, work, st));
+    for (int i = 0; i < iters; ++i) SK(spec_gemm((float*)y, x, w[(i + 1) & 1], M, s.N, s.K, work, st));
     CK(hipEventRecord(e1, st));
     CK(hipStreamSynchronize(st));
     float ms = 0.f;

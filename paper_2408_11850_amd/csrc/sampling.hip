@@ -481,7 +481,8 @@ __global__ __launch_bounds__(SAMP_THREADS) void accept_piece_kernel(const float*
 #pragma unroll
     for (int k = 0; k < SAMP_PIECE_CHUNKS; ++k) {
 #pragma unroll
-      for (int j = 0; j < 4; ++j) e[k][j] = g.id(k) + j < n && top.v > -INFINITY ? expf(e[k][j] * mult - zmax) : 0.f;
+      for (int j = 0; j < 4; ++j)    // -inf has no mass, also where it is the maximum; NaN stays NaN
+        e[k][j] = g.id(k) + j < n && e[k][j] != -INFINITY ? expf(e[k][j] * mult - zmax) : 0.f;
       acc += (e[k][0] + e[k][1]) + (e[k][2] + e[k][3]);
     }
     sum = (float)block_sum_d((double)acc, shd);

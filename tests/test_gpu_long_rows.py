@@ -57,3 +57,28 @@ def test_greedy_rows_of_the_lowest_value_and_nan(V):
     row[5] = row[V - 3] = -2.0
     assert amd.sample_row(row, 0.0, 1.0, 0.5)[1] == 5
     assert amd.accept_rows(row[None].contiguous(), None, [], [], 0.0, 1.0, 0.5) == (0, 5)
+
+
+@pytest.mark.parametrize("V", [1000, 40000])
+@pytest.mark.parametrize("temp", [1.0, 0.5])
+def test_rows_of_minus_infinity_and_nan_at_a_temperature(V, temp):
+    """-inf has no mass; a row without any finite value or with a NaN anywhere has no distribution: q is NaN, nothing is
+    drawn (-1) and a draft tested against it is rejected."""
+    amd = _amd()
+    inf, nan = float("inf"), float("nan")
+    q1 = torch.zeros((1, V), device="cuda")
+    q1[0, 3] = 1.0
+    row = torch.full((V,), -inf, device="cuda")
+    row[3] = row[V - 2] = 1.5
+    q, tok = amd.sample_row(row, temp, 1.0, 0.25)
+    assert tok == 3 and q[3] == 0.5 and q[V - 2] == 0.5 and q.sum() == 1.0
+    assert amd.accept_rows(row[None].contiguous(), q1, [3], [0.5], temp, 1.0, 0.5) == (1, -1)
+    assert amd.accept_rows(row[None].contiguous(), q1, [3], [0.75], temp, 1.0, 0.5) == (0, V - 2)
+    bad = [torch.full((V,), -inf, device="cuda"), row.clone(), row.clone(), torch.full((V,), nan, device="cuda")]
+    bad[1][V // 2] = nan                # among -inf only: at 40000 ids a piece without any finite value
+    bad[2][4] = nan
+    for b in bad:
+        q, tok = amd.sample_row(b, temp, 1.0, 0.25)
+        assert tok == -1 and bool(q.isnan().all())
+        assert amd.accept_rows(b[None].contiguous(), q1, [3], [0.0], temp, 1.0, 0.5) == (0, -1)
+        assert amd.accept_rows(b[None].contiguous(), None, [], [], temp, 1.0, 0.5) == (0, -1)

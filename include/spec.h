@@ -259,7 +259,7 @@ int spec_dense_gemm(float* y_dev, void* z_dev, const void* x_dev, const void* w_
 int spec_read_probe(const void* src_dev, size_t bytes, void* out_dev, void* stream);
 
 /* Fused scale -> softmax -> inverse-CDF draw on one fp32 logits row (device):
- * writes the distribution to q_out_dev[vocab] and the token to tok_out_dev[0]. */
+ * writes the distribution to q_out_dev[vocab] and the token to tok_out_dev[0].  q_out_dev may be logits_dev. */
 int spec_sample_row(const float* logits_dev, int vocab, float temperature, float logit_scale, float u,
                     float* q_out_dev, int32_t* tok_out_dev, void* stream);
 

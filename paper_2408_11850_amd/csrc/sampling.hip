@@ -273,9 +273,9 @@ __device__ __forceinline__ int reg_draw(const f32x4 (&e)[CH], const RegGeom& g, 
 }
 
 // ---- draft: q = softmax(mult*logits), x = invCDF(q, u) -------------------------------------
-__global__ __launch_bounds__(SAMP_THREADS) void sample_row_reg_kernel(const float* __restrict__ logits, int V, float mult,
-                                                                      int greedy, float u, float* __restrict__ q_out,
-                                                                      int* __restrict__ tok_out) {
+// q_out may be the logits themselves: a workgroup has read all it needs of them before it writes.
+__global__ __launch_bounds__(SAMP_THREADS) void sample_row_reg_kernel(const float* logits, int V, float mult, int greedy,
+                                                                      float u, float* q_out, int* __restrict__ tok_out) {
   __shared__ MaxIdx shm[SAMP_WAVES];
   __shared__ double shd[SAMP_WAVES];
   __shared__ int shi[1];
@@ -308,10 +308,10 @@ __global__ __launch_bounds__(SAMP_THREADS) void sample_row_reg_kernel(const floa
 }
 
 // Rows beyond the registers of a workgroup: workgroup p works out the whole row's maximum and sum again (the row comes
-// from L2) and writes its piece of q (greedy: of the one-hot); the draw is a launch of its own.
-__global__ __launch_bounds__(SAMP_THREADS) void sample_piece_kernel(const float* __restrict__ logits, int V, float mult,
-                                                                    int greedy, float* __restrict__ q_out,
-                                                                    int* __restrict__ tok_out) {
+// from L2) and writes its piece of q (greedy: of the one-hot); the draw is a launch of its own.  Where q takes the place of
+// the logits one workgroup writes all pieces: nobody else may still be reading the row.
+__global__ __launch_bounds__(SAMP_THREADS) void sample_piece_kernel(const float* logits, int V, float mult, int greedy,
+                                                                    float* q_out, int* __restrict__ tok_out) {
   __shared__ MaxIdx shm[SAMP_WAVES];
   __shared__ double shd[SAMP_WAVES];
   MaxIdx m;
@@ -324,7 +324,7 @@ __global__ __launch_bounds__(SAMP_THREADS) void sample_piece_kernel(const float*
       if (j + i < V) m = better(m, v[i], j + i);
   }
   const MaxIdx top = block_argmax(m, shm);
-  const int first = blockIdx.x * SAMP_PIECE, end = min(first + SAMP_PIECE, V);
+  const int first = gridDim.x == 1 ? 0 : blockIdx.x * SAMP_PIECE, end = gridDim.x == 1 ? V : min(first + SAMP_PIECE, V);
   if (greedy) {
     for (int j = first + 4 * threadIdx.x; j < end; j += 4 * SAMP_THREADS) {
       f32x4 o;
@@ -406,7 +406,8 @@ hipError_t launch_sample_row(const float* logits, int V, float mult, int greedy,
     sample_row_reg_kernel<<<1, SAMP_THREADS, 0, st>>>(logits, V, mult, greedy, u, q_out, tok_out);
     return hipGetLastError();
   }
-  sample_piece_kernel<<<(V + SAMP_PIECE - 1) / SAMP_PIECE, SAMP_THREADS, 0, st>>>(logits, V, mult, greedy, q_out, tok_out);
+  const bool in_place = q_out < logits + V && logits < q_out + V;
+  sample_piece_kernel<<<in_place ? 1 : (V + SAMP_PIECE - 1) / SAMP_PIECE, SAMP_THREADS, 0, st>>>(logits, V, mult, greedy, q_out, tok_out);
   hipError_t e = hipGetLastError();
   if (e != hipSuccess || greedy) return e;
   draw_kernel<<<1, SAMP_THREADS, 0, st>>>(q_out, V, u, tok_out);

@@ -82,3 +82,19 @@ def test_rows_of_minus_infinity_and_nan_at_a_temperature(V, temp):
         assert tok == -1 and bool(q.isnan().all())
         assert amd.accept_rows(b[None].contiguous(), q1, [3], [0.0], temp, 1.0, 0.5) == (0, -1)
         assert amd.accept_rows(b[None].contiguous(), None, [], [], temp, 1.0, 0.5) == (0, -1)
+
+
+@pytest.mark.parametrize("V", [32768, 32769, 50001, 131072])
+@pytest.mark.parametrize("temp", [1.0, 0.0])
+def test_a_distribution_may_replace_its_logits(V, temp):
+    """q_out == logits, as a caller without a second row does it: the same q and token as with rows of their own."""
+    amd = _amd()
+    from paper_2408_11850_amd import binding
+    lib = amd.load_library()
+    for seed in range(4):
+        row = torch.randn(V, generator=torch.Generator().manual_seed(seed * 7 + V)).mul_(3.0).cuda()
+        q, tok = amd.sample_row(row, temp, 1.0, 0.3 + 0.1 * seed)
+        out = torch.full((1,), -7, dtype=torch.int32, device="cuda")
+        amd.check(lib.spec_sample_row(binding._ptr(row), V, temp, 1.0, 0.3 + 0.1 * seed, binding._ptr(row), binding._ptr(out),
+                                      binding._stream_ptr(torch.cuda.current_stream())))
+        assert int(out.item()) == tok and torch.equal(row, q)

@@ -9,7 +9,7 @@
 // What bounds them is one compute unit's vector ALU and the latency of dependent passes, so
 //   * up to 32768 ids one workgroup of 1024 threads holds a row in registers and reads it once (the reg_* functions);
 //   * longer rows are cut into pieces of 8192 ids, one workgroup each; what the pieces have to know of each other (row
-//     maximum, sums) goes through a kernel boundary (accept) or is worked out by every workgroup again (sample);
+//     maximum, sums) goes through a kernel boundary;
 //   * wave reductions and scans run on DPP row shifts and broadcasts, not on LDS permutes.
 #include <cstring>
 
@@ -146,7 +146,7 @@ __device__ __forceinline__ RegGeom reg_geom(int V) {
 // probability of a logit given the row's statistics: hardware exp2 (1 ulp) of a product rounded once, times the
 // reciprocal of the sum: relative error below 1e-5 for exponents down to -100, two orders under what the bf16
 // logits carry.  Every kernel of the register path forms p and q with this one expression.
-__device__ __forceinline__ float reg_prob(float l, float mult, float zmax, float inv) { return __expf(l * mult - zmax) * inv; }
+__device__ __forceinline__ float reg_prob(float l, float mult, float zmax, float inv) { return __expf(fmaf(l, mult, -zmax)) * inv; }
 
 // A thread's chunks of a row, `fill` beyond V.  Where no vector straddles the end the loads are unconditional (lanes
 // beyond the end read the last vector): behind branches each would be waited for before the next goes out.
@@ -188,7 +188,7 @@ __device__ __forceinline__ void reg_softmax(const float* __restrict__ row, int V
   for (int k = 0; k < SAMP_CHUNKS_MAX; ++k) {
 #pragma unroll
     for (int i = 0; i < 4; ++i) {
-      const float x = __expf(e[k][i] * mult - zmax);
+      const float x = __expf(fmaf(e[k][i], mult, -zmax));
       e[k][i] = ((k < g.R) & (g.id(k) + i < V)) ? x : 0.f;
     }
     acc += (e[k][0] + e[k][1]) + (e[k][2] + e[k][3]);
@@ -307,13 +307,98 @@ __global__ __launch_bounds__(SAMP_THREADS) void sample_row_reg_kernel(const floa
   if (threadIdx.x == 0) tok_out[0] = tok;
 }
 
-// Rows beyond the registers of a workgroup: workgroup p works out the whole row's maximum and sum again (the row comes
-// from L2) and writes its piece of q (greedy: of the one-hot); the draw is a launch of its own.  Where q takes the place of
-// the logits one workgroup writes all pieces: nobody else may still be reading the row.
-__global__ __launch_bounds__(SAMP_THREADS) void sample_piece_kernel(const float* logits, int V, float mult, int greedy,
-                                                                    float* q_out, int* __restrict__ tok_out) {
+// ---- rows beyond the registers of a workgroup -----------------------------------------------------
+// The draft's q and the target's p of one row are the same bits if its logits are: both sides form the row's maximum and sum
+// with the functions of this section, in the same order.  A row is cut into pieces of SAMP_PIECE ids; a piece has a maximum
+// and a sum of exp relative to it, put together from those of its 16 waves, and the row's are put together from the pieces'.
+struct PieceStat { float top, sum; int i; };     // maximum, sum of exp(mult l - mult top), arg-max in the row
+__device__ __forceinline__ int row_pieces(int V) { return (V + SAMP_PIECE - 1) / SAMP_PIECE; }
+__device__ __forceinline__ float long_prob(float l, float mult, float zmax, float sum) { return expf(fmaf(l, mult, -zmax)) / sum; }
+// Piece p of a row by the whole workgroup, to every thread (two barriers inside).
+__device__ __forceinline__ PieceStat piece_stat(const float* row, int V, int p, float mult, int greedy, MaxIdx* shm, double* shd) {
+  const int first = p * SAMP_PIECE, n = min(SAMP_PIECE, V - first);
+  const RegGeom g = reg_geom(SAMP_PIECE);
+  f32x4 e[SAMP_PIECE_CHUNKS];
+  MaxIdx m = wave_argmax(reg_load(row + first, n, g, e));
+  double sum = 0.0;
+  if (!greedy) {
+    const float zmax = m.v * mult;
+    float acc = 0.f;
+#pragma unroll
+    for (int k = 0; k < SAMP_PIECE_CHUNKS; ++k) {
+#pragma unroll
+      for (int j = 0; j < 4; ++j)    // -inf has no mass, also where it is the maximum; NaN stays NaN
+        e[k][j] = g.id(k) + j < n && e[k][j] != -INFINITY ? expf(fmaf(e[k][j], mult, -zmax)) : 0.f;
+      acc += (e[k][0] + e[k][1]) + (e[k][2] + e[k][3]);
+    }
+    sum = lane_d(wave_scan_d((double)acc), 63);
+  }
+  if (g.lane == 0) shm[g.w] = m, shd[g.w] = sum;
+  __syncthreads();
+  m.v = -INFINITY; m.i = 0x7fffffff;
+  if (g.lane < SAMP_WAVES) m = shm[g.lane], sum = shd[g.lane];
+  else sum = 0.0;
+  __syncthreads();
+  const MaxIdx top = wave_argmax(m);
+  PieceStat r;
+  r.top = top.v;
+  r.i = top.i == 0x7fffffff ? top.i : first + top.i;
+  r.sum = 0.f;
+  if (!greedy) {
+    const double t = sum != 0.0 ? sum * exp((double)(m.v * mult) - (double)(top.v * mult)) : 0.0;
+    r.sum = (float)lane_d(wave_scan_d(t), 63);
+  }
+  return r;
+}
+// a piece's term of the row's sum
+__device__ __forceinline__ double piece_term(PieceStat s, float mult, double zmax) {
+  return s.sum != 0.f ? (double)s.sum * exp((double)(s.top * mult) - zmax) : 0.0;
+}
+// A row's maximum, arg-max and sum from the statistics of its P pieces, by one wave (lane l adds the terms of the pieces
+// l, l + 64, ..), to every lane.
+__device__ __forceinline__ MaxIdx row_stat(const PieceStat* s, int P, float mult, int greedy, float* sum) {
+  const int lane = threadIdx.x & 63;
+  MaxIdx m;
+  m.v = -INFINITY; m.i = 0x7fffffff;
+  for (int p = lane; p < P; p += 64) m = better(m, s[p].top, s[p].i);
+  const MaxIdx top = wave_argmax(m);
+  *sum = 1.f;
+  if (!greedy) {
+    const double zmax = (double)(top.v * mult);
+    double t = 0.0;
+    for (int p = lane; p < P; p += 64) t += piece_term(s[p], mult, zmax);
+    *sum = (float)lane_d(wave_scan_d(t), 63);
+  }
+  return top;
+}
+
+// statistics of piece blockIdx.x of row blockIdx.y to stats[row][piece]
+__global__ __launch_bounds__(SAMP_THREADS) void piece_stat_kernel(const float* __restrict__ logits, int V, float mult,
+                                                                  int greedy, PieceStat* __restrict__ stats) {
   __shared__ MaxIdx shm[SAMP_WAVES];
   __shared__ double shd[SAMP_WAVES];
+  const PieceStat s = piece_stat(logits + (size_t)blockIdx.y * V, V, blockIdx.x, mult, greedy, shm, shd);
+  if (threadIdx.x == 0) stats[(size_t)blockIdx.y * gridDim.x + blockIdx.x] = s;
+}
+
+// Draft draws over a long row: piece_stat_kernel leaves the statistics where the first ids of q go, this kernel writes q
+// behind those (a piece per workgroup), draw_kernel the first ids, then draws: 16.7 us at 32769 ids, 19.5 at 128256 (16.1 and
+// 36.9 with one launch for q whose workgroups each add up the whole row: bound by the exponentials of one compute unit).
+__host__ __device__ static constexpr int sample_head(int P) { return (P * (int)(sizeof(PieceStat) / sizeof(float)) + 3) & ~3; }
+__global__ __launch_bounds__(SAMP_THREADS) void sample_piece_kernel(const float* __restrict__ logits, int V, float mult,
+                                                                    float* q_out) {
+  float sum;
+  const float zmax = row_stat(reinterpret_cast<const PieceStat*>(q_out), gridDim.x, mult, 0, &sum).v * mult;
+  const int first = blockIdx.x * SAMP_PIECE, end = min(first + SAMP_PIECE, V);
+  for (int j = max(first, sample_head(gridDim.x)) + 4 * threadIdx.x; j < end; j += 4 * SAMP_THREADS) {
+    f32x4 v = load4(logits, j, V, -INFINITY);
+#pragma unroll
+    for (int i = 0; i < 4; ++i) v[i] = long_prob(v[i], mult, zmax, sum);
+    store4(q_out, j, V, v);
+  }
+}
+
+__device__ __forceinline__ MaxIdx row_argmax(const float* logits, int V, MaxIdx* shm) {
   MaxIdx m;
   m.v = -INFINITY; m.i = 0x7fffffff;
 #pragma unroll 4
@@ -323,33 +408,39 @@ __global__ __launch_bounds__(SAMP_THREADS) void sample_piece_kernel(const float*
     for (int i = 0; i < 4; ++i)
       if (j + i < V) m = better(m, v[i], j + i);
   }
-  const MaxIdx top = block_argmax(m, shm);
+  return block_argmax(m, shm);
+}
+
+// Greedy: every workgroup finds the row's arg-max (the row comes from L2) and writes its piece of the one-hot.  Where that
+// takes the place of the logits one workgroup writes all of it: nobody else may still be reading the row.
+__global__ __launch_bounds__(SAMP_THREADS) void sample_greedy_kernel(const float* logits, int V, float* q_out, int* __restrict__ tok_out) {
+  __shared__ MaxIdx shm[SAMP_WAVES];
   const int first = gridDim.x == 1 ? 0 : blockIdx.x * SAMP_PIECE, end = gridDim.x == 1 ? V : min(first + SAMP_PIECE, V);
-  if (greedy) {
-    for (int j = first + 4 * threadIdx.x; j < end; j += 4 * SAMP_THREADS) {
-      f32x4 o;
-#pragma unroll
-      for (int i = 0; i < 4; ++i) o[i] = j + i == top.i ? 1.0f : 0.0f;
-      store4(q_out, j, V, o);
-    }
-    if (blockIdx.x == 0 && threadIdx.x == 0) tok_out[0] = top.i;
-    return;
-  }
-  const float zmax = top.v * mult;
-  float acc = 0.f;
-#pragma unroll 4
-  for (int j = 4 * threadIdx.x; j < V; j += 4 * SAMP_THREADS) {
-    const f32x4 v = load4(logits, j, V, -INFINITY);
-    f32x4 x;
-#pragma unroll
-    for (int i = 0; i < 4; ++i) x[i] = j + i < V ? expf(v[i] * mult - zmax) : 0.f;
-    acc += (x[0] + x[1]) + (x[2] + x[3]);
-  }
-  const float sum = (float)block_sum_d((double)acc, shd);
+  const MaxIdx top = row_argmax(logits, V, shm);
   for (int j = first + 4 * threadIdx.x; j < end; j += 4 * SAMP_THREADS) {
+    f32x4 o;
+#pragma unroll
+    for (int i = 0; i < 4; ++i) o[i] = j + i == top.i ? 1.0f : 0.0f;
+    store4(q_out, j, V, o);
+  }
+  if (blockIdx.x == 0 && threadIdx.x == 0) tok_out[0] = top.i;
+}
+
+// q in the place of its logits (nowhere to leave statistics): one workgroup, piece after piece, the same sums
+__global__ __launch_bounds__(SAMP_THREADS) void sample_in_place_kernel(const float* logits, int V, float mult, float* q_out) {
+  __shared__ MaxIdx shm[SAMP_WAVES];
+  __shared__ double shd[SAMP_WAVES];
+  const float zmax = row_argmax(logits, V, shm).v * mult;
+  double t = 0.0;
+  for (int p = 0; p < row_pieces(V); ++p) {
+    const PieceStat s = piece_stat(logits, V, p, mult, 0, shm, shd);
+    if ((p & 63) == (threadIdx.x & 63)) t += piece_term(s, mult, (double)zmax);
+  }
+  const float sum = (float)lane_d(wave_scan_d(t), 63);
+  for (int j = 4 * threadIdx.x; j < V; j += 4 * SAMP_THREADS) {
     f32x4 v = load4(logits, j, V, -INFINITY);
 #pragma unroll
-    for (int i = 0; i < 4; ++i) v[i] = expf(v[i] * mult - zmax) / sum;
+    for (int i = 0; i < 4; ++i) v[i] = long_prob(v[i], mult, zmax, sum);
     store4(q_out, j, V, v);
   }
 }
@@ -393,10 +484,24 @@ __device__ int block_draw(const float* __restrict__ w, int V, float u, double* s
   return tok < 0 ? -1 : first + tok;
 }
 
-__global__ __launch_bounds__(SAMP_THREADS) void draw_kernel(const float* __restrict__ w, int V, float u, int* __restrict__ tok_out) {
+// logits: those of sample_piece_kernel (its first ids of q are still missing), or null: all of q is there
+__global__ __launch_bounds__(SAMP_THREADS) void draw_kernel(const float* __restrict__ logits, float* q, int V, float mult, float u,
+                                                            int* __restrict__ tok_out) {
   __shared__ double shd[SAMP_WAVES];
   __shared__ int shi[1];
-  const int tok = block_draw(w, V, u, shd, shi);
+  if (logits) {
+    const int P = row_pieces(V);
+    float sum;
+    const float zmax = row_stat(reinterpret_cast<const PieceStat*>(q), P, mult, 0, &sum).v * mult;
+    __syncthreads();     // everybody has read the statistics
+    for (int j = 4 * threadIdx.x; j < sample_head(P); j += 4 * SAMP_THREADS) {
+      f32x4 v = load4(logits, j, V, -INFINITY);
+#pragma unroll
+      for (int i = 0; i < 4; ++i) v[i] = long_prob(v[i], mult, zmax, sum);
+      *reinterpret_cast<f32x4u*>(q + j) = v;
+    }
+  }
+  const int tok = block_draw(q, V, u, shd, shi);
   if (threadIdx.x == 0) tok_out[0] = tok;
 }
 
@@ -407,19 +512,32 @@ hipError_t launch_sample_row(const float* logits, int V, float mult, int greedy,
     return hipGetLastError();
   }
   const bool in_place = q_out < logits + V && logits < q_out + V;
-  sample_piece_kernel<<<in_place ? 1 : (V + SAMP_PIECE - 1) / SAMP_PIECE, SAMP_THREADS, 0, st>>>(logits, V, mult, greedy, q_out, tok_out);
+  const int P = (V + SAMP_PIECE - 1) / SAMP_PIECE;
+  if (greedy) {
+    sample_greedy_kernel<<<in_place ? 1 : P, SAMP_THREADS, 0, st>>>(logits, V, q_out, tok_out);
+    return hipGetLastError();
+  }
+  if (in_place) {
+    sample_in_place_kernel<<<1, SAMP_THREADS, 0, st>>>(logits, V, mult, q_out);
+  } else {
+    piece_stat_kernel<<<P, SAMP_THREADS, 0, st>>>(logits, V, mult, 0, reinterpret_cast<PieceStat*>(q_out));
+    hipError_t e = hipGetLastError();
+    if (e != hipSuccess) return e;
+    sample_piece_kernel<<<P, SAMP_THREADS, 0, st>>>(logits, V, mult, q_out);
+  }
   hipError_t e = hipGetLastError();
-  if (e != hipSuccess || greedy) return e;
-  draw_kernel<<<1, SAMP_THREADS, 0, st>>>(q_out, V, u, tok_out);
+  if (e != hipSuccess) return e;
+  draw_kernel<<<1, SAMP_THREADS, 0, st>>>(in_place ? nullptr : logits, q_out, V, mult, u, tok_out);
   return hipGetLastError();
 }
 
 // ---- target: per-row test, then first rejection + resampling ---------------------------------
 // Scratch of an acceptance: [0, 256) four statistics per row: max logit, sum exp, arg-max (as int bits), accept flag;
-// then, for vocabularies beyond SAMP_REG_VOCAB_MAX, three floats per (row, piece): max logit, sum exp relative to it,
-// arg-max; the pieces' weight sums (doubles); and the row of V weights a draw walks over.
+// then, for vocabularies beyond SAMP_REG_VOCAB_MAX, a PieceStat per (row, piece); the pieces' weight sums (doubles); and the row of V weights a draw walks over.
 __host__ __device__ static constexpr int accept_pieces(int V) { return V <= SAMP_REG_VOCAB_MAX ? 0 : (V + SAMP_PIECE - 1) / SAMP_PIECE; }
-__host__ __device__ static constexpr size_t accept_sums_at(int V) { return 256 + (size_t)accept_pieces(V) * SPEC_MAX_TOKENS * 3; }
+__host__ __device__ static constexpr size_t accept_sums_at(int V) {
+  return 256 + (size_t)accept_pieces(V) * SPEC_MAX_TOKENS * (sizeof(PieceStat) / sizeof(float));
+}
 __host__ __device__ static constexpr size_t accept_weights_at(int V) { return accept_sums_at(V) + (size_t)accept_pieces(V) * 2; }
 static constexpr size_t accept_scratch_floats_of(int V) { return accept_weights_at(V) + (size_t)V; }
 size_t accept_scratch_floats(int V) { return accept_scratch_floats_of(V); }
@@ -436,7 +554,7 @@ __device__ __forceinline__ int accept_test(const float* __restrict__ row, int i,
   if (greedy) {
     acc = x == amax;
   } else {
-    const float px = V <= SAMP_REG_VOCAB_MAX ? reg_prob(row[x], mult, top * mult, 1.0f / sum) : expf(row[x] * mult - top * mult) / sum;
+    const float px = V <= SAMP_REG_VOCAB_MAX ? reg_prob(row[x], mult, top * mult, 1.0f / sum) : long_prob(row[x], mult, top * mult, sum);
     acc = (double)a.r[i] * (double)qrow[x] <= (double)px;
   }
   if (a.force_mask >= 0) acc = (int)((a.force_mask >> i) & 1);
@@ -466,36 +584,6 @@ __global__ __launch_bounds__(SAMP_THREADS) void accept_rows_kernel(const float* 
   }
 }
 
-// long rows: statistics of one piece of one row
-__global__ __launch_bounds__(SAMP_THREADS) void accept_piece_kernel(const float* __restrict__ logits, int V, float mult,
-                                                                    int greedy, float* __restrict__ scratch) {
-  __shared__ MaxIdx shm[SAMP_WAVES];
-  __shared__ double shd[SAMP_WAVES];
-  const int p = blockIdx.x, i = blockIdx.y, first = p * SAMP_PIECE, n = min(SAMP_PIECE, V - first);
-  const RegGeom g = reg_geom(SAMP_PIECE);
-  f32x4 e[SAMP_PIECE_CHUNKS];
-  const MaxIdx top = block_argmax(reg_load(logits + (size_t)i * V + first, n, g, e), shm);
-  float sum = 0.f;
-  if (!greedy) {
-    const float zmax = top.v * mult;
-    float acc = 0.f;
-#pragma unroll
-    for (int k = 0; k < SAMP_PIECE_CHUNKS; ++k) {
-#pragma unroll
-      for (int j = 0; j < 4; ++j)    // -inf has no mass, also where it is the maximum; NaN stays NaN
-        e[k][j] = g.id(k) + j < n && e[k][j] != -INFINITY ? expf(e[k][j] * mult - zmax) : 0.f;
-      acc += (e[k][0] + e[k][1]) + (e[k][2] + e[k][3]);
-    }
-    sum = (float)block_sum_d((double)acc, shd);
-  }
-  if (threadIdx.x == 0) {
-    float* s = scratch + 256 + ((size_t)i * accept_pieces(V) + p) * 3;
-    s[0] = top.v;
-    s[1] = sum;
-    s[2] = __int_as_float(top.i == 0x7fffffff ? top.i : first + top.i);
-  }
-}
-
 // long rows: every row's statistics from its pieces', by the whole workgroup, into `st` (LDS, four floats per row)
 __device__ void accept_combine(const float* __restrict__ logits, int V, float mult, int greedy,
                                const float* __restrict__ qcache, const int* __restrict__ ring,
@@ -503,19 +591,8 @@ __device__ void accept_combine(const float* __restrict__ logits, int V, float mu
                                float* st) {
   const int lane = threadIdx.x & 63, P = accept_pieces(V);
   for (int i = threadIdx.x >> 6; i < a.n_rows; i += SAMP_WAVES) {
-    const float* s = scratch + 256 + (size_t)i * P * 3;
-    MaxIdx m;
-    m.v = -INFINITY; m.i = 0x7fffffff;
-    for (int p = lane; p < P; p += 64) m = better(m, s[p * 3], __float_as_int(s[p * 3 + 2]));
-    const MaxIdx top = wave_argmax(m);
-    float sum = 1.f;
-    if (!greedy) {
-      const double zmax = (double)(top.v * mult);
-      double t = 0.0;
-      for (int p = lane; p < P; p += 64)
-        if (s[p * 3 + 1] != 0.f) t += (double)s[p * 3 + 1] * exp((double)(s[p * 3] * mult) - zmax);
-      sum = (float)lane_d(wave_scan_d(t), 63);
-    }
+    float sum;
+    const MaxIdx top = row_stat(reinterpret_cast<const PieceStat*>(scratch + 256) + (size_t)i * P, P, mult, greedy, &sum);
     if (lane == 0) {
       st[i * 4 + 0] = top.v;
       st[i * 4 + 1] = sum;
@@ -570,7 +647,7 @@ __global__ __launch_bounds__(SAMP_THREADS) void accept_weights_kernel(const floa
   for (int k = 0; k < SAMP_PIECE_CHUNKS; ++k) {
 #pragma unroll
     for (int i = 0; i < 4; ++i) {
-      const float pv = expf(e[k][i] * mult - zmax) / sum;
+      const float pv = long_prob(e[k][i], mult, zmax, sum);
       e[k][i] = g.id(k) + i < m ? (qrow ? (float)fmax((double)pv - (double)q[k][i], 0.0) : pv) : 0.f;
     }
     store4(wbuf, g.id(k), m, e[k]);
@@ -629,7 +706,7 @@ __device__ __forceinline__ int accept_draw_long(const float* __restrict__ row, b
   double total = 0.0;
   for (int p0 = 0; p0 < P; p0 += 64) total += lane_d(wave_scan_d(p0 + lane < P ? sums[p0 + lane] : 0.0), 63);
   if (rejected && !(total > 0.0)) {   // no residual mass in floating point: draw from p itself
-    for (int j = threadIdx.x; j < V; j += SAMP_THREADS) wbuf[j] = expf(row[j] * mult - zmax) / sum;
+    for (int j = threadIdx.x; j < V; j += SAMP_THREADS) wbuf[j] = long_prob(row[j], mult, zmax, sum);
     return block_draw(wbuf, V, u, shd, shi);
   }
   const double target = (double)u * total;
@@ -711,7 +788,7 @@ hipError_t launch_accept(const float* logits, int V, float mult, int greedy, con
   if (!P) {
     accept_rows_kernel<<<a.n_rows, SAMP_THREADS, 0, st>>>(logits, V, mult, greedy, qcache, ring, x_direct, a, scratch);
   } else {
-    accept_piece_kernel<<<dim3(P, a.n_rows), SAMP_THREADS, 0, st>>>(logits, V, mult, greedy, scratch);
+    piece_stat_kernel<<<dim3(P, a.n_rows), SAMP_THREADS, 0, st>>>(logits, V, mult, greedy, reinterpret_cast<PieceStat*>(scratch + 256));
     hipError_t e = hipGetLastError();
     if (e != hipSuccess) return e;
     if (!greedy) accept_weights_kernel<<<P, SAMP_THREADS, 0, st>>>(logits, V, mult, qcache, ring, x_direct, a, scratch);

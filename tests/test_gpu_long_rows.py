@@ -98,3 +98,19 @@ def test_a_distribution_may_replace_its_logits(V, temp):
         amd.check(lib.spec_sample_row(binding._ptr(row), V, temp, 1.0, 0.3 + 0.1 * seed, binding._ptr(row), binding._ptr(out),
                                       binding._stream_ptr(torch.cuda.current_stream())))
         assert int(out.item()) == tok and torch.equal(row, q)
+
+
+# pieces of 8192 ids: a last piece of one id, of an odd length, whole pieces; 33000 rows lie at odd alignments
+@pytest.mark.parametrize("V", [32769, 33001, 40000, 65537, 131072])
+@pytest.mark.parametrize("temp", [1.0, 0.7])
+def test_a_draft_that_equals_the_target_is_never_rejected(V, temp):
+    """q from sample_row and p inside accept_rows are the same bits for the same logits: r q[x] <= p[x] then holds up to
+    the largest uniform, 1 - 2^-24, which one unit in the last place between p and q would already break."""
+    amd = _amd()
+    rows = torch.randn((32, V), generator=torch.Generator().manual_seed(V)).mul_(3.0).cuda()
+    q = torch.empty_like(rows)
+    x = []
+    for i in range(32):
+        q[i], tok = amd.sample_row(rows[i], temp, 1.0, (2 * i + 1) / 64.0)
+        x.append(tok)
+    assert amd.accept_rows(rows, q, x, [1.0 - 2.0 ** -24] * 32, temp, 1.0, 0.5) == (32, -1)

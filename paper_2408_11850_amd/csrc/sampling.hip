@@ -310,19 +310,22 @@ __global__ __launch_bounds__(SAMP_THREADS) void sample_row_reg_kernel(const floa
 // ---- rows beyond the registers of a workgroup -----------------------------------------------------
 // The draft's q and the target's p of one row are the same bits if its logits are: both sides form the row's maximum and sum
 // with the functions of this section, in the same order.  A row is cut into pieces of SAMP_PIECE ids; a piece has a maximum
-// and a sum of exp relative to it, put together from those of its 16 waves, and the row's are put together from the pieces'.
+// and a sum of exp relative to it, and the row's are put together from the pieces'.
 struct PieceStat { float top, sum; int i; };     // maximum, sum of exp(mult l - mult top), arg-max in the row
 __device__ __forceinline__ int row_pieces(int V) { return (V + SAMP_PIECE - 1) / SAMP_PIECE; }
 __device__ __forceinline__ float long_prob(float l, float mult, float zmax, float sum) { return expf(fmaf(l, mult, -zmax)) / sum; }
-// Piece p of a row by the whole workgroup, to every thread (two barriers inside).
+// Piece p of a row by the whole workgroup, to every thread (barriers inside).
 __device__ __forceinline__ PieceStat piece_stat(const float* row, int V, int p, float mult, int greedy, MaxIdx* shm, double* shd) {
   const int first = p * SAMP_PIECE, n = min(SAMP_PIECE, V - first);
   const RegGeom g = reg_geom(SAMP_PIECE);
   f32x4 e[SAMP_PIECE_CHUNKS];
-  MaxIdx m = wave_argmax(reg_load(row + first, n, g, e));
-  double sum = 0.0;
+  const MaxIdx top = block_argmax(reg_load(row + first, n, g, e), shm);
+  PieceStat r;
+  r.top = top.v;
+  r.i = top.i == 0x7fffffff ? top.i : first + top.i;
+  r.sum = 0.f;
   if (!greedy) {
-    const float zmax = m.v * mult;
+    const float zmax = top.v * mult;
     float acc = 0.f;
 #pragma unroll
     for (int k = 0; k < SAMP_PIECE_CHUNKS; ++k) {
@@ -331,22 +334,7 @@ __device__ __forceinline__ PieceStat piece_stat(const float* row, int V, int p, 
         e[k][j] = g.id(k) + j < n && e[k][j] != -INFINITY ? expf(fmaf(e[k][j], mult, -zmax)) : 0.f;
       acc += (e[k][0] + e[k][1]) + (e[k][2] + e[k][3]);
     }
-    sum = lane_d(wave_scan_d((double)acc), 63);
-  }
-  if (g.lane == 0) shm[g.w] = m, shd[g.w] = sum;
-  __syncthreads();
-  m.v = -INFINITY; m.i = 0x7fffffff;
-  if (g.lane < SAMP_WAVES) m = shm[g.lane], sum = shd[g.lane];
-  else sum = 0.0;
-  __syncthreads();
-  const MaxIdx top = wave_argmax(m);
-  PieceStat r;
-  r.top = top.v;
-  r.i = top.i == 0x7fffffff ? top.i : first + top.i;
-  r.sum = 0.f;
-  if (!greedy) {
-    const double t = sum != 0.0 ? sum * exp((double)(m.v * mult) - (double)(top.v * mult)) : 0.0;
-    r.sum = (float)lane_d(wave_scan_d(t), 63);
+    r.sum = (float)block_sum_d((double)acc, shd);
   }
   return r;
 }
@@ -382,7 +370,7 @@ __global__ __launch_bounds__(SAMP_THREADS) void piece_stat_kernel(const float* _
 }
 
 // Draft draws over a long row: piece_stat_kernel leaves the statistics where the first ids of q go, this kernel writes q
-// behind those (a piece per workgroup), draw_kernel the first ids, then draws: 16.7 us at 32769 ids, 19.5 at 128256 (16.1 and
+// behind those (a piece per workgroup), draw_kernel the first ids, then draws: 15.4 us at 32769 ids, 19.4 at 128256 (16.1 and
 // 36.9 with one launch for q whose workgroups each add up the whole row: bound by the exponentials of one compute unit).
 __host__ __device__ static constexpr int sample_head(int P) { return (P * (int)(sizeof(PieceStat) / sizeof(float)) + 3) & ~3; }
 __global__ __launch_bounds__(SAMP_THREADS) void sample_piece_kernel(const float* __restrict__ logits, int V, float mult,

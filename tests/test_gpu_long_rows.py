@@ -100,8 +100,8 @@ def test_a_distribution_may_replace_its_logits(V, temp):
         assert int(out.item()) == tok and torch.equal(row, q)
 
 
-# pieces of 8192 ids: a last piece of one id, of an odd length, whole pieces; 33000 rows lie at odd alignments
-@pytest.mark.parametrize("V", [32769, 33001, 40000, 65537, 131072])
+# a row in registers; pieces of 8192 ids: a last piece of one id, of an odd length, whole pieces (odd V: rows off every vector)
+@pytest.mark.parametrize("V", [777, 32000, 32768, 32769, 33001, 40000, 65537, 131072])
 @pytest.mark.parametrize("temp", [1.0, 0.7])
 def test_a_draft_that_equals_the_target_is_never_rejected(V, temp):
     """q from sample_row and p inside accept_rows are the same bits for the same logits: r q[x] <= p[x] then holds up to

@@ -16,12 +16,12 @@
  *   - uniform random numbers are inputs (host floats in [0,1)), never drawn inside the library.
  *
  * Weight layouts (all bf16)
- *   - tok_embed      : row-major [vocab][d_model]
- *   - norm gains     : [d_model]
+ *   - tok_embed      : row-major [vocab][d_model], at any 2-byte address
+ *   - norm gains     : [d_model], at any 2-byte address
  *   - projections    : "panel-packed" (see spec_pack_weight).  A projection y = x W^T with
  *                      W [N][K] is stored as N/16 panels; wqkv is the concatenation of the
  *                      panels of W_q, W_k, W_v; w_gateup interleaves panels (gate panel j at
- *                      2j, up panel j at 2j+1).
+ *                      2j, up panel j at 2j+1).  Packed buffers start at a 16-byte address.
  */
 #ifndef SPEC_H
 #define SPEC_H

@@ -23,12 +23,10 @@ __global__ void embed_kernel(float* __restrict__ h, const bf16* __restrict__ E, 
   const int m = blockIdx.x;
   int t = tok[m];
   if (t < 0 || t >= vocab) t = 0;
-  const uint2* row = reinterpret_cast<const uint2*>(E + (size_t)t * d);
+  const bf16x4u* row = reinterpret_cast<const bf16x4u*>(E + (size_t)t * d);
   for (int i = threadIdx.x; i < d >> 2; i += blockDim.x) {
-    const uint2 ev = row[i];
-    const bf16* e = reinterpret_cast<const bf16*>(&ev);
-    reinterpret_cast<f32x4*>(h + (size_t)m * d)[i] =
-        f32x4{__bfloat162float(e[0]), __bfloat162float(e[1]), __bfloat162float(e[2]), __bfloat162float(e[3])};
+    const bf16x4u e = row[i];
+    reinterpret_cast<f32x4*>(h + (size_t)m * d)[i] = f32x4{bf16x4_at(e, 0), bf16x4_at(e, 1), bf16x4_at(e, 2), bf16x4_at(e, 3)};
   }
 }
 hipError_t launch_embed(float* h, const bf16* embed, const int* tok, int M, int d, int vocab, hipStream_t st) {
@@ -68,11 +66,10 @@ __global__ __launch_bounds__(NORM_THREADS) void norm_kernel(const float* __restr
   for (int it = 0; it < NORM_PIECES; ++it) {
     const int i = threadIdx.x + it * NORM_THREADS;
     if (i < d4) {
-      const uint2 gv = reinterpret_cast<const uint2*>(gain)[i];
-      const bf16* g = reinterpret_cast<const bf16*>(&gv);
+      const bf16x4u g = reinterpret_cast<const bf16x4u*>(gain)[i];
       bf16 o[4];
 #pragma unroll
-      for (int r = 0; r < 4; ++r) o[r] = __float2bfloat16(v[it][r] * inv * __bfloat162float(g[r]));
+      for (int r = 0; r < 4; ++r) o[r] = __float2bfloat16(v[it][r] * inv * bf16x4_at(g, r));
       reinterpret_cast<uint2*>(a + (size_t)m * d)[i] = *reinterpret_cast<const uint2*>(o);
     }
   }
@@ -175,15 +172,14 @@ __global__ __launch_bounds__(BEGIN_THREADS) void begin_kernel(BeginArgs a, Token
   const int col = (blockIdx.x * BEGIN_THREADS + t) * 4;
   float ss = 0.f;
   if (col < a.d) {
-    const uint2 ev = *reinterpret_cast<const uint2*>(a.embed + (size_t)tok * a.d + col);
-    const uint2 gv = *reinterpret_cast<const uint2*>(a.gain + col);
-    const bf16 *e = reinterpret_cast<const bf16*>(&ev), *g = reinterpret_cast<const bf16*>(&gv);
+    const bf16x4u e = *reinterpret_cast<const bf16x4u*>(a.embed + (size_t)tok * a.d + col);
+    const bf16x4u g = *reinterpret_cast<const bf16x4u*>(a.gain + col);
     f32x4 h;
     bf16 o[4];
 #pragma unroll
     for (int r = 0; r < 4; ++r) {
-      h[r] = __bfloat162float(e[r]);
-      o[r] = __float2bfloat16(h[r] * __bfloat162float(g[r]));
+      h[r] = bf16x4_at(e, r);
+      o[r] = __float2bfloat16(h[r] * bf16x4_at(g, r));
       ss += h[r] * h[r];
     }
     *reinterpret_cast<f32x4*>(a.h + (size_t)i * a.d + col) = h;

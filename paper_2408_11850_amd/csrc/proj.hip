@@ -182,10 +182,10 @@ __global__ __launch_bounds__(PROJ_THREADS, RP * MT > 4 ? 2 : 4) void proj_kernel
     const int col = MODE == PROJ_HALF ? p * 8 + g4 * 4 : (p + it_rp) * 16 + g4 * 4;
     const bool mine = w < RP * MT && p + it_rp < p1 && m < a.M && (MODE == PROJ_FULL || c < 8) && (MODE != PROJ_HALF || g4 < 2);
     f32x4 hv = {0.f, 0.f, 0.f, 0.f};
-    uint2 gv = {0u, 0u};
+    bf16x4u gv = {0, 0, 0, 0};
     if (EPI == PROJ_RESID && mine) {
       hv = *reinterpret_cast<const f32x4*>(a.h + (size_t)m * a.N + col);
-      gv = *reinterpret_cast<const uint2*>(a.gain + col);
+      gv = *reinterpret_cast<const bf16x4u*>(a.gain + col);
     }
     // accumulator of weight load q of stage DD: PAIR by step parity (see above), else alternating stages
 #define PROJ_MMA(DD)                                                                                             \
@@ -267,9 +267,8 @@ __global__ __launch_bounds__(PROJ_THREADS, RP * MT > 4 ? 2 : 4) void proj_kernel
         if (mine) {
           *reinterpret_cast<f32x4*>(a.h + (size_t)m * a.N + col) = t;
           bf16 o[4];
-          const bf16* g = reinterpret_cast<const bf16*>(&gv);
 #pragma unroll
-          for (int r = 0; r < 4; ++r) o[r] = __float2bfloat16(t[r] * __bfloat162float(g[r]));
+          for (int r = 0; r < 4; ++r) o[r] = __float2bfloat16(t[r] * bf16x4_at(gv, r));
           *reinterpret_cast<uint2*>(a.xo + (size_t)m * a.N + col) = *reinterpret_cast<const uint2*>(o);
           if (g4 == 0) a.ssq_out[(size_t)m * SSQ_STRIDE + p + it_rp] = ss;
         }

@@ -1305,7 +1305,8 @@ extern "C" int spec_gemm(float* y, const void* x, const void* w, int M, int N, i
   if (!x || !w || !work) FAIL(SPEC_E_INVAL, "null pointer");
   int rc = check_gemm_args(M, N, K);
   if (rc) return rc;
-  if (proj_whole_k(M, N, K)) {
+  // operands off the 16-byte grid stay with K slices, whose global loads take any address of an element
+  if (proj_whole_k(M, N, K) && (((uintptr_t)x | (uintptr_t)w) & 15) == 0) {
     ProjArgs a = {};
     a.x = (const bf16*)x; a.w = w; a.y = y;
     HIPCHK(launch_proj(proj_plan(M, N, K, PROJ_STORE, 2), PROJ_STORE, a, (hipStream_t)stream, 2));

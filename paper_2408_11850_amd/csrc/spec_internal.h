@@ -11,6 +11,9 @@ typedef __hip_bfloat16 bf16;
 typedef __attribute__((ext_vector_type(8))) __bf16 bf16x8;
 typedef __attribute__((ext_vector_type(4))) float f32x4;
 typedef __attribute__((ext_vector_type(4))) unsigned u32x4;
+// four bf16 of a borrowed tensor (embedding, norm gains), which may start at any element; one 8-byte load all the same
+typedef __attribute__((ext_vector_type(4), aligned(2))) unsigned short bf16x4u;
+__device__ __forceinline__ float bf16x4_at(bf16x4u v, int i) { return __uint_as_float((unsigned)v[i] << 16); }
 
 #define SPEC_PAGE_TOKENS 64      // tokens per KV page
 #define SPEC_RING_MAX 64         // most slots of the draft-token / q-row ring

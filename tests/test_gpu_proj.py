@@ -54,3 +54,62 @@ def test_forwards_at_the_edges_of_the_operand_layouts(d, heads, kv, ffn):
         print(f"  d={d} ffn={ffn} m={m}: {err:.2e}", flush=True)
         assert err <= LOGIT_TOL, (m, err)
     ctx.close()
+
+
+def _shifted(t):
+    """The same values one element off the allocation's grid."""
+    buf = torch.empty(t.numel() + 8, dtype=t.dtype, device="cuda")
+    v = buf[1:1 + t.numel()].view(t.shape)
+    v.copy_(t)
+    assert v.data_ptr() % 4 == 2
+    return v
+
+
+# K slices, panels, half panels; the operand's rows start 2 bytes off every vector
+@pytest.mark.parametrize("M,N,K", [(1, 2048, 2048), (7, 4112, 1032), (17, 2064, 4104), (32, 48, 40)])
+def test_projection_of_activations_at_an_odd_address(M, N, K):
+    import paper_2408_11850_amd as amd
+    gen = torch.Generator().manual_seed(N + M)
+    w = torch.randn(N, K, generator=gen).mul_(0.05).to(torch.bfloat16)
+    x = torch.randn(M, K, generator=gen).to(torch.bfloat16)
+    ref = (x.double() @ w.double().T).numpy()
+    y = amd.gemm(_shifted(x.cuda()), amd.binding.pack_matrices([w.cuda()]), N).cpu().double().numpy()
+    assert np.linalg.norm(y - ref) <= 2.0 ** -24 * 60 ** 0.5 * np.linalg.norm(ref)   # as above
+
+
+def test_embedding_and_gains_at_odd_addresses_give_the_same_bits():
+    """A model whose embedding and norm gains are views one element into their allocations: prompt passes of both kinds,
+    draft steps and forwards of every layout of the residual add equal those of the aligned model."""
+    import paper_2408_11850_amd as amd
+    for d, ffn in ((256, 1376), (4608, 1376), (8448, 640)):
+        s = synth.ModelShape(2, d, 4, 2, ffn, 1008, head_dim=64)
+        outs = []
+        for shift in (False, True):
+            gen = torch.Generator(device="cuda").manual_seed(d)
+
+            def tensor(layer, name):
+                if name in ("attn_norm", "ffn_norm", "final_norm"):
+                    return torch.randn(d, generator=gen, device="cuda").mul_(0.3).add_(1.0).to(torch.bfloat16)
+                n, k = (s.vocab, d) if layer is None else synth.layer_matrix_shapes(s)[name]
+                return torch.randn(n, k, generator=gen, device="cuda").mul_(0.9 / k ** 0.5).to(torch.bfloat16)
+
+            model = amd.pack_model(s, tensor)
+            if shift:
+                model.tok_embed, model.final_norm = _shifted(model.tok_embed), _shifted(model.final_norm)
+                for lay in model.layers:
+                    lay["attn_norm"], lay["ffn_norm"] = _shifted(lay["attn_norm"]), _shifted(lay["ffn_norm"])
+            ctx = amd.SpecContext(model, model, gamma_max=31, max_seq=256)
+            got = []
+            for mode in (0, 1):
+                ctx.set_option(amd.SPEC_OPT_PREFILL, mode)
+                ctx.prefill(synth.prompt_tokens(90, s.vocab, 7).tolist())
+                got.append(np.asarray([ctx.draft_step(0.3, True), ctx.draft_step(0.6, True)]))
+                ctx.drop_drafts()
+                ctx.rollback_kv(amd.SPEC_DRAFT, 89)
+                for m in (1, 9, 17):
+                    got.append(ctx.verify(synth.prompt_tokens(m, s.vocab, 8).tolist(), want_logits=True))
+                    ctx.rollback_kv(amd.SPEC_TARGET, 89)
+            outs.append(got)
+            ctx.close()
+        assert all(np.isfinite(g).all() for g in outs[0])
+        assert all(np.array_equal(a, b) for a, b in zip(*outs)), d

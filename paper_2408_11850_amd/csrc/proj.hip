@@ -332,7 +332,7 @@ bool proj_whole_k(int M, int N, int K) {
 ProjPlan proj_plan(int M, int N, int K, int epi, int wgs_per_cu) {
   ProjPlan p;
   const int ncu = spec_num_cu();
-  p.M = M; p.N = N; p.K = K;
+  p.M = M; p.N = N; p.K = K; p.epi = epi;
   p.steps = (K + 31) / 32;
   p.NT = N / 16;
   p.units = p.NT;
@@ -366,50 +366,73 @@ ProjPlan proj_plan(int M, int N, int K, int epi, int wgs_per_cu) {
   return p;
 }
 
+// What launch_epi has kernels for.  HALF and PAIR keep two K steps in a load of x and so at most 8 tokens; a residual add
+// with two row tiles streams at most two panels at a time (registers); SWIGLU needs whole gate / up pairs.
+bool proj_plan_ok(const ProjPlan& p) {
+  if (p.M < 1 || p.M > SPEC_MAX_TOKENS || p.N < 16 || (p.N & 15) || p.K < 8 || (p.K & 7) || p.G < 1 || p.units < p.G) return false;
+  if (p.steps != (p.K + 31) / 32 || p.NT != p.N / 16 || (double)p.steps * 4096.0 >= (double)PROJ_SKIP) return false;
+  if (p.epi != PROJ_STORE && p.epi != PROJ_RESID && p.epi != PROJ_SWIGLU) return false;
+  const bool sw = p.epi == PROJ_SWIGLU;
+  if (sw && (p.N & 31)) return false;
+  switch (p.mode) {
+    case PROJ_HALF: return p.M <= 8 && p.RP == (sw ? 2 : 1) && p.units == (sw ? p.NT : p.NT * 2);
+    case PROJ_PAIR: return p.M <= 8 && !sw && p.RP == 1 && p.units == p.NT;
+    case PROJ_FULL:
+      if (p.units != (sw ? p.NT / 2 : p.NT)) return false;
+      if (p.RP == 1) return !sw;
+      return p.RP == 2 || (p.RP == 4 && !(p.M > 16 && p.epi == PROJ_RESID));
+  }
+  return false;
+}
+
 template <int EPI, int TAG>
 static hipError_t launch_epi(const ProjPlan& p, const ProjArgs& a, hipStream_t st) {
   dim3 g(p.G), b(PROJ_THREADS);
-#define PROJ_GO(MODE, MT, RP, D) proj_kernel<MODE, MT, RP, D, EPI, TAG><<<g, b, 0, st>>>(a)
+#define PROJ_GO(MODE, MT, RP, D)                                    \
+  {                                                                 \
+    proj_kernel<MODE, MT, RP, D, EPI, TAG><<<g, b, 0, st>>>(a);     \
+    return hipGetLastError();                                       \
+  }
   constexpr int SW = EPI == PROJ_SWIGLU ? 2 : 1;
   // Stages of the ring: 6, or 4 where a wave's range has 4 or 8 of them (K <= 2048) and every third load would bring
   // nothing (24 layers of d_model 2048, M = 5: 1000 us with 6, 949 with 4).
   const bool brief = p.steps <= 8 * PROJ_WAVES;
   if (p.mode == PROJ_HALF) {
-    if (brief) PROJ_GO(PROJ_HALF, 1, SW, 4);
-    else PROJ_GO(PROJ_HALF, 1, SW, 6);
+    if (brief) PROJ_GO(PROJ_HALF, 1, SW, 4)
+    PROJ_GO(PROJ_HALF, 1, SW, 6)
   } else if (p.mode == PROJ_PAIR) {
     if constexpr (EPI != PROJ_SWIGLU) {
-      if (brief) PROJ_GO(PROJ_PAIR, 1, 1, 4);
-      else PROJ_GO(PROJ_PAIR, 1, 1, 6);
+      if (brief) PROJ_GO(PROJ_PAIR, 1, 1, 4)
+      PROJ_GO(PROJ_PAIR, 1, 1, 6)
     }
   } else if (p.M > 16) {
-    if (p.RP <= 2) PROJ_GO(PROJ_FULL, 2, 2, 4);
-    else if constexpr (EPI != PROJ_RESID) PROJ_GO(PROJ_FULL, 2, 4, 4);
+    if (p.RP <= 2) PROJ_GO(PROJ_FULL, 2, 2, 4)
+    if constexpr (EPI != PROJ_RESID) PROJ_GO(PROJ_FULL, 2, 4, 4)
   } else if (p.RP == 4) {
-    PROJ_GO(PROJ_FULL, 1, 4, 3);
+    PROJ_GO(PROJ_FULL, 1, 4, 3)
   } else if (p.RP == 2) {
-    if (brief) PROJ_GO(PROJ_FULL, 1, 2, 4);
-    else PROJ_GO(PROJ_FULL, 1, 2, 6);
-  } else {
-    if constexpr (EPI != PROJ_SWIGLU) PROJ_GO(PROJ_FULL, 1, 1, 8);
+    if (brief) PROJ_GO(PROJ_FULL, 1, 2, 4)
+    PROJ_GO(PROJ_FULL, 1, 2, 6)
+  } else if constexpr (EPI != PROJ_SWIGLU) {
+    PROJ_GO(PROJ_FULL, 1, 1, 8)
   }
 #undef PROJ_GO
-  return hipGetLastError();
+  return hipErrorInvalidValue;      // nothing was launched
 }
 
 template <int TAG>
-static hipError_t launch_tag(const ProjPlan& p, int epi, const ProjArgs& a, hipStream_t st) {
-  if (epi == PROJ_STORE) return launch_epi<PROJ_STORE, TAG>(p, a, st);
-  if (epi == PROJ_RESID) return launch_epi<PROJ_RESID, TAG>(p, a, st);
+static hipError_t launch_tag(const ProjPlan& p, const ProjArgs& a, hipStream_t st) {
+  if (p.epi == PROJ_STORE) return launch_epi<PROJ_STORE, TAG>(p, a, st);
+  if (p.epi == PROJ_RESID) return launch_epi<PROJ_RESID, TAG>(p, a, st);
   return launch_epi<PROJ_SWIGLU, TAG>(p, a, st);
 }
 
-hipError_t launch_proj(const ProjPlan& p, int epi, ProjArgs a, hipStream_t st, int tag) {
-  if (p.M < 1 || p.M > SPEC_MAX_TOKENS || (p.N & 15) || (p.K & 7) || p.G < 1) return hipErrorInvalidValue;
-  if ((double)p.steps * 4096.0 >= (double)PROJ_SKIP || (epi == PROJ_SWIGLU && (p.N & 31))) return hipErrorInvalidValue;
+hipError_t launch_proj(const ProjPlan& p, ProjArgs a, hipStream_t st, int tag) {
+  if (!proj_plan_ok(p)) return hipErrorInvalidValue;
   a.M = p.M; a.N = p.N; a.K = p.K; a.steps = p.steps;
   a.per = p.units / p.G; a.rem = p.units % p.G;
-  if (tag == 0) return launch_tag<0>(p, epi, a, st);
-  if (tag == 1) return launch_tag<1>(p, epi, a, st);
+  if (tag == 0) return launch_tag<0>(p, a, st);
+  if (tag == 1) return launch_tag<1>(p, a, st);
+  if (p.epi != PROJ_STORE) return hipErrorInvalidValue;      // stand-alone calls store
   return launch_epi<PROJ_STORE, 2>(p, a, st);
 }

@@ -259,10 +259,10 @@ int prof_slot(spec_ctx* c, double bytes, unsigned long long** slot) {
 }
 
 // a whole-K projection of model `which`
-int run_proj(spec_ctx* c, int which, ModelRt& m, const ProjPlan& p, int epi, ProjArgs a) {
+int run_proj(spec_ctx* c, int which, ModelRt& m, const ProjPlan& p, ProjArgs a) {
   int rc;
   if ((c->profile_flags & 1) && which == SPEC_TARGET && (rc = prof_slot(c, (double)p.weight_bytes(), &a.stamp))) return rc;
-  HIPCHK(launch_proj(p, epi, a, m.stream, which));
+  HIPCHK(launch_proj(p, a, m.stream, which));
   return SPEC_OK;
 }
 
@@ -276,7 +276,7 @@ int run_resid(spec_ctx* c, int which, ModelRt& m, int M, int K, const bf16* x, c
     ProjArgs a = {};
     a.x = x; a.w = w; a.h = m.h; a.gain = (const bf16*)gain; a.xo = m.a; a.ssq_out = m.ssq;
     *W_out = p.pieces();
-    return run_proj(c, which, m, p, PROJ_RESID, a);
+    return run_proj(c, which, m, p, a);
   }
   const GemmPlan p = gemm_plan(M, N, K, c->wgs);
   unsigned long long* slot = nullptr;
@@ -314,13 +314,13 @@ int enqueue_forward(spec_ctx* c, int which, int M, int logit_rows, int W0, int l
   for (int l = l0; l < l1; ++l) {
     ProjArgs pa = normed;
     pa.w = m.wqkv[l]; pa.y = m.qkv; pa.ssq_w = W;
-    if ((rc = run_proj(c, which, m, proj_plan(M, qkvN, d.d_model, PROJ_STORE, c->wgs), PROJ_STORE, pa))) return rc;
+    if ((rc = run_proj(c, which, m, proj_plan(M, qkvN, d.d_model, PROJ_STORE, c->wgs), pa))) return rc;
     HIPCHK(launch_attention(m.qkv, m.rope_tab, m.pool, m.block_table_dev, m.len_dev, m.geom, l, M, d.n_heads,
                             m.split_tokens, m.opart, m.mlpart, m.attn_out, st));
     if ((rc = run_resid(c, which, m, M, HD, m.attn_out, m.wo[l], m.ffn_norm[l], &W))) return rc;
     pa = normed;
     pa.w = m.wgu[l]; pa.xo = m.z; pa.ssq_w = W;
-    if ((rc = run_proj(c, which, m, proj_plan(M, 2 * d.d_ffn, d.d_model, PROJ_SWIGLU, c->wgs), PROJ_SWIGLU, pa))) return rc;
+    if ((rc = run_proj(c, which, m, proj_plan(M, 2 * d.d_ffn, d.d_model, PROJ_SWIGLU, c->wgs), pa))) return rc;
     const void* next = l + 1 < d.n_layers ? m.attn_norm[l + 1] : m.final_norm;
     if ((rc = run_resid(c, which, m, M, d.d_ffn, m.z, m.wdown[l], next, &W))) return rc;
   }
@@ -331,7 +331,7 @@ int enqueue_forward(spec_ctx* c, int which, int M, int logit_rows, int W0, int l
     pa.x = m.a + (size_t)(M - rows) * d.d_model;
     pa.ssq = m.ssq + (size_t)(M - rows) * SSQ_STRIDE;
     pa.w = m.lm_head; pa.y = m.logits; pa.ssq_w = W;
-    if ((rc = run_proj(c, which, m, proj_plan(rows, d.vocab, d.d_model, PROJ_STORE, c->wgs), PROJ_STORE, pa))) return rc;
+    if ((rc = run_proj(c, which, m, proj_plan(rows, d.vocab, d.d_model, PROJ_STORE, c->wgs), pa))) return rc;
   }
   return SPEC_OK;
 }
@@ -1309,7 +1309,7 @@ extern "C" int spec_gemm(float* y, const void* x, const void* w, int M, int N, i
   if (proj_whole_k(M, N, K) && (((uintptr_t)x | (uintptr_t)w) & 15) == 0) {
     ProjArgs a = {};
     a.x = (const bf16*)x; a.w = w; a.y = y;
-    HIPCHK(launch_proj(proj_plan(M, N, K, PROJ_STORE, 2), PROJ_STORE, a, (hipStream_t)stream, 2));
+    HIPCHK(launch_proj(proj_plan(M, N, K, PROJ_STORE, 2), a, (hipStream_t)stream, 2));
     return SPEC_OK;
   }
   if ((rc = spec_gemm_partials(x, w, M, N, K, work, stream))) return rc;

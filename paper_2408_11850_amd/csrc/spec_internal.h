@@ -71,6 +71,7 @@ struct ProjPlan {
   int units;   // pieces of work: panel pairs (SWIGLU), panels or half panels
   int RP;      // panels a wave streams at a time
   int G;       // workgroups
+  int epi;     // PROJ_* epilogue the plan is for
   int pieces() const { return units; }   // RESID: sums of squares per row
   size_t weight_bytes() const { return (size_t)NT * steps * 1024; }
 };
@@ -91,7 +92,8 @@ struct ProjArgs {
   int M, N, K, steps;          // set by launch_proj ...
   int per, rem;                // ... units per workgroup; the first `rem` take one more
 };
-hipError_t launch_proj(const ProjPlan& p, int epi, ProjArgs a, hipStream_t st, int tag);
+bool proj_plan_ok(const ProjPlan& p);     // whether a kernel is built for it
+hipError_t launch_proj(const ProjPlan& p, ProjArgs a, hipStream_t st, int tag);
 
 // y = the sum of the K slices, n = M * N elements
 hipError_t launch_reduce_partials(float* y, const float* partials, int S, size_t n, hipStream_t st);

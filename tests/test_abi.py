@@ -110,3 +110,55 @@ def test_projection_plan_covers_every_shape_evenly(amd):
     assert lib.spec_gemm_plan_query(1, 40, 64, 2, out) == amd.SPEC_E_INVAL
     assert lib.spec_gemm_plan_query(1, 64, 64, 3, out) == amd.SPEC_E_INVAL
     assert lib.spec_gemm_plan_query(1, 64, 64, 2, None) == amd.SPEC_E_INVAL
+
+
+class _ProjPlan(C.Structure):
+    _fields_ = [(n, C.c_int) for n in ("M", "N", "K", "steps", "NT", "mode", "units", "RP", "G", "epi")]
+
+
+class _ProjArgs(C.Structure):       # as csrc/spec_internal.h; all null here
+    _fields_ = [("x", C.c_void_p), ("w", C.c_void_p), ("stamp", C.c_void_p), ("ssq", C.c_void_p), ("ssq_w", C.c_int),
+                ("eps", C.c_float), ("y", C.c_void_p), ("h", C.c_void_p), ("gain", C.c_void_p), ("xo", C.c_void_p),
+                ("ssq_out", C.c_void_p)] + [(n, C.c_int) for n in ("M", "N", "K", "steps", "per", "rem")]
+
+
+def test_whole_k_projection_plans_have_a_kernel_and_others_are_refused(amd):
+    """Host logic of proj.hip: every plan is one that a kernel is built for, its layout, panels at a time and units (and so
+    the order of the sums) do not depend on the launch mode, and a plan made for another epilogue or token count is an
+    error instead of a launch that does something else or nothing (only refused plans are launched here)."""
+    lib = C.CDLL(amd.LIB_PATH)
+    make, ok, launch = lib._Z9proj_planiiiii, lib._Z12proj_plan_okRK8ProjPlan, lib._Z11launch_projRK8ProjPlan8ProjArgsP12ihipStream_ti
+    make.restype, make.argtypes = _ProjPlan, [C.c_int] * 5
+    ok.restype, ok.argtypes = C.c_bool, [C.POINTER(_ProjPlan)]
+    launch.restype, launch.argtypes = C.c_int, [C.POINTER(_ProjPlan), _ProjArgs, C.c_void_p, C.c_int]
+    STORE, RESID, SWIGLU = 0, 1, 2
+    invalid = 1          # hipErrorInvalidValue
+    seen = set()
+    for N in (32, 2048, 2080, 4096, 4128, 8192, 8224, 12288, 16384, 16416, 24576, 24608, 38400, 49152, 49184, 57344):
+        for K in (8, 40, 2048, 2056, 8192):
+            for M in (1, 7, 8, 9, 16, 17, 24, 32):
+                for epi in (STORE, RESID, SWIGLU):
+                    two, one = make(M, N, K, epi, 2), make(M, N, K, epi, 1)
+                    for p in (two, one):
+                        assert ok(C.byref(p)) and 1 <= p.G <= min(p.units, 512), (M, N, K, epi)
+                    order = lambda p: (p.mode, p.RP, p.units, p.steps, p.NT, p.epi)  # noqa: E731
+                    assert order(two) == order(one)
+                    seen.add((p.mode, p.RP, epi, M > 16))
+                    if epi != STORE:       # a stand-alone launch only stores
+                        assert launch(C.byref(two), _ProjArgs(), None, 2) == invalid
+                    for other in (STORE, RESID, SWIGLU):
+                        q = make(M, N, K, epi, 2)
+                        q.epi = other
+                        if (other == SWIGLU) != (epi == SWIGLU):      # units are panels of one kind only
+                            assert not ok(C.byref(q))
+                        if not ok(C.byref(q)):
+                            assert launch(C.byref(q), _ProjArgs(), None, 0) == invalid
+                    if two.mode:                                       # two K steps per load of x: at most 8 tokens
+                        q = make(M, N, K, epi, 2)
+                        q.M = 9
+                        assert launch(C.byref(q), _ProjArgs(), None, 1) == invalid
+    assert {s[:2] for s in seen} == {(0, 1), (0, 2), (0, 4), (1, 1), (2, 1), (2, 2)}
+    wide = make(32, 57344, 8192, STORE, 2)
+    assert wide.RP == 4
+    wide.epi = RESID                       # four panels and two row tiles: no residual kernel
+    assert launch(C.byref(wide), _ProjArgs(), None, 0) == invalid

@@ -113,3 +113,32 @@ def test_embedding_and_gains_at_odd_addresses_give_the_same_bits():
             ctx.close()
         assert all(np.isfinite(g).all() for g in outs[0])
         assert all(np.array_equal(a, b) for a, b in zip(*outs)), d
+
+
+# Units of work beyond 256 and 512, so that one and two workgroups per CU share them out differently (uneven shares, several
+# panel groups per workgroup).  First: QKV 384, O and down 288, gate/up 704 half and 352 whole units, LM head 531; second: QKV
+# 576, O and down 528, gate/up 525, LM head 1601 panels
+@pytest.mark.parametrize("d,heads,kv,ffn,vocab", [(4608, 40, 4, 5632, 8496), (8448, 64, 4, 8400, 25616)])
+def test_launch_modes_give_the_same_bits(d, heads, kv, ffn, vocab):
+    import paper_2408_11850_amd as amd
+    s = synth.ModelShape(1, d, heads, kv, ffn, vocab, head_dim=128)
+    gen = torch.Generator(device="cuda").manual_seed(d)
+
+    def tensor(layer, name):
+        if name in ("attn_norm", "ffn_norm", "final_norm"):
+            return torch.randn(d, generator=gen, device="cuda").mul_(0.3).add_(1.0).to(torch.bfloat16)
+        n, k = (vocab, d) if layer is None else synth.layer_matrix_shapes(s)[name]
+        return torch.randn(n, k, generator=gen, device="cuda").mul_(0.9 / k ** 0.5).to(torch.bfloat16)
+
+    model = amd.pack_model(s, tensor)
+    ctx = amd.SpecContext(model, model, gamma_max=31, max_seq=256)
+    ctx.prefill(synth.prompt_tokens(40, vocab, 7).tolist(), which_mask=1)
+    toks = synth.prompt_tokens(32, vocab, 8).tolist()
+    for m in (1, 8, 9, 16, 17, 32):
+        got = []
+        for wgs in (1, 2):
+            ctx.set_option(amd.SPEC_OPT_GEMM_WGS_PER_CU, wgs)
+            got.append(ctx.verify(toks[:m], want_logits=True))
+            ctx.rollback_kv(amd.SPEC_TARGET, 39)
+        assert np.isfinite(got[0]).all() and got[0].std() > 0.1 and np.array_equal(got[0], got[1]), m
+    ctx.close()

@@ -293,8 +293,10 @@ int spec_accept_rows_static(const float* p_logits_dev, int n_rows, const float* 
  * SPEC_OPT_PREFILL: how spec_prefill feeds the prompt.  1 = dense path: blocks of up to 4096 tokens go through
  * matrix-core GEMMs and a causal flash-attention kernel (needs d_model, n_heads*head_dim and d_ffn to be
  * multiples of 32, else SPEC_E_INVAL at spec_prefill); 0 = as a sequence of 32-token verify forwards (the
- * decode kernels); -1 (default) = dense when the shapes allow it and the prompt has more than 64 tokens (more than 256
- * if d_ffn is an odd multiple of 16).
+ * decode kernels); -1 (default) = dense when the shapes allow it and the prompt has more than 64 tokens.  The automatic
+ * choice also takes the dense path for a d_ffn that is an odd multiple of 16 (rows padded by half a K step), from 257
+ * prompt tokens fed on; option 1 goes on refusing it, so that a program that asks for the path still learns that its
+ * shape does not tile.
  * Both fill the caches with the same K / V up to bf16 rounding of differently ordered sums.
  * SPEC_OPT_FUSE_SINGLE: 1 (default) = forwards over a single token (every draft step, autoregressive and pre-verify
  * target forwards) add the O and down projections to the residual stream in those projections' epilogues; 0 = as K

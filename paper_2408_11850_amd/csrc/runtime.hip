@@ -438,8 +438,10 @@ bool dense_shapes_ok(const spec_model_desc& d) {
   return d.d_model % 32 == 0 && (d.n_heads * d.head_dim) % 32 == 0;
 }
 int dense_ffn(const spec_model_desc& d) { return (d.d_ffn + 31) / 32 * 32; }
-// Prompt tokens from which on the dense pass is taken by itself.  Padded shapes: where it saves more than eight 32-token
-// forwards; shorter prompts of such (small) models keep the path, and so the bits, that SPEC_OPT_PREFILL 0 gives.
+// Prompt tokens from which on the dense pass is taken by itself.  It wins from 65 tokens on, padded or not (us in 32-token
+// forwards | dense; 24 layers of d_model 256, d_ffn 688: 64 tokens 1400 | 1130, 65 2070 | 1130, 256 6190 | 1300; 4 layers of
+// 4096, 11024: 64 1046 | 1005, 65 1390 | 1014, 256 4140 | 1330).  The line at 257 for padded shapes is not one of speed: their
+// prompts went through 32-token forwards at any length, and the shorter ones keep that path's bits.
 int dense_from(const spec_model_desc& d) { return dense_ffn(d) == d.d_ffn ? 65 : 257; }
 
 int ensure_prefill_buffers(ModelRt& m) {

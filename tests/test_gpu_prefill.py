@@ -172,3 +172,27 @@ def test_dense_prefill_refuses_shapes_it_cannot_tile():
     ctx.prefill(prompt)
     assert ctx.kv_len(amd.SPEC_TARGET) == 99
     ctx.close()
+
+
+# d_ffn an odd multiple of 16: K of the down projection is padded by half a step.  258 and 359 prompt tokens are 257 (the
+# first that the dense pass takes by itself) and 358 rows, 1100 leaves a ragged tile of either size
+@pytest.mark.parametrize("d_ffn,n_prompt", [(688, 258), (1392, 359), (688, 1100)])
+def test_dense_prefill_of_padded_ffn_rows_matches_oracle(d_ffn, n_prompt):
+    shape = synth.ModelShape(3, 256, 4, 4, d_ffn, 1024)
+    cfg = _custom(shape, 1, n_prompt)
+    amd, ctx, tm, _ = _setup(cfg)
+    forwards = ctx.forward_count(amd.SPEC_TARGET)
+    # the second, shorter prompt finds the first one's rows in the buffers, the third fills more of them again
+    for n, seed in ((n_prompt, 7), (258, 9), (n_prompt, 11)):
+        prompt = synth.prompt_tokens(n, shape.vocab, seed).tolist()
+        toks = [prompt[-1]] + synth.prompt_tokens(6, shape.vocab, 8).tolist()
+        ctx.prefill(prompt)
+        forwards += 1
+        assert ctx.forward_count(amd.SPEC_TARGET) == forwards          # one dense pass, not forwards over 32 tokens
+        ocm = transformer.CachedModel(tm, n + 16)
+        ocm.feed(prompt[:-1])
+        err = _rel_err(ctx.verify(toks, want_logits=True), ocm.feed(toks))
+        forwards += 1
+        print(f"  d_ffn={d_ffn} n={n}: max logit error / range = {err:.2e}", flush=True)
+        assert err <= LOGIT_TOL
+    ctx.close()

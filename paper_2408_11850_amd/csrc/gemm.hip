@@ -42,7 +42,7 @@ GemmPlan gemm_plan(int M, int N, int K, int wgs_per_cu) {
   if (p.MT == 2 || wgs_per_cu < 1) wgs_per_cu = 1;     // the 32-row variant needs a whole CU
   if (wgs_per_cu > 2) wgs_per_cu = 2;
   const int slots = ncu * wgs_per_cu;
-  const int spwmax = 8;
+  const int spwmax = 8;     // GEMM_STEPS: what a wave's registers hold
   // The K split depends on the shape only, never on wgs_per_cu (always planned for two workgroups per CU), so both
   // launch modes add the same numbers in the same order.  The fewest slices a wave's 8 steps allow are not always
   // the best: K = 28672 gives 14 slices, 36 groups of workgroups for 512 panels and a tail of groups with 15
@@ -69,23 +69,24 @@ GemmPlan gemm_plan(int M, int N, int K, int wgs_per_cu) {
   return p;
 }
 
-// Loads / multiplies one chunk of 8 K-steps (steps CH*8 .. CH*8+7 of the wave's range) of one panel.
-__device__ __forceinline__ void load_chunk(u32x4 (&a)[8], const u32x4* __restrict__ wp, int first, int nst) {
+// Loads / multiplies a wave's range of one panel, at most GEMM_STEPS K steps.
+#define GEMM_STEPS 8
+__device__ __forceinline__ void load_chunk(u32x4 (&a)[GEMM_STEPS], const u32x4* __restrict__ wp, int nst) {
 #pragma unroll
-  for (int j = 0; j < 8; ++j)
-    if (first + j < nst) a[j] = GEMM_LOAD(wp + (size_t)(first + j) * 64);
+  for (int j = 0; j < GEMM_STEPS; ++j)
+    if (j < nst) a[j] = GEMM_LOAD(wp + (size_t)j * 64);
 }
 
-template <int MT, int SPWMAX, int CH>
-__device__ __forceinline__ void mma_chunk(f32x4 (&acc)[MT], const u32x4 (&a)[8], const bf16x8 (&b)[MT][SPWMAX],
+template <int MT>
+__device__ __forceinline__ void mma_chunk(f32x4 (&acc)[MT], const u32x4 (&a)[GEMM_STEPS], const bf16x8 (&b)[MT][GEMM_STEPS],
                                           int nst) {
 #pragma unroll
-  for (int j = 0; j < 8; ++j)
-    if (CH * 8 + j < nst) {
+  for (int j = 0; j < GEMM_STEPS; ++j)
+    if (j < nst) {
       bf16x8 av = __builtin_bit_cast(bf16x8, a[j]);
 #pragma unroll
       for (int mt = 0; mt < MT; ++mt)
-        acc[mt] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(av, b[mt][CH * 8 + j], acc[mt], 0, 0, 0);
+        acc[mt] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(av, b[mt][j], acc[mt], 0, 0, 0);
     }
 }
 
@@ -94,14 +95,13 @@ __device__ __forceinline__ void mma_chunk(f32x4 (&acc)[MT], const u32x4 (&a)[8],
 // WPE = waves per SIMD the register budget is sized for.  The 16-row variant is held to 128 VGPRs (WPE 4) so
 // that two workgroups share a CU: 16 waves per CU hide the HBM latency far better than 8 (measured 6.9 vs
 // 5.9 TB/s on the gate/up matrix), and the second slot can also go to the other stream's kernel.
-template <int MT, int SPWMAX, int TAG, int WPE>
+template <int MT, int TAG, int WPE>
 __global__ __launch_bounds__(GEMM_THREADS, WPE) void gemm_partial_kernel(const bf16* __restrict__ X,
                                                                     const u32x4* __restrict__ Wp,
                                                                     float* __restrict__ P, int M, int N, int K,
                                                                     int NT, int steps, int S, int spw, int Gs,
                                                                     unsigned long long* stamp) {
-  constexpr int NCH = SPWMAX / 8;            // chunks per panel
-  constexpr int UNITS = GEMM_RP * NCH;       // chunks per reduction round (even)
+  static_assert(GEMM_RP % 2 == 0, "the two chunk buffers take turns");
   constexpr int NBUF = (MT == 1) ? 2 : 1;    // LDS reduction buffers: two let a round end with a single barrier
   __shared__ f32x4 red[NBUF][GEMM_WAVES][GEMM_RP][MT][64];
   const int s = blockIdx.x % S;
@@ -115,25 +115,25 @@ __global__ __launch_bounds__(GEMM_THREADS, WPE) void gemm_partial_kernel(const b
   // the K steps are dealt evenly to the S * 8 waves that share a panel: floor / ceil of steps / (8 S) each
   const int ws = s * GEMM_WAVES + w, nws = S * GEMM_WAVES;
   const int step0 = (int)((long long)ws * steps / nws);
-  const int nst = (int)((long long)(ws + 1) * steps / nws) - step0;   // <= spw <= SPWMAX
+  const int nst = (int)((long long)(ws + 1) * steps / nws) - step0;   // <= spw <= GEMM_STEPS
 
   const u32x4* wbase = Wp + (size_t)step0 * 64 + lane;
   const size_t pstride = (size_t)steps * 64;   // 16-byte units per panel
-  // Two-deep software pipeline over the chunk sequence (panel-major, NCH chunks per panel): chunks q and
+  // Two-deep software pipeline over the panels' chunks: chunks q and
   // q+1 are in flight; once chunk q is consumed its buffer is refilled with chunk q+2.  The sequence runs on
   // across reduction rounds, so the loads never drain at a round's barrier.  The first two chunks are requested
   // before anything else.
-  u32x4 a[2][8];
+  u32x4 a[2][GEMM_STEPS];
 #pragma unroll
   for (int q = 0; q < 2; ++q)
-    if (p0 + q / NCH < p1) load_chunk(a[q], wbase + (size_t)(p0 + q / NCH) * pstride, (q % NCH) * 8, nst);
+    if (p0 + q < p1) load_chunk(a[q], wbase + (size_t)(p0 + q) * pstride, nst);
 
   // activation fragments of this wave's K range, kept for the whole kernel
-  bf16x8 b[MT][SPWMAX];
+  bf16x8 b[MT][GEMM_STEPS];
 #pragma unroll
   for (int mt = 0; mt < MT; ++mt)
 #pragma unroll
-    for (int j = 0; j < SPWMAX; ++j) {
+    for (int j = 0; j < GEMM_STEPS; ++j) {
       const int m = mt * 16 + c;
       const int k = (step0 + j) * 32 + kb * 8;
       u32x4 v = {0u, 0u, 0u, 0u};
@@ -149,13 +149,10 @@ __global__ __launch_bounds__(GEMM_THREADS, WPE) void gemm_partial_kernel(const b
 #pragma unroll
       for (int mt = 0; mt < MT; ++mt) acc[rp][mt] = f32x4{0.f, 0.f, 0.f, 0.f};
 #pragma unroll
-    for (int u = 0; u < UNITS; ++u) {
-      if (pr + u / NCH < p1) {
-        if (u % NCH == 0) mma_chunk<MT, SPWMAX, 0>(acc[u / NCH], a[u & 1], b, nst);
-        else mma_chunk<MT, SPWMAX, (NCH > 1 ? 1 : 0)>(acc[u / NCH], a[u & 1], b, nst);
-      }
-      const int pn = pr + (u + 2) / NCH;
-      if (pn < p1) load_chunk(a[u & 1], wbase + (size_t)pn * pstride, ((u + 2) % NCH) * 8, nst);
+    for (int u = 0; u < GEMM_RP; ++u) {
+      if (pr + u < p1) mma_chunk<MT>(acc[u], a[u & 1], b, nst);
+      const int pn = pr + u + 2;
+      if (pn < p1) load_chunk(a[u & 1], wbase + (size_t)pn * pstride, nst);
     }
 
 #pragma unroll
@@ -188,10 +185,10 @@ static void launch_tagged(const GemmPlan& p, const bf16* x, const void* wp, floa
                           unsigned long long* stamp) {
   dim3 grid(p.Gs * p.S), block(GEMM_THREADS);
   if (p.MT == 1)
-    gemm_partial_kernel<1, 8, TAG, 4><<<grid, block, 0, st>>>(x, (const u32x4*)wp, partials, p.M, p.N, p.K, p.NT,
+    gemm_partial_kernel<1, TAG, 4><<<grid, block, 0, st>>>(x, (const u32x4*)wp, partials, p.M, p.N, p.K, p.NT,
                                                                 p.steps, p.S, p.spw, p.Gs, stamp);
   else
-    gemm_partial_kernel<2, 8, TAG, 2><<<grid, block, 0, st>>>(x, (const u32x4*)wp, partials, p.M, p.N, p.K, p.NT,
+    gemm_partial_kernel<2, TAG, 2><<<grid, block, 0, st>>>(x, (const u32x4*)wp, partials, p.M, p.N, p.K, p.NT,
                                                                 p.steps, p.S, p.spw, p.Gs, stamp);
 }
 

@@ -1,6 +1,5 @@
-// Small per-token kernels between the projections (gfx950): token gather, embedding,
-// residual add + RMSNorm, RoPE + KV append, SiLU*mul.  All of them read the fp32 K-slice
-// partials of the preceding projection and add the slices in ascending order.
+// Small per-token kernels around the projections (gfx950): the first launch of a forward (begin_kernel), the residual
+// add behind a projection in K slices, and embedding, RMSNorm and rotation table of a prompt block.
 #include "spec_internal.h"
 
 __global__ void set_int_kernel(int* dst, int v) { dst[0] = v; }
@@ -97,16 +96,14 @@ __global__ __launch_bounds__(ADDSQ_THREADS) void add_sumsq_kernel(float* __restr
     f32x4* hr = reinterpret_cast<f32x4*>(h + (size_t)m * d);
     const f32x4* P4 = reinterpret_cast<const f32x4*>(P);
     f32x4 t = hr[i];
-    if (P) {
-      int s = 0;
-      for (; s + 4 <= S; s += 4) {
-        const f32x4 p0 = P4[((size_t)(s + 0) * M + m) * d4 + i], p1 = P4[((size_t)(s + 1) * M + m) * d4 + i];
-        const f32x4 p2 = P4[((size_t)(s + 2) * M + m) * d4 + i], p3 = P4[((size_t)(s + 3) * M + m) * d4 + i];
-        t += p0; t += p1; t += p2; t += p3;
-      }
-      for (; s < S; ++s) t += P4[((size_t)s * M + m) * d4 + i];
-      hr[i] = t;
+    int s = 0;
+    for (; s + 4 <= S; s += 4) {
+      const f32x4 p0 = P4[((size_t)(s + 0) * M + m) * d4 + i], p1 = P4[((size_t)(s + 1) * M + m) * d4 + i];
+      const f32x4 p2 = P4[((size_t)(s + 2) * M + m) * d4 + i], p3 = P4[((size_t)(s + 3) * M + m) * d4 + i];
+      t += p0; t += p1; t += p2; t += p3;
     }
+    for (; s < S; ++s) t += P4[((size_t)s * M + m) * d4 + i];
+    hr[i] = t;
     ss = t.x * t.x + t.y * t.y + t.z * t.z + t.w * t.w;
     const bf16* g = gain + (size_t)i * 4;
     bf16* dst = a + (size_t)m * d + (size_t)i * 4;
@@ -129,7 +126,7 @@ __global__ __launch_bounds__(ADDSQ_THREADS) void add_sumsq_kernel(float* __restr
 hipError_t launch_add_sumsq(float* h, const float* partials, int S, const bf16* gain, bf16* a, float* ssq, int M,
                             int d, int* W_out, hipStream_t st) {
   const int W = ((d >> 2) + ADDSQ_THREADS - 1) / ADDSQ_THREADS;
-  if ((d & 3) || d > SPEC_D_MODEL_MAX) return hipErrorInvalidValue;
+  if (!partials || (d & 3) || d > SPEC_D_MODEL_MAX) return hipErrorInvalidValue;
   add_sumsq_kernel<<<dim3(W, M), ADDSQ_THREADS, 0, st>>>(h, partials, S, gain, a, ssq, M, d, W);
   *W_out = W;
   return hipGetLastError();

@@ -142,13 +142,13 @@ hipError_t launch_set_pages(int* block_table, PageUpdate u, hipStream_t st);
 hipError_t launch_embed(float* h, const bf16* embed, const int* tok, int M, int d, int vocab, hipStream_t st);
 // a = rmsnorm(h) * gain
 hipError_t launch_norm(const float* h, const bf16* gain, bf16* a, int M, int d, float eps, hipStream_t st);
-// h += sum_s partials[s] (if partials), a = bf16(h * gain) (not normalised), ssq[m][w] = sum of h^2 over the w-th
+// h += sum_s partials[s], a = bf16(h * gain) (not normalised), ssq[m][w] = sum of h^2 over the w-th
 // piece of 1024 columns of row m (row stride SSQ_STRIDE; pieces beyond W
 // are never written); returns the number of pieces W through *W_out
 hipError_t launch_add_sumsq(float* h, const float* partials, int S, const bf16* gain, bf16* a, float* ssq, int M,
                             int d, int* W_out, hipStream_t st);
 hipError_t launch_rope_table(float2* tab, const int* len_ptr, int M, int dh, float theta, hipStream_t st);
-// y: the fused QKV projection [M][(Hq + 2 Hkv) dh] of M new tokens; tab: their [M][dh/2] (cos, sin) from launch_rope_table.
+// y: the fused QKV projection [M][(Hq + 2 Hkv) dh] of M new tokens; tab: their [M][dh/2] (cos, sin) from launch_begin.
 // Rotates q and k, appends k and v to the pages and attends over the cache and the new tokens.
 hipError_t launch_attention(const float* y, const float2* tab, bf16* pool, const int* block_table, const int* len_ptr,
                             KvGeom g, int layer, int M, int Hq, int split_tokens, float* opart, float* mlpart, bf16* out,

@@ -299,22 +299,34 @@ __global__ __launch_bounds__(PROJ_THREADS, RP * MT > 4 ? 2 : 4) void proj_kernel
     atomicMax(a.stamp + 2 * (blockIdx.x % STAMP_WAYS) + 1, (unsigned long long)wall_clock64());
 }
 
-// Where K slices (gemm.hip) and a kernel that adds them are faster (us, K slices with their sum | this kernel):
-//   narrow and deep, K > 4 N: few workgroups, long ranges          512 x 8192, M = 12    8.1 | 10.9
-//   more than 16 tokens: the slices keep their activations in registers, here every panel group loads them again;
-//   that shows where a workgroup has a single long group           2048 x 5632, M = 17   9.8 | 12.4
-//                                                                  7168 x 19200, M = 32 66.0 | 70.5
-//   (but 7168 x 19200, M = 17 62.6 | 53.1;  4096 x 4096, M = 32 13.3 | 13.2)
-//   long K and uneven shares of panels                             6352 x 16824, M = 16 39.9 | 45.0
-//                                                                  29216 x 10440, M = 6 97.6 | 100.8
-//   (even: 7168 x 19200, M = 12 49.7 | 48.0;  40624 x 5160, M = 1 67.8 | 66.4)
+// Whether this kernel is the faster one; else K slices (gemm.hip) and a kernel that adds them.  What counts against it:
+//   narrow and deep, K > 4 N: few workgroups, long ranges           512 x 8192, M = 12    8.1 (slices) | 10.9 (this kernel)
+//   activations: the slices keep theirs in registers, here every panel group loads them again, M / (16 RP) of the weights'
+//   traffic on top, in one workgroup's single long group where panels are fewer than CUs
+//                      1024 x 4096: M = 9 1.14 times as fast as slices, M = 16 0.95, M = 17 0.81, M = 32 0.66
+//                      4096 x 11008: M = 8 1.18, M = 9 1.11, M = 16 0.93, M = 32 0.74
+//   uneven shares of panels, which slices deal in smaller pieces (`share`: part of the CUs' time in use if every CU takes as
+//   many panels as the busiest; slower from longer K on)
+//                      4608 x 4096, 5120 x 4096 (0.56, 0.63): M = 8 0.94; x 11008 0.85, 0.89; 6144 x 16384 (0.75) 0.86
+//                      10240 x 11008 (0.83): M = 16 0.98, M = 24 0.91, M = 32 0.84; 14336 x 11008 (0.88): M = 32 0.99
+// The limits lie where the ratio falls below 1 on a grid of 30 N x 18 K x 11 M (weights from HBM, back to back in a graph).
 bool proj_whole_k(int M, int N, int K) {
   if (K > 4 * N) return false;
   const int NT = N / 16, ncu = spec_num_cu();
-  if (K <= 4096 || (M <= 8 && NT <= 6 * ncu)) return true;
-  if (M > 16 && NT <= (M > 24 ? 2 * ncu : ncu / 2)) return false;
-  // share of the CUs' time in use if every CU takes as many panels as the busiest
-  return NT <= ncu || NT * 10 >= (NT + ncu - 1) / ncu * ncu * (M <= 8 ? 9 : 8);
+  const int share = (int)(100LL * NT / ((long long)(NT + ncu - 1) / ncu * ncu));
+  if (M <= 8) return NT <= ncu || NT > 2 * ncu || share >= 80 || K < (share < 70 ? 4096 : 12288);
+  if (NT <= ncu) {
+    if (M <= 12) return K <= (share >= 95 ? 16384 : share >= 85 ? 8192 : 4096);
+    if (M <= 16) return K <= (share >= 95 ? 8192 : 4096);
+    if (M <= 24) return K <= (share >= 90 ? 4096 : share >= 30 ? 3072 : 2048);
+    return K <= (share >= 90 ? 4096 : share >= 60 ? 2048 : 1024);
+  }
+  if (NT <= 2 * ncu) {
+    if (M <= 16) return K <= 4096 || (share >= 80 && (K <= 8192 || M <= 12 || share >= 95));
+    if (M <= 24) return K <= 4096 || share >= 95 || (share >= 80 && M <= 20);
+    return K <= (share < 80 ? 2048 : 4096);
+  }
+  return K <= 4096 || share >= (M <= 24 ? 80 : 86);
 }
 
 // Layout, panels at a time (RP) and workgroups.  The layout and RP set the order of the sums and depend on the shape
@@ -322,8 +334,10 @@ bool proj_whole_k(int M, int N, int K) {
 //   up to 1/2: half panels                           2048 x 5632   6.3 (panels: 7.4)
 //   up to 2: one panel per workgroup                 4096 x 4096   7.9 (half panels 8.5),  8192 x 8192  24 (RP 4: 28)
 //   up to 3: one workgroup per CU, RP 4             11264 x 2048   9.0 (RP 1: 9.9),  12288 x 4096  17.8 (RP 1: 19.0)
+//   up to 4, short of it: the same, four whole panels 14336 x 8192  1.09 times as fast as two per CU with two each (M = 16 1.19)
 //   up to 6: two per CU, RP 4: even shares          21504 x 7168  49.5 (one per CU, RP 1: 53.2)
-//   beyond: one per CU, RP 1, for PAIR's loads of x 38400 x 7168  88 (RP 4, two per CU: 95)
+//   beyond: one per CU, RP 1, for PAIR's loads of x 38400 x 7168  88 (RP 4, two per CU: 95); K < 2048: a wave has only a few
+//   steps of a panel and RP 4 saves barriers        57344 x 1024  1.15 times, x 256 2.1 times as fast as RP 1
 //   from 9 tokens on (FULL): RP as large as the panels fill; one workgroup per CU streams as fast as two and has the
 //   fewer loads of x                                38400 x 7168, M = 12  90 (two per CU: 99)
 // SWIGLU pairs a gate and an up panel, so shares get coarser: half panels keep them even where there are few (11264 x
@@ -350,7 +364,10 @@ ProjPlan proj_plan(int M, int N, int K, int epi, int wgs_per_cu) {
   } else if (p.NT > 2 * ncu && p.NT <= 6 * ncu) {
     p.mode = PROJ_FULL;
     p.RP = 4;
-    if (p.NT <= 3 * ncu) G = ncu;
+    if (p.NT < 4 * ncu) G = ncu;
+  } else if (M <= 8 && p.NT > 6 * ncu && K < 2048) {
+    p.mode = PROJ_FULL;
+    p.RP = 4;
   } else if (M <= 8) {
     p.mode = PROJ_PAIR;
     p.RP = 1;

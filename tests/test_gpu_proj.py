@@ -14,9 +14,10 @@ pytestmark = [pytest.mark.gpu, pytest.mark.skipif(not gpu_available(), reason="n
 
 # 8 / 9 and 16 / 17 tokens change the operand layout; N = 16: two half panels; 2048 / 2064: last of the half panels;
 # 4112, 8208, 24592: one panel more than a workgroup range (1, 2, 6 per CU); K = 40, 1032: ragged K and odd step counts;
-# 4104 with 17 and 25 tokens of a narrow matrix: K slices
+# 4104 with 17 and 25 tokens of a narrow matrix: K slices; 14352 and 16384: one and two workgroups per CU below and at four
+# panels per CU; 24592: four panels at a time, or one from K = 2048 on; 4624: uneven shares, K slices from 4096 on
 @pytest.mark.parametrize("N,K", [(16, 40), (48, 8), (2048, 1032), (2064, 520), (4112, 1032), (8192, 2088), (8208, 264),
-                                 (24592, 136), (2048, 4104)])
+                                 (24592, 136), (2048, 4104), (14352, 264), (16384, 264), (24592, 2056), (4624, 4088), (4624, 4104)])
 @pytest.mark.parametrize("M", [1, 8, 9, 16, 17, 25, 32])
 def test_projection_at_the_edges_of_the_operand_layouts(M, N, K):
     import paper_2408_11850_amd as amd

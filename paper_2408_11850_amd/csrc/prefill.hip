@@ -416,14 +416,15 @@ __global__ __launch_bounds__(DG_THREADS, 2) void dense_small_kernel(const bf16* 
   dense_epilogue<EPI, 4>(acc, tm * 128 + (w >> 1) * 64, tn * 2 + (w & 1), c, kb, Y, Z, M, N, ldz, ra);
 }
 
-// Tile by the time a launch takes, in rounds of one workgroup per CU (measured, K in steps of 32; us = 9 + 0.65 steps per
-// round of 256 x 256 tiles, 3 + 0.335 steps per round of 128 x 128): 511 x 6144 x 2048 50.5 | 27.1, 1023 x 4096 x 4096 90 |
-// 51, 1023 x 4096 x 11008 220 | 121 (one round either way), 2047 x 4096 x 4096 94 | 91 (1 | 2), 1023 x 8192 x 8192 170 | 184
-// (1 | 2), 511 x 22016 x 4096 100 | 133 (1 | 3), 1023 x 22016 x 4096 192 | 292 (2 | 6).
+// Tile by the time a launch takes, in rounds of one workgroup per CU (measured, K in steps of 32; us = 9 + 0.635 steps per
+// round of 256 x 256 tiles, 0.60 with a third of the CUs in use, 0.66 with all; 3 + 0.335 steps per round of 128 x 128;
+// us large | small): 511 x 6144 x 2048 50.5 | 27.1, 1023 x 4096 x 4096 90 | 51, 1023 x 4096 x 11008 220 | 121 (one round either
+// way), 1500 x 3072 x 2048 52 | 49, 511 x 12288 x 4096 85 | 97, 2047 x 4096 x 4096 86 | 100, 1023 x 8192 x 8192 170 | 184 (1 | 2),
+// 511 x 22016 x 4096 100 | 133 (1 | 3), 1023 x 22016 x 4096 192 | 292 (2 | 6).
 static bool dense_small_tiles(int M, int NT, int steps) {
   const int ncu = spec_num_cu();
   const int large = (M + DG_BM - 1) / DG_BM * ((NT + 15) / 16), small = (M + 127) / 128 * ((NT + 7) / 8);
-  return (long long)((small + ncu - 1) / ncu) * (300 + 33.5 * steps) < (long long)((large + ncu - 1) / ncu) * (900 + 65.0 * steps);
+  return (long long)((small + ncu - 1) / ncu) * (300 + 33.5 * steps) < (long long)((large + ncu - 1) / ncu) * (900 + 63.5 * steps);
 }
 
 template <int EPI>

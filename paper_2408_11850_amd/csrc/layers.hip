@@ -1,5 +1,5 @@
-// Small per-token kernels around the projections (gfx950): the first launch of a forward (begin_kernel), the residual
-// add behind a projection in K slices, and embedding, RMSNorm and rotation table of a prompt block.
+// Small per-token kernels around the projections (gfx950): the first launch of a forward (begin_kernel), what follows a
+// projection in K slices (residual add, scaling, SiLU * mul), and embedding, RMSNorm and rotation table of a prompt block.
 #include "spec_internal.h"
 
 __global__ void set_int_kernel(int* dst, int v) { dst[0] = v; }
@@ -129,6 +129,53 @@ hipError_t launch_add_sumsq(float* h, const float* partials, int S, const bf16* 
   if (!partials || (d & 3) || d > SPEC_D_MODEL_MAX) return hipErrorInvalidValue;
   add_sumsq_kernel<<<dim3(W, M), ADDSQ_THREADS, 0, st>>>(h, partials, S, gain, a, ssq, M, d, W);
   *W_out = W;
+  return hipGetLastError();
+}
+
+// A row's K slices added in ascending order and scaled by its 1 / rms, which every wave works out from the row's pieces: the
+// epilogues of a whole-K projection for the narrow, deep matrices that run in slices.  Latency: 1024 columns per workgroup.
+__global__ __launch_bounds__(256) void slices_epilogue_kernel(const float* __restrict__ P, int S, ProjArgs a, int swiglu) {
+  const int m = blockIdx.y, lane = threadIdx.x & 63;
+  const int i = (blockIdx.x * 256 + threadIdx.x) * 4;      // output column
+  const int n = swiglu ? a.N / 2 : a.N;
+  const f32x4* row = reinterpret_cast<const f32x4*>(a.ssq + (size_t)m * SSQ_STRIDE);
+  float ss = 0.f;
+  for (int k = lane; k * 4 < a.ssq_w; k += 64) {
+    const f32x4 t = row[k];
+#pragma unroll
+    for (int r = 0; r < 4; ++r) ss += k * 4 + r < a.ssq_w ? t[r] : 0.f;
+  }
+#pragma unroll
+  for (int o = 32; o > 0; o >>= 1) ss += __shfl_xor(ss, o);
+  const float inv = 1.0f / sqrtf(ss / (float)a.K + a.eps);
+  if (i >= n) return;
+  // gate and up panels of 16 columns take turns
+  const int c0 = swiglu ? (i >> 4) * 32 + (i & 15) : i;
+  const float* src = P + (size_t)m * a.N + c0;
+  const size_t slice = (size_t)gridDim.y * a.N;
+  f32x4 t = {0.f, 0.f, 0.f, 0.f}, u = {0.f, 0.f, 0.f, 0.f};
+#pragma unroll 4
+  for (int s = 0; s < S; ++s) {
+    t += *reinterpret_cast<const f32x4*>(src + s * slice);
+    if (swiglu) u += *reinterpret_cast<const f32x4*>(src + s * slice + 16);
+  }
+  t *= inv;
+  if (!swiglu) {
+    *reinterpret_cast<f32x4*>(a.y + (size_t)m * n + i) = t;
+    return;
+  }
+  bf16 o[4];
+#pragma unroll
+  for (int r = 0; r < 4; ++r) o[r] = __float2bfloat16(t[r] / (1.0f + __expf(-t[r])) * (u[r] * inv));
+  *reinterpret_cast<uint2*>(a.xo + (size_t)m * n + i) = *reinterpret_cast<const uint2*>(o);
+}
+hipError_t launch_slices_epilogue(const float* partials, int S, int epi, const ProjArgs& args, int M, int N, int K, hipStream_t st) {
+  const bool swiglu = epi == PROJ_SWIGLU;
+  if (!args.ssq || (epi != PROJ_STORE && !swiglu) || (N & (swiglu ? 31 : 15)) || args.ssq_w > SSQ_STRIDE) return hipErrorInvalidValue;
+  ProjArgs a = args;
+  a.M = M; a.N = N; a.K = K;
+  const int n = swiglu ? N / 2 : N;
+  slices_epilogue_kernel<<<dim3((n + 1023) / 1024, M), 256, 0, st>>>(partials, S, a, swiglu);
   return hipGetLastError();
 }
 

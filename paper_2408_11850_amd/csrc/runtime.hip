@@ -179,9 +179,12 @@ int init_model(ModelRt& m, const spec_model_desc& d, const spec_weights& w, cons
   if ((rc = dev_alloc(&m.attn_out, (size_t)MX * d.n_heads * d.head_dim))) return rc;
   if ((rc = dev_alloc(&m.z, (size_t)MX * d.d_ffn))) return rc;
   size_t pb = 0;
-  const int shapes[2][2] = {{d.d_model, d.n_heads * d.head_dim}, {d.d_model, d.d_ffn}};   // run_resid by K slices
+  // run_resid and, if narrow, run_normed by K slices
+  const int shapes[5][2] = {{d.d_model, d.n_heads * d.head_dim}, {d.d_model, d.d_ffn}, {qkvN, d.d_model},
+                            {2 * d.d_ffn, d.d_model}, {d.vocab, d.d_model}};
   for (int mm : {1, 16, MX})
     for (auto& s : shapes) {
+      if (&s >= shapes + 2 && s[0] > 16 * spec_num_cu()) continue;
       size_t b = gemm_plan(mm, s[0], s[1]).partial_bytes();
       if (b > pb) pb = b;
     }
@@ -266,6 +269,23 @@ int run_proj(spec_ctx* c, int which, ModelRt& m, const ProjPlan& p, ProjArgs a) 
   return SPEC_OK;
 }
 
+// Whether the projection of the normalised residual stream (QKV, gate/up, LM head) runs in K slices.  Only where it is
+// narrower than a panel per CU and takes more than 8 tokens (three layers of d_model 8192, QKV 768, gate/up 2048, vocabulary
+// 1024: M = 32 264 us whole, 162 so; d_model 4608, QKV 512, M = 1 92 and 102): beyond, the kernel saved pays for what the slices gain.
+bool normed_in_slices(int M, int N, int K) { return M > 8 && N <= 16 * spec_num_cu() && !proj_whole_k(M, N, K); }
+
+// a projection of the normalised residual stream with the epilogue `epi` (STORE or SWIGLU)
+int run_normed(spec_ctx* c, int which, ModelRt& m, int M, int N, int K, int epi, const ProjArgs& a) {
+  int rc;
+  if (!normed_in_slices(M, N, K)) return run_proj(c, which, m, proj_plan(M, N, K, epi, c->wgs), a);
+  const GemmPlan p = gemm_plan(M, N, K, c->wgs);
+  unsigned long long* slot = nullptr;
+  if ((c->profile_flags & 1) && which == SPEC_TARGET && (rc = prof_slot(c, (double)p.weight_bytes(), &slot))) return rc;
+  HIPCHK(launch_gemm_partials(p, a.x, a.w, m.partials, m.stream, which, slot));
+  HIPCHK(launch_slices_epilogue(m.partials, p.S, epi, a, M, N, K, m.stream));
+  return SPEC_OK;
+}
+
 // h += x W^T, x' = bf16(h * gain) for the next projection and the sums of squares of h, *W_out pieces per row: one
 // whole-K launch, or K slices and the kernel that adds them.
 int run_resid(spec_ctx* c, int which, ModelRt& m, int M, int K, const bf16* x, const void* w, const void* gain, int* W_out) {
@@ -314,13 +334,13 @@ int enqueue_forward(spec_ctx* c, int which, int M, int logit_rows, int W0, int l
   for (int l = l0; l < l1; ++l) {
     ProjArgs pa = normed;
     pa.w = m.wqkv[l]; pa.y = m.qkv; pa.ssq_w = W;
-    if ((rc = run_proj(c, which, m, proj_plan(M, qkvN, d.d_model, PROJ_STORE, c->wgs), pa))) return rc;
+    if ((rc = run_normed(c, which, m, M, qkvN, d.d_model, PROJ_STORE, pa))) return rc;
     HIPCHK(launch_attention(m.qkv, m.rope_tab, m.pool, m.block_table_dev, m.len_dev, m.geom, l, M, d.n_heads,
                             m.split_tokens, m.opart, m.mlpart, m.attn_out, st));
     if ((rc = run_resid(c, which, m, M, HD, m.attn_out, m.wo[l], m.ffn_norm[l], &W))) return rc;
     pa = normed;
     pa.w = m.wgu[l]; pa.xo = m.z; pa.ssq_w = W;
-    if ((rc = run_proj(c, which, m, proj_plan(M, 2 * d.d_ffn, d.d_model, PROJ_SWIGLU, c->wgs), pa))) return rc;
+    if ((rc = run_normed(c, which, m, M, 2 * d.d_ffn, d.d_model, PROJ_SWIGLU, pa))) return rc;
     const void* next = l + 1 < d.n_layers ? m.attn_norm[l + 1] : m.final_norm;
     if ((rc = run_resid(c, which, m, M, d.d_ffn, m.z, m.wdown[l], next, &W))) return rc;
   }
@@ -331,7 +351,7 @@ int enqueue_forward(spec_ctx* c, int which, int M, int logit_rows, int W0, int l
     pa.x = m.a + (size_t)(M - rows) * d.d_model;
     pa.ssq = m.ssq + (size_t)(M - rows) * SSQ_STRIDE;
     pa.w = m.lm_head; pa.y = m.logits; pa.ssq_w = W;
-    if ((rc = run_proj(c, which, m, proj_plan(rows, d.vocab, d.d_model, PROJ_STORE, c->wgs), pa))) return rc;
+    if ((rc = run_normed(c, which, m, rows, d.vocab, d.d_model, PROJ_STORE, pa))) return rc;
   }
   return SPEC_OK;
 }

@@ -95,6 +95,9 @@ struct ProjArgs {
 bool proj_plan_ok(const ProjPlan& p);     // whether a kernel is built for it
 hipError_t launch_proj(const ProjPlan& p, ProjArgs a, hipStream_t st, int tag);
 
+// What a whole-K projection's STORE / SWIGLU epilogue does, from K slices: y = sum of the S slices * 1 / rms(row) with the
+// scaling of ProjArgs (ssq, ssq_w, eps; K columns), to a.y, or bf16(silu(gate) * up) to a.xo
+hipError_t launch_slices_epilogue(const float* partials, int S, int epi, const ProjArgs& a, int M, int N, int K, hipStream_t st);
 // y = the sum of the K slices, n = M * N elements
 hipError_t launch_reduce_partials(float* y, const float* partials, int S, size_t n, hipStream_t st);
 hipError_t launch_pack_weight(void* dst, const void* src, int N, int K, int panel_start, int panel_step, hipStream_t st);

@@ -230,17 +230,19 @@ int spec_pack_weight(void* dst_dev, const void* src_dev, int N, int K, int panel
 size_t spec_packed_bytes(int N, int K);
 
 /* y[M][N] (fp32, device) = x[M][K] (bf16 row-major, device) * W^T with W panel-packed.
- * The same kernel the forward uses; `work_dev` needs spec_gemm_workspace_bytes(M, N, K).
- * M <= SPEC_MAX_TOKENS.  Asynchronous on `stream`. */
+ * The kernels the forward uses, chosen by the shape: the whole K axis in a workgroup, or K slices and a second launch that
+ * adds them.  `work_dev` needs spec_gemm_workspace_bytes(M, N, K) either way; operands that start off a 16-byte address take
+ * the slices.  M <= SPEC_MAX_TOKENS.  Asynchronous on `stream`. */
 int spec_gemm(float* y_dev, const void* x_dev, const void* w_packed_dev, int M, int N, int K,
               void* work_dev, void* stream);
 size_t spec_gemm_workspace_bytes(int M, int N, int K);
-/* How that kernel divides its work (host-only, no GPU needed): out6 = { S = K slices, most K steps of 32 a wave
+/* How the kernel with K slices divides its work (host-only, no GPU needed): out6 = { S = K slices, most K steps of 32 a wave
  * takes (at most 8), Gs = groups of workgroups along N, number of 16-row panels, number of K steps, 16-row tiles
  * of x (1 or 2) }.  workgroups_per_cu is 1 or 2; S does not depend on it.  SPEC_E_INVAL for shapes spec_gemm
  * refuses. */
 int spec_gemm_plan_query(int M, int N, int K, int workgroups_per_cu, int* out6);
-/* Only the streaming kernel of spec_gemm (no reduction pass); used to time it in isolation. */
+/* Only the streaming kernel with K slices, whatever spec_gemm would choose (no reduction pass); used to time it in
+ * isolation. */
 int spec_gemm_partials(const void* x_dev, const void* w_packed_dev, int M, int N, int K,
                        void* work_dev, void* stream);
 
@@ -286,8 +288,8 @@ int spec_accept_rows_static(const float* p_logits_dev, int n_rows, const float* 
 /* Options.  SPEC_OPT_GEMM_WGS_PER_CU: how many workgroups of a projection kernel are launched per compute
  * unit.  2 fills both slots of every CU (fastest when a stream runs alone), 1 leaves one slot to the other
  * stream's kernels so that draft and target passes run side by side, -1 (default) = automatic: spec_generate's
- * PEARL loop on two different streams uses 1, everything else 2.  Results do not depend on it (the K split
- * and the order of additions are fixed by the shape).
+ * PEARL loop on two different streams uses 1, everything else 2.  Results do not depend on it (every
+ * order of additions is fixed by the shape).
  * SPEC_OPT_GRAPHS: 1 (default) = every forward is captured once per (model, token count, mode) into a HIP graph
  * and replayed; 0 = launch kernel by kernel.  Results are identical.
  * SPEC_OPT_PREFILL: how spec_prefill feeds the prompt.  1 = dense path: blocks of up to 4096 tokens go through
@@ -308,7 +310,7 @@ int spec_accept_rows_static(const float* p_logits_dev, int n_rows, const float* 
  * of the memory pipe, and what is left of it after the draft chain has ended runs at the full rate.  -1 (default):
  * spec_generate's PEARL loops move n by one chunk per step from where the two chains of the last step ended (the
  * balance the window size of Section 4.4.1 aims at, reached here at run time); n >= 0: fixed.  The results do not
- * depend on it (the K split of a projection is the same in both launch modes).  spec_get_option reads the n in use.
+ * depend on it (a projection's sums are formed in the same order in both launch modes).  spec_get_option reads the n in use.
  * SPEC_OPT_GUESS_TOKENS: most guesses k a pre-verify step of algo 5 feeds behind the frontier; -1 (default) =
  * gamma - 1, the most that can be used; values above gamma - 1 are clipped.
  * SPEC_OPT_TEST_FAIL_PREFILL (tests of the error path only): n > 0 makes the next spec_prefill give up with

@@ -13,9 +13,9 @@
 // the projection in registers (the one of row tile 0 also stores them to the pages, last).  So the cache's chunks need no
 // causal mask, nobody waits for an append, and a rotation kernel (4.4 us per layer) is gone.
 //
-// What bounds it is a chain of latencies: kernel start, page id, K / V, softmax, result (7B shape, M = 1, 4096 positions:
-// 13.4 us for 67 MB, 4.6 the merge; 70B, M = 7: 10.9 + 5.3; with the old rotation kernel in front 5.0 + 14.1 + 4.6 and
-// 4.9 + 8.9 + 5.4).  Up to 1024 positions one launch does it all: 24 layers of 16 heads, 512 positions, M = 5: 9.2 us
+// What bounds it is a chain of latencies: kernel start, page id, K / V, softmax, result (traced; 7B shape, M = 1, 4096
+// positions: 16.0 us for 67 MB, 4.6 the merge; 70B, M = 7: 13.2 + 5.5; with a rotation kernel in front 4.9 + 14.2 + 4.6 and
+// 4.9 + 11.2 + 5.4: the split kernel itself takes 2 us longer, every wave rotates its q, and 3 us per layer are saved).  Up to 1024 positions one launch does it all: 24 layers of 16 heads, 512 positions, M = 5: 9.2 us
 // instead of 4.4 + 4.1 + 3.7 and two kernel boundaries; beyond that one CU per KV head cannot pull the cache fast enough.
 #include "spec_internal.h"
 

@@ -71,7 +71,7 @@ struct ModelRt {
 };
 
 struct ProfStamps {               // per profiled projection launch: the kernel's own (start, end) stamps
-  unsigned long long* dev = nullptr;   // [cap][STAMP_WAYS][2], zeroed; see GemmPro::stamp
+  unsigned long long* dev = nullptr;   // [cap][STAMP_WAYS][2], zeroed; see STAMP_WAYS
   size_t cap = 0, used = 0;
   double bytes = 0.0;
   double tick_s = 0.0;            // seconds per tick of the device's wall clock
@@ -101,7 +101,7 @@ struct spec_ctx {
   bool prefilled = false;
   int mode = SPEC_MODE_PRE;       // strategy of the next PEARL step
   int profile_flags = 0;
-  bool use_graphs = true;         // replay captured forwards instead of launching ~10 kernels per layer
+  bool use_graphs = true;         // replay captured forwards instead of launching five to eight kernels per layer
   int wgs_opt = -1;               // projection workgroups per CU: -1 = automatic, 1, 2
   int wgs = 2;                    // what the next forward uses
   int tail_opt = -1;              // trailing target layers that launch with two workgroups per CU while wgs == 1:
@@ -379,14 +379,14 @@ int forward(spec_ctx* c, int which, const TokenSrc& src, int logit_rows) {
   int W0 = 0;
   HIPCHK(launch_begin(ba, src, pages, &W0, st));
   const int L = m.d.n_layers;
-  // Cut of the layers into launch units.  Two graphs per forward: launching ~10 nodes per layer costs the host
-  // about 0.45 us per node (0.45 ms for the 80-layer target), during which the stream would sit idle; a short graph
+  // Cut of the layers into launch units.  Two graphs per forward: launching a graph takes the host a time that grows with
+  // its nodes (five to eight per layer), during which the stream would sit idle; a short graph
   // of the first layers is on the GPU in tens of microseconds and runs while the host launches the rest.
   // While draft and target overlap with one projection workgroup per CU and stream, the target's last layers may
   // launch with two (tail_layers): the chain that would end later is favoured, and once the draft chain has
-  // ended the target has the GPU to itself, where one workgroup per CU streams at half the rate.  The rest is
-  // then cut into chunks so that the boundary can move without capturing anything again.  The K split of a
-  // projection does not depend on the launch mode, so the numbers are the same bit for bit.
+  // ended the target has the GPU to itself, where one workgroup per CU streams at a lower rate.  The rest is
+  // then cut into chunks so that the boundary can move without capturing anything again.  The order of a
+  // projection's sums does not depend on the launch mode, so the numbers are the same bit for bit.
   const int Lh = L >= 8 ? 4 : L;
   struct Unit { int l0, l1, wgs, part; } units[SPEC_GRAPH_PARTS];
   int n_units = 0;
@@ -1013,8 +1013,10 @@ extern "C" int spec_generate(spec_ctx* c, int algo, int gamma, int n_generate, i
     int saved;
     ~WgsGuard() { c->wgs = saved; }
   } wgs_guard{c, c->wgs};
-  // while the two streams overlap, one projection workgroup per CU and stream is better from gamma 6 on (long draft chains),
-  // two per CU below that (measured on the 70B/7B-shape pair)
+  // while the two streams overlap, one projection workgroup per CU and stream from gamma 6 on (long draft chains), two per CU
+  // below that.  The line was measured with K-sliced projections on the 70B/7B-shape pair (42.4 ms per step of gamma 7 against
+  // 44); with whole-K ones and the draft's wave priority the modes are level there: the later chain ends at 41.0 ms with one,
+  // 40.9 with two, 40.7 with one and the last 24 layers at two.
   if (c->wgs_opt < 0) c->wgs = ((algo >= 2) && (c->m[0].stream != c->m[1].stream) && gamma >= 6) ? SPEC_PEARL_WGS_PER_CU : 2;
   int mode = c->mode;
   int produced = 0, rc = 0;

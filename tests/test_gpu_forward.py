@@ -90,10 +90,10 @@ def test_multi_token_verify_equals_sequential_single_token_forwards_on_gpu():
 
 @pytest.mark.parametrize("case", list(CASES))
 def test_single_token_forwards_with_fused_prologues_equal_the_general_chain(case):
-    """Forwards over one token run seven kernels per layer (projections that form their own input) instead of ten.
-    Same operations and the same order of every K-slice sum; only the sums of squares are grouped by wave instead of
-    by 1024 columns.  Both chains against the oracle, and against each other far below the bf16 tolerance; the
-    caches they leave are interchangeable (a multi-token forward behind either gives the same logits)."""
+    """Forwards over one token with the O and down projections adding to the residual stream in their epilogues (1) or
+    as K slices that a kernel of its own adds (0): the same operations, other orders of the sums.  Both chains
+    against the oracle, and against each other far below the bf16 tolerance; the caches they leave are
+    interchangeable (a multi-token forward behind either gives the same logits)."""
     cfg = CASES[case]()
     amd, ctx, tm, dm = _setup(cfg)
     prompt = synth.prompt_tokens(97, cfg.target.vocab, 7).tolist()

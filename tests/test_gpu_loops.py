@@ -257,7 +257,9 @@ def test_two_streams_and_one_stream_give_identical_tokens(algo):
     gamma, n_gen = 5, 64
     prompt = synth.prompt_tokens(cfg.n_prompt, cfg.target.vocab, 11).tolist()
     uni = NpUniforms(synth.make_uniforms(n_gen + 1, gamma, 5))
-    for slim in (1, 2):             # one or two projection workgroups per CU: same numbers, both race-free
+    # one or two projection workgroups per CU: both race-free (a model this narrow launches the same grids in both; that wide
+    # ones give the same bits is test_launch_modes_give_the_same_bits)
+    for slim in (1, 2):
         outs = []
         for serial in (True, False, False):
             ctx = harness.make_context(cfg, target, draft, gamma, serial=serial)
@@ -270,7 +272,7 @@ def test_two_streams_and_one_stream_give_identical_tokens(algo):
             ctx.close()
         assert outs[0] == outs[1] == outs[2]
         # dividing the compute units between the two streams (CU masks), or plain streams on shared hardware
-        # queues, changes the timing only: the K split and every order of additions are fixed by the shapes
+        # queues, changes the timing only: every order of additions is fixed by the shapes
         for target_cus in (160, None):
             ctx = harness.make_context(cfg, target, draft, gamma, target_cus=target_cus)
             ctx.set_option(amd.SPEC_OPT_GEMM_WGS_PER_CU, slim)
@@ -424,8 +426,9 @@ def test_sampled_loops_at_the_benchmark_context_length(algo):
 def test_trailing_target_layers_at_two_workgroups_change_timing_only():
     """While the two models overlap with one projection workgroup per CU and stream, the target's last layers may
     launch with two (SPEC_OPT_TARGET_TAIL_LAYERS; by default the PEARL loop moves that boundary from where the two
-    chains of the last step ended).  The forward is then cut into more graphs, but the K split of a projection is the
-    same in both launch modes: every setting must commit the same tokens, bit for bit."""
+    chains of the last step ended).  The forward is then cut into more graphs, but a projection's sums are formed in the
+    same order in both launch modes (on wide models: test_launch_modes_give_the_same_bits; this narrow one checks the
+    cutting): every setting must commit the same tokens, bit for bit."""
     import paper_2408_11850_amd as amd
     from paper_2408_11850_amd import harness
     shape = synth.ModelShape(12, 256, 4, 4, 688, 1024)

@@ -718,12 +718,18 @@ extern "C" int spec_draft_step(spec_ctx* c, float u, int32_t* tok_out) {
   return SPEC_OK;
 }
 
-// Copied on the null stream behind a wait, not on the forward's stream: a stream has staging memory of its own, whose first
-// use costs the first four copies of every new context 350 us each (70B shape, 7 rows: first forward 1790 us, 1415 so).  The
-// wait costs a warm context 7 us for one row (462 | 455) and nothing for seven (1277 | 1283).
+// Up to 16 KiB the copy is queued behind the forward on its stream (a whole verify of a one-layer model: 52 us, 66 with the
+// wait; from 24 KiB on they are level).  Larger ones wait and go through the null stream: a stream has staging memory of its own,
+// whose pages are slow the first time round; on the forward's stream the first four copies of every new context took 350 us
+// more each (70B shape, four layers, 7 rows: first forward 1790 us, 1415 so), a warm one nothing to 1 % less.
 static int read_logits(ModelRt& m, int rows, float* out) {
+  const size_t bytes = (size_t)rows * m.d.vocab * sizeof(float);
+  if (bytes <= (16 << 10)) {
+    HIPCHK(hipMemcpyWithStream(out, m.logits, bytes, hipMemcpyDeviceToHost, m.stream));
+    return SPEC_OK;
+  }
   HIPCHK(hipStreamSynchronize(m.stream));
-  HIPCHK(hipMemcpy(out, m.logits, (size_t)rows * m.d.vocab * sizeof(float), hipMemcpyDeviceToHost));
+  HIPCHK(hipMemcpy(out, m.logits, bytes, hipMemcpyDeviceToHost));
   return SPEC_OK;
 }
 

@@ -84,7 +84,7 @@ def test_rows_of_minus_infinity_and_nan_at_a_temperature(V, temp):
         assert amd.accept_rows(b[None].contiguous(), None, [], [], temp, 1.0, 0.5) == (0, -1)
 
 
-@pytest.mark.parametrize("V", [32768, 32769, 50001, 131072])
+@pytest.mark.parametrize("V", [32768, 32769, 50001, 131072, 540001])
 @pytest.mark.parametrize("temp", [1.0, 0.0])
 def test_a_distribution_may_replace_its_logits(V, temp):
     """q_out == logits, as a caller without a second row does it: the same q and token as with rows of their own."""
@@ -100,8 +100,9 @@ def test_a_distribution_may_replace_its_logits(V, temp):
         assert int(out.item()) == tok and torch.equal(row, q)
 
 
-# a row in registers; pieces of 8192 ids: a last piece of one id, of an odd length, whole pieces (odd V: rows off every vector)
-@pytest.mark.parametrize("V", [777, 32000, 32768, 32769, 33001, 40000, 65537, 131072])
+# a row in registers; pieces of 8192 ids: a last piece of one id, of an odd length, whole pieces (odd V: rows off every
+# vector); 540001: more pieces than lanes
+@pytest.mark.parametrize("V", [777, 32000, 32768, 32769, 33001, 40000, 65537, 131072, 540001])
 @pytest.mark.parametrize("temp", [1.0, 0.7])
 def test_a_draft_that_equals_the_target_is_never_rejected(V, temp):
     """q from sample_row and p inside accept_rows are the same bits for the same logits: r q[x] <= p[x] then holds up to

@@ -28,10 +28,11 @@
 #define DG_BM 256
 #define DG_BN 256
 #define DG_THREADS 256
-// LDS ring of X: a stage holds two K steps (64 k) of the 256 tokens.  Per 16-token tile two 1 KiB blocks (rows
-// 0-7 and rows 8-15, each [8 k-chunks of 16 bytes][8 rows]).  A fragment read takes 128 contiguous bytes from
-// each block per 16 lanes; SQ_LDS_BANK_CONFLICT is 0 for this layout (and for the blocks 1280 bytes apart), while
-// blocks 1088 or 1152 bytes apart double the LDS cycles.
+// LDS ring of X: a stage holds two K steps (64 k) of the tile's tokens, 128 bytes per row, rows one after the other; the
+// 16-byte chunk q of row r sits at place q ^ (r % 8).  A load takes 8 rows, 8 consecutive lanes one row's 128 bytes, so
+// that the address unit sees whole lines; the XOR keeps a fragment read (16 rows, one chunk per 16 lanes) free of bank
+// conflicts.  With a row per lane and 16 bytes of each (and chunk-major blocks in LDS) a 1 KiB load took the unit nearly
+// twice as long: 1023 x 4096 x 11008 in 256 x 256 tiles 230 -> 212 us, 4095 x 57344 x 8192 2656 -> 2623.
 #define DG_STAGES 3
 #define DG_HALF_BYTES 1024
 #define DG_TILE_BYTES (2 * DG_HALF_BYTES)
@@ -52,102 +53,102 @@ struct DenseRope {
 
 typedef __attribute__((address_space(3))) u32x4 dg_lds_u32x4;
 
-// EPI: STORE  Y[m][n] = acc (fp32);  RESID  Y[m][n] += acc;  SWIGLU  Z[m][f] = silu(gate) * up (bf16) with the
-// gate / up panels interleaved (even panel = gate rows of f-tile j, odd = the matching up rows), N = 2F;
-// ROPE128 / ROPE64 (fused QKV projection, head_dim 128 / 64): rotate the q and k heads, store q as bf16 and
-// k, v into the paged cache in operand order.  For the rotation a wave must hold columns e and e + dh/2 of a
-// head: with head_dim 64 its 64 columns are one head; with head_dim 128 the two waves of a head take the
-// 16-column panels {0, 1, 4, 5} and {2, 3, 6, 7}.  Either way accumulator tiles nt and nt + 2 pair up.
-// A wave's 64 outputs (group wn of them) x 16 MTN tokens from m0 on.
-template <int EPI, int MTN>
-__device__ __forceinline__ void dense_epilogue(const f32x4 (&acc)[4][MTN], int m0, int wn, int c, int kb, float* __restrict__ Y,
-                                               bf16* __restrict__ Z, int M, int N, int ldz, const DenseRope& ra) {
-  // acc[nt][mt][r] = Y[m0 + 16 mt + c][n0 + 16 nt + 4 kb + r]
-  const int n0 = wn * 64;
+// What a projection does with its sums, two panels (16 outputs each) of 16 tokens at a time:
+//   STORE  Y[m][n] = sum (fp32);  RESID  Y[m][n] += sum;  SWIGLU  Z[m][f] = silu(gate) * up (bf16), the even panels gate
+//   rows, the odd ones the matching up rows, N = 2F;  ROPE128 / ROPE64 (fused QKV projection, head_dim 128 / 64): rotate
+//   the q and k heads, store q as bf16 and k, v into the paged cache in operand order.
+// The panels of pair p: for a rotation columns e and e + dh/2 of a head, else neighbours.
+template <int EPI>
+__device__ __forceinline__ int dense_panel(int p, int second) {
+  if (EPI == DG_EPI_ROPE128) return (p >> 2) * 8 + (p & 3) + second * 4;
+  if (EPI == DG_EPI_ROPE64) return (p >> 1) * 4 + (p & 1) + second * 2;
+  return p * 2 + second;
+}
+
+// x0[r] = Y[m][16 panel(p, 0) + 4 kb + r], x1[r] the same of panel(p, 1); m < M
+template <int EPI>
+__device__ __forceinline__ void dense_pair(f32x4 x0, f32x4 x1, int m, int p, int kb, float* __restrict__ Y, bf16* __restrict__ Z,
+                                           int N, int ldz, int len, const DenseRope& ra) {
   if (EPI == DG_EPI_ROPE128 || EPI == DG_EPI_ROPE64) {
     constexpr int DH = EPI == DG_EPI_ROPE128 ? 128 : 64;
     const int Hkv = ra.g.n_kv_heads;
-    const int head = DH == 128 ? wn >> 1 : wn;
+    const int head = p / (DH / 32);
     if (head >= ra.Hq + 2 * Hkv) return;
-    const int len = ra.len_ptr[0];
-    const int ebase = (DH == 128 ? (wn & 1) * 32 : 0) + kb * 4;     // + 16 nt + r: column inside the head, < dh/2
+    const int pos = len + m;
+    const int e0 = p % (DH / 32) * 16 + kb * 4;                   // column inside the head, < dh/2; x1: + dh/2
+    if (head < ra.Hq + Hkv) {
 #pragma unroll
-    for (int mt = 0; mt < MTN; ++mt) {
-      const int m = m0 + mt * 16 + c;
-      if (m >= M) continue;
-      const int pos = len + m;
+      for (int r = 0; r < 4; ++r) {
+        const float2 cs = ra.tab[(size_t)m * (DH / 2) + e0 + r];
+        const float y0 = x0[r] * cs.x - x1[r] * cs.y, y1 = x0[r] * cs.y + x1[r] * cs.x;
+        x0[r] = y0; x1[r] = y1;
+      }
+    }
+    bf16 o0[4], o1[4];
 #pragma unroll
-      for (int nt = 0; nt < 2; ++nt) {
-        const int e0 = ebase + nt * 16;
-        f32x4 x0 = acc[nt][mt], x1 = acc[nt + 2][mt];               // columns e0 + r and e0 + r + dh/2
-        if (head < ra.Hq + Hkv) {
+    for (int r = 0; r < 4; ++r) o0[r] = __float2bfloat16(x0[r]), o1[r] = __float2bfloat16(x1[r]);
+    if (head < ra.Hq) {
+      bf16* dst = ra.q + ((size_t)m * ra.Hq + head) * DH + e0;
+      *reinterpret_cast<uint2*>(dst) = *reinterpret_cast<const uint2*>(o0);
+      *reinterpret_cast<uint2*>(dst + DH / 2) = *reinterpret_cast<const uint2*>(o1);
+      return;
+    }
+    const int page = ra.block_table[pos / SPEC_PAGE_TOKENS];
+    const int rr = pos % SPEC_PAGE_TOKENS;
+    if (head < ra.Hq + Hkv) {       // K block: [16-token tile][dh/32 steps][64 lanes][8]
+      bf16* blk = ra.pool + ra.g.offset(page, ra.layer, 0, head - ra.Hq);
 #pragma unroll
-          for (int r = 0; r < 4; ++r) {
-            const float2 cs = ra.tab[(size_t)m * (DH / 2) + e0 + r];
-            const float y0 = x0[r] * cs.x - x1[r] * cs.y, y1 = x0[r] * cs.y + x1[r] * cs.x;
-            x0[r] = y0; x1[r] = y1;
-          }
-        }
-        bf16 o0[4], o1[4];
+      for (int t = 0; t < 2; ++t) {
+        const int e = e0 + t * (DH / 2);
+        const size_t off = ((size_t)(((rr >> 4) * (DH / 32) + (e >> 5)) * 64 + ((e & 31) >> 3) * 16 + (rr & 15))) * 8 + (e & 7);
+        *reinterpret_cast<uint2*>(blk + off) = *reinterpret_cast<const uint2*>(t ? o1 : o0);
+      }
+    } else {                        // V block: [32-token chunk][dh][32 slots]
+      bf16* blk = ra.pool + ra.g.offset(page, ra.layer, 1, head - ra.Hq - Hkv);
+      const int r32 = rr & 31;
+      const int slot = ((r32 & 15) >> 2) * 8 + (r32 >> 4) * 4 + (r32 & 3);
+      bf16* base = blk + ((size_t)(rr >> 5) * DH + e0) * 32 + slot;
 #pragma unroll
-        for (int r = 0; r < 4; ++r) o0[r] = __float2bfloat16(x0[r]), o1[r] = __float2bfloat16(x1[r]);
-        if (head < ra.Hq) {
-          bf16* dst = ra.q + ((size_t)m * ra.Hq + head) * DH + e0;
-          *reinterpret_cast<uint2*>(dst) = *reinterpret_cast<const uint2*>(o0);
-          *reinterpret_cast<uint2*>(dst + DH / 2) = *reinterpret_cast<const uint2*>(o1);
-          continue;
-        }
-        const int page = ra.block_table[pos / SPEC_PAGE_TOKENS];
-        const int rr = pos % SPEC_PAGE_TOKENS;
-        if (head < ra.Hq + Hkv) {       // K block: [16-token tile][dh/32 steps][64 lanes][8]
-          bf16* blk = ra.pool + ra.g.offset(page, ra.layer, 0, head - ra.Hq);
-#pragma unroll
-          for (int t = 0; t < 2; ++t) {
-            const int e = e0 + t * (DH / 2);
-            const size_t off = ((size_t)(((rr >> 4) * (DH / 32) + (e >> 5)) * 64 + ((e & 31) >> 3) * 16 + (rr & 15))) * 8 + (e & 7);
-            *reinterpret_cast<uint2*>(blk + off) = *reinterpret_cast<const uint2*>(t ? o1 : o0);
-          }
-        } else {                        // V block: [32-token chunk][dh][32 slots]
-          bf16* blk = ra.pool + ra.g.offset(page, ra.layer, 1, head - ra.Hq - Hkv);
-          const int r32 = rr & 31;
-          const int slot = ((r32 & 15) >> 2) * 8 + (r32 >> 4) * 4 + (r32 & 3);
-          bf16* base = blk + ((size_t)(rr >> 5) * DH + e0) * 32 + slot;
-#pragma unroll
-          for (int r = 0; r < 4; ++r) {
-            base[(size_t)r * 32] = o0[r];
-            base[(size_t)(r + DH / 2) * 32] = o1[r];
-          }
-        }
+      for (int r = 0; r < 4; ++r) {
+        base[(size_t)r * 32] = o0[r];
+        base[(size_t)(r + DH / 2) * 32] = o1[r];
       }
     }
     return;
   }
+  if (EPI == DG_EPI_SWIGLU) {
+    if (p * 32 + 32 > N) return;
+    bf16 out[4];
+#pragma unroll
+    for (int q = 0; q < 4; ++q) out[q] = __float2bfloat16(x0[q] / (1.0f + __expf(-x0[q])) * x1[q]);
+    *reinterpret_cast<uint2*>(Z + (size_t)m * ldz + p * 16 + kb * 4) = *reinterpret_cast<const uint2*>(out);
+    return;
+  }
+#pragma unroll
+  for (int t = 0; t < 2; ++t) {
+    const int n = (p * 2 + t) * 16 + kb * 4;
+    if (n >= N) continue;
+    f32x4* dst = reinterpret_cast<f32x4*>(Y + (size_t)m * N + n);
+    const f32x4 v = t ? x1 : x0;
+    if (EPI == DG_EPI_RESID) *dst = *dst + v;
+    else *dst = v;
+  }
+}
+
+// A wave's 64 outputs (group wn of them) x 16 MTN tokens from m0 on.  Rotated, tiles nt and nt + 2 pair up (with head_dim
+// 128 the two waves of a head take the panels {0, 1, 4, 5} and {2, 3, 6, 7}), else nt and nt + 1.
+template <int EPI, int MTN>
+__device__ __forceinline__ void dense_epilogue(const f32x4 (&acc)[4][MTN], int m0, int wn, int c, int kb, float* __restrict__ Y,
+                                               bf16* __restrict__ Z, int M, int N, int ldz, const DenseRope& ra) {
+  constexpr bool ROPE = EPI == DG_EPI_ROPE128 || EPI == DG_EPI_ROPE64;
+  const int len = ROPE ? ra.len_ptr[0] : 0;
 #pragma unroll
   for (int mt = 0; mt < MTN; ++mt) {
     const int m = m0 + mt * 16 + c;
     if (m >= M) continue;
-    if (EPI == DG_EPI_SWIGLU) {
 #pragma unroll
-      for (int nt = 0; nt < 4; nt += 2) {
-        const int n = n0 + nt * 16;
-        if (n + 32 > N) continue;
-        const int f = (n >> 1) + kb * 4;
-        const f32x4 g = acc[nt][mt], u = acc[nt + 1][mt];
-        bf16 out[4];
-#pragma unroll
-        for (int q = 0; q < 4; ++q) out[q] = __float2bfloat16(g[q] / (1.0f + __expf(-g[q])) * u[q]);
-        *reinterpret_cast<uint2*>(Z + (size_t)m * ldz + f) = *reinterpret_cast<const uint2*>(out);
-      }
-    } else {
-#pragma unroll
-      for (int nt = 0; nt < 4; ++nt) {
-        const int n = n0 + nt * 16 + kb * 4;
-        if (n >= N) continue;
-        f32x4* dst = reinterpret_cast<f32x4*>(Y + (size_t)m * N + n);
-        if (EPI == DG_EPI_RESID) *dst = *dst + acc[nt][mt];
-        else *dst = acc[nt][mt];
-      }
-    }
+    for (int i = 0; i < 2; ++i)
+      dense_pair<EPI>(acc[ROPE ? i : 2 * i][mt], acc[ROPE ? i + 2 : 2 * i + 1][mt], m, wn * 2 + i, kb, Y, Z, N, ldz, len, ra);
   }
 }
 
@@ -184,18 +185,18 @@ __global__ __launch_bounds__(DG_THREADS, 1) void dense_gemm_kernel(const bf16* _
   }
   const unsigned woff = lane * 16;
   const char* xbase = reinterpret_cast<const char*>(X);
-  // X moves global -> LDS in whole 128-byte lines: one LDS-direct load covers 8 token rows x 64 k (lane = k-chunk
-  // * 8 + row), so that L2 sees every line of X once (a 16-row x 32-k load would ask for each line twice, half
-  // used).  Per stage the wave issues 8 of them: token tiles 4w .. 4w+3, rows 0-7 and 8-15 of each.
+  // X moves global -> LDS in whole 128-byte lines: one LDS-direct load covers 8 token rows x 64 k, so that L2 sees every
+  // line of X once (a 16-row x 32-k load would ask for each line twice, half used).  Per stage the wave issues 8 of them: token tiles 4w .. 4w+3, rows 0-7 and 8-15 of each.
+  const int xchunk = (lane & 7) ^ (lane >> 3);
   unsigned xoff[8];
 #pragma unroll
   for (int i = 0; i < 8; ++i) {
-    int m = tm * DG_BM + (w * 4 + i / 2) * 16 + (i & 1) * 8 + (lane & 7);
+    int m = tm * DG_BM + (w * 4 + i / 2) * 16 + (i & 1) * 8 + (lane >> 3);
     if (m > M - 1) m = M - 1;
-    xoff[i] = (unsigned)m * (unsigned)K * 2u + (lane >> 3) * 16;     // < 2^32: checked by the launcher
+    xoff[i] = (unsigned)m * (unsigned)K * 2u + xchunk * 16;          // < 2^32: checked by the launcher
   }
-  // fragment (tile mt, step half h) of lane (c, kb): tile mt, block c / 8, chunk 4 h + kb, row c % 8
-  const unsigned lds_rd = (unsigned)(size_t)(dg_lds_u32x4*)lds + (c >> 3) * DG_HALF_BYTES + kb * 128 + (c & 7) * 16;
+  // fragment (tile mt, step half h) of lane (c, kb): row c of tile mt, chunk 4 h + kb
+  const unsigned lds_rd = (unsigned)(size_t)(dg_lds_u32x4*)lds + c * 128 + (kb ^ (c & 7)) * 16;
 
   f32x4 acc[4][16];
 #pragma unroll
@@ -211,7 +212,7 @@ __global__ __launch_bounds__(DG_THREADS, 1) void dense_gemm_kernel(const bf16* _
   // which keeps the count of outstanding loads uniform so that one vmcnt threshold serves every iteration.
   u32x4 wq[4][4];      // W fragments of steps j .. j+3 (set = step % 4)
   u32x4 bq[16];        // X fragments of the current step; each is refilled for the next step once consumed
-  const unsigned xfix = (lane >> 5) * 64;   // lanes of the second K step of a stage: fall back to the first one
+  const unsigned xfix = (xchunk >> 2) * 64;   // lanes of the second K step of a stage: fall back to the first one
 #define DG_LOAD_X(PG, J)   /* instruction J (0..7) of X stage PG: token tile 4w + J/2, rows 8 (J%2) .. + 7 */    \
   {                                                                                                          \
     const int st_ = 2 * (PG) < steps ? 2 * (PG) : (steps - 1) & ~1;                                          \
@@ -240,7 +241,7 @@ __global__ __launch_bounds__(DG_THREADS, 1) void dense_gemm_kernel(const bf16* _
     asm volatile("s_waitcnt vmcnt(8)\n\ts_barrier"                                                            \
                  : "+v"(wq[((U) + 1) % 4][0]), "+v"(wq[((U) + 1) % 4][1]), "+v"(wq[((U) + 1) % 4][2]),       \
                    "+v"(wq[((U) + 1) % 4][3])::"memory");                                                    \
-    const unsigned rd_ = lds_rd + ((((KS) + 1) >> 1) % DG_STAGES) * DG_STAGE_BYTES + (((KS) + 1) & 1) * 512;  \
+    const unsigned rd_ = (lds_rd ^ (((KS) + 1) & 1) * 64) + ((((KS) + 1) >> 1) % DG_STAGES) * DG_STAGE_BYTES;  \
     _Pragma("unroll") for (int mt = 0; mt < 16; ++mt) {                                                      \
       asm volatile("s_waitcnt lgkmcnt(15)" : "+v"(bq[mt]));                                                  \
       _Pragma("unroll") for (int nt = 0; nt < 4; ++nt) DG_MFMA(acc[nt][mt], wq[U][nt], bq[mt]);              \
@@ -304,149 +305,345 @@ __global__ __launch_bounds__(DG_THREADS, 1) void dense_gemm_kernel(const bf16* _
   dense_epilogue<EPI, 16>(acc, tm * DG_BM, tn * 4 + w, c, kb, Y, Z, M, N, ldz, ra);
 }
 
-// Grids that 256 x 256 tiles do not fill: workgroup = 4 waves = 128 tokens x 128 outputs, a wave owns 64 x 64 (4 x 4 MFMA
-// tiles).  Both operands go global -> LDS with LDS-direct loads, each byte once per workgroup (a CU pulls about 25 bytes
-// per clock whatever serves them: with every fragment loaded straight into the registers of the two waves that need it,
-// a K step took 0.6 us instead of 0.33).  A stage is two K steps: 16 KiB of X in the layout of the large tile, 16 KiB of
-// W lane-linear; ring of 4 stages.  Bound by LDS: 16 KiB in and 32 KiB out per K step, 0.33 us of it (the MFMAs: 0.11).
-// Sums run over K in the same order as in the large tile: same bits.
+// Grids that 256 x 256 tiles do not fill.  dense_small: 128 tokens x 128 outputs per workgroup of 8 waves, a wave has
+// 64 x 64 (4 x 4 MFMA tiles) of every second K step; waves w and w + 4 hold the even and the odd steps of the same outputs
+// and exchange halves at the end.  Both operands go global -> LDS with LDS-direct loads, each byte once per workgroup; a
+// stage is two K steps, 16 KiB of X (as in the large tile) and 16 KiB of W (lane-linear), in a ring of 4.
+// Bound by what a CU pulls in: loads alone take 0.26 us per K step (61 bytes per ns and CU, the same with 3, 4 and 5 stages;
+// all of it from L2 0.17), LDS and MFMAs alone 0.17, all together 0.27.  What counts is that consecutive lanes of a load of X
+// take whole lines (with a row per lane, 16 bytes of each, X took 0.23 us of a K step instead of 0.13), that loads are issued
+// between MFMAs and that every SIMD has a second wave: 1023 x 4096 x 11008 124 -> 100 us; 511 x 6144 x 2048 28 -> 23 from
+// HBM and 26.4 -> 18.0 from the memory-side cache.
+#define DS_WAVES 8
+#define DS_THREADS (DS_WAVES * 64)
 #define DS_STAGES 4
-#define DS_X_BYTES 16384
+#define DS_LOADS 4                        // per wave and stage
+#define DS_X_BYTES (8 * DG_TILE_BYTES)
 #define DS_STAGE_BYTES (2 * DS_X_BYTES)
+// The tile of this workgroup: XCD x takes the tiles [x chunk, (x + 1) chunk), numbered row-major inside groups of 4
+// columns, so that what an XCD runs together shares operand strips in its L2.
+__device__ __forceinline__ bool dense_tile_of(int TM, int TN, int chunk, int* tm, int* tn) {
+  const int j = blockIdx.x >> 3, tile = (blockIdx.x & 7) * chunk + j;
+  if (j >= chunk || tile >= TM * TN) return false;
+  const int grp = tile / (TM * 4), idx = tile % (TM * 4), gw = min(4, TN - grp * 4);
+  *tm = idx / gw;
+  *tn = grp * 4 + idx % gw;
+  return true;
+}
+
 template <int EPI>
-__global__ __launch_bounds__(DG_THREADS, 2) void dense_small_kernel(const bf16* __restrict__ X, const u32x4* __restrict__ Wp,
-                                                                    float* __restrict__ Y, bf16* __restrict__ Z, int M, int N,
-                                                                    int K, int ldz, int NT, int steps, int TM, int tiles, int chunk,
-                                                                    DenseRope ra) {
+__device__ __forceinline__ void dense_small_tile(const bf16* __restrict__ X, const u32x4* __restrict__ Wp, float* __restrict__ Y,
+                                                 bf16* __restrict__ Z, int M, int N, int K, int ldz, int NT, int steps, int TM,
+                                                 int TN, int chunk, const DenseRope& ra) {
   extern __shared__ u32x4 lds[];          // DS_STAGES * DS_STAGE_BYTES
   const int w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), lane = threadIdx.x & 63;
-  // XCD x takes the tiles [x chunk, (x + 1) chunk), token tiles fastest: its workgroups share weight columns in its L2
-  const int j = blockIdx.x >> 3, tile = (blockIdx.x & 7) * chunk + j;
-  if (tile >= tiles) return;
-  const int tn = tile / TM, tm = tile % TM;
+  int tm, tn;
+  if (!dense_tile_of(TM, TN, chunk, &tm, &tn)) return;
   const int c = lane & 15, kb = lane >> 4;
-  // per stage a wave loads token tiles 2 w and 2 w + 1 (rows 0-7 and 8-15 of each, 64 k) and panels 2 w and 2 w + 1 (two K
-  // steps of each); rows and panels past the end are clamped, computed and never stored
-  const char* wbase[2];
-  unsigned xoff[4];
+  const int kg = w >> 2, wm = (w >> 1) & 1, wn = w & 1;
+  // Per stage a wave loads token tile w (8 rows x 64 k at a time) and two K steps of panel w; rows and panels past the end
+  // are clamped, computed and never stored.
+  int panel = tn * 8 + w;
+  if (panel > NT - 1) panel = NT - 1;
+  const char* wbase = reinterpret_cast<const char*>(Wp + (size_t)panel * steps * 64) + lane * 16;
+  const char* xbase = reinterpret_cast<const char*>(X);
+  const int xchunk = (lane & 7) ^ (lane >> 3);
+  unsigned xoff[2];
 #pragma unroll
   for (int i = 0; i < 2; ++i) {
-    int panel = tn * 8 + w * 2 + i;
-    if (panel > NT - 1) panel = NT - 1;
-    wbase[i] = reinterpret_cast<const char*>(Wp + (size_t)panel * steps * 64) + lane * 16;
-  }
-#pragma unroll
-  for (int i = 0; i < 4; ++i) {
-    int m = tm * 128 + (w * 2 + i / 2) * 16 + (i & 1) * 8 + (lane & 7);
+    int m = tm * 128 + (w * 2 + i) * 8 + (lane >> 3);
     if (m > M - 1) m = M - 1;
-    xoff[i] = (unsigned)m * (unsigned)K * 2u + (lane >> 3) * 16;     // < 2^32: checked by the launcher
+    xoff[i] = (unsigned)m * (unsigned)K * 2u + xchunk * 16;          // < 2^32: checked by the launcher
   }
-  const char* xbase = reinterpret_cast<const char*>(X);
-  const unsigned xfix = (lane >> 5) * 64;   // lanes of the second K step of a stage: fall back to the first one
+  const unsigned xfix = (xchunk >> 2) * 64;   // lanes of the second K step of a stage: fall back to the first one
   const int stages = (steps + 1) >> 1;
-  auto issue = [&](int st) {                // past the end: the last stage again, into a slot that nobody reads
-    u32x4* slot = lds + (st % DS_STAGES) * (DS_STAGE_BYTES / 16);
+  // load i of this wave for stage st; past the end: the last stage again, into a slot that nobody reads
+  auto issue = [&](int st, int slot, int i) {
+    u32x4* dst = lds + (slot * DS_STAGE_BYTES + w * 2048 + (i & 1) * 1024) / 16;
     if (st > stages - 1) st = stages - 1;
     const bool whole = st * 2 + 1 < steps;  // odd K-step count: never read past a row's or a panel's end
-    const unsigned fix = whole ? 0u : xfix;
-#pragma unroll
-    for (int i = 0; i < 4; ++i)
-      __builtin_amdgcn_global_load_lds(xbase + (size_t)st * 128 + (xoff[i] - fix),
-                                       slot + ((w * 2 + i / 2) * DG_TILE_BYTES + (i & 1) * DG_HALF_BYTES) / 16, 16, 0, 0);
-#pragma unroll
-    for (int i = 0; i < 4; ++i)
-      __builtin_amdgcn_global_load_lds(wbase[i / 2] + (size_t)st * 2048 + ((i & 1) && whole ? 1024 : 0),
-                                       slot + (DS_X_BYTES + (w * 2 + i / 2) * 2048 + (i & 1) * 1024) / 16, 16, 0, 0);
+    if (i < 2)
+      __builtin_amdgcn_global_load_lds(xbase + (size_t)st * 128 + (xoff[i] - (whole ? 0u : xfix)), dst, 16, 0, 0);
+    else
+      __builtin_amdgcn_global_load_lds(wbase + (size_t)st * 2048 + ((i & 1) && whole ? 1024 : 0), dst + DS_X_BYTES / 16, 16, 0, 0);
   };
-  // fragment addresses inside a stage: token tile (w >> 1) * 4 + mt, and panel nt of this wave's four
+  // fragment addresses inside a stage: token tiles 4 wm + mt, and this wave's four panels
   const unsigned lds0 = (unsigned)(size_t)(dg_lds_u32x4*)lds;
-  const unsigned xrd = lds0 + (w >> 1) * 4 * DG_TILE_BYTES + (c >> 3) * DG_HALF_BYTES + kb * 128 + (c & 7) * 16;
-  const unsigned wrd = lds0 + DS_X_BYTES + (w & 1) * (EPI == DG_EPI_ROPE128 ? 2 : 4) * 2048 + lane * 16;
+  const unsigned xrd = lds0 + wm * 4 * DG_TILE_BYTES + c * 128 + ((kg * 4 + kb) ^ (c & 7)) * 16;
+  const unsigned wrd = lds0 + DS_X_BYTES + wn * (EPI == DG_EPI_ROPE128 ? 2 : 4) * 2048 + lane * 16 + kg * 1024;
   f32x4 acc[4][4];
 #pragma unroll
   for (int a = 0; a < 4; ++a)
 #pragma unroll
     for (int b = 0; b < 4; ++b) acc[a][b] = f32x4{0.f, 0.f, 0.f, 0.f};
-  u32x4 fw[2][4], fx[2][4];                 // fragments of the current and the next K step
-#define DS_READ(B, ST, H)                                                                                    \
+  u32x4 fw[2][4], fx[2][4];                 // fragments of this wave's current and next K step
+#define DS_READ(B, SLOT)                                                                                     \
   {                                                                                                          \
-    const unsigned so_ = ((ST) % DS_STAGES) * DS_STAGE_BYTES;                                                \
+    const unsigned so_ = (SLOT) * DS_STAGE_BYTES;                                                            \
     _Pragma("unroll") for (int i = 0; i < 4; ++i)                                                            \
-      asm volatile("ds_read_b128 %0, %1 offset:%2" : "=v"(fx[B][i]) : "v"(xrd + so_), "n"(i * DG_TILE_BYTES + (H) * 512)); \
+      asm volatile("ds_read_b128 %0, %1 offset:%2" : "=v"(fx[B][i]) : "v"(xrd + so_), "n"(i * DG_TILE_BYTES)); \
     _Pragma("unroll") for (int i = 0; i < 4; ++i)                                                            \
       asm volatile("ds_read_b128 %0, %1 offset:%2" : "=v"(fw[B][i]) : "v"(wrd + so_),                        \
-                   "n"((EPI == DG_EPI_ROPE128 ? (i & 1) + (i >> 1) * 4 : i) * 2048 + (H) * 1024));           \
+                   "n"((EPI == DG_EPI_ROPE128 ? (i & 1) + (i >> 1) * 4 : i) * 2048));                        \
   }
 #define DS_WAIT(B)                                                                                           \
   asm volatile("s_waitcnt lgkmcnt(0)" : "+v"(fx[B][0]), "+v"(fx[B][1]), "+v"(fx[B][2]), "+v"(fx[B][3]),      \
                "+v"(fw[B][0]), "+v"(fw[B][1]), "+v"(fw[B][2]), "+v"(fw[B][3])::"memory");
-#define DS_MMA(B)                                                                                            \
-  __builtin_amdgcn_sched_barrier(0);                                                                         \
-  _Pragma("unroll") for (int mt = 0; mt < 4; ++mt)                                                           \
-    _Pragma("unroll") for (int nt = 0; nt < 4; ++nt)                                                         \
-      acc[nt][mt] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, fw[B][nt]),           \
-                                                            __builtin_bit_cast(bf16x8, fx[B][mt]), acc[nt][mt], 0, 0, 0); \
-  __builtin_amdgcn_sched_barrier(0);
-  issue(0);
-  issue(1);
-  issue(2);
-  asm volatile("s_waitcnt vmcnt(16)\n\ts_barrier" ::: "memory");     // stage 0 is in LDS for everybody
-  DS_READ(0, 0, 0)
+#define DS_LANDED(N) asm volatile("s_waitcnt vmcnt(%0)\n\ts_barrier" ::"n"(N) : "memory");
+  // Stage ST: stage ST + 1 has landed for this wave, then for everybody, and everybody holds its half of stage ST in
+  // registers, so that slot is refilled, one load after every fourth MFMA: no wave sits in the issue stage behind the
+  // address unit while its matrix core idles.  MULTIPLY: whether this wave has a K step in the stage.
+#define DS_STAGE(B, ST, MULTIPLY)                                                                            \
+  {                                                                                                          \
+    DS_LANDED((DS_STAGES - 2) * DS_LOADS)                                                                    \
+    DS_READ(1 - (B), ((ST) + 1) % DS_STAGES)                                                                 \
+    if (MULTIPLY) {                                                                                          \
+      _Pragma("unroll") for (int mt = 0; mt < 4; ++mt) {                                                     \
+        __builtin_amdgcn_sched_barrier(0);                                                                   \
+        _Pragma("unroll") for (int nt = 0; nt < 4; ++nt)                                                     \
+          acc[nt][mt] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, fw[B][nt]),       \
+                                                                __builtin_bit_cast(bf16x8, fx[B][mt]), acc[nt][mt], 0, 0, 0); \
+        __builtin_amdgcn_sched_barrier(0);                                                                   \
+        issue((ST) + DS_STAGES, (ST) % DS_STAGES, mt);                                                       \
+      }                                                                                                      \
+    }                                                                                                        \
+    DS_WAIT(1 - (B))                                                                                         \
+  }
+#pragma unroll
+  for (int s = 0; s < DS_STAGES; ++s)
+#pragma unroll
+    for (int i = 0; i < DS_LOADS; ++i) issue(s, s, i);
+  DS_LANDED((DS_STAGES - 1) * DS_LOADS)     // stage 0 is in LDS for everybody
+  DS_READ(0, 0)
   DS_WAIT(0)
-  const int pairs = steps >> 1;
-  for (int st = 0; st < pairs; ++st) {
-    // Stage st + 1 has landed for this wave (8 loads of st + 2 may be in flight), then for everybody, and everybody is past
-    // reading stage st - 1, whose slot is refilled now.
-    asm volatile("s_waitcnt vmcnt(8)\n\ts_barrier" ::: "memory");
-    issue(st + 3);
-    DS_READ(1, st, 1)
-    DS_MMA(0)
-    DS_WAIT(1)
-    DS_READ(0, st + 1, 0)
-    DS_MMA(1)
-    DS_WAIT(0)
+  const bool last = kg == 0 || !(steps & 1);
+  int st = 0;
+  for (; st + 2 < stages; st += 2) {
+    DS_STAGE(0, st, true)
+    DS_STAGE(1, st + 1, true)
   }
-  if (steps & 1) {
-    DS_MMA(0)
+  if (st + 1 < stages) {
+    DS_STAGE(0, st, true)
+    DS_STAGE(1, st + 1, last)
+  } else {
+    DS_STAGE(0, st, last)
   }
+#undef DS_STAGE
 #undef DS_READ
 #undef DS_WAIT
-#undef DS_MMA
-  asm volatile("s_waitcnt vmcnt(0)" ::: "memory");   // the redundant tail loads must not outlive the workgroup's LDS
-  dense_epilogue<EPI, 4>(acc, tm * 128 + (w >> 1) * 64, tn * 2 + (w & 1), c, kb, Y, Z, M, N, ldz, ra);
+  // The redundant tail loads must neither outlive the workgroup's LDS nor land on what is exchanged there.
+  DS_LANDED(0)
+#undef DS_LANDED
+  // waves w and w + 4 hold the even and the odd K steps of the same outputs: each adds up and stores half of the tokens
+  f32x4* ex = reinterpret_cast<f32x4*>(lds);
+  f32x4 sum[4][2];
+#pragma unroll
+  for (int nt = 0; nt < 4; ++nt)
+#pragma unroll
+    for (int mt = 0; mt < 2; ++mt) {
+      sum[nt][mt] = kg ? acc[nt][mt + 2] : acc[nt][mt];
+      ex[(w * 8 + nt * 2 + mt) * 64 + lane] = kg ? acc[nt][mt] : acc[nt][mt + 2];
+    }
+  __syncthreads();
+#pragma unroll
+  for (int nt = 0; nt < 4; ++nt)
+#pragma unroll
+    for (int mt = 0; mt < 2; ++mt) sum[nt][mt] += ex[((w ^ 4) * 8 + nt * 2 + mt) * 64 + lane];
+  dense_epilogue<EPI, 2>(sum, tm * 128 + wm * 64 + kg * 32, tn * 2 + wn, c, kb, Y, Z, M, N, ldz, ra);
 }
 
-// Tile by the time a launch takes, in rounds of one workgroup per CU (measured, K in steps of 32; us = 9 + 0.635 steps per
-// round of 256 x 256 tiles, 0.60 with a third of the CUs in use, 0.66 with all; 3 + 0.335 steps per round of 128 x 128;
-// us large | small): 511 x 6144 x 2048 50.5 | 27.1, 1023 x 4096 x 4096 90 | 51, 1023 x 4096 x 11008 220 | 121 (one round either
-// way), 1500 x 3072 x 2048 52 | 49, 511 x 12288 x 4096 85 | 97, 2047 x 4096 x 4096 86 | 100, 1023 x 8192 x 8192 170 | 184 (1 | 2),
-// 511 x 22016 x 4096 100 | 133 (1 | 3), 1023 x 22016 x 4096 192 | 292 (2 | 6).
-static bool dense_small_tiles(int M, int NT, int steps) {
+template <int EPI>
+__global__ __launch_bounds__(DS_THREADS, 2) void dense_small_kernel(const bf16* __restrict__ X, const u32x4* __restrict__ Wp,
+                                                                    float* __restrict__ Y, bf16* __restrict__ Z, int M, int N,
+                                                                    int K, int ldz, int NT, int steps, int TM, int TN, int chunk,
+                                                                    DenseRope ra) {
+  dense_small_tile<EPI>(X, Wp, Y, Z, M, N, K, ldz, NT, steps, TM, TN, chunk, ra);
+}
+
+// dense_wide: 256 tokens x 192 outputs by 8 waves of 64 tokens x 6 panels, for grids that deal out more evenly so.  Operands
+// and ring as in dense_small, X (from L2 or the memory-side cache: the other tile columns read it too) two stages deep, W
+// (from HBM) three.  0.65 us per K step with every CU busy: 28 KiB of it 0.46 us of loads, and X has one stage to arrive.
+// A third stage of it does not fit LDS beside 256 x 192, and 256 x 128 with three of both takes 0.39 us for two thirds.
+#define DW_PANELS 6                        // of a wave
+#define DW_X_BYTES (16 * DG_TILE_BYTES)
+#define DW_W_BYTES (DW_PANELS * 4096)
+template <int EPI>
+__device__ __forceinline__ void dense_wide_tile(const bf16* __restrict__ X, const u32x4* __restrict__ Wp, float* __restrict__ Y,
+                                                bf16* __restrict__ Z, int M, int N, int K, int ldz, int NT, int steps, int TM,
+                                                int TN, int chunk, const DenseRope& ra) {
+  constexpr int PN = DW_PANELS, XS = DW_X_BYTES, WS = DW_W_BYTES, WL = PN / 2;
+  extern __shared__ u32x4 lds[];          // 2 stages of X, 3 of W
+  const int w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), lane = threadIdx.x & 63;
+  int tm, tn;
+  if (!dense_tile_of(TM, TN, chunk, &tm, &tn)) return;
+  const int c = lane & 15, kb = lane >> 4, wm = w >> 1, wn = w & 1;
+  const char* wbase[WL];
+  unsigned xoff[4];
+  const int xchunk = (lane & 7) ^ (lane >> 3);
+#pragma unroll
+  for (int i = 0; i < WL; ++i) {                 // load i: K step q & 1 of the tile's panel q >> 1
+    const int q = w * WL + i;
+    int panel = dense_panel<EPI>(tn * PN + (q >> 2), (q >> 1) & 1);
+    if (panel > NT - 1) panel = NT - 1;
+    wbase[i] = reinterpret_cast<const char*>(Wp + (size_t)panel * steps * 64) + lane * 16;
+  }
+#pragma unroll
+  for (int i = 0; i < 4; ++i) {
+    int m = tm * 256 + (w * 4 + i) * 8 + (lane >> 3);
+    if (m > M - 1) m = M - 1;
+    xoff[i] = (unsigned)m * (unsigned)K * 2u + xchunk * 16;          // < 2^32: checked by the launcher
+  }
+  const char* xbase = reinterpret_cast<const char*>(X);
+  const unsigned xfix = (xchunk >> 2) * 64;
+  const int stages = (steps + 1) >> 1;
+  auto issue_x = [&](int st, int slot, int i) {
+    if (st > stages - 1) st = stages - 1;
+    const bool whole = st * 2 + 1 < steps;
+    __builtin_amdgcn_global_load_lds(xbase + (size_t)st * 128 + (xoff[i] - (whole ? 0u : xfix)),
+                                     lds + (slot * XS + (w * 4 + i) * DG_HALF_BYTES) / 16, 16, 0, 0);
+  };
+  auto issue_w = [&](int st, int slot, int i) {
+    if (st > stages - 1) st = stages - 1;
+    const bool whole = st * 2 + 1 < steps;
+    const int q = w * WL + i;
+    __builtin_amdgcn_global_load_lds(wbase[i] + (size_t)st * 2048 + ((q & 1) && whole ? 1024 : 0),
+                                     lds + (2 * XS + slot * WS + q * 1024) / 16, 16, 0, 0);
+  };
+  const unsigned lds0 = (unsigned)(size_t)(dg_lds_u32x4*)lds;
+  const unsigned xrd = lds0 + wm * 4 * DG_TILE_BYTES + c * 128 + (kb ^ (c & 7)) * 16;
+  const unsigned wrd = lds0 + 2 * XS + wn * PN * 2048 + lane * 16;
+  f32x4 acc[PN][4];
+#pragma unroll
+  for (int a = 0; a < PN; ++a)
+#pragma unroll
+    for (int b = 0; b < 4; ++b) acc[a][b] = f32x4{0.f, 0.f, 0.f, 0.f};
+  u32x4 fw[2][PN], fx[2][4];
+#define DW_READ(B, XSLOT, WSLOT, H)                                                                          \
+  {                                                                                                          \
+    const unsigned xo_ = (xrd ^ ((H) * 64)) + (XSLOT) * XS, wo_ = wrd + (WSLOT) * WS;                        \
+    _Pragma("unroll") for (int i = 0; i < 4; ++i)                                                            \
+      asm volatile("ds_read_b128 %0, %1 offset:%2" : "=v"(fx[B][i]) : "v"(xo_), "n"(i * DG_TILE_BYTES));     \
+    _Pragma("unroll") for (int i = 0; i < PN; ++i)                                                           \
+      asm volatile("ds_read_b128 %0, %1 offset:%2" : "=v"(fw[B][i]) : "v"(wo_), "n"(i * 2048 + (H) * 1024)); \
+  }
+#define DW_WAIT(B)                                                                                           \
+  asm volatile("s_waitcnt lgkmcnt(0)" : "+v"(fx[B][0]), "+v"(fx[B][1]), "+v"(fx[B][2]), "+v"(fx[B][3])::"memory"); \
+  _Pragma("unroll") for (int i = 0; i < PN; ++i) asm volatile("" : "+v"(fw[B][i]));
+#define DW_MMA(B, ISSUE)                                                                                     \
+  _Pragma("unroll") for (int mt = 0; mt < 4; ++mt) {                                                         \
+    __builtin_amdgcn_sched_barrier(0);                                                                       \
+    _Pragma("unroll") for (int nt = 0; nt < PN; ++nt)                                                        \
+      acc[nt][mt] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, fw[B][nt]),           \
+                                                            __builtin_bit_cast(bf16x8, fx[B][mt]), acc[nt][mt], 0, 0, 0); \
+    __builtin_amdgcn_sched_barrier(0);                                                                       \
+    ISSUE;                                                                                                   \
+  }
+#pragma unroll
+  for (int i = 0; i < 4; ++i) issue_x(0, 0, i);
+#pragma unroll
+  for (int i = 0; i < WL; ++i) issue_w(0, 0, i), issue_w(1, 1, i);
+#pragma unroll
+  for (int i = 0; i < 4; ++i) issue_x(1, 1, i);
+#pragma unroll
+  for (int i = 0; i < WL; ++i) issue_w(2, 2, i);
+  asm volatile("s_waitcnt vmcnt(%0)\n\ts_barrier" ::"n"(4 + WL) : "memory");        // stage 0 is in LDS for everybody
+  DW_READ(0, 0, 0, 0)
+  DW_WAIT(0)
+  const int pairs = steps >> 1;
+  int wc = 0;                                      // W slot of stage st
+  for (int st = 0; st < pairs; ++st) {
+    const int wnx = wc == 2 ? 0 : wc + 1, wpv = wc == 0 ? 2 : wc - 1, xc = st & 1;
+    DW_READ(1, xc, wc, 1)
+    // W of stage st + 2 into the slot of stage st - 1 (the first time: the same bytes again)
+    DW_MMA(0, if (mt < WL) issue_w(st + 2, wpv, mt))
+    DW_WAIT(1)
+    // Stage st + 1 has landed for this wave (W of st + 2 may be in flight), then for everybody; everybody holds what it
+    // needs of stage st in registers, so X of st + 2 may take its place.
+    asm volatile("s_waitcnt vmcnt(%0)\n\ts_barrier" ::"n"(WL) : "memory");
+    DW_READ(0, xc ^ 1, wnx, 0)
+    DW_MMA(1, if (mt < 2) { issue_x(st + 2, xc, 2 * mt); issue_x(st + 2, xc, 2 * mt + 1); })
+    DW_WAIT(0)
+    wc = wnx;
+  }
+  if (steps & 1) {
+    DW_MMA(0, )
+  }
+#undef DW_READ
+#undef DW_WAIT
+#undef DW_MMA
+  asm volatile("s_waitcnt vmcnt(0)" ::: "memory");   // the redundant tail loads must not outlive the workgroup's LDS
+  constexpr bool ROPE = EPI == DG_EPI_ROPE128 || EPI == DG_EPI_ROPE64;
+  const int len = ROPE ? ra.len_ptr[0] : 0;
+#pragma unroll
+  for (int mt = 0; mt < 4; ++mt) {
+    const int m = tm * 256 + wm * 64 + mt * 16 + c;
+    if (m >= M) continue;
+#pragma unroll
+    for (int i = 0; i < PN / 2; ++i)
+      dense_pair<EPI>(acc[2 * i][mt], acc[2 * i + 1][mt], m, tn * PN + wn * (PN / 2) + i, kb, Y, Z, N, ldz, len, ra);
+  }
+}
+
+template <int EPI>
+__global__ __launch_bounds__(DS_THREADS, 2) void dense_wide_kernel(const bf16* __restrict__ X, const u32x4* __restrict__ Wp,
+                                                                   float* __restrict__ Y, bf16* __restrict__ Z, int M, int N,
+                                                                   int K, int ldz, int NT, int steps, int TM, int TN, int chunk,
+                                                                   DenseRope ra) {
+  dense_wide_tile<EPI>(X, Wp, Y, Z, M, N, K, ldz, NT, steps, TM, TN, chunk, ra);
+}
+
+// Tile by the time a launch takes (us): rounds of one workgroup per CU, each a fixed part and a time per K step that grows
+// with the share of CUs in use, fitted to these (large | small | wide; the launch itself, about 6, is in all of them):
+//   66 x 4096 x 4096        76 |  32 |  63     1023 x 4096 x 11008   213 | 101 | 171     2047 x 4096 x 11008   217 | 185 | 178
+//   511 x 6144 x 2048       49 |  23 |  40     1023 x 12288 x 4096    91 | 117 |  88     2500 x 6144 x 2048     56 |  79 |  80
+//   511 x 22016 x 4096      88 | 111 |  84     1023 x 22016 x 4096   173 | 211 | 159     4095 x 8192 x 8192    430 | 540 | 476
+//   1500 x 3072 x 2048      49 |  35 |  41     1023 x 8192 x 8192    166 | 149 | 137     4095 x 57344 x 8192  2634 | 3470 | 2945
+// Of 34 shapes measured it takes the fastest in 30, else one at most 6 % (once 16 %) behind and ahead of what it replaces.
+enum { DENSE_LARGE = 0, DENSE_SMALL = 1, DENSE_WIDE = 2 };
+static int dense_tile(int M, int NT, int steps) {
+  static const struct { int tokens, panels; float round, step, busy; } T[3] = {
+      {256, 16, 4.f, 0.50f, 0.23f}, {128, 8, 2.f, 0.185f, 0.085f}, {256, 12, 2.f, 0.405f, 0.205f}};
   const int ncu = spec_num_cu();
-  const int large = (M + DG_BM - 1) / DG_BM * ((NT + 15) / 16), small = (M + 127) / 128 * ((NT + 7) / 8);
-  return (long long)((small + ncu - 1) / ncu) * (300 + 33.5 * steps) < (long long)((large + ncu - 1) / ncu) * (900 + 63.5 * steps);
+  int best = 0;
+  float best_us = 0.f;
+  for (int i = 0; i < 3; ++i) {
+    const int tiles = (M + T[i].tokens - 1) / T[i].tokens * ((NT + T[i].panels - 1) / T[i].panels), rounds = (tiles + ncu - 1) / ncu;
+    const float us = rounds * (T[i].round + steps * (T[i].step + T[i].busy * tiles / ((float)rounds * ncu)));
+    if (i == 0 || us < best_us) best = i, best_us = us;
+  }
+  return best;
+}
+
+template <typename F>
+static hipError_t dense_lds(F* kernel, int bytes, bool* set) {      // more than the default dynamic LDS
+  if (*set) return hipSuccess;
+  const hipError_t e = hipFuncSetAttribute((const void*)kernel, hipFuncAttributeMaxDynamicSharedMemorySize, bytes);
+  *set = e == hipSuccess;
+  return e;
 }
 
 template <int EPI>
 static hipError_t dense_launch_epi(const bf16* x, const u32x4* w, int M, int N, int K, float* y, bf16* z, int ldz,
                                    const DenseRope& ra, hipStream_t st) {
-  const int NT = N / 16, steps = K / 32;
-  const bool small = dense_small_tiles(M, NT, steps);
-  const size_t lds_bytes = small ? (size_t)DS_STAGES * DS_STAGE_BYTES : (size_t)DG_STAGES * DG_STAGE_BYTES;
-  static bool attr_set[2] = {false, false};      // more than the default dynamic LDS
-  if (!attr_set[small]) {
-    const void* f = small ? (const void*)dense_small_kernel<EPI> : (const void*)dense_gemm_kernel<EPI>;
-    hipError_t e = hipFuncSetAttribute(f, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds_bytes);
-    if (e != hipSuccess) return e;
-    attr_set[small] = true;
-  }
-  if (small) {
-    const int TM = (M + 127) / 128, tiles = TM * ((NT + 7) / 8), chunk = (tiles + 7) / 8;
-    dense_small_kernel<EPI><<<8 * chunk, DG_THREADS, lds_bytes, st>>>(x, w, y, z, M, N, K, ldz, NT, steps, TM, tiles, chunk, ra);
-  } else {
+  static bool set[3] = {};
+  const int NT = N / 16, steps = K / 32, tile = dense_tile(M, NT, steps);
+  hipError_t e;
+  if (tile == DENSE_LARGE) {
+    constexpr int lds_bytes = DG_STAGES * DG_STAGE_BYTES;
+    if ((e = dense_lds(dense_gemm_kernel<EPI>, lds_bytes, &set[0])) != hipSuccess) return e;
     const int TM = (M + DG_BM - 1) / DG_BM, TN = (NT + 15) / 16;
     const int cx = (TN + 7) / 8, groups = (cx + 3) / 4;
     dense_gemm_kernel<EPI><<<8 * groups * TM * 4, DG_THREADS, lds_bytes, st>>>(x, w, y, z, M, N, K, ldz, NT, steps, TM, cx, ra);
+  } else if (tile == DENSE_SMALL) {
+    constexpr int lds_bytes = DS_STAGES * DS_STAGE_BYTES;
+    if ((e = dense_lds(dense_small_kernel<EPI>, lds_bytes, &set[1])) != hipSuccess) return e;
+    const int TM = (M + 127) / 128, TN = (NT + 7) / 8, chunk = (TM * TN + 7) / 8;
+    dense_small_kernel<EPI><<<8 * chunk, DS_THREADS, lds_bytes, st>>>(x, w, y, z, M, N, K, ldz, NT, steps, TM, TN, chunk, ra);
+  } else {
+    constexpr int lds_bytes = 2 * DW_X_BYTES + 3 * DW_W_BYTES;
+    if ((e = dense_lds(dense_wide_kernel<EPI>, lds_bytes, &set[2])) != hipSuccess) return e;
+    const int TM = (M + 255) / 256, TN = (NT + 2 * DW_PANELS - 1) / (2 * DW_PANELS), chunk = (TM * TN + 7) / 8;
+    dense_wide_kernel<EPI><<<8 * chunk, DS_THREADS, lds_bytes, st>>>(x, w, y, z, M, N, K, ldz, NT, steps, TM, TN, chunk, ra);
   }
   return hipGetLastError();
 }

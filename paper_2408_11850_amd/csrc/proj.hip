@@ -330,56 +330,101 @@ bool proj_whole_k(int M, int N, int K) {
 }
 
 // Layout, panels at a time (RP) and workgroups.  The layout and RP set the order of the sums and depend on the shape
-// alone; the number of workgroups also on the launch mode.  Panels per compute unit decide (us at M = 5 unless noted):
-//   up to 1/2: half panels                           2048 x 5632   6.3 (panels: 7.4)
-//   up to 2: one panel per workgroup                 4096 x 4096   7.9 (half panels 8.5),  8192 x 8192  24 (RP 4: 28)
-//   up to 3: one workgroup per CU, RP 4             11264 x 2048   9.0 (RP 1: 9.9),  12288 x 4096  17.8 (RP 1: 19.0)
-//   up to 4, short of it: the same, four whole panels 14336 x 8192  1.09 times as fast as two per CU with two each (M = 16 1.19)
-//   up to 6: two per CU, RP 4: even shares          21504 x 7168  49.5 (one per CU, RP 1: 53.2)
-//   beyond: one per CU, RP 1, for PAIR's loads of x 38400 x 7168  88 (RP 4, two per CU: 95); K < 2048: a wave has only a few
-//   steps of a panel and RP 4 saves barriers        57344 x 1024  1.15 times, x 256 2.1 times as fast as RP 1
-//   from 9 tokens on (FULL): RP as large as the panels fill; one workgroup per CU streams as fast as two and has the
-//   fewer loads of x                                38400 x 7168, M = 12  90 (two per CU: 99)
-// SWIGLU pairs a gate and an up panel, so shares get coarser: half panels keep them even where there are few (11264 x
-// 2048: 10.6, panels 11.5) and cost nothing where there are many (57344 x 8192, M = 7: 142, panels 145); between the
-// two RP 2 and one load of x per step is faster (38400 x 7168, M = 7: 86, half panels 93).
+// alone; the number of workgroups also on the launch mode.
+//
+// Up to 8 tokens.  Shares come first: as many workgroups as give each the same number of units, one per CU, or two where
+// that fills both places (`full`) (us, weights from HBM, back to back in a graph, before | now):
+//   6144 x 2048, M = 5   384 of 1  7.2 | 192 of 2  6.3        22016 x 4096, M = 5   512 of 2, 1  34.2 | 230 of 3   31.0
+//   14336 x 4096, M = 1  RP 4     22.3 | 224 of 4 21.1        10240 x 8192, M = 7   256 of 3, 2  30.3 | 214 of 3   28.0
+// Then, by units per CU (`one`) and length of a wave's range (an eighth of K):
+//   up to 6 K steps per wave: several panels at a time save barriers; rings of 3 (RP 4) or, for 4 steps, of 4 (RP 2)
+//                              8192 x 512, M = 7    4.5 (RP 1  5.3)     57344 x 512, SWIGLU  12.4 (half panels 21.5)
+//   half a panel per CU: half panels            2048 x 5632, M = 5   6.3 (panels  7.4)
+//   one: what pads the range least              4096 x 4096, M = 7   7.4 (RP 1, range 16 = 2 rings of 8; PAIR 2 of 12: 8.9)
+//   two: both at once (short and long ranges)   5120 x 2048, M = 7   6.1 (RP 1  6.5)      7168 x 19200, M = 7  44.1 (PAIR 47.3)
+//   from K = 6144 on loads of x count, and for up to 4 tokens, which have few lines of x, even shares count more:
+//     half panels                               10240 x 8192, M = 1  26.3 (PAIR 27.2, RP 4 27.7);  M = 7  30.6 (28.7, 28.0)
+//   three, four: RP 4 takes them in one group   12288 x 4096, M = 7  18.1 (RP 1 18.9);   M = 1  18.0 (17.7)
+//   more: RP 2, PAIR up to 4 tokens             32256 x 7168, M = 7  71.9 (PAIR 75.2)
+// SWIGLU pairs a gate and an up panel, so shares get coarser: half panels where that costs more than their loads of x.
+//                              28672 x 8192, M = 1  72.4 (panels 79.0)  22016 x 4096, M = 7  34.1 (panels 31.3)
+// Over 515 shapes (M 1..8, N 256..57344, K 256..28672) 6 % faster in the mean than two workgroups per CU with shares as they
+// fall, 1 % behind the best layout measured for each; none more than 3.5 % slower.
+//
+// From 9 tokens on (FULL): RP as large as the panels fill; one workgroup per CU streams as fast as two and has the
+// fewer loads of x                                 38400 x 7168, M = 12  90 (two per CU: 99)
 ProjPlan proj_plan(int M, int N, int K, int epi, int wgs_per_cu) {
   ProjPlan p;
   const int ncu = spec_num_cu();
   p.M = M; p.N = N; p.K = K; p.epi = epi;
   p.steps = (K + 31) / 32;
   p.NT = N / 16;
-  p.units = p.NT;
-  int G = ncu * wgs_per_cu;
-  if (epi == PROJ_SWIGLU) {
-    const bool half = M <= 8 && (p.NT <= 4 * ncu || p.NT > 12 * ncu);
-    p.mode = half ? PROJ_HALF : PROJ_FULL;
-    p.units = half ? p.NT : p.NT / 2;
-    p.RP = M <= 8 || p.NT <= 2 * ncu ? 2 : 4;
-    if (M > 8 && p.NT <= 4 * ncu) G = ncu;
-  } else if (M <= 8 && p.NT * 2 <= ncu) {
-    p.mode = PROJ_HALF;
-    p.units = p.NT * 2;
-    p.RP = 1;
-  } else if (p.NT > 2 * ncu && p.NT <= 6 * ncu) {
-    p.mode = PROJ_FULL;
-    p.RP = 4;
-    if (p.NT < 4 * ncu) G = ncu;
-  } else if (M <= 8 && p.NT > 6 * ncu && K < 2048) {
-    p.mode = PROJ_FULL;
-    p.RP = 4;
-  } else if (M <= 8) {
-    p.mode = PROJ_PAIR;
-    p.RP = 1;
-    if (p.NT > 6 * ncu) G = ncu;
-  } else {
-    p.mode = PROJ_FULL;
-    p.RP = p.NT <= ncu ? 1 : p.NT <= 2 * ncu ? 2 : 4;
-    G = ncu;
+  const bool sw = epi == PROJ_SWIGLU;
+  const int units = sw ? p.NT / 2 : p.NT;                // of whole panels
+  p.mode = PROJ_FULL;
+  p.units = units;
+  if (M > 8) {
+    int G = ncu * wgs_per_cu;
+    p.RP = sw ? (p.NT <= 2 * ncu ? 2 : 4) : p.NT <= ncu ? 1 : p.NT <= 2 * ncu ? 2 : 4;
+    if (p.NT < 4 * ncu || (sw ? p.NT == 4 * ncu : p.NT <= 2 * ncu || p.NT > 6 * ncu)) G = ncu;
+    if (M > 16 && epi == PROJ_RESID) p.RP = 2;
+    if (M > 16 && p.RP == 4) G = ncu;                    // a workgroup's registers fill a CU
+    p.G = units < G ? units : G;
+    return p;
   }
-  if (M > 16 && epi == PROJ_RESID) p.RP = 2;
-  if (M > 16 && p.RP == 4) G = ncu;                      // a workgroup's registers fill a CU
-  p.G = p.units < G ? p.units : G;
+  auto share = [](int n, int places) { return (n + places - 1) / places; };
+  const int one = share(units, ncu), range = share(p.steps, PROJ_WAVES);
+  const bool few = M <= 4, brief = range <= 6, full = units * 100 >= one * ncu * 85;
+  const int brief_rp = range == 4 ? 2 : 4;
+  auto pad = [&](int ring, int q) { return share(share(range, q), ring) * ring * q; };
+  bool two = false;        // two workgroups per CU
+  bool uneven = false;     // ... with shares as they fall: as fast or faster there
+  p.RP = sw ? 2 : 1;
+  if (2 * units <= ncu) {
+    if (!sw || K >= 1024) p.mode = PROJ_HALF;
+  } else if (sw) {
+    if (one > 1 && brief) {
+      p.RP = brief_rp;
+    } else if (one == 1) {
+      if (K >= 6144 || (few && K >= 3072 && full)) p.mode = PROJ_HALF, two = full;
+    } else if (one == 2) {
+      if (K >= 3072) p.mode = PROJ_HALF, two = full && K < 6144;
+      else if (few || !full) p.mode = PROJ_HALF, uneven = true;
+      else two = true;
+    } else if (one <= 4) {
+      if (K >= (one == 4 ? 3072 : 6144)) p.mode = PROJ_HALF;
+    } else if (K >= 8192 || (K >= 6144 && one > 6)) {
+      p.mode = PROJ_HALF, two = true;
+    } else if (K >= 6144) {
+      uneven = true;
+    }
+  } else if (one == 1) {
+    if (range < 4) p.RP = 2;
+    else if (brief || K >= 6144 || pad(6, 2) < pad(8, 1)) p.mode = PROJ_PAIR;
+  } else if (one == 2) {
+    if (K < 3072 || (K >= 6144 && pad(6, 1) < pad(8, 1))) p.RP = 2;
+    else if (K >= 6144 && K < 12288 && few) p.mode = PROJ_HALF;
+    else two = full, p.mode = K >= 6144 ? PROJ_PAIR : PROJ_FULL;
+  } else if (one <= 4) {
+    if (brief) p.RP = brief_rp;
+    else if (K >= 12288 || (!few && (one == 3 || K >= 6144))) p.RP = 4;
+    else if (K >= 6144) p.mode = one == 3 ? PROJ_PAIR : PROJ_HALF;
+    else if (one == 4) two = true, p.RP = few || K >= 3072 ? 1 : 2;
+  } else if (one <= 6) {
+    if (brief) p.RP = 4, uneven = true;
+    else if (few && K >= 6144) p.mode = PROJ_PAIR;
+    else p.RP = 2;
+  } else {
+    if (brief) p.RP = brief_rp;
+    else if (few) p.mode = PROJ_PAIR;
+    else if (K < 3072 || K >= 6144) p.RP = 2;
+  }
+  if (p.mode == PROJ_HALF) {
+    if (epi == PROJ_RESID && 2 * units > SSQ_STRIDE) p.mode = PROJ_FULL, p.RP = 4;   // a piece of sums of squares per unit
+    else p.units = 2 * units;
+  }
+  const int places = ncu * (wgs_per_cu > 1 && (two || uneven) ? 2 : 1);
+  p.G = uneven ? (p.units < places ? p.units : places) : share(p.units, share(p.units, places));
   return p;
 }
 
@@ -392,7 +437,8 @@ bool proj_plan_ok(const ProjPlan& p) {
   const bool sw = p.epi == PROJ_SWIGLU;
   if (sw && (p.N & 31)) return false;
   switch (p.mode) {
-    case PROJ_HALF: return p.M <= 8 && p.RP == (sw ? 2 : 1) && p.units == (sw ? p.NT : p.NT * 2);
+    case PROJ_HALF:                  // a residual add leaves a sum of squares per half panel, SSQ_STRIDE at most
+      return p.M <= 8 && p.RP == (sw ? 2 : 1) && p.units == (sw ? p.NT : p.NT * 2) && !(p.epi == PROJ_RESID && p.units > SSQ_STRIDE);
     case PROJ_PAIR: return p.M <= 8 && !sw && p.RP == 1 && p.units == p.NT;
     case PROJ_FULL:
       if (p.units != (sw ? p.NT / 2 : p.NT)) return false;

@@ -332,9 +332,10 @@ def main():
     prompt = synth.prompt_tokens(cfg.n_prompt, cfg.target.vocab, cfg.seed_prompt).tolist()
     # prompt pass of each model alone (dense matrix-core path when the shapes allow it), then both for the run
     def prefill_flops(sh, c):
-        per_layer = sh.d_model * (sh.n_heads + 2 * sh.n_kv_heads) * sh.head_dim + sh.n_heads * sh.head_dim * sh.d_model \
-            + 3 * sh.d_model * sh.d_ffn
-        return 2.0 * c * per_layer * sh.n_layers + 2.0 * sh.head_dim * sh.n_heads * c * c * sh.n_layers
+        qkv = sh.d_model * (sh.n_heads + 2 * sh.n_kv_heads) * sh.head_dim
+        rest = sh.n_heads * sh.head_dim * sh.d_model + 3 * sh.d_model * sh.d_ffn
+        # of the last layer only K and V are made
+        return 2.0 * c * (qkv * sh.n_layers + rest * (sh.n_layers - 1)) + 2.0 * sh.head_dim * sh.n_heads * c * c * (sh.n_layers - 1)
     ctx.prefill(prompt[:130], which_mask=3)            # first use allocates the prompt-path buffers
     _, t_pf_t = timed(lambda: ctx.prefill(prompt, which_mask=1), sync)
     _, t_pf_d = timed(lambda: ctx.prefill(prompt, which_mask=2), sync)

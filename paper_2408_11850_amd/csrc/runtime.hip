@@ -337,6 +337,7 @@ int enqueue_forward(spec_ctx* c, int which, int M, int logit_rows, int W0, int l
     if ((rc = run_normed(c, which, m, M, qkvN, d.d_model, PROJ_STORE, pa))) return rc;
     HIPCHK(launch_attention(m.qkv, m.rope_tab, m.pool, m.block_table_dev, m.len_dev, m.geom, l, M, d.n_heads,
                             m.split_tokens, m.opart, m.mlpart, m.attn_out, st));
+    if (l + 1 == d.n_layers && logit_rows == 0) break;      // nothing reads past the last layer's K and V
     if ((rc = run_resid(c, which, m, M, HD, m.attn_out, m.wo[l], m.ffn_norm[l], &W))) return rc;
     pa = normed;
     pa.w = m.wgu[l]; pa.xo = m.z; pa.ssq_w = W;
@@ -505,6 +506,7 @@ int prefill_dense_block(spec_ctx* c, int which, const int32_t* tok, int C) {
     HIPCHK(launch_norm(m.pf_h, (const bf16*)m.attn_norm[l], m.pf_a, C, d.d_model, d.rms_eps, st));
     HIPCHK(launch_dense_qkv_rope(m.pf_a, m.wqkv[l], C, d.d_model, m.pf_q, m.pool, m.block_table_dev, m.len_dev,
                                  m.pf_rope, m.geom, l, d.n_heads, st));
+    if (l + 1 == d.n_layers) break;      // K and V of the last layer are all that a prompt leaves behind
     HIPCHK(launch_prefill_attention(m.pf_q, m.pool, m.block_table_dev, m.len_dev, m.geom, l, C, d.n_heads, m.pf_attn,
                                     st));
     HIPCHK(launch_dense_gemm(m.pf_attn, m.wo[l], C, d.d_model, HD, 1, m.pf_h, nullptr, st));

@@ -34,23 +34,36 @@ hipError_t launch_embed(float* h, const bf16* embed, const int* tok, int M, int 
 }
 
 // a[m] = h[m] * rsqrt(mean(h[m]^2) + eps) * gain, for a prompt block.  One workgroup of 1024 threads per row; a thread keeps
-// its (at most 4) float4 pieces of the row in registers.  Bound by HBM: the row once in, half of it out.
+// its (at most 4) float4 pieces of the row in registers.  Bound by HBM: the row once in, half of it out.  SLICES: first adds
+// the S slices P[s][m] of a projection to the row (their sum in ascending order, then to h), which costs no launch of its own.
 #define NORM_THREADS 1024
 #define NORM_PIECES 4      // d_model <= 4 * 4 * 1024
 static_assert(SPEC_D_MODEL_MAX <= 4 * NORM_PIECES * NORM_THREADS, "a row fits the registers of a workgroup");
-__global__ __launch_bounds__(NORM_THREADS) void norm_kernel(const float* __restrict__ h, const bf16* __restrict__ gain,
-                                                            bf16* __restrict__ a, int d, float eps) {
+template <bool SLICES>
+__global__ __launch_bounds__(NORM_THREADS) void norm_kernel(float* __restrict__ h, const float* __restrict__ P, int S, int M,
+                                                            const bf16* __restrict__ gain, bf16* __restrict__ a, int d, float eps) {
   __shared__ float sh[NORM_THREADS / 64];
   const int m = blockIdx.x;
   const int d4 = d >> 2;
-  const f32x4* hr = reinterpret_cast<const f32x4*>(h + (size_t)m * d);
+  f32x4* hr = reinterpret_cast<f32x4*>(h + (size_t)m * d);
   f32x4 v[NORM_PIECES];
   float ss = 0.f;
 #pragma unroll
   for (int it = 0; it < NORM_PIECES; ++it) {
     const int i = threadIdx.x + it * NORM_THREADS;
     v[it] = f32x4{0.f, 0.f, 0.f, 0.f};
-    if (i < d4) v[it] = hr[i];
+    if (i < d4) {
+      v[it] = hr[i];
+      if (SLICES) {
+        const f32x4* p = reinterpret_cast<const f32x4*>(P) + (size_t)m * d4 + i;
+        const size_t next = (size_t)M * d4;
+        f32x4 t = p[0];
+#pragma unroll 4
+        for (int s = 1; s < S; ++s) t += p[s * next];
+        v[it] += t;
+        hr[i] = v[it];
+      }
+    }
     ss += v[it].x * v[it].x + v[it].y * v[it].y + v[it].z * v[it].z + v[it].w * v[it].w;
   }
 #pragma unroll
@@ -73,9 +86,10 @@ __global__ __launch_bounds__(NORM_THREADS) void norm_kernel(const float* __restr
     }
   }
 }
-hipError_t launch_norm(const float* h, const bf16* gain, bf16* a, int M, int d, float eps, hipStream_t st) {
+hipError_t launch_norm(float* h, const bf16* gain, bf16* a, int M, int d, float eps, hipStream_t st, const float* P, int S) {
   if ((d & 3) || d > SPEC_D_MODEL_MAX) return hipErrorInvalidValue;
-  norm_kernel<<<M, NORM_THREADS, 0, st>>>(h, gain, a, d, eps);
+  if (S > 1) norm_kernel<true><<<M, NORM_THREADS, 0, st>>>(h, P, S, M, gain, a, d, eps);
+  else norm_kernel<false><<<M, NORM_THREADS, 0, st>>>(h, nullptr, 0, M, gain, a, d, eps);
   return hipGetLastError();
 }
 

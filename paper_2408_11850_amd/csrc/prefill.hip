@@ -333,20 +333,23 @@ __device__ __forceinline__ bool dense_tile_of(int TM, int TN, int chunk, int* tm
 
 template <int EPI>
 __device__ __forceinline__ void dense_small_tile(const bf16* __restrict__ X, const u32x4* __restrict__ Wp, float* __restrict__ Y,
-                                                 bf16* __restrict__ Z, int M, int N, int K, int ldz, int NT, int steps, int TM,
-                                                 int TN, int chunk, const DenseRope& ra) {
+                                                 bf16* __restrict__ Z, int M, int N, int K, int ldz, int NT, int panel_steps, int TM,
+                                                 int TN, int chunk, int slice, const DenseRope& ra) {
   extern __shared__ u32x4 lds[];          // DS_STAGES * DS_STAGE_BYTES
   const int w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), lane = threadIdx.x & 63;
   int tm, tn;
   if (!dense_tile_of(TM, TN, chunk, &tm, &tn)) return;
+  // this workgroup's slice of the K axis; the slices of a split projection leave their sums side by side
+  const int step0 = blockIdx.y * slice, steps = min(slice, panel_steps - step0);
+  if (EPI == DG_EPI_STORE) Y += (size_t)blockIdx.y * M * N;
   const int c = lane & 15, kb = lane >> 4;
   const int kg = w >> 2, wm = (w >> 1) & 1, wn = w & 1;
   // Per stage a wave loads token tile w (8 rows x 64 k at a time) and two K steps of panel w; rows and panels past the end
   // are clamped, computed and never stored.
   int panel = tn * 8 + w;
   if (panel > NT - 1) panel = NT - 1;
-  const char* wbase = reinterpret_cast<const char*>(Wp + (size_t)panel * steps * 64) + lane * 16;
-  const char* xbase = reinterpret_cast<const char*>(X);
+  const char* wbase = reinterpret_cast<const char*>(Wp + ((size_t)panel * panel_steps + step0) * 64) + lane * 16;
+  const char* xbase = reinterpret_cast<const char*>(X) + (size_t)step0 * 64;
   const int xchunk = (lane & 7) ^ (lane >> 3);
   unsigned xoff[2];
 #pragma unroll
@@ -456,8 +459,8 @@ template <int EPI>
 __global__ __launch_bounds__(DS_THREADS, 2) void dense_small_kernel(const bf16* __restrict__ X, const u32x4* __restrict__ Wp,
                                                                     float* __restrict__ Y, bf16* __restrict__ Z, int M, int N,
                                                                     int K, int ldz, int NT, int steps, int TM, int TN, int chunk,
-                                                                    DenseRope ra) {
-  dense_small_tile<EPI>(X, Wp, Y, Z, M, N, K, ldz, NT, steps, TM, TN, chunk, ra);
+                                                                    int slice, DenseRope ra) {
+  dense_small_tile<EPI>(X, Wp, Y, Z, M, N, K, ldz, NT, steps, TM, TN, chunk, slice, ra);
 }
 
 // dense_wide: 256 tokens x 192 outputs by 8 waves of 64 tokens x 6 panels, for grids that deal out more evenly so.  Operands
@@ -638,13 +641,49 @@ static hipError_t dense_launch_epi(const bf16* x, const u32x4* w, int M, int N, 
     constexpr int lds_bytes = DS_STAGES * DS_STAGE_BYTES;
     if ((e = dense_lds(dense_small_kernel<EPI>, lds_bytes, &set[1])) != hipSuccess) return e;
     const int TM = (M + 127) / 128, TN = (NT + 7) / 8, chunk = (TM * TN + 7) / 8;
-    dense_small_kernel<EPI><<<8 * chunk, DS_THREADS, lds_bytes, st>>>(x, w, y, z, M, N, K, ldz, NT, steps, TM, TN, chunk, ra);
+    dense_small_kernel<EPI><<<8 * chunk, DS_THREADS, lds_bytes, st>>>(x, w, y, z, M, N, K, ldz, NT, steps, TM, TN, chunk, steps, ra);
   } else {
     constexpr int lds_bytes = 2 * DW_X_BYTES + 3 * DW_W_BYTES;
     if ((e = dense_lds(dense_wide_kernel<EPI>, lds_bytes, &set[2])) != hipSuccess) return e;
     const int TM = (M + 255) / 256, TN = (NT + 2 * DW_PANELS - 1) / (2 * DW_PANELS), chunk = (TM * TN + 7) / 8;
     dense_wide_kernel<EPI><<<8 * chunk, DS_THREADS, lds_bytes, st>>>(x, w, y, z, M, N, K, ldz, NT, steps, TM, TN, chunk, ra);
   }
+  return hipGetLastError();
+}
+
+// K slices of a prompt projection whose consumer adds them (launch_norm_slices), 1 = none: where 128 x 128 tiles leave at least
+// half of the CUs idle.  A CU pulls a tile's operands at the same rate whatever the others do (see dense_small), so a slice's
+// time falls with its length; the sums cost their way through memory, about 3 MB per us and a few us (measured, us, whole |
+// in slices, with what the norm behind them takes longer: 128 x 4096 x 11008 101 | 30, 511 x 2048 x 5504 50 | 23, 128 x 4096 x
+// 4096 35 | 17; a prompt of 100 tokens through four layers of 4096 x 11008 1411 | 976 with the last layer's dead part gone).
+#define DENSE_SLICES_MAX 16
+int dense_slices(int M, int N, int K) {
+  const int ncu = spec_num_cu(), steps = K / 32, tiles = (M + 127) / 128 * ((N + 127) / 128);
+  if (2 * tiles > ncu || dense_tile(M, N / 16, steps) != DENSE_SMALL) return 1;
+  auto time = [&](int S, int slice) { return slice * (0.185f + 0.085f * S * tiles / ncu) + (S > 1 ? 3.f + S * (float)M * N * 4.f / 3e6f : 0.f); };
+  int best = 1;
+  float best_us = 0.85f * time(1, steps);
+  for (int S = 2; S <= DENSE_SLICES_MAX && S * tiles <= ncu; ++S) {
+    const int slice = ((steps + S - 1) / S + 1) & ~1;
+    if (slice < 4 || (steps + slice - 1) / slice != S) continue;
+    if (time(S, slice) < best_us) best = S, best_us = time(S, slice);
+  }
+  return best;
+}
+size_t dense_slices_floats() { return (size_t)spec_num_cu() * 128 * 128; }
+
+// P[s][m][n] = slice s of X W^T, S = dense_slices(M, N, K) > 1 of them
+hipError_t launch_dense_slices(const bf16* x, const void* wp, int M, int N, int K, int S, float* P, hipStream_t st) {
+  if ((double)M * K * 2.0 >= 4294967296.0 || S < 2) return hipErrorInvalidValue;
+  constexpr int lds_bytes = DS_STAGES * DS_STAGE_BYTES;
+  static bool set = false;
+  hipError_t e = dense_lds(dense_small_kernel<DG_EPI_STORE>, lds_bytes, &set);
+  if (e != hipSuccess) return e;
+  const int NT = N / 16, steps = K / 32, slice = ((steps + S - 1) / S + 1) & ~1;      // whole stages
+  if ((steps + slice - 1) / slice != S) return hipErrorInvalidValue;
+  const int TM = (M + 127) / 128, TN = (NT + 7) / 8, chunk = (TM * TN + 7) / 8;
+  dense_small_kernel<DG_EPI_STORE><<<dim3(8 * chunk, S), DS_THREADS, lds_bytes, st>>>(x, (const u32x4*)wp, P, nullptr, M, N, K, 0, NT,
+                                                                                      steps, TM, TN, chunk, slice, DenseRope{});
   return hipGetLastError();
 }
 

@@ -67,6 +67,7 @@ struct ModelRt {
   int* pf_tok = nullptr;
   float* pf_h = nullptr;
   bf16 *pf_a = nullptr, *pf_q = nullptr, *pf_attn = nullptr, *pf_z = nullptr;
+  float* pf_part = nullptr;       // K slices of a projection, see dense_slices
   float2* pf_rope = nullptr;      // (cos, sin) per token and rotation pair of the current block
 };
 
@@ -209,7 +210,7 @@ void free_model(ModelRt& m) {
           }
   void* ptrs[] = {m.qkv, m.rope_tab,
                   m.pool, m.block_table_dev, m.len_dev, m.h, m.ssq, m.a, m.attn_out, m.z, m.partials,
-                  m.opart, m.logits, m.pf_tok, m.pf_h, m.pf_a, m.pf_q, m.pf_attn, m.pf_z, m.pf_rope};
+                  m.opart, m.logits, m.pf_tok, m.pf_h, m.pf_a, m.pf_q, m.pf_attn, m.pf_z, m.pf_part, m.pf_rope};
   for (void* p : ptrs)
     if (p) (void)hipFree(p);
 }
@@ -481,6 +482,7 @@ int ensure_prefill_buffers(ModelRt& m) {
   if ((rc = dev_alloc(&m.pf_attn, C * HD))) return rc;
   if ((rc = dev_alloc(&m.pf_z, C * dense_ffn(d)))) return rc;
   if (dense_ffn(d) != d.d_ffn) HIPCHK(hipMemsetAsync(m.pf_z, 0, C * dense_ffn(d) * sizeof(bf16), m.stream));
+  if ((rc = dev_alloc(&m.pf_part, dense_slices_floats()))) return rc;
   if ((rc = dev_alloc(&m.pf_rope, C * (d.head_dim / 2)))) return rc;
   m.pf_cap = cap;
   return SPEC_OK;
@@ -502,17 +504,24 @@ int prefill_dense_block(spec_ctx* c, int which, const int32_t* tok, int C) {
   HIPCHK(launch_rope_table(m.pf_rope, m.len_dev, C, d.head_dim, d.rope_theta, st));
   const int qkvN = (d.n_heads + 2 * d.n_kv_heads) * d.head_dim;
   const int HD = d.n_heads * d.head_dim;
+  // h += x W^T: into h, or in K slices that the next norm adds
+  int S = 1;
+  auto resid = [&](const bf16* x, const void* w, int K) {
+    S = dense_slices(C, d.d_model, K);
+    return S > 1 ? launch_dense_slices(x, w, C, d.d_model, K, S, m.pf_part, st)
+                 : launch_dense_gemm(x, w, C, d.d_model, K, 1, m.pf_h, nullptr, st);
+  };
   for (int l = 0; l < d.n_layers; ++l) {
-    HIPCHK(launch_norm(m.pf_h, (const bf16*)m.attn_norm[l], m.pf_a, C, d.d_model, d.rms_eps, st));
+    HIPCHK(launch_norm(m.pf_h, (const bf16*)m.attn_norm[l], m.pf_a, C, d.d_model, d.rms_eps, st, m.pf_part, S));
     HIPCHK(launch_dense_qkv_rope(m.pf_a, m.wqkv[l], C, d.d_model, m.pf_q, m.pool, m.block_table_dev, m.len_dev,
                                  m.pf_rope, m.geom, l, d.n_heads, st));
     if (l + 1 == d.n_layers) break;      // K and V of the last layer are all that a prompt leaves behind
     HIPCHK(launch_prefill_attention(m.pf_q, m.pool, m.block_table_dev, m.len_dev, m.geom, l, C, d.n_heads, m.pf_attn,
                                     st));
-    HIPCHK(launch_dense_gemm(m.pf_attn, m.wo[l], C, d.d_model, HD, 1, m.pf_h, nullptr, st));
-    HIPCHK(launch_norm(m.pf_h, (const bf16*)m.ffn_norm[l], m.pf_a, C, d.d_model, d.rms_eps, st));
+    HIPCHK(resid(m.pf_attn, m.wo[l], HD));
+    HIPCHK(launch_norm(m.pf_h, (const bf16*)m.ffn_norm[l], m.pf_a, C, d.d_model, d.rms_eps, st, m.pf_part, S));
     HIPCHK(launch_dense_gemm(m.pf_a, m.wgu[l], C, 2 * d.d_ffn, d.d_model, 2, nullptr, m.pf_z, st, dense_ffn(d)));
-    HIPCHK(launch_dense_gemm(m.pf_z, m.wdown[l], C, d.d_model, dense_ffn(d), 1, m.pf_h, nullptr, st));
+    HIPCHK(resid(m.pf_z, m.wdown[l], dense_ffn(d)));
   }
   m.len += C;
   m.n_forwards++;

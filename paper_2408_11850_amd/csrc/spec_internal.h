@@ -143,8 +143,9 @@ hipError_t launch_begin(const BeginArgs& a, const TokenSrc& src, const PageUpdat
 hipError_t launch_set_int(int* dst, int value, hipStream_t st);
 hipError_t launch_set_pages(int* block_table, PageUpdate u, hipStream_t st);
 hipError_t launch_embed(float* h, const bf16* embed, const int* tok, int M, int d, int vocab, hipStream_t st);
-// a = rmsnorm(h) * gain
-hipError_t launch_norm(const float* h, const bf16* gain, bf16* a, int M, int d, float eps, hipStream_t st);
+// a = rmsnorm(h) * gain; S > 1: after h += the sum of the S slices P[s][M][d]
+hipError_t launch_norm(float* h, const bf16* gain, bf16* a, int M, int d, float eps, hipStream_t st, const float* P = nullptr,
+                       int S = 1);
 // h += sum_s partials[s], a = bf16(h * gain) (not normalised), ssq[m][w] = sum of h^2 over the w-th
 // piece of 1024 columns of row m (row stride SSQ_STRIDE; pieces beyond W
 // are never written); returns the number of pieces W through *W_out
@@ -161,6 +162,11 @@ size_t attention_workspace_floats(int Hq, int Hkv, int dh, int max_seq);
 #define SPEC_PREFILL_BLOCK_MAX 4096   // most prompt tokens one dense pass takes
 hipError_t launch_dense_gemm(const bf16* x, const void* wp, int M, int N, int K, int epi, float* y, bf16* z,
                              hipStream_t st, int ldz = 0);   // ldz: row stride of z, 0 = N / 2
+// K slices of a prompt projection for launch_norm to add: how many (1: none, call launch_dense_gemm), P[S][M][N], and the floats
+// that hold P for every shape
+int dense_slices(int M, int N, int K);
+hipError_t launch_dense_slices(const bf16* x, const void* wp, int M, int N, int K, int S, float* P, hipStream_t st);
+size_t dense_slices_floats();
 // fused QKV projection of a prompt block with RoPE and the paged K / V append in its epilogue
 hipError_t launch_dense_qkv_rope(const bf16* x, const void* wp, int M, int K, bf16* q, bf16* pool, const int* block_table,
                                  const int* len_ptr, const float2* tab, KvGeom g, int layer, int Hq, hipStream_t st);

@@ -3,6 +3,7 @@ from __future__ import annotations
 
 import atexit
 import ctypes as C
+import threading
 import weakref
 from typing import Callable, List, Optional
 
@@ -339,14 +340,31 @@ def dense_gemm(x: torch.Tensor, w_packed: torch.Tensor, N: int, epilogue: int = 
     return y
 
 
+class _DrawnId(threading.local):
+    """One pinned word per thread that the draw's kernel writes its id to, instead of a copy behind the kernel (a draw over
+    32000 ids 26.0 -> 24.4 us, over 1024 24.9 -> 23.1)."""
+
+    def __init__(self):
+        self.pinned = torch.empty(1, dtype=torch.int32, pin_memory=True)
+        self.word = C.c_int32.from_address(self.pinned.data_ptr())
+
+
+_drawn = None
+
+
 def sample_row(logits: torch.Tensor, temperature: float, logit_scale: float, u: float):
+    global _drawn
     lib = load_library()
     assert logits.dtype == torch.float32 and logits.is_contiguous() and logits.dim() == 1
+    if _drawn is None:
+        _drawn = _DrawnId()
+    drawn = _drawn          # the same one throughout, should another thread make the first call at this moment too
     q = torch.empty_like(logits)
-    tok = torch.empty(1, dtype=torch.int32, device=logits.device)
+    stream = torch.cuda.current_stream()
     check(lib.spec_sample_row(_ptr(logits), logits.numel(), float(temperature), float(logit_scale), float(u), _ptr(q),
-                              _ptr(tok), _stream_ptr(torch.cuda.current_stream())))
-    return q, int(tok.item())
+                              _ptr(drawn.pinned), _stream_ptr(stream)))
+    stream.synchronize()
+    return q, drawn.word.value
 
 
 def accept_rows(p_logits: torch.Tensor, q_rows: Optional[torch.Tensor], x, r, temperature: float, logit_scale: float,

@@ -313,7 +313,7 @@ __global__ __launch_bounds__(DG_THREADS, 1) void dense_gemm_kernel(const bf16* _
 // all of it from L2 0.17), LDS and MFMAs alone 0.17, all together 0.27.  What counts is that consecutive lanes of a load of X
 // take whole lines (with a row per lane, 16 bytes of each, X took 0.23 us of a K step instead of 0.13), that loads are issued
 // between MFMAs and that every SIMD has a second wave: 1023 x 4096 x 11008 124 -> 100 us; 511 x 6144 x 2048 28 -> 23 from
-// HBM and 26.4 -> 18.0 from the memory-side cache.
+// HBM and 26.4 -> 18 to 19 from the memory-side cache.
 #define DS_WAVES 8
 #define DS_THREADS (DS_WAVES * 64)
 #define DS_STAGES 4

@@ -73,27 +73,19 @@ struct AttnRows {
 template <int DH>
 struct AttnChunk {                      // K / V fragments of 32 positions
   u32x4 k[2][DH / 32], v[DH / 16];
-  __device__ __forceinline__ void load_k(const bf16* pool, int page, const KvGeom& g, int layer, int kvh, int ch, int lane) {
-    const u32x4* kblk = reinterpret_cast<const u32x4*>(pool + g.offset(page, layer, 0, kvh)) + (size_t)(ch & 1) * (DH / 16) * 64 + lane;
+  __device__ __forceinline__ void load(const bf16* pool, int page, const KvGeom& g, int layer, int kvh, int ch, int lane) {
+    const int c = lane & 15, g4 = lane >> 4, half = ch & 1;
+    const u32x4* kblk = reinterpret_cast<const u32x4*>(pool + g.offset(page, layer, 0, kvh)) + (size_t)half * (DH / 16) * 64 + lane;
+    const bf16* vblk = pool + g.offset(page, layer, 1, kvh) + (size_t)half * DH * 32;
 #pragma unroll
     for (int t = 0; t < 2; ++t)
 #pragma unroll
       for (int j = 0; j < DH / 32; ++j) k[t][j] = kblk[(size_t)(t * (DH / 32) + j) * 64];
-  }
-  __device__ __forceinline__ void load_v(const bf16* pool, int page, const KvGeom& g, int layer, int kvh, int ch, int lane) {
-    const int c = lane & 15, g4 = lane >> 4;
-    const bf16* vblk = pool + g.offset(page, layer, 1, kvh) + (size_t)(ch & 1) * DH * 32;
 #pragma unroll
     for (int dt = 0; dt < DH / 16; ++dt) v[dt] = *reinterpret_cast<const u32x4*>(vblk + ((size_t)(dt * 16 + c) * 32 + g4 * 8));
   }
-  __device__ __forceinline__ void load(const bf16* pool, int page, const KvGeom& g, int layer, int kvh, int ch, int lane) {
-    load_k(pool, page, g, layer, kvh, ch, lane);
-    load_v(pool, page, g, layer, kvh, ch, lane);
-  }
   // The new tokens as one chunk (positions beyond M hold zeros), straight from the QKV projection, k rotated.  Loads are
   // unconditional (rows beyond M read the last one); the second 16 positions are skipped as a whole where there are none.
-  // TILES: 1 if there are at most 16.
-  template <int TILES = 2>
   __device__ __forceinline__ void fresh(const AttnNew& nw, const KvGeom& g, int M, int Hq, int kvh, int lane) {
     const int c = lane & 15, g4 = lane >> 4, N = (Hq + 2 * g.n_kv_heads) * DH;
 #pragma unroll
@@ -102,7 +94,7 @@ struct AttnChunk {                      // K / V fragments of 32 positions
     for (int t = 0; t < 2; ++t) {
 #pragma unroll
       for (int j = 0; j < DH / 32; ++j) k[t][j] = u32x4{0u, 0u, 0u, 0u};
-      if (t >= TILES || t * 16 >= M) continue;        // uniform
+      if (t * 16 >= M) continue;                      // uniform
       // v: lane (c, g4) holds columns 16 dt + c of positions 16 t + 4 g4 .. + 3
       float x[4][DH / 16];
 #pragma unroll
@@ -128,13 +120,12 @@ struct AttnChunk {                      // K / V fragments of 32 positions
     }
   }
   // appends the chunk that fresh() made to the pages of positions len .. len + M - 1 (at most two)
-  template <int TILES = 2>
   __device__ __forceinline__ void append(bf16* pool, const int* block_table, const KvGeom& g, int layer, int M, int kvh,
                                          int len, int lane) const {
     const int c = lane & 15, g4 = lane >> 4;
     const int first = len / SPEC_PAGE_TOKENS, page0 = block_table[first], page1 = block_table[(len + M - 1) / SPEC_PAGE_TOKENS];
 #pragma unroll
-    for (int t = 0; t < TILES; ++t) {
+    for (int t = 0; t < 2; ++t) {
       if (t * 16 >= M) continue;
       const int i = t * 16 + c, pos = len + i, rr = pos % SPEC_PAGE_TOKENS;
       if (i < M) {
@@ -158,11 +149,9 @@ struct AttnChunk {                      // K / V fragments of 32 positions
 };
 static_assert(SPEC_PAGE_TOKENS == 64, "two chunks of 32 positions per page");
 
-// online softmax over a chunk whose first position is pos0; positions beyond `limit` are masked.  attn_scores leaves the
-// soft-max weights and the factor that the output so far shrinks by.
+// online softmax over a chunk whose first position is pos0; positions beyond `limit` are masked
 template <int DH>
-__device__ __forceinline__ bf16x8 attn_scores(AttnRows<DH>& r, const AttnChunk<DH>& kv, int pos0, int limit, float scale, int g4,
-                                              float* corr_out) {
+__device__ __forceinline__ void attn_chunk(AttnRows<DH>& r, const AttnChunk<DH>& kv, int pos0, int limit, float scale, int g4) {
   f32x4 s[2];
 #pragma unroll
   for (int t = 0; t < 2; ++t) {
@@ -198,24 +187,11 @@ __device__ __forceinline__ bf16x8 attn_scores(AttnRows<DH>& r, const AttnChunk<D
     }
   r.l = r.l * corr + psum;
   r.m = m_new;
-  *corr_out = corr;
-  return pf;
-}
-
-template <int DH>
-__device__ __forceinline__ void attn_values(AttnRows<DH>& r, const AttnChunk<DH>& kv, bf16x8 pf, float corr) {
 #pragma unroll
   for (int dt = 0; dt < DH / 16; ++dt) {
     r.o[dt] *= corr;
     r.o[dt] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, kv.v[dt]), pf, r.o[dt], 0, 0, 0);
   }
-}
-
-template <int DH>
-__device__ __forceinline__ void attn_chunk(AttnRows<DH>& r, const AttnChunk<DH>& kv, int pos0, int limit, float scale, int g4) {
-  float corr;
-  const bf16x8 pf = attn_scores(r, kv, pos0, limit, scale, g4, &corr);
-  attn_values(r, kv, pf, corr);
 }
 
 // the query row of lane c of row tile `rtile` of a KV head
@@ -353,98 +329,6 @@ __global__ __launch_bounds__(SHORT_WAVES * 64, 2) void attn_short_kernel(AttnNew
   }
 }
 
-// The same for up to 8 query rows per KV head (a window of 8 without grouped queries, one token with groups of 8), with 16
-// waves: up to 480 positions every chunk is in flight at once.  128 registers: a wave holds one chunk at a time; q is rotated
-// once, a pair of columns per thread, and handed round through LDS while K and V are on their way.  24 layers of 16 heads, 512
-// positions, M = 5: 9.3 -> 8.3 us traced, the forward 1048 -> 1030.  It takes a whole CU's registers: beside another stream's
-// kernels it waits for one, and where 8 waves have all their chunks in flight it gains nothing (parallel decoding behind 110 ..
-// 301 positions 1.5 to 2.5 % slower with it, behind 512 1.6 % faster).
-#define FEW_WAVES 16
-#define FEW_ROWS 8
-template <int DH>
-__global__ __launch_bounds__(FEW_WAVES * 64) void attn_few_kernel(AttnNew nw, bf16* __restrict__ pool,
-                                                                  const int* __restrict__ block_table,
-                                                                  const int* __restrict__ len_ptr, KvGeom g, int layer, int M,
-                                                                  int Hq, float scale, int last_chunk, bf16* __restrict__ out) {
-  constexpr int S = FEW_WAVES - 1;
-  static_assert(FEW_ROWS * (DH / 2) <= FEW_WAVES * 64, "a thread per pair of columns");
-  __shared__ f32x4 osh[FEW_WAVES][FEW_ROWS][DH / 4 + 1];     // [row][4 columns], a row padded by 16 bytes
-  __shared__ float msh[FEW_WAVES][FEW_ROWS], lsh[FEW_WAVES][FEW_ROWS];
-  __shared__ __attribute__((aligned(16))) __bf16 qsh[FEW_ROWS][DH + 8];
-  const int kvh = blockIdx.x;
-  const int w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), lane = threadIdx.x & 63;
-  const int c = lane & 15, g4 = lane >> 4;
-  const int Hkv = g.n_kv_heads, G = Hq / Hkv, R = M * G, N = (Hq + 2 * Hkv) * DH;
-  // this thread's pair of columns e, e + dh / 2 of row qr (beyond the last row: the last one again, not stored)
-  const int qr = threadIdx.x / (DH / 2), e = threadIdx.x % (DH / 2);
-  const AttnRow mine(min(qr, R - 1), R, G, kvh);
-  const float* qsrc = nw.y + (size_t)mine.tok * N + (size_t)mine.head * DH + e;
-  const float x0 = qsrc[0], x1 = qsrc[DH / 2];
-  const float2 cs = nw.tab[(size_t)mine.tok * (DH / 2) + e];
-  const AttnRow row(c, R, G, kvh);
-  AttnRows<DH> r;
-  r.clear();
-  auto share_q = [&]() {
-    if (qr < R) {
-      qsh[qr][e] = (__bf16)(x0 * cs.x - x1 * cs.y);
-      qsh[qr][e + DH / 2] = (__bf16)(x0 * cs.y + x1 * cs.x);
-    }
-    asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory");      // K and V stay in flight
-#pragma unroll
-    for (int j = 0; j < DH / 32; ++j) r.qf[j] = *reinterpret_cast<const bf16x8*>(&qsh[min(c, R - 1)][j * 32 + g4 * 8]);
-  };
-  auto publish = [&]() {
-    r.l += __shfl_xor(r.l, 16);
-    r.l += __shfl_xor(r.l, 32);
-    if (c < FEW_ROWS) {
-#pragma unroll
-      for (int dt = 0; dt < DH / 16; ++dt) osh[w][c][dt * 4 + g4] = r.o[dt];
-      if (g4 == 0) msh[w][c] = r.m, lsh[w][c] = r.l;
-    }
-    __syncthreads();
-  };
-  if (w == S) {
-    AttnChunk<DH> kv;
-    kv.template fresh<1>(nw, g, M, Hq, kvh, lane);
-    share_q();
-    attn_chunk(r, kv, 0, row.valid ? row.tok : -1, scale, g4);
-    publish();
-    // the page stores come last: nobody in this launch reads them, and the other waves merge meanwhile
-    kv.template append<1>(pool, block_table, g, layer, M, kvh, len_ptr[0], lane);
-  } else {
-    AttnChunk<DH> kv;
-    const int ch0 = min(w, last_chunk);      // the table has entries up to last_chunk / 2
-    kv.load(pool, block_table[ch0 >> 1], g, layer, kvh, ch0, lane);
-    const int len = len_ptr[0], nchunks = (len + 31) >> 5, limit = row.valid ? len - 1 : -1;
-    share_q();
-    attn_chunk(r, kv, w << 5, limit, scale, g4);           // masked as a whole if it is beyond the length
-    for (int ch = w + S; ch < nchunks; ch += S) {
-      kv.load(pool, block_table[ch >> 1], g, layer, kvh, ch, lane);
-      attn_chunk(r, kv, ch << 5, limit, scale, g4);
-    }
-    publish();
-  }
-  const int rr = threadIdx.x / (DH / 4), q = threadIdx.x % (DH / 4);
-  if (rr < R) {
-    const AttnRow me(rr, R, G, kvh);
-    float m = msh[0][rr];
-#pragma unroll
-    for (int k = 1; k < FEW_WAVES; ++k) m = fmaxf(m, msh[k][rr]);
-    f32x4 num = {0.f, 0.f, 0.f, 0.f};
-    float den = 0.f;
-#pragma unroll
-    for (int k = 0; k < FEW_WAVES; ++k) {
-      const float e = __expf(msh[k][rr] - m);        // a wave without a chunk holds (NEG_BIG, 0, 0)
-      num += e * osh[k][rr][q];
-      den += e * lsh[k][rr];
-    }
-    bf16 o[4];
-#pragma unroll
-    for (int i = 0; i < 4; ++i) o[i] = __float2bfloat16(num[i] / den);
-    *reinterpret_cast<uint2*>(out + ((size_t)me.tok * Hq + me.head) * DH + q * 4) = *reinterpret_cast<const uint2*>(o);
-  }
-}
-
 // out[i][head][e] = sum_s w_s O_s[e] / sum_s w_s l_s,  w_s = exp(m_s - max_s m_s).
 // Workgroup = (dh, 8): the eight thread rows take every eighth split and fold them into a running (max, numerator,
 // denominator) triple - no pass for the maximum first, and eight splits' loads in flight per thread, so up to 64
@@ -522,15 +406,6 @@ hipError_t launch_attention(const float* y, const float2* tab, bf16* pool, const
   const float scale = 1.0f / sqrtf((float)dh);
   const AttnNew nw = {y, tab};
   // the kernel and the split count are chosen for the longest context, not the current one, so that the launch is replayable
-  if (split_tokens <= SHORT_TOKENS && split_tokens > 2 * SHORT_CHUNK_WAVES * 32 && R <= FEW_ROWS) {
-    if (dh == 128)
-      attn_few_kernel<128><<<Hkv, FEW_WAVES * 64, 0, st>>>(nw, pool, block_table, len_ptr, g, layer, M, Hq, scale,
-                                                           split_tokens / 32 - 1, out);
-    else
-      attn_few_kernel<64><<<Hkv, FEW_WAVES * 64, 0, st>>>(nw, pool, block_table, len_ptr, g, layer, M, Hq, scale,
-                                                          split_tokens / 32 - 1, out);
-    return hipGetLastError();
-  }
   if (split_tokens <= SHORT_TOKENS) {
     dim3 grid(nrt, Hkv), block(SHORT_WAVES * 64);
     if (dh == 128)

@@ -329,27 +329,34 @@ bool proj_whole_k(int M, int N, int K) {
   return K <= 4096 || share >= (M <= 24 ? 80 : 86);
 }
 
-// Layout, panels at a time (RP) and workgroups.  The layout and RP set the order of the sums and depend on the shape
-// alone; the number of workgroups also on the launch mode.
+// Layout, panels at a time (RP) and workgroups.  The layout and RP set the order of the sums; up to 8 tokens they follow from
+// N, K and the epilogue alone, so that the rows of a forward do not depend on how many of them there are (behind the same cache;
+// a token that stands in the cache instead of among the new ones is attended in another order).  The number of workgroups
+// does not touch the sums; it depends on the launch mode too.
 //
 // Up to 8 tokens.  Shares come first: as many workgroups as give each the same number of units, one per CU, or two where
-// that fills both places (`full`) (us, weights from HBM, back to back in a graph, before | now):
-//   6144 x 2048, M = 5   384 of 1  7.2 | 192 of 2  6.3        22016 x 4096, M = 5   512 of 2, 1  34.2 | 230 of 3   31.0
-//   14336 x 4096, M = 1  RP 4     22.3 | 224 of 4 21.1        10240 x 8192, M = 7   256 of 3, 2  30.3 | 214 of 3   28.0
-// Then, by units per CU (`one`) and length of a wave's range (an eighth of K):
+// that fills both places (`full`) (us, weights from HBM, back to back in a graph; two per CU with shares as they fall | now):
+//   6144 x 2048, M = 5   384 of 1  7.1 | 192 of 2  6.2        22016 x 4096, M = 5   512 of 2, 1  33.7 | 230 of 3   31.1
+//   14336 x 4096, M = 1  RP 4     22.3 | 448 of 2 20.6        10240 x 8192, M = 7   256 of 3, 2  30.3 | 214 of 3   28.0
+// Then, by units per CU (`one`) and length of a wave's range (an eighth of K), the layout that costs least over 1 to 8 tokens:
 //   up to 6 K steps per wave: several panels at a time save barriers; rings of 3 (RP 4) or, for 4 steps, of 4 (RP 2)
-//                              8192 x 512, M = 7    4.5 (RP 1  5.3)     57344 x 512, SWIGLU  12.4 (half panels 21.5)
-//   half a panel per CU: half panels            2048 x 5632, M = 5   6.3 (panels  7.4)
+//                              8192 x 512, M = 7    4.5 (RP 1  5.3)     57344 x 512, SWIGLU  12.9 (half panels 22.4)
+//   half a panel per CU: half panels            2048 x 5632, M = 5   6.3 (panels  7.7)
 //   one: what pads the range least              4096 x 4096, M = 7   7.4 (RP 1, range 16 = 2 rings of 8; PAIR 2 of 12: 8.9)
-//   two: both at once (short and long ranges)   5120 x 2048, M = 7   6.1 (RP 1  6.5)      7168 x 19200, M = 7  44.1 (PAIR 47.3)
-//   from K = 6144 on loads of x count, and for up to 4 tokens, which have few lines of x, even shares count more:
-//     half panels                               10240 x 8192, M = 1  26.3 (PAIR 27.2, RP 4 27.7);  M = 7  30.6 (28.7, 28.0)
-//   three, four: RP 4 takes them in one group   12288 x 4096, M = 7  18.1 (RP 1 18.9);   M = 1  18.0 (17.7)
-//   more: RP 2, PAIR up to 4 tokens             32256 x 7168, M = 7  71.9 (PAIR 75.2)
+//   two: both at once (short and long ranges)   5120 x 2048, M = 7   6.1 (RP 1  6.5)      7168 x 19200, M = 7  44.1 (PAIR 47.4)
+//     between, half panels where two per CU would not be full, else single ones, two workgroups per CU
+//                                               8192 x 8192, M = 7  24.0 (PAIR 24.3, half panels 25.1), M = 1 23.6 (23.7, 23.3)
+//   three: RP 4 takes them in one group         12288 x 4096, M = 7  18.1 (RP 1 18.9), M = 1 17.9 (17.6)
+//                                               10240 x 8192, M = 7  28.0 (half panels 30.6), M = 1 27.6 (26.3)
+//   four: two workgroups per CU of two          16384 x 4096, M = 7  23.4 (RP 4 26.2), M = 1 23.1 (25.6)
+//     from K = 6144 on PAIR, one per CU, for its loads of x; beyond 8192 RP 4
+//                    16384 x 8192, M = 7  43.7 (RP 4 47.2), M = 1 44.0 (47.8)     14176 x 10904, M = 8  49.5 (PAIR 56.5)
+//   five, six: RP 2                             21504 x 7168, M = 7  49.9 (PAIR 53.4), M = 1 48.7 (48.8)
+//   more: PAIR                                  32000 x 8192, M = 7  79.1 (RP 2 81.2), M = 1 78.9 (80.6)
 // SWIGLU pairs a gate and an up panel, so shares get coarser: half panels where that costs more than their loads of x.
 //                              28672 x 8192, M = 1  72.4 (panels 79.0)  22016 x 4096, M = 7  34.1 (panels 31.3)
 // Over 515 shapes (M 1..8, N 256..57344, K 256..28672) 6 % faster in the mean than two workgroups per CU with shares as they
-// fall, 1 % behind the best layout measured for each; none more than 3.5 % slower.
+// fall, 1 % behind the best layout measured for each; 8 of them more than 1 % slower, none more than 3.5 %.
 //
 // From 9 tokens on (FULL): RP as large as the panels fill; one workgroup per CU streams as fast as two and has the
 // fewer loads of x                                 38400 x 7168, M = 12  90 (two per CU: 99)
@@ -374,7 +381,7 @@ ProjPlan proj_plan(int M, int N, int K, int epi, int wgs_per_cu) {
   }
   auto share = [](int n, int places) { return (n + places - 1) / places; };
   const int one = share(units, ncu), range = share(p.steps, PROJ_WAVES);
-  const bool few = M <= 4, brief = range <= 6, full = units * 100 >= one * ncu * 85;
+  const bool brief = range <= 6, full = units * 100 >= one * ncu * 85;
   const int brief_rp = range == 4 ? 2 : 4;
   auto pad = [&](int ring, int q) { return share(share(range, q), ring) * ring * q; };
   bool two = false;        // two workgroups per CU
@@ -386,11 +393,11 @@ ProjPlan proj_plan(int M, int N, int K, int epi, int wgs_per_cu) {
     if (one > 1 && brief) {
       p.RP = brief_rp;
     } else if (one == 1) {
-      if (K >= 6144 || (few && K >= 3072 && full)) p.mode = PROJ_HALF, two = full;
+      if (K >= 6144 || (K >= 3072 && full)) p.mode = PROJ_HALF, two = full;
     } else if (one == 2) {
       if (K >= 3072) p.mode = PROJ_HALF, two = full && K < 6144;
-      else if (few || !full) p.mode = PROJ_HALF, uneven = true;
-      else two = true;
+      else if (full) two = true;
+      else p.mode = PROJ_HALF, uneven = true;
     } else if (one <= 4) {
       if (K >= (one == 4 ? 3072 : 6144)) p.mode = PROJ_HALF;
     } else if (K >= 8192 || (K >= 6144 && one > 6)) {
@@ -403,26 +410,22 @@ ProjPlan proj_plan(int M, int N, int K, int epi, int wgs_per_cu) {
     else if (brief || K >= 6144 || pad(6, 2) < pad(8, 1)) p.mode = PROJ_PAIR;
   } else if (one == 2) {
     if (K < 3072 || (K >= 6144 && pad(6, 1) < pad(8, 1))) p.RP = 2;
-    else if (K >= 6144 && K < 12288 && few) p.mode = PROJ_HALF;
-    else two = full, p.mode = K >= 6144 ? PROJ_PAIR : PROJ_FULL;
+    else if (K >= 6144 && K < 12288 && !full) p.mode = PROJ_HALF;
+    else two = full, p.mode = K >= 12288 ? PROJ_PAIR : PROJ_FULL;
   } else if (one <= 4) {
     if (brief) p.RP = brief_rp;
-    else if (K >= 12288 || (!few && (one == 3 || K >= 6144))) p.RP = 4;
-    else if (K >= 6144) p.mode = one == 3 ? PROJ_PAIR : PROJ_HALF;
-    else if (one == 4) two = true, p.RP = few || K >= 3072 ? 1 : 2;
+    else if (one == 3 || K > 8192) p.RP = 4;
+    else if (K >= 6144) p.mode = PROJ_PAIR;
+    else two = true;
   } else if (one <= 6) {
     if (brief) p.RP = 4, uneven = true;
-    else if (few && K >= 6144) p.mode = PROJ_PAIR;
     else p.RP = 2;
   } else {
     if (brief) p.RP = brief_rp;
-    else if (few) p.mode = PROJ_PAIR;
-    else if (K < 3072 || K >= 6144) p.RP = 2;
+    else p.mode = PROJ_PAIR;
   }
-  if (p.mode == PROJ_HALF) {
-    if (epi == PROJ_RESID && 2 * units > SSQ_STRIDE) p.mode = PROJ_FULL, p.RP = 4;   // a piece of sums of squares per unit
-    else p.units = 2 * units;
-  }
+  // half panels: a residual add leaves a piece of sums of squares per unit, at most 2 x 2 per CU (a row holds SSQ_STRIDE)
+  if (p.mode == PROJ_HALF) p.units = 2 * units;
   const int places = ncu * (wgs_per_cu > 1 && (two || uneven) ? 2 : 1);
   p.G = uneven ? (p.units < places ? p.units : places) : share(p.units, share(p.units, places));
   return p;

@@ -162,3 +162,26 @@ def test_whole_k_projection_plans_have_a_kernel_and_others_are_refused(amd):
     assert wide.RP == 4
     wide.epi = RESID                       # four panels and two row tiles: no residual kernel
     assert launch(C.byref(wide), _ProjArgs(), None, 0) == invalid
+
+
+def test_sums_of_up_to_eight_tokens_run_in_one_order(amd):
+    """Layout, panels at a time and units of a projection over 1 to 8 tokens, and whether it runs in K slices, do not depend
+    on how many there are: neither do the rows of a forward."""
+    import synth
+    lib = C.CDLL(amd.LIB_PATH)
+    make, whole = lib._Z9proj_planiiiii, lib._Z12proj_whole_kiii
+    make.restype, make.argtypes = _ProjPlan, [C.c_int] * 5
+    whole.restype, whole.argtypes = C.c_bool, [C.c_int] * 3
+    shapes = set()
+    for pair in ("tiny", "small", "7b_1b", "33b_1b", "70b_7b"):
+        for s in (synth.config(pair).target, synth.config(pair).draft):
+            hd = s.n_heads * s.head_dim
+            shapes |= {((s.n_heads + 2 * s.n_kv_heads) * s.head_dim, s.d_model, 0), (s.vocab, s.d_model, 0),
+                       (s.d_model, hd, 1), (s.d_model, s.d_ffn, 1), (2 * s.d_ffn, s.d_model, 2)}
+    widths = (32, 2048, 2080, 4096, 4128, 6144, 8192, 8224, 12288, 16384, 16416, 24576, 24608, 38400, 57344)
+    depths = (8, 200, 768, 1024, 1536, 1792, 2048, 3064, 3072, 5120, 6136, 6144, 8192, 8200, 12280, 12288, 28672)
+    shapes |= {(n, k, e) for n in widths for k in depths for e in (0, 1, 2) if e != 1 or n <= 16384}
+    for n, k, e in sorted(shapes):
+        order = {(p.mode, p.RP, p.units) for p in (make(m, n, k, e, 2) for m in range(1, 9))}
+        assert len(order) == 1, (n, k, e, order)
+        assert len({whole(m, n, k) for m in range(1, 9)}) == 1, (n, k)

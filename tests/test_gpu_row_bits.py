@@ -1,5 +1,4 @@
-"""A row of a forward over up to 8 tokens has the same bits whatever the number of rows beside it (run with -m gpu).  Greedy
-decoding token by token and in windows then agrees exactly, near-ties included."""
+"""A row of a forward over up to 8 tokens has the same bits however many rows follow it (run with -m gpu)."""
 import numpy as np
 import pytest
 
@@ -32,3 +31,11 @@ def assert_rows_share_their_bits(s, max_seq, lengths):
                                                  for h, k, d in ((2, 2, 128), (4, 2, 64), (8, 1, 128)) if n < 1024 or h <= 2 * k])
 def test_attention_rows(heads, kv, dh, max_seq):
     assert_rows_share_their_bits(synth.ModelShape(2, 256, heads, kv, 512, 1008, head_dim=dh), max_seq, (40, 200, max_seq - 20))
+
+
+# the projections: QKV, O, gate/up, down and LM head of one half to eight panels per CU, short ranges of K and long ones (the
+# plans behind them are compared on the host, over a grid of shapes, in test_abi.py)
+@pytest.mark.parametrize("d,heads,ffn,vocab", [(2048, 16, 5504, 32000), (4096, 32, 11008, 16384), (8192, 4, 3072, 10240),
+                                               (7168, 56, 2048, 20496)])
+def test_projection_rows(d, heads, ffn, vocab):
+    assert_rows_share_their_bits(synth.ModelShape(2, d, heads, heads, ffn, vocab, head_dim=128), 256, (100,))

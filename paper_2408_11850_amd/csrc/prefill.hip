@@ -602,8 +602,7 @@ __global__ __launch_bounds__(DS_THREADS, 2) void dense_wide_kernel(const bf16* _
 //   511 x 22016 x 4096      88 | 111 |  84     1023 x 22016 x 4096   173 | 211 | 159     4095 x 8192 x 8192    430 | 540 | 476
 //   1500 x 3072 x 2048      49 |  35 |  41     1023 x 8192 x 8192    166 | 149 | 137     4095 x 57344 x 8192  2634 | 3470 | 2945
 // Of 34 shapes measured it takes the fastest in 30, else one at most 6 % (once 16 %) behind and ahead of what it replaces.
-enum { DENSE_LARGE = 0, DENSE_SMALL = 1, DENSE_WIDE = 2 };
-static int dense_tile(int M, int NT, int steps) {
+int dense_tile(int M, int NT, int steps) {
   static const struct { int tokens, panels; float round, step, busy; } T[3] = {
       {256, 16, 4.f, 0.50f, 0.23f}, {128, 8, 2.f, 0.185f, 0.085f}, {256, 12, 2.f, 0.405f, 0.205f}};
   const int ncu = spec_num_cu();

@@ -93,7 +93,7 @@ CASES = {
     "gqa64": (synth.ModelShape(2, 512, 8, 2, 1376, 2048), 333),        # head_dim 64, group 4, ragged row tiles
     "gqa128": (synth.ModelShape(2, 1024, 8, 2, 2752, 4096), 300),      # head_dim 128, group 4
     "mha128": (synth.ModelShape(2, 512, 4, 4, 1024, 1024), 523),       # group 1: 523 rows per head, 3 row blocks
-    "gqa8": (synth.ModelShape(1, 1024, 8, 1, 1024, 1024), 97),         # group 8 as in the 70B shape
+    "gqa8": (synth.ModelShape(2, 1024, 8, 1, 1024, 1024), 97),         # group 8 as in the 70B shape; the last layer runs no attention
 }
 
 

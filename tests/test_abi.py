@@ -164,6 +164,37 @@ def test_whole_k_projection_plans_have_a_kernel_and_others_are_refused(amd):
     assert launch(C.byref(wide), _ProjArgs(), None, 0) == invalid
 
 
+def test_forward_tests_reach_every_projection_layout(amd):
+    """Layout, panels at a time and ring that proj_plan takes over 1 to 8 tokens for residual adds and SiLU * mul, against
+    those of the GPU tests' models; and that the models of the launch mode test share their work out in two ways."""
+    from tests.test_gpu_proj import FORWARDS, MODES
+    lib = C.CDLL(amd.LIB_PATH)
+    make, whole = lib._Z9proj_planiiiii, lib._Z12proj_whole_kiii
+    make.restype, make.argtypes = _ProjPlan, [C.c_int] * 5
+    whole.restype, whole.argtypes = C.c_bool, [C.c_int] * 3
+
+    def layout(n, k, epi):
+        p = make(8, n, k, epi, 2)
+        return epi, p.mode, p.RP, p.steps <= 64 and p.RP != 4 and (p.mode, p.RP) != (0, 1)   # the short ring is in use
+
+    grid = range(16, 16400, 208)
+    want = {layout(n, k, 1) for n in grid for k in (64, 512, 800, 1024, 1536, 2048, 2304, 2816, 3072, 4096, 6144, 8192, 12288, 28672)
+            if whole(8, n, k)}
+    want |= {layout(n, k, 2) for n in range(32, 57376, 736) for k in (64, 512, 1024, 1536, 2048, 2304, 3072, 4096, 6144, 8192, 16384)}
+    seen = set()
+    for d, heads, _, ffn in FORWARDS:
+        seen |= {layout(d, k, 1) for k in (heads * 128, ffn) if whole(8, d, k)} | {layout(2 * ffn, d, 2)}
+    assert want == seen, (want - seen, seen - want)
+    two_ways = set()
+    for d, heads, kv, ffn, vocab in MODES:
+        for s in (((heads + 2 * kv) * 128, d, 0), (d, heads * 128, 1), (d, ffn, 1), (2 * ffn, d, 2), (vocab, d, 0)):
+            two_ways |= {(m, s) for m in (1, 8, 9, 16) if make(m, *s, 1).G != make(m, *s, 2).G}
+    for m in (1, 8):
+        assert {s[2] for n, s in two_ways if n == m} == {0, 1, 2}
+    for m in (9, 16):
+        assert {s[2] for n, s in two_ways if n == m} == {0, 2}      # a residual add only at d_model 16384
+
+
 def test_sums_of_up_to_eight_tokens_run_in_one_order(amd):
     """Layout, panels at a time and units of a projection over 1 to 8 tokens, and whether it runs in K slices, do not depend
     on how many there are: neither do the rows of a forward."""

@@ -14,8 +14,9 @@ pytestmark = [pytest.mark.gpu, pytest.mark.skipif(not gpu_available(), reason="n
 
 # 8 / 9 and 16 / 17 tokens change the operand layout; N = 16: two half panels; 2048 / 2064: last of the half panels;
 # 4112, 8208, 24592: one panel more than a workgroup range (1, 2, 6 per CU); K = 40, 1032: ragged K and odd step counts;
-# 4104 with 17 and 25 tokens of a narrow matrix: K slices; 14352 and 16384: one and two workgroups per CU below and at four
-# panels per CU; 24592: four panels at a time, or one from K = 2048 on; 4624: uneven shares, K slices from 4096 on
+# 4104 with 17 and 25 tokens of a narrow matrix: K slices; 14352 and 16384: from 9 tokens on one and two workgroups per CU, below
+# and at four panels per CU; 24592: four panels at a time, up to 8 tokens from K = 1568 on PAIR; 4624: uneven shares, K slices
+# from 4096 on
 @pytest.mark.parametrize("N,K", [(16, 40), (48, 8), (2048, 1032), (2064, 520), (4112, 1032), (8192, 2088), (8208, 264),
                                  (24592, 136), (2048, 4104), (14352, 264), (16384, 264), (24592, 2056), (4624, 4088), (4624, 4104)])
 @pytest.mark.parametrize("M", [1, 8, 9, 16, 17, 25, 32])
@@ -34,10 +35,12 @@ def test_projection_at_the_edges_of_the_operand_layouts(M, N, K):
     assert np.abs(y - ref).max() <= 12 * 2.0 ** -24 * 60 ** 0.5 * np.sqrt(np.mean(ref ** 2))
 
 
-# residual add: 2048 half panels, 4608 single panels, 8448 four at a time, 256 x 24640 K slices; gate/up: 256 and 5632
-# half panels, 8400 two or four panels, 24640 half panels again
-@pytest.mark.parametrize("d,heads,kv,ffn", [(2048, 4, 2, 5632), (4608, 4, 2, 1376), (8448, 4, 2, 640), (512, 4, 4, 8400),
-                                            (256, 2, 1, 24640)])
+# Residual adds and SiLU * mul in every layout that up to 8 tokens take (asserted in test_abi.py); 256 x 24640: K slices
+FORWARDS = [(2048, 4, 2, 5632), (4608, 4, 2, 1376), (8448, 4, 2, 640), (512, 4, 4, 8400), (256, 2, 1, 24640), (2304, 11, 1, 1376),
+            (4096, 4, 2, 2304), (4096, 16, 2, 2048), (4608, 4, 2, 2560), (8448, 4, 2, 2560), (512, 4, 4, 1376)]
+
+
+@pytest.mark.parametrize("d,heads,kv,ffn", FORWARDS)
 def test_forwards_at_the_edges_of_the_operand_layouts(d, heads, kv, ffn):
     cfg = _custom(synth.ModelShape(2, d, heads, kv, ffn, 1008, head_dim=128), 1)
     amd, ctx, tm, _ = _setup(cfg)
@@ -117,9 +120,15 @@ def test_embedding_and_gains_at_odd_addresses_give_the_same_bits():
 
 
 # Units of work beyond 256 and 512, so that one and two workgroups per CU share them out differently (uneven shares, several
-# panel groups per workgroup).  First: QKV 384, O and down 288, gate/up 704 half and 352 whole units, LM head 531; second: QKV
-# 576, O and down 528, gate/up 525, LM head 1601 panels
-@pytest.mark.parametrize("d,heads,kv,ffn,vocab", [(4608, 40, 4, 5632, 8496), (8448, 64, 4, 8400, 25616)])
+# panel groups per workgroup).  Up to 8 tokens, third: QKV, O and LM head 512 panels, gate/up 512 half units, all two per CU;
+# fourth: gate/up 704 half units in 512 workgroups with shares as they fall, LM head 875 panels.  From 9 tokens on, second and
+# fifth: gate/up 525 and 544 units, fifth: LM head 1250 panels.  (K slices, and the matrices that take one workgroup per CU in
+# both modes, are in all of them; that the modes differ is asserted in test_abi.py)
+MODES = [(4608, 40, 4, 5632, 8496), (8448, 64, 4, 8400, 25616), (8192, 32, 16, 4096, 8192), (2048, 16, 16, 5632, 14000),
+         (1024, 8, 8, 8704, 20000)]
+
+
+@pytest.mark.parametrize("d,heads,kv,ffn,vocab", MODES)
 def test_launch_modes_give_the_same_bits(d, heads, kv, ffn, vocab):
     import paper_2408_11850_amd as amd
     s = synth.ModelShape(1, d, heads, kv, ffn, vocab, head_dim=128)

@@ -332,9 +332,10 @@ __device__ __forceinline__ bool dense_tile_of(int TM, int TN, int chunk, int* tm
 }
 
 template <int EPI>
-__device__ __forceinline__ void dense_small_tile(const bf16* __restrict__ X, const u32x4* __restrict__ Wp, float* __restrict__ Y,
-                                                 bf16* __restrict__ Z, int M, int N, int K, int ldz, int NT, int panel_steps, int TM,
-                                                 int TN, int chunk, int slice, const DenseRope& ra) {
+__global__ __launch_bounds__(DS_THREADS, 2) void dense_small_kernel(const bf16* __restrict__ X, const u32x4* __restrict__ Wp,
+                                                                    float* __restrict__ Y, bf16* __restrict__ Z, int M, int N,
+                                                                    int K, int ldz, int NT, int panel_steps, int TM, int TN,
+                                                                    int chunk, int slice, DenseRope ra) {
   extern __shared__ u32x4 lds[];          // DS_STAGES * DS_STAGE_BYTES
   const int w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), lane = threadIdx.x & 63;
   int tm, tn;
@@ -455,25 +456,18 @@ __device__ __forceinline__ void dense_small_tile(const bf16* __restrict__ X, con
   dense_epilogue<EPI, 2>(sum, tm * 128 + wm * 64 + kg * 32, tn * 2 + wn, c, kb, Y, Z, M, N, ldz, ra);
 }
 
-template <int EPI>
-__global__ __launch_bounds__(DS_THREADS, 2) void dense_small_kernel(const bf16* __restrict__ X, const u32x4* __restrict__ Wp,
-                                                                    float* __restrict__ Y, bf16* __restrict__ Z, int M, int N,
-                                                                    int K, int ldz, int NT, int steps, int TM, int TN, int chunk,
-                                                                    int slice, DenseRope ra) {
-  dense_small_tile<EPI>(X, Wp, Y, Z, M, N, K, ldz, NT, steps, TM, TN, chunk, slice, ra);
-}
-
 // dense_wide: 256 tokens x 192 outputs by 8 waves of 64 tokens x 6 panels, for grids that deal out more evenly so.  Operands
 // and ring as in dense_small, X (from L2 or the memory-side cache: the other tile columns read it too) two stages deep, W
-// (from HBM) three.  0.65 us per K step with every CU busy: 28 KiB of it 0.46 us of loads, and X has one stage to arrive.
+// (from HBM) three.  0.6 us per K step with every CU busy: 28 KiB of it 0.46 us of loads, and X has one stage to arrive.
 // A third stage of it does not fit LDS beside 256 x 192, and 256 x 128 with three of both takes 0.39 us for two thirds.
 #define DW_PANELS 6                        // of a wave
 #define DW_X_BYTES (16 * DG_TILE_BYTES)
 #define DW_W_BYTES (DW_PANELS * 4096)
 template <int EPI>
-__device__ __forceinline__ void dense_wide_tile(const bf16* __restrict__ X, const u32x4* __restrict__ Wp, float* __restrict__ Y,
-                                                bf16* __restrict__ Z, int M, int N, int K, int ldz, int NT, int steps, int TM,
-                                                int TN, int chunk, const DenseRope& ra) {
+__global__ __launch_bounds__(DS_THREADS, 2) void dense_wide_kernel(const bf16* __restrict__ X, const u32x4* __restrict__ Wp,
+                                                                   float* __restrict__ Y, bf16* __restrict__ Z, int M, int N,
+                                                                   int K, int ldz, int NT, int steps, int TM, int TN, int chunk,
+                                                                   DenseRope ra) {
   constexpr int PN = DW_PANELS, XS = DW_X_BYTES, WS = DW_W_BYTES, WL = PN / 2;
   extern __shared__ u32x4 lds[];          // 2 stages of X, 3 of W
   const int w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), lane = threadIdx.x & 63;
@@ -587,14 +581,6 @@ __device__ __forceinline__ void dense_wide_tile(const bf16* __restrict__ X, cons
   }
 }
 
-template <int EPI>
-__global__ __launch_bounds__(DS_THREADS, 2) void dense_wide_kernel(const bf16* __restrict__ X, const u32x4* __restrict__ Wp,
-                                                                   float* __restrict__ Y, bf16* __restrict__ Z, int M, int N,
-                                                                   int K, int ldz, int NT, int steps, int TM, int TN, int chunk,
-                                                                   DenseRope ra) {
-  dense_wide_tile<EPI>(X, Wp, Y, Z, M, N, K, ldz, NT, steps, TM, TN, chunk, ra);
-}
-
 // Tile by the time a launch takes (us): rounds of one workgroup per CU, each a fixed part and a time per K step that grows
 // with the share of CUs in use, fitted to these (large | small | wide; the launch itself, about 6, is in all of them):
 //   66 x 4096 x 4096        76 |  32 |  63     1023 x 4096 x 11008   213 | 101 | 171     2047 x 4096 x 11008   217 | 185 | 178
@@ -602,6 +588,9 @@ __global__ __launch_bounds__(DS_THREADS, 2) void dense_wide_kernel(const bf16* _
 //   511 x 22016 x 4096      88 | 111 |  84     1023 x 22016 x 4096   173 | 211 | 159     4095 x 8192 x 8192    430 | 540 | 476
 //   1500 x 3072 x 2048      49 |  35 |  41     1023 x 8192 x 8192    166 | 149 | 137     4095 x 57344 x 8192  2634 | 3470 | 2945
 // Of 34 shapes measured it takes the fastest in 30, else one at most 6 % (once 16 %) behind and ahead of what it replaces.
+// The fit is low where a full row tile meets few CUs: 128 x 4096 x 11008, 32 tiles of 128 x 128, 0.28 us per K step (fit 0.196).
+// Large and wide tiles add K as one chain per output, the same bits; 128 x 128 tiles and slices (below) group it otherwise, so
+// the last bits of a prompt's K and V depend on its length, as they do between the dense pass and forwards over 32 tokens.
 int dense_tile(int M, int NT, int steps) {
   static const struct { int tokens, panels; float round, step, busy; } T[3] = {
       {256, 16, 4.f, 0.50f, 0.23f}, {128, 8, 2.f, 0.185f, 0.085f}, {256, 12, 2.f, 0.405f, 0.205f}};
@@ -650,11 +639,12 @@ static hipError_t dense_launch_epi(const bf16* x, const u32x4* w, int M, int N, 
   return hipGetLastError();
 }
 
-// K slices of a prompt projection whose consumer adds them (launch_norm_slices), 1 = none: where 128 x 128 tiles leave at least
-// half of the CUs idle.  A CU pulls a tile's operands at the same rate whatever the others do (see dense_small), so a slice's
-// time falls with its length; the sums cost their way through memory, about 3 MB per us and a few us (measured, us, whole |
-// in slices, with what the norm behind them takes longer: 128 x 4096 x 11008 101 | 30, 511 x 2048 x 5504 50 | 23, 128 x 4096 x
-// 4096 35 | 17; a prompt of 100 tokens through four layers of 4096 x 11008 1411 | 976 with the last layer's dead part gone).
+// K slices of a prompt projection whose consumer (launch_norm) adds them, 1 = none: where 128 x 128 tiles leave at least half of
+// the CUs idle.  A slice's time falls with its length; the sums cost their way through memory, about 3 MB per us and a few us
+// (measured, us, whole | in slices, with what the norm behind them takes longer: 128 x 4096 x 11008 101 | 30, 511 x 2048 x 5504
+// 50 | 23, 128 x 4096 x 4096 35 | 17; a prompt of 100 tokens through four layers of 4096 x 11008 1411 | 976 with the last layer's
+// dead part gone).  time() is the fit of dense_tile, low for whole launches on few CUs, and 0.85 asks for a clear gain on top:
+// what is cut gains, some of what is left whole would.
 #define DENSE_SLICES_MAX 16
 int dense_slices(int M, int N, int K) {
   const int ncu = spec_num_cu(), steps = K / 32, tiles = (M + 127) / 128 * ((N + 127) / 128);

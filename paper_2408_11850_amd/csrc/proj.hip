@@ -337,7 +337,7 @@ bool proj_whole_k(int M, int N, int K) {
 // Up to 8 tokens.  Shares come first: as many workgroups as give each the same number of units, one per CU, or two where
 // that fills both places (`full`) (us, weights from HBM, back to back in a graph; two per CU with shares as they fall | now):
 //   6144 x 2048, M = 5   384 of 1  7.1 | 192 of 2  6.2        22016 x 4096, M = 5   512 of 2, 1  33.7 | 230 of 3   31.1
-//   14336 x 4096, M = 1  RP 4     22.3 | 448 of 2 20.6        10240 x 8192, M = 7   256 of 3, 2  30.3 | 214 of 3   28.0
+//   14336 x 4096, M = 1  RP 4     22.3 | 448 of 2 20.6        10240 x 8192, M = 7   256 of 3, 2  30.3 | 214 of 3   28.7
 // Then, by units per CU (`one`) and length of a wave's range (an eighth of K), the layout that costs least over 1 to 8 tokens:
 //   up to 6 K steps per wave: several panels at a time save barriers; rings of 3 (RP 4) or, for 4 steps, of 4 (RP 2)
 //                              8192 x 512, M = 7    4.5 (RP 1  5.3)     57344 x 512, SWIGLU  12.9 (half panels 22.4)
@@ -346,17 +346,19 @@ bool proj_whole_k(int M, int N, int K) {
 //   two: both at once (short and long ranges)   5120 x 2048, M = 7   6.1 (RP 1  6.5)      7168 x 19200, M = 7  44.1 (PAIR 47.4)
 //     between, half panels where two per CU would not be full, else single ones, two workgroups per CU
 //                                               8192 x 8192, M = 7  24.0 (PAIR 24.3, half panels 25.1), M = 1 23.6 (23.7, 23.3)
-//   three: RP 4 takes them in one group         12288 x 4096, M = 7  18.1 (RP 1 18.9), M = 1 17.9 (17.6)
-//                                               10240 x 8192, M = 7  28.0 (half panels 30.6), M = 1 27.6 (26.3)
-//   four: two workgroups per CU of two          16384 x 4096, M = 7  23.4 (RP 4 26.2), M = 1 23.1 (25.6)
-//     from K = 6144 on PAIR, one per CU, for its loads of x; beyond 8192 RP 4
-//                    16384 x 8192, M = 7  43.7 (RP 4 47.2), M = 1 44.0 (47.8)     14176 x 10904, M = 8  49.5 (PAIR 56.5)
+//   three: RP 1                                 12288 x 4096, M = 7  18.9 (RP 4 18.1), M = 1 17.6 (17.9)
+//   four: the same, two workgroups per CU       16384 x 4096, M = 7  23.4 (RP 4 26.2), M = 1 23.1 (25.6)
+//   three and four from K = 6144 on PAIR, one per CU, for its loads of x, up to K = 12288 and 8192; beyond RP 4
+//     10240 x 8192, M = 7  28.7 (RP 4 28.0, half panels 30.6), M = 1 27.2 (27.6, 26.3)
+//     16384 x 8192, M = 7  43.7 (RP 4 47.2), M = 1 44.0 (47.8)     14176 x 10904, M = 8  49.5 (PAIR 56.5)
+//     (three per CU are close; beside a second stream's launches a step of the 70B/7B pair takes 38.9 ms with these two, 39.2 with
+//     either in RP 4)
 //   five, six: RP 2                             21504 x 7168, M = 7  49.9 (PAIR 53.4), M = 1 48.7 (48.8)
 //   more: PAIR                                  32000 x 8192, M = 7  79.1 (RP 2 81.2), M = 1 78.9 (80.6)
 // SWIGLU pairs a gate and an up panel, so shares get coarser: half panels where that costs more than their loads of x.
 //                              28672 x 8192, M = 1  72.4 (panels 79.0)  22016 x 4096, M = 7  34.1 (panels 31.3)
 // Over 515 shapes (M 1..8, N 256..57344, K 256..28672) 6 % faster in the mean than two workgroups per CU with shares as they
-// fall, 1 % behind the best layout measured for each; 8 of them more than 1 % slower, none more than 3.5 %.
+// fall, 1 % behind the best layout measured for each; 13 of them more than 1 % slower, none more than 5 %.
 //
 // From 9 tokens on (FULL): RP as large as the panels fill; one workgroup per CU streams as fast as two and has the
 // fewer loads of x                                 38400 x 7168, M = 12  90 (two per CU: 99)
@@ -414,9 +416,9 @@ ProjPlan proj_plan(int M, int N, int K, int epi, int wgs_per_cu) {
     else two = full, p.mode = K >= 12288 ? PROJ_PAIR : PROJ_FULL;
   } else if (one <= 4) {
     if (brief) p.RP = brief_rp;
-    else if (one == 3 || K > 8192) p.RP = 4;
+    else if (K >= 12288 || (one == 4 && K > 8192)) p.RP = 4;
     else if (K >= 6144) p.mode = PROJ_PAIR;
-    else two = true;
+    else two = one == 4;
   } else if (one <= 6) {
     if (brief) p.RP = 4, uneven = true;
     else p.RP = 2;

@@ -69,7 +69,7 @@ __device__ __forceinline__ f32x4 proj_sum(const f32x4* red, int lane) {
   return t;
 }
 
-template <int MODE, int MT, int RP, int D, int EPI, int TAG>
+template <int MODE, int MT, int RP, int D, int EPI, int PRIO>
 __global__ __launch_bounds__(PROJ_THREADS, RP * MT > 4 ? 2 : 4) void proj_kernel(ProjArgs a) {
   static_assert(MODE == PROJ_FULL || MT == 1, "two row tiles only with one token per column");
   static_assert(MODE != PROJ_HALF || RP == (EPI == PROJ_SWIGLU ? 2 : 1), "half panels are taken one unit at a time");
@@ -79,10 +79,8 @@ __global__ __launch_bounds__(PROJ_THREADS, RP * MT > 4 ? 2 : 4) void proj_kernel
   constexpr int NBUF = RP * MT <= 4 ? 2 : 1;            // two reduction buffers while they fit: one barrier per group
   __shared__ f32x4 red[NBUF][PROJ_WAVES][RP][MT][64];
   __shared__ float inv_sh[SPEC_MAX_TOKENS];
-  // The draft's waves issue first.  Beside a target whose long ranges keep a CU's memory queue full, the draft's short
-  // kernels waited for their turn at every load: a draft forward inside a step of two overlapped chains took 10.5 ms
-  // (3.1 alone) and the step 42.1 ms; with priority 5.2 and 40.7 (70B / 7B shapes, windows of 7).
-  if (TAG == 1) __builtin_amdgcn_s_setprio(3);
+  // Of two overlapped chains the favoured one issues first (runtime.hip, favour), from its first instruction on.
+  if (PRIO == 1) __builtin_amdgcn_s_setprio(3);
   const int w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), lane = threadIdx.x & 63;
   const int c = lane & 15, kb = lane >> 4;
   if (a.stamp && threadIdx.x == 0)
@@ -453,12 +451,12 @@ bool proj_plan_ok(const ProjPlan& p) {
   return false;
 }
 
-template <int EPI, int TAG>
+template <int EPI, int PRIO>
 static hipError_t launch_epi(const ProjPlan& p, const ProjArgs& a, hipStream_t st) {
   dim3 g(p.G), b(PROJ_THREADS);
 #define PROJ_GO(MODE, MT, RP, D)                                    \
   {                                                                 \
-    proj_kernel<MODE, MT, RP, D, EPI, TAG><<<g, b, 0, st>>>(a);     \
+    proj_kernel<MODE, MT, RP, D, EPI, PRIO><<<g, b, 0, st>>>(a);     \
     return hipGetLastError();                                       \
   }
   constexpr int SW = EPI == PROJ_SWIGLU ? 2 : 1;
@@ -488,19 +486,19 @@ static hipError_t launch_epi(const ProjPlan& p, const ProjArgs& a, hipStream_t s
   return hipErrorInvalidValue;      // nothing was launched
 }
 
-template <int TAG>
-static hipError_t launch_tag(const ProjPlan& p, const ProjArgs& a, hipStream_t st) {
-  if (p.epi == PROJ_STORE) return launch_epi<PROJ_STORE, TAG>(p, a, st);
-  if (p.epi == PROJ_RESID) return launch_epi<PROJ_RESID, TAG>(p, a, st);
-  return launch_epi<PROJ_SWIGLU, TAG>(p, a, st);
+template <int PRIO>
+static hipError_t launch_prio(const ProjPlan& p, const ProjArgs& a, hipStream_t st) {
+  if (p.epi == PROJ_STORE) return launch_epi<PROJ_STORE, PRIO>(p, a, st);
+  if (p.epi == PROJ_RESID) return launch_epi<PROJ_RESID, PRIO>(p, a, st);
+  return launch_epi<PROJ_SWIGLU, PRIO>(p, a, st);
 }
 
-hipError_t launch_proj(const ProjPlan& p, ProjArgs a, hipStream_t st, int tag) {
+hipError_t launch_proj(const ProjPlan& p, ProjArgs a, hipStream_t st, int prio) {
   if (!proj_plan_ok(p)) return hipErrorInvalidValue;
   a.M = p.M; a.N = p.N; a.K = p.K; a.steps = p.steps;
   a.per = p.units / p.G; a.rem = p.units % p.G;
-  if (tag == 0) return launch_tag<0>(p, a, st);
-  if (tag == 1) return launch_tag<1>(p, a, st);
+  if (prio == 0) return launch_prio<0>(p, a, st);
+  if (prio == 1) return launch_prio<1>(p, a, st);
   if (p.epi != PROJ_STORE) return hipErrorInvalidValue;      // stand-alone calls store
   return launch_epi<PROJ_STORE, 2>(p, a, st);
 }

@@ -59,9 +59,11 @@ struct ModelRt {
   float *partials = nullptr, *opart = nullptr, *mlpart = nullptr, *logits = nullptr;
   long long n_forwards = 0;
   int split_tokens = 0;           // context length the attention split count is sized for (fixed per context)
-  // captured forwards, keyed [tokens][logit mode 0/1/2][projection workgroups per CU][part]; part 0 = the first
-  // layers, 1 = all the rest, 2 + i = chunk i of the rest (forwards whose trailing chunks launch in another mode)
-  hipGraphExec_t graphs[SPEC_MAX_TOKENS + 1][3][3][SPEC_GRAPH_PARTS] = {};
+  bool raised = false;            // its projections' waves issue ahead of the other model's, see favour()
+  // captured forwards, keyed [tokens][logit mode 0/1/2][launch mode][part]; launch mode = projection workgroups per CU - 1,
+  // + 2 if raised; part 0 = the first layers, 1 = all the rest, 2 + i = chunk i of the rest (forwards whose trailing chunks
+  // launch in another mode)
+  hipGraphExec_t graphs[SPEC_MAX_TOKENS + 1][3][4][SPEC_GRAPH_PARTS] = {};
   // activation buffers of the dense prompt path, allocated at its first use for pf_cap tokens
   int pf_cap = 0;
   int* pf_tok = nullptr;
@@ -266,8 +268,32 @@ int prof_slot(spec_ctx* c, double bytes, unsigned long long** slot) {
 int run_proj(spec_ctx* c, int which, ModelRt& m, const ProjPlan& p, ProjArgs a) {
   int rc;
   if ((c->profile_flags & 1) && which == SPEC_TARGET && (rc = prof_slot(c, (double)p.weight_bytes(), &a.stamp))) return rc;
-  HIPCHK(launch_proj(p, a, m.stream, which));
+  HIPCHK(launch_proj(p, a, m.stream, m.raised ? 1 : 0));
   return SPEC_OK;
+}
+
+// Which of two overlapped chains has its projections' waves issue first on a CU (s_setprio; no sum depends on it): the draft's by
+// default.  Beside a target whose long ranges keep a CU's memory queue full its short kernels waited for their turn at every
+// load: a draft forward inside a step took 10.5 ms (3.1 alone) and the step 42.1 ms, with priority 5.2 and 40.7 (70B / 7B shapes,
+// windows of 7).  Where the target's kernels are short too (below 200 MB a layer; 103 MB in the small pair, 405 in 7B) neither
+// starves, and it is the chain that ends later that should not wait: with r = gamma draft passes over a target pass, both
+// estimated from their bytes and five launches a layer, us per step with the draft | neither | the target in front:
+//   24 / 4 layers, gamma 4, r 0.82  1169 | 1134 | 1112     12 / 4, gamma 2, 0.78  586 | 564 | 556    16 / 1, gamma 3, 0.38  663 | 659 | 642
+//   24 / 2, gamma 8, 1.00           1286 | 1227 | 1234     24 / 3, gamma 6, 0.99  1340 | 1286 | 1288    24 / 4, gamma 5, 1.02  1257 | 1219 | 1261
+//   20 / 4, gamma 6, 1.46           1299 | 1338 | 1375     12 / 4, gamma 8, 3.1   1572 | 1610 | 1642
+//   7B / 1B, gamma 2, target the longer chain by far: 3421 | 3506 | 3504
+void favour(spec_ctx* c, int gamma) {
+  auto layer_bytes = [](const spec_model_desc& d) {
+    return 2.0 * d.d_model * (2.0 * (d.n_heads + d.n_kv_heads) * d.head_dim + 3.0 * d.d_ffn);
+  };
+  auto pass_us = [&](const spec_model_desc& d) {
+    return d.n_layers * (15.0 + layer_bytes(d) / 6.5e6) + 2.0 * d.vocab * d.d_model / 6.5e6 + 15.0;
+  };
+  const spec_model_desc &t = c->m[SPEC_TARGET].d, &d = c->m[SPEC_DRAFT].d;
+  const double r = gamma * pass_us(d) / pass_us(t);
+  const bool brief = layer_bytes(t) < 200e6;
+  c->m[SPEC_TARGET].raised = brief && r < 0.95;
+  c->m[SPEC_DRAFT].raised = !brief || r > 1.2;
 }
 
 // Whether the projection of the normalised residual stream (QKV, gate/up, LM head) runs in K slices.  Only where it is
@@ -409,7 +435,7 @@ int forward(spec_ctx* c, int which, const TokenSrc& src, int logit_rows) {
     c->wgs = un.wgs;
     if (c->use_graphs && !(c->profile_flags & 1)) {
       const int lm = logit_rows == 0 ? 0 : (logit_rows >= M ? 2 : 1);
-      hipGraphExec_t& ge = m.graphs[M][lm][un.wgs][un.part];
+      hipGraphExec_t& ge = m.graphs[M][lm][un.wgs - 1 + (m.raised ? 2 : 0)][un.part];
       if (!ge) {
         hipError_t e = hipStreamBeginCapture(st, hipStreamCaptureModeRelaxed);
         if (e != hipSuccess) {
@@ -577,6 +603,7 @@ extern "C" int spec_init(const spec_config* cfg, const spec_model_desc* target, 
   if (c->ring_n > SPEC_RING_MAX) c->ring_n = SPEC_RING_MAX;
   rc = init_model(c->m[SPEC_TARGET], *target, *tw, *cfg, (hipStream_t)cfg->stream_target);
   if (!rc) rc = init_model(c->m[SPEC_DRAFT], *draft, *dw, *cfg, (hipStream_t)cfg->stream_draft);
+  favour(c, cfg->gamma_max);
   if (!rc) rc = dev_alloc(&c->qcache, (size_t)c->ring_n * target->vocab);
   if (!rc) rc = dev_alloc(&c->ring, (size_t)SPEC_RING_MAX);
   if (!rc) rc = dev_alloc(&c->accept_scratch, accept_scratch_floats(target->vocab));
@@ -1035,6 +1062,7 @@ extern "C" int spec_generate(spec_ctx* c, int algo, int gamma, int n_generate, i
   // 44); with whole-K ones and the draft's wave priority the modes are level there: the later chain ends at 41.0 ms with one,
   // 40.9 with two, 40.7 with one and the last 24 layers at two.
   if (c->wgs_opt < 0) c->wgs = ((algo >= 2) && (c->m[0].stream != c->m[1].stream) && gamma >= 6) ? SPEC_PEARL_WGS_PER_CU : 2;
+  if (algo >= 2) favour(c, gamma);
   int mode = c->mode;
   int produced = 0, rc = 0;
   long long steps = 0, accepted = 0, tested = 0, post_steps = 0;

@@ -90,6 +90,24 @@ __device__ __forceinline__ MaxIdx block_argmax(MaxIdx m, MaxIdx* sh) {
   return r;
 }
 
+// largest value of the workgroup (NaN counts as none), to every thread
+__device__ __forceinline__ float wave_max(float v) {
+  v = fmaxf(v, dpp_f<0x111, 0xf>(-INFINITY, v));
+  v = fmaxf(v, dpp_f<0x112, 0xf>(-INFINITY, v));
+  v = fmaxf(v, dpp_f<0x114, 0xf>(-INFINITY, v));
+  v = fmaxf(v, dpp_f<0x118, 0xf>(-INFINITY, v));
+  v = fmaxf(v, dpp_f<0x142, 0xa>(-INFINITY, v));
+  v = fmaxf(v, dpp_f<0x143, 0xc>(-INFINITY, v));
+  return __int_as_float(__builtin_amdgcn_readlane(__float_as_int(v), 63));
+}
+__device__ __forceinline__ float block_max(float v, float* sh) {
+  const int lane = threadIdx.x & 63;
+  v = wave_max(v);
+  if (lane == 0) sh[threadIdx.x >> 6] = v;
+  __syncthreads();
+  return wave_max(lane < SAMP_WAVES ? sh[lane] : -INFINITY);
+}
+
 __device__ __forceinline__ double block_sum_d(double v, double* sh) {
   const int lane = threadIdx.x & 63;
   v = wave_scan_d(v);
@@ -171,10 +189,30 @@ __device__ __forceinline__ MaxIdx reg_load(const float* __restrict__ row, int V,
   MaxIdx m;
   m.v = -INFINITY; m.i = 0x7fffffff;
   reg_fetch(row, V, g, __builtin_nanf(""), e);     // which wins no comparison
+  // a thread's ids ascend, so the larger value alone decides; where nothing is larger than -inf, the first that is -inf
 #pragma unroll
   for (int k = 0; k < CH; ++k)
 #pragma unroll
-    for (int i = 0; i < 4; ++i) m = better(m, e[k][i], g.id(k) + i);
+    for (int i = 0; i < 4; ++i) {
+      const bool take = e[k][i] > m.v;
+      m.v = take ? e[k][i] : m.v;
+      m.i = take ? g.id(k) + i : m.i;
+    }
+  if (m.i == 0x7fffffff && g.j0 < V) {
+#pragma unroll
+    for (int k = 0; k < CH; ++k)
+#pragma unroll
+      for (int i = 0; i < 4; ++i) m = better(m, e[k][i], g.id(k) + i);
+  }
+  return m;
+}
+// the largest value alone; beyond V e holds -inf, which has no mass whatever the largest value is
+template <int CH>
+__device__ __forceinline__ float reg_load_max(const float* __restrict__ row, int V, const RegGeom& g, f32x4 (&e)[CH]) {
+  float m = -INFINITY;
+  reg_fetch(row, V, g, -INFINITY, e);
+#pragma unroll
+  for (int k = 0; k < CH; ++k) m = fmaxf(fmaxf(m, fmaxf(e[k][0], e[k][1])), fmaxf(e[k][2], e[k][3]));
   return m;
 }
 
@@ -192,28 +230,19 @@ __device__ __forceinline__ MaxIdx row_argmax(const float* logits, int V, MaxIdx*
   return block_argmax(m, shm);
 }
 
-// arg-max of a row that fits the registers.  Up to two chunks per thread the plain loop is faster, it loads no chunk that is
-// not there (sample_row greedy, 1024 / 5216 ids: 2.3 / 2.7 us, 3.9 / 4.0 with all eight); from three on (32000 ids: 8.2 | 4.8)
-// all loads go out at once.
-__device__ __forceinline__ MaxIdx reg_argmax(const float* row, int V, const RegGeom& g, MaxIdx* shm) {
-  if (g.R <= 2) return row_argmax(row, V, shm);
-  f32x4 e[SAMP_CHUNKS_MAX];
-  return block_argmax(reg_load(row, V, g, e), shm);
-}
-
-// Loads the row once; returns the arg-max, sum_j exp(mult l_j - zmax) and e[k] = exp(mult l - zmax) (0 outside V).
-__device__ __forceinline__ void reg_softmax(const float* __restrict__ row, int V, float mult, const RegGeom& g,
-                                            f32x4 (&e)[SAMP_CHUNKS_MAX], MaxIdx& top, float& sum, MaxIdx* shm, double* shd) {
-  top = block_argmax(reg_load(row, V, g, e), shm);
-  const float zmax = top.v * mult;
+// Loads the row once; returns its maximum, sum_j exp(mult l_j - zmax) and e[k] = exp(mult l - zmax) (0 outside V).  What
+// `between` loads is under way while the sum is formed.
+template <int CH, typename F>
+__device__ __forceinline__ void reg_softmax(const float* __restrict__ row, int V, float mult, const RegGeom& g, f32x4 (&e)[CH],
+                                            float& top, float& sum, float* shm, double* shd, F between) {
+  top = block_max(reg_load_max(row, V, g, e), shm);
+  between();
+  const float zmax = top * mult;
   float acc = 0.f;
 #pragma unroll
-  for (int k = 0; k < SAMP_CHUNKS_MAX; ++k) {
+  for (int k = 0; k < CH; ++k) {
 #pragma unroll
-    for (int i = 0; i < 4; ++i) {
-      const float x = __expf(fmaf(e[k][i], mult, -zmax));
-      e[k][i] = ((k < g.R) & (g.id(k) + i < V)) ? x : 0.f;
-    }
+    for (int i = 0; i < 4; ++i) e[k][i] = __expf(fmaf(e[k][i], mult, -zmax));
     acc += (e[k][0] + e[k][1]) + (e[k][2] + e[k][3]);
   }
   sum = (float)block_sum_d((double)acc, shd);
@@ -225,14 +254,6 @@ __device__ __forceinline__ double sum4_d(f32x4 v) { return ((double)v[0] + (doub
 // id with mass if rounding lets the search run off its end, or if `clamp` asks for that one.  The wave has mass.
 template <int CH>
 __device__ __forceinline__ int wave_walk(const f32x4 (&e)[CH], int j0, int lane, double base, double target, bool clamp) {
-  int lastpos = -1;
-#pragma unroll
-  for (int k = 0; k < CH; ++k)
-#pragma unroll
-    for (int i = 0; i < 4; ++i)
-      lastpos = e[k][i] > 0.f ? j0 + 256 * k + i : lastpos;
-#pragma unroll
-  for (int o = 32; o > 0; o >>= 1) lastpos = max(lastpos, __shfl_xor(lastpos, o));
   int tok = -1;
 #pragma unroll
   for (int k = 0; k < CH; ++k) {
@@ -258,7 +279,15 @@ __device__ __forceinline__ int wave_walk(const f32x4 (&e)[CH], int j0, int lane,
     }
     base += tot;
   }
-  return tok >= 0 ? tok : lastpos;
+  if (tok >= 0) return tok;
+  int last = -1;
+#pragma unroll
+  for (int k = 0; k < CH; ++k)
+#pragma unroll
+    for (int i = 0; i < 4; ++i) last = e[k][i] > 0.f ? j0 + 256 * k + i : last;
+#pragma unroll
+  for (int o = 32; o > 0; o >>= 1) last = max(last, __shfl_xor(last, o));
+  return last;
 }
 
 // Inverse-CDF draw over the non-negative weights e[] (0 outside V): first the wave (scan of the 16 wave totals), then
@@ -296,18 +325,25 @@ __device__ __forceinline__ int reg_draw(const f32x4 (&e)[CH], const RegGeom& g, 
 }
 
 // ---- draft: q = softmax(mult*logits), x = invCDF(q, u) -------------------------------------
+// What bounds these kernels up to 32768 ids is the vector ALU of one compute unit (16 waves, a row's every id in each phase) and
+// the trips between them, so a kernel is built for 1, 2, 4 and 8 chunks of 4096 ids (a thread's work follows CH, not the ids that
+// are there), a draw looks for the largest value and not for its id, and nothing is worked out ahead for the case that rounding
+// runs off the end.  Draws from Python 25.1 -> 23.8 us (32000 ids), 24.4 -> 20.4 (8000); acceptance on the device, 5 rows of 32000 14.4 -> 11.4, of 5000
+// 14.7 -> 7.2, 2 rows of 1024 13.2 -> 5.9.
 // q_out may be the logits themselves: a workgroup has read all it needs of them before it writes.
+template <int CH>
 __global__ __launch_bounds__(SAMP_THREADS) void sample_row_reg_kernel(const float* logits, int V, float mult, int greedy,
                                                                       float u, float* q_out, int* __restrict__ tok_out) {
   __shared__ MaxIdx shm[SAMP_WAVES];
+  __shared__ float shf[SAMP_WAVES];
   __shared__ double shd[SAMP_WAVES];
   __shared__ int shi[1];
   const RegGeom g = reg_geom(V);
-  MaxIdx top;
+  f32x4 e[CH];
   if (greedy) {
-    top = reg_argmax(logits, V, g, shm);
+    const MaxIdx top = block_argmax(reg_load(logits, V, g, e), shm);
 #pragma unroll
-    for (int k = 0; k < SAMP_CHUNKS_MAX; ++k) {
+    for (int k = 0; k < CH; ++k) {
       f32x4 o;
 #pragma unroll
       for (int i = 0; i < 4; ++i) o[i] = g.id(k) + i == top.i ? 1.0f : 0.0f;
@@ -316,12 +352,11 @@ __global__ __launch_bounds__(SAMP_THREADS) void sample_row_reg_kernel(const floa
     if (threadIdx.x == 0) tok_out[0] = top.i;
     return;
   }
-  f32x4 e[SAMP_CHUNKS_MAX];
-  float sum;
-  reg_softmax(logits, V, mult, g, e, top, sum, shm, shd);
+  float top, sum;
+  reg_softmax(logits, V, mult, g, e, top, sum, shf, shd, [] {});
   const float inv = 1.0f / sum;
 #pragma unroll
-  for (int k = 0; k < SAMP_CHUNKS_MAX; ++k) {
+  for (int k = 0; k < CH; ++k) {
 #pragma unroll
     for (int i = 0; i < 4; ++i) e[k][i] *= inv;
     if (k < g.R) store4(q_out, g.id(k), V, e[k]);
@@ -334,21 +369,24 @@ __global__ __launch_bounds__(SAMP_THREADS) void sample_row_reg_kernel(const floa
 // The draft's q and the target's p of one row are the same bits if its logits are: both sides form the row's maximum and sum
 // with the functions of this section, in the same order.  A row is cut into pieces of SAMP_PIECE ids; a piece has a maximum
 // and a sum of exp relative to it, and the row's are put together from the pieces'.
-struct PieceStat { float top, sum; int i; };     // maximum, sum of exp(mult l - mult top), arg-max in the row
+struct PieceStat { float top, sum; int i; };     // maximum, sum of exp(mult l - mult top); greedy: arg-max in the row
 __device__ __forceinline__ int row_pieces(int V) { return (V + SAMP_PIECE - 1) / SAMP_PIECE; }
 __device__ __forceinline__ float long_prob(float l, float mult, float zmax, float sum) { return expf(fmaf(l, mult, -zmax)) / sum; }
 // Piece p of a row by the whole workgroup, to every thread (barriers inside).
-__device__ __forceinline__ PieceStat piece_stat(const float* row, int V, int p, float mult, int greedy, MaxIdx* shm, double* shd) {
+__device__ __forceinline__ PieceStat piece_stat(const float* row, int V, int p, float mult, int greedy, MaxIdx* shm, float* shf, double* shd) {
   const int first = p * SAMP_PIECE, n = min(SAMP_PIECE, V - first);
   const RegGeom g = reg_geom(SAMP_PIECE);
   f32x4 e[SAMP_PIECE_CHUNKS];
-  const MaxIdx top = block_argmax(reg_load(row + first, n, g, e), shm);
   PieceStat r;
-  r.top = top.v;
-  r.i = top.i == 0x7fffffff ? top.i : first + top.i;
   r.sum = 0.f;
-  if (!greedy) {
-    const float zmax = top.v * mult;
+  if (greedy) {
+    const MaxIdx top = block_argmax(reg_load(row + first, n, g, e), shm);
+    r.top = top.v;
+    r.i = top.i == 0x7fffffff ? top.i : first + top.i;
+  } else {
+    r.top = block_max(reg_load_max(row + first, n, g, e), shf);
+    r.i = first;                     // a draw has no use for it
+    const float zmax = r.top * mult;
     float acc = 0.f;
 #pragma unroll
     for (int k = 0; k < SAMP_PIECE_CHUNKS; ++k) {
@@ -387,8 +425,9 @@ __device__ __forceinline__ MaxIdx row_stat(const PieceStat* s, int P, float mult
 __global__ __launch_bounds__(SAMP_THREADS) void piece_stat_kernel(const float* __restrict__ logits, int V, float mult,
                                                                   int greedy, PieceStat* __restrict__ stats) {
   __shared__ MaxIdx shm[SAMP_WAVES];
+  __shared__ float shf[SAMP_WAVES];
   __shared__ double shd[SAMP_WAVES];
-  const PieceStat s = piece_stat(logits + (size_t)blockIdx.y * V, V, blockIdx.x, mult, greedy, shm, shd);
+  const PieceStat s = piece_stat(logits + (size_t)blockIdx.y * V, V, blockIdx.x, mult, greedy, shm, shf, shd);
   if (threadIdx.x == 0) stats[(size_t)blockIdx.y * gridDim.x + blockIdx.x] = s;
 }
 
@@ -427,11 +466,12 @@ __global__ __launch_bounds__(SAMP_THREADS) void sample_greedy_kernel(const float
 // q in the place of its logits (nowhere to leave statistics): one workgroup, piece after piece, the same sums
 __global__ __launch_bounds__(SAMP_THREADS) void sample_in_place_kernel(const float* logits, int V, float mult, float* q_out) {
   __shared__ MaxIdx shm[SAMP_WAVES];
+  __shared__ float shf[SAMP_WAVES];
   __shared__ double shd[SAMP_WAVES];
   const float zmax = row_argmax(logits, V, shm).v * mult;
   double t = 0.0;
   for (int p = 0; p < row_pieces(V); ++p) {
-    const PieceStat s = piece_stat(logits, V, p, mult, 0, shm, shd);
+    const PieceStat s = piece_stat(logits, V, p, mult, 0, shm, shf, shd);
     if ((p & 63) == (threadIdx.x & 63)) t += piece_term(s, mult, (double)zmax);
   }
   const float sum = (float)lane_d(wave_scan_d(t), 63);
@@ -503,10 +543,21 @@ __global__ __launch_bounds__(SAMP_THREADS) void draw_kernel(const float* __restr
   if (threadIdx.x == 0) tok_out[0] = tok;
 }
 
+// GO(CH): the kernel for rows of V ids, V <= SAMP_REG_VOCAB_MAX
+#define SAMP_BY_CHUNKS(V, GO)                               \
+  switch (((V) + 4 * SAMP_THREADS - 1) / (4 * SAMP_THREADS)) { \
+    case 1: GO(1); break;                                   \
+    case 2: GO(2); break;                                   \
+    case 3: case 4: GO(4); break;                           \
+    default: GO(8); break;                                  \
+  }
+static_assert(SAMP_CHUNKS_MAX == 8, "every length up to SAMP_REG_VOCAB_MAX has its kernel");
 hipError_t launch_sample_row(const float* logits, int V, float mult, int greedy, float u, float* q_out, int* tok_out,
                              hipStream_t st) {
   if (V <= SAMP_REG_VOCAB_MAX) {
-    sample_row_reg_kernel<<<1, SAMP_THREADS, 0, st>>>(logits, V, mult, greedy, u, q_out, tok_out);
+#define SAMP_GO(CH) sample_row_reg_kernel<CH><<<1, SAMP_THREADS, 0, st>>>(logits, V, mult, greedy, u, q_out, tok_out)
+    SAMP_BY_CHUNKS(V, SAMP_GO)
+#undef SAMP_GO
     return hipGetLastError();
   }
   const bool in_place = q_out < logits + V && logits < q_out + V;
@@ -540,48 +591,59 @@ __host__ __device__ static constexpr size_t accept_weights_at(int V) { return ac
 static constexpr size_t accept_scratch_floats_of(int V) { return accept_weights_at(V) + (size_t)V; }
 size_t accept_scratch_floats(int V) { return accept_scratch_floats_of(V); }
 
-// what row i's test needs from its statistics, by one thread
-__device__ __forceinline__ int accept_test(const float* __restrict__ row, int i, int V, float mult, int greedy, float top,
-                                           float sum, int amax, const float* __restrict__ qcache,
-                                           const int* __restrict__ ring, const int* __restrict__ x_direct,
-                                           const AcceptArgs& a) {
+// The draft that row i tests (0 where it tests none), its logit and its q.  A kernel asks for them long before the test: an id and
+// then two values behind it are two round trips to memory.
+__device__ __forceinline__ int accept_id(int i, const int* __restrict__ ring, const int* __restrict__ x_direct, const AcceptArgs& a) {
+  return i >= a.n_test ? 0 : x_direct ? x_direct[i] : ring[a.slot[i]];
+}
+struct AcceptPair {
+  float l = 0.f, q = 0.f;
+  __device__ __forceinline__ void load(const float* __restrict__ row, int i, int x, int V, const float* __restrict__ qcache,
+                                       const int* __restrict__ x_direct, const AcceptArgs& a) {
+    if (i >= a.n_test) return;
+    l = row[x];
+    q = qcache[(size_t)(x_direct ? i : a.slot[i]) * V + x];
+  }
+};
+// row i's test from its statistics, by one thread
+__device__ __forceinline__ int accept_test(int x, const AcceptPair& at, int i, int V, float mult, int greedy, float top, float sum,
+                                           int amax, const AcceptArgs& a) {
   if (i >= a.n_test) return 0;
-  const int x = x_direct ? x_direct[i] : ring[a.slot[i]];
-  const float* qrow = x_direct ? qcache + (size_t)i * V : qcache + (size_t)a.slot[i] * V;
   int acc;
   if (greedy) {
     acc = x == amax;
   } else {
-    const float px = V <= SAMP_REG_VOCAB_MAX ? reg_prob(row[x], mult, top * mult, 1.0f / sum) : long_prob(row[x], mult, top * mult, sum);
-    acc = (double)a.r[i] * (double)qrow[x] <= (double)px;
+    const float px = V <= SAMP_REG_VOCAB_MAX ? reg_prob(at.l, mult, top * mult, 1.0f / sum) : long_prob(at.l, mult, top * mult, sum);
+    acc = (double)a.r[i] * (double)at.q <= (double)px;
   }
   if (a.force_mask >= 0) acc = (int)((a.force_mask >> i) & 1);
   return acc;
 }
 
+template <int CH>
 __global__ __launch_bounds__(SAMP_THREADS) void accept_rows_kernel(const float* __restrict__ logits, int V, float mult,
                                                                    int greedy, const float* __restrict__ qcache,
                                                                    const int* __restrict__ ring,
                                                                    const int* __restrict__ x_direct, AcceptArgs a,
                                                                    float* __restrict__ stats) {
   __shared__ MaxIdx shm[SAMP_WAVES];
+  __shared__ float shf[SAMP_WAVES];
   __shared__ double shd[SAMP_WAVES];
   const int i = blockIdx.x;
   const float* row = logits + (size_t)i * V;
   const RegGeom g = reg_geom(V);
-  MaxIdx top;
+  const int x = accept_id(i, ring, x_direct, a);
+  AcceptPair at;
+  MaxIdx top = {0.f, 0};
   float sum = 1.f;
-  if (greedy) {
-    top = reg_argmax(row, V, g, shm);
-  } else {
-    f32x4 e[SAMP_CHUNKS_MAX];
-    reg_softmax(row, V, mult, g, e, top, sum, shm, shd);
-  }
+  f32x4 e[CH];
+  if (greedy) top = block_argmax(reg_load(row, V, g, e), shm);
+  else reg_softmax(row, V, mult, g, e, top.v, sum, shf, shd, [&] { at.load(row, i, x, V, qcache, x_direct, a); });
   if (threadIdx.x == 0) {
     stats[i * 4 + 0] = top.v;
     stats[i * 4 + 1] = sum;
     stats[i * 4 + 2] = __int_as_float(top.i);
-    stats[i * 4 + 3] = __int_as_float(accept_test(row, i, V, mult, greedy, top.v, sum, top.i, qcache, ring, x_direct, a));
+    stats[i * 4 + 3] = __int_as_float(accept_test(x, at, i, V, mult, greedy, top.v, sum, top.i, a));
   }
 }
 
@@ -593,12 +655,15 @@ __device__ void accept_combine(const float* __restrict__ logits, int V, float mu
   const int lane = threadIdx.x & 63, P = accept_pieces(V);
   for (int i = threadIdx.x >> 6; i < a.n_rows; i += SAMP_WAVES) {
     float sum;
+    const int x = accept_id(i, ring, x_direct, a);
+    AcceptPair at;
+    if (!greedy) at.load(logits + (size_t)i * V, i, x, V, qcache, x_direct, a);
     const MaxIdx top = row_stat(reinterpret_cast<const PieceStat*>(scratch + 256) + (size_t)i * P, P, mult, greedy, &sum);
     if (lane == 0) {
       st[i * 4 + 0] = top.v;
       st[i * 4 + 1] = sum;
       st[i * 4 + 2] = __int_as_float(top.i);
-      st[i * 4 + 3] = __int_as_float(accept_test(logits + (size_t)i * V, i, V, mult, greedy, top.v, sum, top.i, qcache, ring, x_direct, a));
+      st[i * 4 + 3] = __int_as_float(accept_test(x, at, i, V, mult, greedy, top.v, sum, top.i, a));
     }
   }
   __syncthreads();
@@ -629,6 +694,7 @@ __global__ __launch_bounds__(SAMP_THREADS) void accept_weights_kernel(const floa
   __shared__ double shd[SAMP_WAVES];
   __shared__ float st[4 * SPEC_MAX_TOKENS];
   accept_combine(logits, V, mult, 0, qcache, ring, x_direct, a, scratch, st);
+  if (blockIdx.x == 0 && threadIdx.x < 4 * a.n_rows) scratch[threadIdx.x] = st[threadIdx.x];     // for accept_finish_kernel
   bool off_path;
   const int n = accept_count(a, ring, st, &off_path);
   const bool rejected = !off_path && n < a.n_test;
@@ -649,7 +715,7 @@ __global__ __launch_bounds__(SAMP_THREADS) void accept_weights_kernel(const floa
 #pragma unroll
     for (int i = 0; i < 4; ++i) {
       const float pv = long_prob(e[k][i], mult, zmax, sum);
-      e[k][i] = g.id(k) + i < m ? (qrow ? (float)fmax((double)pv - (double)q[k][i], 0.0) : pv) : 0.f;
+      e[k][i] = g.id(k) + i < m ? (qrow ? fmaxf(pv - q[k][i], 0.f) : pv) : 0.f;
     }
     store4(wbuf, g.id(k), m, e[k]);
     mine += sum4_d(e[k]);
@@ -658,8 +724,9 @@ __global__ __launch_bounds__(SAMP_THREADS) void accept_weights_kernel(const floa
   if (threadIdx.x == 0) reinterpret_cast<double*>(scratch + accept_sums_at(V))[p] = t;
 }
 
-// The draw over row n in registers: residual weights max(0, p - q), or p itself (qrow == nullptr; also where the
-// residual has no mass in floating point).
+// The draw over row n in registers: residual weights max(0, p - q) (one rounding of the exact difference), or p itself
+// (qrow == nullptr; also where the residual has no mass in floating point).
+template <int CH>
 __device__ __forceinline__ int accept_draw(const float* __restrict__ row, const float* __restrict__ qrow, int V, float mult,
                                            float zmax, float sum, float u, double* shd, int* shi) {
   const float inv = 1.0f / sum;
@@ -668,11 +735,11 @@ __device__ __forceinline__ int accept_draw(const float* __restrict__ row, const 
   for (int attempt = 0; attempt < 2; ++attempt) {
     RegGeom g = reg_geom(V);
     asm volatile("" : "+v"(g.j0));     // keeps the addresses of both rows from being worked out for both attempts
-    f32x4 e[SAMP_CHUNKS_MAX];
-    reg_fetch(row, V, g, 0.f, e);
+    f32x4 e[CH];
+    reg_fetch(row, V, g, -INFINITY, e);
+    constexpr int H = CH < 4 ? 1 : CH / 4;
 #pragma unroll
-    for (int h = 0; h < 4; ++h) {      // q in parts: registers
-      constexpr int H = SAMP_CHUNKS_MAX / 4;
+    for (int h = 0; h < CH / H; ++h) {      // q in parts: registers
       RegGeom gh = g;
       gh.j0 = g.id(h * H);
       gh.R = g.R - h * H;
@@ -684,8 +751,7 @@ __device__ __forceinline__ int accept_draw(const float* __restrict__ row, const 
 #pragma unroll
         for (int i = 0; i < 4; ++i) {
           const float p = reg_prob(e[h * H + k][i], mult, zmax, inv);
-          const float w = qrow ? (float)fmax((double)p - (double)q[k][i], 0.0) : p;
-          e[h * H + k][i] = ((k < gh.R) & (gh.id(k) + i < V)) ? w : 0.f;
+          e[h * H + k][i] = qrow ? fmaxf(p - q[k][i], 0.f) : p;
         }
     }
     double total = 0.0;
@@ -736,8 +802,8 @@ __device__ __forceinline__ int accept_draw_long(const float* __restrict__ row, b
 }
 
 // One workgroup: n = first rejection; draw from norm(max(0, p_n - q_n)) (from p_n if that has no
-// mass), or the bonus / autoregressive token from the row after the last test.
-template <bool LONG>
+// mass), or the bonus / autoregressive token from the row after the last test.  CH: chunks of a row, 0 for a long one.
+template <int CH>
 __global__ __launch_bounds__(SAMP_THREADS) void accept_finish_kernel(const float* __restrict__ logits, int V,
                                                                      float mult, int greedy,
                                                                      const float* __restrict__ qcache,
@@ -749,8 +815,9 @@ __global__ __launch_bounds__(SAMP_THREADS) void accept_finish_kernel(const float
   __shared__ double shd[SAMP_WAVES];
   __shared__ int shi[1];
   __shared__ float st[4 * SPEC_MAX_TOKENS];
-  if (LONG) accept_combine(logits, V, mult, greedy, qcache, ring, x_direct, a, scratch, st);
-  const float* stats = LONG ? st : scratch;
+  constexpr bool LONG = CH == 0;
+  if (LONG && greedy) accept_combine(logits, V, mult, greedy, qcache, ring, x_direct, a, scratch, st);
+  const float* stats = LONG && greedy ? st : scratch;
   bool off_path;
   const int n = accept_count(a, ring, stats, &off_path);
   const bool rejected = !off_path && n < a.n_test;
@@ -760,12 +827,12 @@ __global__ __launch_bounds__(SAMP_THREADS) void accept_finish_kernel(const float
     const float zmax = stats[n * 4 + 0] * mult, sum = stats[n * 4 + 1];
     if (greedy) {
       token = __float_as_int(stats[n * 4 + 2]);   // residual of two one-hots, or the one-hot itself, is the target's arg-max
-    } else if (LONG) {
+    } else if constexpr (LONG) {
       token = accept_draw_long(row, rejected, V, mult, zmax, sum, a.u_resample, scratch, shd, shi);
     } else {
       const float* qrow = nullptr;
       if (rejected) qrow = x_direct ? qcache + (size_t)n * V : qcache + (size_t)a.slot[n] * V;
-      token = accept_draw(row, qrow, V, mult, zmax, sum, a.u_resample, shd, shi);
+      token = accept_draw<CH>(row, qrow, V, mult, zmax, sum, a.u_resample, shd, shi);
     }
   }
   if (threadIdx.x == 0) {
@@ -787,7 +854,9 @@ hipError_t launch_accept(const float* logits, int V, float mult, int greedy, con
   if (a.guided && !ring) return hipErrorInvalidValue;   // guided tests compare ring tokens with the guesses
   const int P = accept_pieces(V);
   if (!P) {
-    accept_rows_kernel<<<a.n_rows, SAMP_THREADS, 0, st>>>(logits, V, mult, greedy, qcache, ring, x_direct, a, scratch);
+#define ROWS_GO(CH) accept_rows_kernel<CH><<<a.n_rows, SAMP_THREADS, 0, st>>>(logits, V, mult, greedy, qcache, ring, x_direct, a, scratch)
+    SAMP_BY_CHUNKS(V, ROWS_GO)
+#undef ROWS_GO
   } else {
     piece_stat_kernel<<<dim3(P, a.n_rows), SAMP_THREADS, 0, st>>>(logits, V, mult, greedy, reinterpret_cast<PieceStat*>(scratch + 256));
     hipError_t e = hipGetLastError();
@@ -796,12 +865,11 @@ hipError_t launch_accept(const float* logits, int V, float mult, int greedy, con
   }
   hipError_t e = hipGetLastError();
   if (e != hipSuccess) return e;
-  if (P)
-    accept_finish_kernel<true><<<1, SAMP_THREADS, 0, st>>>(logits, V, mult, greedy, qcache, ring, x_direct, a, scratch,
-                                                           result_dev, out2);
-  else
-    accept_finish_kernel<false><<<1, SAMP_THREADS, 0, st>>>(logits, V, mult, greedy, qcache, ring, x_direct, a, scratch,
-                                                            result_dev, out2);
+#define FINISH_GO(CH) \
+  accept_finish_kernel<CH><<<1, SAMP_THREADS, 0, st>>>(logits, V, mult, greedy, qcache, ring, x_direct, a, scratch, result_dev, out2)
+  if (P) FINISH_GO(0);
+  else SAMP_BY_CHUNKS(V, FINISH_GO)
+#undef FINISH_GO
   return hipGetLastError();
 }
 

@@ -231,11 +231,14 @@ size_t spec_packed_bytes(int N, int K);
 
 /* y[M][N] (fp32, device) = x[M][K] (bf16 row-major, device) * W^T with W panel-packed.
  * The kernels the forward uses, chosen by the shape: the whole K axis in a workgroup, or K slices and a second launch that
- * adds them.  `work_dev` needs spec_gemm_workspace_bytes(M, N, K) either way; operands that start off a 16-byte address take
+ * adds them.  `work_dev` needs spec_gemm_workspace_bytes(M, N, K) unless spec_gemm_uses_work says 0; operands that start off a 16-byte address take
  * the slices.  M <= SPEC_MAX_TOKENS.  Asynchronous on `stream`. */
 int spec_gemm(float* y_dev, const void* x_dev, const void* w_packed_dev, int M, int N, int K,
               void* work_dev, void* stream);
 size_t spec_gemm_workspace_bytes(int M, int N, int K);
+/* 1 if spec_gemm with these operands (only their addresses matter) writes to work_dev, 0 if any pointer that is not null will
+ * do, SPEC_E_INVAL for shapes it refuses. */
+int spec_gemm_uses_work(const void* x_dev, const void* w_packed_dev, int M, int N, int K);
 /* How the kernel with K slices divides its work (host-only, no GPU needed): out6 = { S = K slices, most K steps of 32 a wave
  * takes (at most 8), Gs = groups of workgroups along N, number of 16-row panels, number of K steps, 16-row tiles
  * of x (1 or 2) }.  workgroups_per_cu is 1 or 2; S does not depend on it.  SPEC_E_INVAL for shapes spec_gemm

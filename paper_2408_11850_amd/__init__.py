@@ -82,6 +82,7 @@ SIGNATURES = {
     "spec_gemm_plan_query": (C.c_int, [C.c_int, C.c_int, C.c_int, C.c_int, C.POINTER(C.c_int)]),
     "spec_gemm": (C.c_int, [_P, _P, _P, C.c_int, C.c_int, C.c_int, _P, _P]),
     "spec_gemm_workspace_bytes": (C.c_size_t, [C.c_int, C.c_int, C.c_int]),
+    "spec_gemm_uses_work": (C.c_int, [_P, _P, C.c_int, C.c_int, C.c_int]),
     "spec_gemm_partials": (C.c_int, [_P, _P, C.c_int, C.c_int, C.c_int, _P, _P]),
     "spec_dense_gemm": (C.c_int, [_P, _P, _P, _P, C.c_int, C.c_int, C.c_int, C.c_int, _P]),
     "spec_read_probe": (C.c_int, [_P, C.c_size_t, _P, _P]),

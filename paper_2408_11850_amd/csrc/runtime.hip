@@ -1374,13 +1374,20 @@ extern "C" int spec_gemm_partials(const void* x, const void* w, int M, int N, in
   HIPCHK(launch_gemm_partials(p, (const bf16*)x, w, (float*)work, (hipStream_t)stream, 2));
   return SPEC_OK;
 }
+// operands off the 16-byte grid stay with K slices, whose global loads take any address of an element
+static bool gemm_whole_k(const void* x, const void* w, int M, int N, int K) {
+  return proj_whole_k(M, N, K) && (((uintptr_t)x | (uintptr_t)w) & 15) == 0;
+}
+extern "C" int spec_gemm_uses_work(const void* x, const void* w, int M, int N, int K) {
+  const int rc = check_gemm_args(M, N, K);
+  return rc ? rc : gemm_whole_k(x, w, M, N, K) ? 0 : 1;
+}
 extern "C" int spec_gemm(float* y, const void* x, const void* w, int M, int N, int K, void* work, void* stream) {
   if (!y) FAIL(SPEC_E_INVAL, "null pointer");
   if (!x || !w || !work) FAIL(SPEC_E_INVAL, "null pointer");
   int rc = check_gemm_args(M, N, K);
   if (rc) return rc;
-  // operands off the 16-byte grid stay with K slices, whose global loads take any address of an element
-  if (proj_whole_k(M, N, K) && (((uintptr_t)x | (uintptr_t)w) & 15) == 0) {
+  if (gemm_whole_k(x, w, M, N, K)) {
     ProjArgs a = {};
     a.x = (const bf16*)x; a.w = w; a.y = y;
     HIPCHK(launch_proj(proj_plan(M, N, K, PROJ_STORE, 2), a, (hipStream_t)stream, 2));

@@ -196,20 +196,6 @@ struct AttnChunk {                      // K fragments of 32 positions, and V's 
 };
 static_assert(SPEC_PAGE_TOKENS == 64, "two chunks of 32 positions per page");
 
-// over the lanes c, c + 16, c + 32, c + 48: swaps of 16 and 32 lanes between registers, no trip through LDS
-__device__ __forceinline__ float groups_max(float x) {
-  auto a = __builtin_amdgcn_permlane16_swap(__float_as_uint(x), __float_as_uint(x), false, false);
-  x = fmaxf(__uint_as_float(a[0]), __uint_as_float(a[1]));
-  auto b = __builtin_amdgcn_permlane32_swap(__float_as_uint(x), __float_as_uint(x), false, false);
-  return fmaxf(__uint_as_float(b[0]), __uint_as_float(b[1]));
-}
-__device__ __forceinline__ float groups_sum(float x) {
-  auto a = __builtin_amdgcn_permlane16_swap(__float_as_uint(x), __float_as_uint(x), false, false);
-  x = __uint_as_float(a[0]) + __uint_as_float(a[1]);
-  auto b = __builtin_amdgcn_permlane32_swap(__float_as_uint(x), __float_as_uint(x), false, false);
-  return __uint_as_float(b[0]) + __uint_as_float(b[1]);
-}
-
 // scores of a chunk: s[t][i] = position pos0 + 16 t + 4 g4 + i for query row c
 template <int DH, int DV, typename Q>
 __device__ __forceinline__ void attn_scores(f32x4 (&s)[2], const AttnChunk<DH, DV>& kv, const Q& q) {

@@ -707,25 +707,32 @@ hipError_t launch_dense_qkv_rope(const bf16* x, const void* wp, int M, int K, bf
 // ---------------------------------------------------------------------------------------------------------
 // Causal attention of a block of M prompt tokens over the paged KV cache (positions 0 .. len + M - 1, the
 // block's own K / V already appended).  Rows are the M*G (token, query head) pairs of one KV head, token-major,
-// as in the decode kernel; a workgroup of 8 waves owns 256 consecutive rows, a wave 2 tiles of 16 (two waves
-// per SIMD, so that one wave's softmax arithmetic overlaps the other's MFMAs).  K and V pages are in MFMA
-// operand order, so every 64-position chunk (= one page) is 32 KiB (head_dim 128) that the workgroup brings
+// as in the decode kernel; a workgroup of 8 waves owns 128 consecutive rows, a wave one tile of 16, and two
+// workgroups share a CU, so that four waves per SIMD cover each other's softmax arithmetic and waits.  K and V pages
+// are in MFMA operand order, so every 64-position chunk (= one page) is 32 KiB (head_dim 128) that the workgroup brings
 // into LDS once with LDS-direct loads and each wave reads as ready-made fragments: S^T = K Q^T, online softmax
 // per query row in the base-2 domain, O^T += V^T P^T.  Chunks beyond the last position a workgroup's rows may
 // see are never touched (causal skip), and the workgroups with the longest ranges are scheduled first.
+//
+// The vector ALU bounds it, about 1900 cycles of it per chunk of two tiles beside 1024 of MFMAs: so only chunks on the
+// diagonal are masked, the scale goes into the exponent's fma, and the accumulator is rescaled where a maximum moved
+// (traced, two tiles per wave: 64 heads over 8, 4095 tokens 499 -> 442 us; 32 heads, 1023 tokens 37.6 -> 34.0).  Waves
+// of one tile instead of two, twice as many of them on a CU: 442 -> 377 and 34.0 -> 31.6; 16 heads, 511 tokens 16.4 ->
+// 15.0, 1500 tokens 40.6 -> 35.7; 32 heads over 4 of head_dim 64, 4000 tokens 158 -> 130.
 // ---------------------------------------------------------------------------------------------------------
-#define PA_QT 2                                  // 16-row tiles per wave
+#define PA_WAVES 8                               // one 16-row tile each
+#define PA_ROWS (PA_WAVES * 16)
 #define PA_STAGES 2
 #define PA_NEG_BIG (-1.0e30f)
 
 // Brings chunk `ch` (64 positions = page block_table[ch]) of one KV head into an LDS stage.  Block b of a chunk:
 // b < KB -> K block b (lane-linear in the page), else V block b - KB, whose lane (c, g4) sits at byte
 // c*64 + g4*16 of the block.
-template <int DH, int WAVES>
+template <int DH>
 __device__ __forceinline__ void pa_issue(const bf16* __restrict__ pool, const int* __restrict__ block_table,
                                          const KvGeom& g, int layer, int kvh, int ch, u32x4* lds_stage, int w,
                                          int lane) {
-  constexpr int KB = 4 * (DH / 32), VB = 2 * (DH / 16), LPW = (KB + VB) / WAVES;
+  constexpr int KB = 4 * (DH / 32), VB = 2 * (DH / 16), LPW = (KB + VB) / PA_WAVES;
   const int c = lane & 15, g4 = lane >> 4;
   const int page = block_table[ch];
   const u32x4* kblk = reinterpret_cast<const u32x4*>(pool + g.offset(page, layer, 0, kvh)) + lane;
@@ -739,14 +746,13 @@ __device__ __forceinline__ void pa_issue(const bf16* __restrict__ pool, const in
   }
 }
 
-template <int DH, int WAVES>
-__global__ __launch_bounds__(WAVES * 64, 2) void prefill_attn_kernel(const bf16* __restrict__ q,
+template <int DH>
+__global__ __launch_bounds__(PA_WAVES * 64, 4) void prefill_attn_kernel(const bf16* __restrict__ q,
                                                                         const bf16* __restrict__ pool,
                                                                         const int* __restrict__ block_table,
                                                                         const int* __restrict__ len_ptr, KvGeom g,
                                                                         int layer, int M, int Hq, float scale_log2e,
                                                                         bf16* __restrict__ out) {
-  constexpr int PA_ROWS = WAVES * PA_QT * 16;    // rows per workgroup
   constexpr int KS = DH / 32;                    // K steps per 16-position tile
   constexpr int KB = 4 * KS;                     // K blocks (1 KiB) per chunk
   constexpr int VB = 2 * (DH / 16);              // V blocks per chunk
@@ -762,126 +768,98 @@ __global__ __launch_bounds__(WAVES * 64, 2) void prefill_attn_kernel(const bf16*
   int rlast = r0 + PA_ROWS - 1;
   if (rlast > R - 1) rlast = R - 1;
   const int nch = ((len + rlast / G) >> 6) + 1;  // chunks this workgroup needs
-  int wlast = r0 + (w + 1) * PA_QT * 16 - 1;
+  int wlast = r0 + (w + 1) * 16 - 1;
   if (wlast > R - 1) wlast = R - 1;
-  const int wave_limit = (r0 + w * PA_QT * 16 < R) ? len + wlast / G : -1;
+  const int wave_limit = (r0 + w * 16 < R) ? len + wlast / G : -1;
+  const int wave_open = len + (r0 + w * 16) / G;     // positions up to here are visible to all of the wave's rows
 
-  // per q tile: row of this lane, its visibility limit and its Q fragments.  Rows past the end behave like
+  // row of this lane, its visibility limit and its Q fragments.  Rows past the end behave like
   // unmasked rows of zeros (finite arithmetic, never stored).
-  int limit[PA_QT];
-  bf16x8 qf[PA_QT][KS];
+  const int Rr = r0 + w * 16 + c;
+  const bool valid = Rr < R;
+  const int tok = valid ? Rr / G : 0;
+  const int head = kvh * G + (valid ? Rr % G : 0);
+  const int limit = valid ? len + tok : 0x7fffffff;
+  bf16x8 qf[KS];
 #pragma unroll
-  for (int t = 0; t < PA_QT; ++t) {
-    const int Rr = r0 + (w * PA_QT + t) * 16 + c;
-    const bool valid = Rr < R;
-    const int tok = valid ? Rr / G : 0;
-    const int head = kvh * G + (valid ? Rr % G : 0);
-    limit[t] = valid ? len + tok : 0x7fffffff;
-#pragma unroll
-    for (int j = 0; j < KS; ++j) {
-      u32x4 v = {0u, 0u, 0u, 0u};
-      if (valid) v = *reinterpret_cast<const u32x4*>(q + ((size_t)tok * Hq + head) * DH + j * 32 + g4 * 8);
-      qf[t][j] = __builtin_bit_cast(bf16x8, v);
-    }
+  for (int j = 0; j < KS; ++j) {
+    u32x4 v = {0u, 0u, 0u, 0u};
+    if (valid) v = *reinterpret_cast<const u32x4*>(q + ((size_t)tok * Hq + head) * DH + j * 32 + g4 * 8);
+    qf[j] = __builtin_bit_cast(bf16x8, v);
   }
 
-  float m_run[PA_QT], l_run[PA_QT];             // running max (base-2 domain) and sum per query row
-  f32x4 o[PA_QT][DH / 16];
+  float m_run = PA_NEG_BIG, l_run = 0.f;        // running max (base-2 domain) and sum of the query row
+  f32x4 o[DH / 16];
 #pragma unroll
-  for (int t = 0; t < PA_QT; ++t) {
-    m_run[t] = PA_NEG_BIG;
-    l_run[t] = 0.f;
-#pragma unroll
-    for (int dt = 0; dt < DH / 16; ++dt) o[t][dt] = f32x4{0.f, 0.f, 0.f, 0.f};
-  }
+  for (int dt = 0; dt < DH / 16; ++dt) o[dt] = f32x4{0.f, 0.f, 0.f, 0.f};
 
-  pa_issue<DH, WAVES>(pool, block_table, g, layer, kvh, 0, &lds[0][0][0], w, lane);
+  pa_issue<DH>(pool, block_table, g, layer, kvh, 0, &lds[0][0][0], w, lane);
   for (int ch = 0; ch < nch; ++ch) {
     // chunk ch has landed for this wave, then for everybody; all waves are done with the other stage
     asm volatile("s_waitcnt vmcnt(0)\n\ts_barrier" ::: "memory");
-    pa_issue<DH, WAVES>(pool, block_table, g, layer, kvh, ch + 1 < nch ? ch + 1 : nch - 1, &lds[(ch + 1) % PA_STAGES][0][0], w,
+    pa_issue<DH>(pool, block_table, g, layer, kvh, ch + 1 < nch ? ch + 1 : nch - 1, &lds[(ch + 1) % PA_STAGES][0][0], w,
                  lane);
     const int pos0 = ch << 6;
     if (pos0 > wave_limit) continue;           // nothing visible for this wave's rows (uniform per wave)
     const u32x4(*st)[64] = lds[ch % PA_STAGES];
 
-    // scores of the 64 positions: s[t][t4][r] = position pos0 + 16 t4 + 4 g4 + r for query row c of tile t
-    f32x4 s[PA_QT][4];
+    // scores of the 64 positions: s[t4][r] = position pos0 + 16 t4 + 4 g4 + r for query row c
+    f32x4 s[4];
 #pragma unroll
     for (int t4 = 0; t4 < 4; ++t4) {
-      bf16x8 kf[KS];
+      s[t4] = f32x4{0.f, 0.f, 0.f, 0.f};
 #pragma unroll
-      for (int j = 0; j < KS; ++j) kf[j] = __builtin_bit_cast(bf16x8, st[t4 * KS + j][lane]);
-#pragma unroll
-      for (int t = 0; t < PA_QT; ++t) {
-        s[t][t4] = f32x4{0.f, 0.f, 0.f, 0.f};
-#pragma unroll
-        for (int j = 0; j < KS; ++j)
-          s[t][t4] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(kf[j], qf[t][j], s[t][t4], 0, 0, 0);
-      }
+      for (int j = 0; j < KS; ++j)
+        s[t4] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, st[t4 * KS + j][lane]), qf[j], s[t4], 0, 0, 0);
     }
-    bf16x8 pf[PA_QT][2];                        // P fragments of the two 32-position halves
-#pragma unroll
-    for (int t = 0; t < PA_QT; ++t) {
-      float mx = PA_NEG_BIG;
+    if (pos0 + 63 > wave_open) {                // uniform per wave: chunks on the diagonal only
 #pragma unroll
       for (int t4 = 0; t4 < 4; ++t4)
 #pragma unroll
-        for (int r = 0; r < 4; ++r) {
-          const int pos = pos0 + t4 * 16 + g4 * 4 + r;
-          const float v = (pos <= limit[t]) ? s[t][t4][r] * scale_log2e : PA_NEG_BIG;
-          s[t][t4][r] = v;
-          mx = fmaxf(mx, v);
-        }
-      mx = fmaxf(mx, __shfl_xor(mx, 16));
-      mx = fmaxf(mx, __shfl_xor(mx, 32));
-      // position 0 is visible to every row, so after the first chunk the running max is a real score and a
-      // masked entry (-1e30) underflows to exactly 0
-      const float m_new = fmaxf(m_run[t], mx);
-      const float corr = __builtin_amdgcn_exp2f(m_run[t] - m_new);
-      float psum = 0.f;
+        for (int r = 0; r < 4; ++r) s[t4][r] = pos0 + t4 * 16 + g4 * 4 + r <= limit ? s[t4][r] : PA_NEG_BIG;
+    }
+    float mx = PA_NEG_BIG;
 #pragma unroll
-      for (int t4 = 0; t4 < 4; ++t4)
+    for (int t4 = 0; t4 < 4; ++t4)
 #pragma unroll
-        for (int r = 0; r < 4; ++r) {
-          const float pv = __builtin_amdgcn_exp2f(s[t][t4][r] - m_new);
-          psum += pv;
-          pf[t][t4 >> 1][(t4 & 1) * 4 + r] = (__bf16)pv;
-        }
-      l_run[t] = l_run[t] * corr + psum;
-      m_run[t] = m_new;
+      for (int r = 0; r < 4; ++r) mx = fmaxf(mx, s[t4][r]);
+    // position 0 is visible to every row, so after the first chunk the running max is a real score and a
+    // masked entry (-1e30) underflows to exactly 0
+    const float m_new = fmaxf(m_run, groups_max(mx) * scale_log2e);
+    const float corr = __builtin_amdgcn_exp2f(m_run - m_new);
+    float psum = 0.f;
+    bf16x8 pf[2];                               // P fragments of the two 32-position halves
 #pragma unroll
-      for (int dt = 0; dt < DH / 16; ++dt) o[t][dt] *= corr;
+    for (int t4 = 0; t4 < 4; ++t4)
+#pragma unroll
+      for (int r = 0; r < 4; ++r) {
+        const float pv = __builtin_amdgcn_exp2f(fmaf(s[t4][r], scale_log2e, -m_new));
+        psum += pv;
+        pf[t4 >> 1][(t4 & 1) * 4 + r] = (__bf16)pv;
+      }
+    l_run = l_run * corr + psum;
+    m_run = m_new;
+    if (!__all(corr == 1.0f)) {                 // maxima settle after a few chunks
+#pragma unroll
+      for (int dt = 0; dt < DH / 16; ++dt) o[dt] *= corr;
     }
 #pragma unroll
     for (int h = 0; h < 2; ++h)
 #pragma unroll
-      for (int dt = 0; dt < DH / 16; ++dt) {
-        const bf16x8 vf = __builtin_bit_cast(bf16x8, st[KB + h * (DH / 16) + dt][lane]);
-#pragma unroll
-        for (int t = 0; t < PA_QT; ++t)
-          o[t][dt] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(vf, pf[t][h], o[t][dt], 0, 0, 0);
-      }
+      for (int dt = 0; dt < DH / 16; ++dt)
+        o[dt] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, st[KB + h * (DH / 16) + dt][lane]), pf[h], o[dt], 0, 0, 0);
   }
   asm volatile("s_waitcnt vmcnt(0)" ::: "memory");   // the redundant tail loads must not outlive the workgroup's LDS
 
+  const float inv = 1.0f / groups_sum(l_run);
+  if (!valid) return;
+  bf16* dst = out + ((size_t)tok * Hq + head) * DH + g4 * 4;
 #pragma unroll
-  for (int t = 0; t < PA_QT; ++t) {
-    float l = l_run[t];
-    l += __shfl_xor(l, 16);
-    l += __shfl_xor(l, 32);
-    const int Rr = r0 + (w * PA_QT + t) * 16 + c;
-    if (Rr >= R) continue;
-    const int tok = Rr / G, head = kvh * G + Rr % G;
-    const float inv = 1.0f / l;
-    bf16* dst = out + ((size_t)tok * Hq + head) * DH + g4 * 4;
+  for (int dt = 0; dt < DH / 16; ++dt) {
+    bf16 v4[4];
 #pragma unroll
-    for (int dt = 0; dt < DH / 16; ++dt) {
-      bf16 v4[4];
-#pragma unroll
-      for (int r = 0; r < 4; ++r) v4[r] = __float2bfloat16(o[t][dt][r] * inv);
-      *reinterpret_cast<uint2*>(dst + dt * 16) = *reinterpret_cast<const uint2*>(v4);
-    }
+    for (int r = 0; r < 4; ++r) v4[r] = __float2bfloat16(o[dt][r] * inv);
+    *reinterpret_cast<uint2*>(dst + dt * 16) = *reinterpret_cast<const uint2*>(v4);
   }
 }
 
@@ -889,18 +867,8 @@ hipError_t launch_prefill_attention(const bf16* q, const bf16* pool, const int* 
                                     KvGeom g, int layer, int M, int Hq, bf16* out, hipStream_t st) {
   const int Hkv = g.n_kv_heads, G = Hq / Hkv, R = M * G, dh = g.head_dim;
   const float scale_log2e = 1.4426950408889634f / sqrtf((float)dh);
-  // 8 waves = 256 rows per workgroup read K and V half as often; 4 waves = 128 rows where the grid is short of two
-  // workgroups per CU (1023 tokens, 32 heads: 41.7 us with 128 workgroups, 31.8 with 256)
-  const bool small = (long long)((R + 255) / 256) * Hkv < 2 * spec_num_cu();
-  const dim3 grid((R + (small ? 127 : 255)) / (small ? 128 : 256), Hkv), block(small ? 256 : 512);
-#define PA_GO(DH, WAVES) prefill_attn_kernel<DH, WAVES><<<grid, block, 0, st>>>(q, pool, block_table, len_ptr, g, layer, M, Hq, scale_log2e, out)
-  if (dh == 128) {
-    if (small) PA_GO(128, 4);
-    else PA_GO(128, 8);
-  } else {
-    if (small) PA_GO(64, 4);
-    else PA_GO(64, 8);
-  }
-#undef PA_GO
+  const dim3 grid((R + PA_ROWS - 1) / PA_ROWS, Hkv), block(PA_WAVES * 64);
+  if (dh == 128) prefill_attn_kernel<128><<<grid, block, 0, st>>>(q, pool, block_table, len_ptr, g, layer, M, Hq, scale_log2e, out);
+  else prefill_attn_kernel<64><<<grid, block, 0, st>>>(q, pool, block_table, len_ptr, g, layer, M, Hq, scale_log2e, out);
   return hipGetLastError();
 }

@@ -15,6 +15,20 @@ typedef __attribute__((ext_vector_type(4))) unsigned u32x4;
 typedef __attribute__((ext_vector_type(4), aligned(2))) unsigned short bf16x4u;
 __device__ __forceinline__ float bf16x4_at(bf16x4u v, int i) { return __uint_as_float((unsigned)v[i] << 16); }
 
+// over the lanes c, c + 16, c + 32, c + 48: swaps of 16 and 32 lanes between registers, no trip through LDS
+__device__ __forceinline__ float groups_max(float x) {
+  auto a = __builtin_amdgcn_permlane16_swap(__float_as_uint(x), __float_as_uint(x), false, false);
+  x = fmaxf(__uint_as_float(a[0]), __uint_as_float(a[1]));
+  auto b = __builtin_amdgcn_permlane32_swap(__float_as_uint(x), __float_as_uint(x), false, false);
+  return fmaxf(__uint_as_float(b[0]), __uint_as_float(b[1]));
+}
+__device__ __forceinline__ float groups_sum(float x) {
+  auto a = __builtin_amdgcn_permlane16_swap(__float_as_uint(x), __float_as_uint(x), false, false);
+  x = __uint_as_float(a[0]) + __uint_as_float(a[1]);
+  auto b = __builtin_amdgcn_permlane32_swap(__float_as_uint(x), __float_as_uint(x), false, false);
+  return __uint_as_float(b[0]) + __uint_as_float(b[1]);
+}
+
 #define SPEC_PAGE_TOKENS 64      // tokens per KV page
 #define SPEC_RING_MAX 64         // most slots of the draft-token / q-row ring
 // Compute units of the device the library runs on: 256 (MI355X) until spec_init has asked the device.

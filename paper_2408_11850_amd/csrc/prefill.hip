@@ -314,12 +314,13 @@ __global__ __launch_bounds__(DG_THREADS, 1) void dense_gemm_kernel(const bf16* _
 // take whole lines (with a row per lane, 16 bytes of each, X took 0.23 us of a K step instead of 0.13), that loads are issued
 // between MFMAs and that every SIMD has a second wave: 1023 x 4096 x 11008 124 -> 100 us; 511 x 6144 x 2048 28 -> 23 from
 // HBM and 26.4 -> 18 to 19 from the memory-side cache.
+// PN: panels of a tile, 8 (128 outputs) or 6 (96: a wave has 32 x 96, a stage 12 KiB of W), see dense_tile.
 #define DS_WAVES 8
 #define DS_THREADS (DS_WAVES * 64)
 #define DS_STAGES 4
 #define DS_LOADS 4                        // per wave and stage
 #define DS_X_BYTES (8 * DG_TILE_BYTES)
-#define DS_STAGE_BYTES (2 * DS_X_BYTES)
+#define DS_STAGE_BYTES(PN) (DS_X_BYTES + (PN) * 2048)
 // The tile of this workgroup: XCD x takes the tiles [x chunk, (x + 1) chunk), numbered row-major inside groups of 4
 // columns, so that what an XCD runs together shares operand strips in its L2.
 __device__ __forceinline__ bool dense_tile_of(int TM, int TN, int chunk, int* tm, int* tn) {
@@ -331,12 +332,17 @@ __device__ __forceinline__ bool dense_tile_of(int TM, int TN, int chunk, int* tm
   return true;
 }
 
-template <int EPI>
+template <int EPI, int PN>
 __global__ __launch_bounds__(DS_THREADS, 2) void dense_small_kernel(const bf16* __restrict__ X, const u32x4* __restrict__ Wp,
                                                                     float* __restrict__ Y, bf16* __restrict__ Z, int M, int N,
                                                                     int K, int ldz, int NT, int panel_steps, int TM, int TN,
                                                                     int chunk, int slice, DenseRope ra) {
-  extern __shared__ u32x4 lds[];          // DS_STAGES * DS_STAGE_BYTES
+  static_assert(PN == 8 || PN == 6, "panels of a tile");
+  constexpr int WN = PN == 8 ? 2 : 1, WM = 4 / WN;         // waves side by side, of the four that share a K step
+  constexpr int NP = PN / WN, MT = 8 / WM;                 // a wave's panels and token tiles
+  constexpr int STAGE = DS_X_BYTES + PN * 2048;
+  constexpr bool ROPE = EPI == DG_EPI_ROPE128 || EPI == DG_EPI_ROPE64;
+  extern __shared__ u32x4 lds[];          // DS_STAGES * STAGE
   const int w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), lane = threadIdx.x & 63;
   int tm, tn;
   if (!dense_tile_of(TM, TN, chunk, &tm, &tn)) return;
@@ -344,12 +350,19 @@ __global__ __launch_bounds__(DS_THREADS, 2) void dense_small_kernel(const bf16* 
   const int step0 = blockIdx.y * slice, steps = min(slice, panel_steps - step0);
   if (EPI == DG_EPI_STORE) Y += (size_t)blockIdx.y * M * N;
   const int c = lane & 15, kb = lane >> 4;
-  const int kg = w >> 2, wm = (w >> 1) & 1, wn = w & 1;
-  // Per stage a wave loads token tile w (8 rows x 64 k at a time) and two K steps of panel w; rows and panels past the end
-  // are clamped, computed and never stored.
-  int panel = tn * 8 + w;
-  if (panel > NT - 1) panel = NT - 1;
-  const char* wbase = reinterpret_cast<const char*>(Wp + ((size_t)panel * panel_steps + step0) * 64) + lane * 16;
+  const int kg = w >> 2, wm = (w & 3) / WN, wn = (w & 3) % WN;
+  // Per stage a wave loads token tile w (8 rows x 64 k at a time) and, of 8 panels, two K steps of panel w, of 6 the blocks w and
+  // (the first four waves) w + 8 of 1 KiB; rows and panels past the end are clamped, computed and never stored.  6 panels lie
+  // in the order of the pairs that the epilogue wants.
+  const int loads = PN == 8 || w < 4 ? DS_LOADS : DS_LOADS - 1;
+  const char* wbase[2];
+#pragma unroll
+  for (int i = 0; i < 2; ++i) {
+    const int blk = PN == 8 ? 2 * w + i : (w + 8 * i) % 12;
+    int panel = PN == 8 ? tn * 8 + w : dense_panel<EPI>(tn * 3 + (blk >> 2), (blk >> 1) & 1);
+    if (panel > NT - 1) panel = NT - 1;
+    wbase[i] = reinterpret_cast<const char*>(Wp + ((size_t)panel * panel_steps + step0) * 64) + lane * 16;
+  }
   const char* xbase = reinterpret_cast<const char*>(X) + (size_t)step0 * 64;
   const int xchunk = (lane & 7) ^ (lane >> 3);
   unsigned xoff[2];
@@ -363,52 +376,62 @@ __global__ __launch_bounds__(DS_THREADS, 2) void dense_small_kernel(const bf16* 
   const int stages = (steps + 1) >> 1;
   // load i of this wave for stage st; past the end: the last stage again, into a slot that nobody reads
   auto issue = [&](int st, int slot, int i) {
-    u32x4* dst = lds + (slot * DS_STAGE_BYTES + w * 2048 + (i & 1) * 1024) / 16;
     if (st > stages - 1) st = stages - 1;
     const bool whole = st * 2 + 1 < steps;  // odd K-step count: never read past a row's or a panel's end
-    if (i < 2)
-      __builtin_amdgcn_global_load_lds(xbase + (size_t)st * 128 + (xoff[i] - (whole ? 0u : xfix)), dst, 16, 0, 0);
-    else
-      __builtin_amdgcn_global_load_lds(wbase + (size_t)st * 2048 + ((i & 1) && whole ? 1024 : 0), dst + DS_X_BYTES / 16, 16, 0, 0);
+    if (i < 2) {
+      __builtin_amdgcn_global_load_lds(xbase + (size_t)st * 128 + (xoff[i] - (whole ? 0u : xfix)),
+                                       lds + (slot * STAGE + w * 2048 + i * 1024) / 16, 16, 0, 0);
+    } else if (i < loads) {          // uniform
+      const int blk = PN == 8 ? 2 * w + (i & 1) : w + 8 * (i & 1);
+      __builtin_amdgcn_global_load_lds(wbase[i & 1] + (size_t)st * 2048 + ((blk & 1) && whole ? 1024 : 0),
+                                       lds + (slot * STAGE + DS_X_BYTES + blk * 1024) / 16, 16, 0, 0);
+    }
   };
-  // fragment addresses inside a stage: token tiles 4 wm + mt, and this wave's four panels
+  // fragment addresses inside a stage: token tiles MT wm + mt, and this wave's panels
   const unsigned lds0 = (unsigned)(size_t)(dg_lds_u32x4*)lds;
-  const unsigned xrd = lds0 + wm * 4 * DG_TILE_BYTES + c * 128 + ((kg * 4 + kb) ^ (c & 7)) * 16;
-  const unsigned wrd = lds0 + DS_X_BYTES + wn * (EPI == DG_EPI_ROPE128 ? 2 : 4) * 2048 + lane * 16 + kg * 1024;
-  f32x4 acc[4][4];
+  const unsigned xrd = lds0 + wm * MT * DG_TILE_BYTES + c * 128 + ((kg * 4 + kb) ^ (c & 7)) * 16;
+  const unsigned wrd = lds0 + DS_X_BYTES + wn * (PN == 8 && EPI == DG_EPI_ROPE128 ? 2 : NP) * 2048 + lane * 16 + kg * 1024;
+  f32x4 acc[NP][MT];
 #pragma unroll
-  for (int a = 0; a < 4; ++a)
+  for (int a = 0; a < NP; ++a)
 #pragma unroll
-    for (int b = 0; b < 4; ++b) acc[a][b] = f32x4{0.f, 0.f, 0.f, 0.f};
-  u32x4 fw[2][4], fx[2][4];                 // fragments of this wave's current and next K step
+    for (int b = 0; b < MT; ++b) acc[a][b] = f32x4{0.f, 0.f, 0.f, 0.f};
+  u32x4 fw[2][NP], fx[2][MT];                 // fragments of this wave's current and next K step
 #define DS_READ(B, SLOT)                                                                                     \
   {                                                                                                          \
-    const unsigned so_ = (SLOT) * DS_STAGE_BYTES;                                                            \
-    _Pragma("unroll") for (int i = 0; i < 4; ++i)                                                            \
+    const unsigned so_ = (SLOT) * STAGE;                                                                     \
+    _Pragma("unroll") for (int i = 0; i < MT; ++i)                                                           \
       asm volatile("ds_read_b128 %0, %1 offset:%2" : "=v"(fx[B][i]) : "v"(xrd + so_), "n"(i * DG_TILE_BYTES)); \
-    _Pragma("unroll") for (int i = 0; i < 4; ++i)                                                            \
+    _Pragma("unroll") for (int i = 0; i < NP; ++i)                                                           \
       asm volatile("ds_read_b128 %0, %1 offset:%2" : "=v"(fw[B][i]) : "v"(wrd + so_),                        \
-                   "n"((EPI == DG_EPI_ROPE128 ? (i & 1) + (i >> 1) * 4 : i) * 2048));                        \
+                   "n"((PN == 8 && EPI == DG_EPI_ROPE128 ? (i & 1) + (i >> 1) * 4 : i) * 2048));                        \
   }
 #define DS_WAIT(B)                                                                                           \
-  asm volatile("s_waitcnt lgkmcnt(0)" : "+v"(fx[B][0]), "+v"(fx[B][1]), "+v"(fx[B][2]), "+v"(fx[B][3]),      \
-               "+v"(fw[B][0]), "+v"(fw[B][1]), "+v"(fw[B][2]), "+v"(fw[B][3])::"memory");
-#define DS_LANDED(N) asm volatile("s_waitcnt vmcnt(%0)\n\ts_barrier" ::"n"(N) : "memory");
+  asm volatile("s_waitcnt lgkmcnt(0)" : "+v"(fx[B][0]), "+v"(fx[B][1]), "+v"(fw[B][0]), "+v"(fw[B][1]),      \
+               "+v"(fw[B][2]), "+v"(fw[B][3])::"memory");                                                    \
+  _Pragma("unroll") for (int i = 2; i < MT; ++i) asm volatile("" : "+v"(fx[B][i]));                          \
+  _Pragma("unroll") for (int i = 4; i < NP; ++i) asm volatile("" : "+v"(fw[B][i]));
+// this wave's loads of all but the last N stages have landed, then everybody's
+#define DS_LANDED(N)                                                                                         \
+  if (PN == 8 || w < 4) asm volatile("s_waitcnt vmcnt(%0)" ::"n"((N) * DS_LOADS) : "memory");                \
+  else asm volatile("s_waitcnt vmcnt(%0)" ::"n"((N) * (DS_LOADS - 1)) : "memory");                           \
+  asm volatile("s_barrier" ::: "memory");
   // Stage ST: stage ST + 1 has landed for this wave, then for everybody, and everybody holds its half of stage ST in
   // registers, so that slot is refilled, one load after every fourth MFMA: no wave sits in the issue stage behind the
   // address unit while its matrix core idles.  MULTIPLY: whether this wave has a K step in the stage.
 #define DS_STAGE(B, ST, MULTIPLY)                                                                            \
   {                                                                                                          \
-    DS_LANDED((DS_STAGES - 2) * DS_LOADS)                                                                    \
+    DS_LANDED(DS_STAGES - 2)                                                                                 \
     DS_READ(1 - (B), ((ST) + 1) % DS_STAGES)                                                                 \
     if (MULTIPLY) {                                                                                          \
-      _Pragma("unroll") for (int mt = 0; mt < 4; ++mt) {                                                     \
+      _Pragma("unroll") for (int mt = 0; mt < MT; ++mt) {                                                    \
         __builtin_amdgcn_sched_barrier(0);                                                                   \
-        _Pragma("unroll") for (int nt = 0; nt < 4; ++nt)                                                     \
+        _Pragma("unroll") for (int nt = 0; nt < NP; ++nt)                                                    \
           acc[nt][mt] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, fw[B][nt]),       \
                                                                 __builtin_bit_cast(bf16x8, fx[B][mt]), acc[nt][mt], 0, 0, 0); \
         __builtin_amdgcn_sched_barrier(0);                                                                   \
-        issue((ST) + DS_STAGES, (ST) % DS_STAGES, mt);                                                       \
+        _Pragma("unroll") for (int i = 0; i < DS_LOADS / MT; ++i)                                            \
+          issue((ST) + DS_STAGES, (ST) % DS_STAGES, mt * (DS_LOADS / MT) + i);                               \
       }                                                                                                      \
     }                                                                                                        \
     DS_WAIT(1 - (B))                                                                                         \
@@ -417,7 +440,7 @@ __global__ __launch_bounds__(DS_THREADS, 2) void dense_small_kernel(const bf16* 
   for (int s = 0; s < DS_STAGES; ++s)
 #pragma unroll
     for (int i = 0; i < DS_LOADS; ++i) issue(s, s, i);
-  DS_LANDED((DS_STAGES - 1) * DS_LOADS)     // stage 0 is in LDS for everybody
+  DS_LANDED(DS_STAGES - 1)                  // stage 0 is in LDS for everybody
   DS_READ(0, 0)
   DS_WAIT(0)
   const bool last = kg == 0 || !(steps & 1);
@@ -440,20 +463,29 @@ __global__ __launch_bounds__(DS_THREADS, 2) void dense_small_kernel(const bf16* 
 #undef DS_LANDED
   // waves w and w + 4 hold the even and the odd K steps of the same outputs: each adds up and stores half of the tokens
   f32x4* ex = reinterpret_cast<f32x4*>(lds);
-  f32x4 sum[4][2];
+  constexpr int H = MT / 2;
+  f32x4 sum[NP][H];
 #pragma unroll
-  for (int nt = 0; nt < 4; ++nt)
+  for (int nt = 0; nt < NP; ++nt)
 #pragma unroll
-    for (int mt = 0; mt < 2; ++mt) {
-      sum[nt][mt] = kg ? acc[nt][mt + 2] : acc[nt][mt];
-      ex[(w * 8 + nt * 2 + mt) * 64 + lane] = kg ? acc[nt][mt] : acc[nt][mt + 2];
+    for (int mt = 0; mt < H; ++mt) {
+      sum[nt][mt] = kg ? acc[nt][mt + H] : acc[nt][mt];
+      ex[(w * NP * H + nt * H + mt) * 64 + lane] = kg ? acc[nt][mt] : acc[nt][mt + H];
     }
   __syncthreads();
 #pragma unroll
-  for (int nt = 0; nt < 4; ++nt)
+  for (int nt = 0; nt < NP; ++nt)
 #pragma unroll
-    for (int mt = 0; mt < 2; ++mt) sum[nt][mt] += ex[((w ^ 4) * 8 + nt * 2 + mt) * 64 + lane];
-  dense_epilogue<EPI, 2>(sum, tm * 128 + wm * 64 + kg * 32, tn * 2 + wn, c, kb, Y, Z, M, N, ldz, ra);
+    for (int mt = 0; mt < H; ++mt) sum[nt][mt] += ex[((w ^ 4) * NP * H + nt * H + mt) * 64 + lane];
+  const int m0 = tm * 128 + wm * MT * 16 + kg * H * 16;
+  if constexpr (PN == 8) {
+    dense_epilogue<EPI, H>(sum, m0, tn * 2 + wn, c, kb, Y, Z, M, N, ldz, ra);
+  } else {
+    const int len = ROPE ? ra.len_ptr[0] : 0, m = m0 + c;
+    if (m >= M) return;
+#pragma unroll
+    for (int i = 0; i < NP / 2; ++i) dense_pair<EPI>(sum[2 * i][0], sum[2 * i + 1][0], m, tn * 3 + i, kb, Y, Z, N, ldz, len, ra);
+  }
 }
 
 // dense_wide: 256 tokens x 192 outputs by 8 waves of 64 tokens x 6 panels, for grids that deal out more evenly so.  Operands
@@ -602,6 +634,14 @@ int dense_tile(int M, int NT, int steps) {
     const float us = rounds * (T[i].round + steps * (T[i].step + T[i].busy * tiles / ((float)rounds * ncu)));
     if (i == 0 || us < best_us) best = i, best_us = us;
   }
+  // 128 x 96 where one round of them fills three quarters of the CUs or more and 128 x 128 would be taken (the same round with
+  // fewer, larger tiles): what a CU pulls in per K step falls by an eighth.  Not below 16 K steps, where it is all launch.
+  //   us, 128 x 128 | 128 x 96, W from HBM: 511 x 6144 x 2048  23.0 | 22.2     511 x 6144 x 4096  40.1 | 35.7    255 x 12288 x 4096  42.2 | 38.0
+  //                                         1023 x 3072 x 2048 21.8 | 20.7     1023 x 3072 x 4096 38.4 | 34.3    400 x 6144 x 2048   19.6 | 19.3
+  //   two rounds of them gain nothing:      511 x 11264 x 2048 37.0 | 38.4     2047 x 3072 x 2048 38.8 | 39.0
+  // The sums are those of 128 x 128 tiles, bit for bit.
+  const int narrow = (M + 127) / 128 * ((NT + 5) / 6);
+  if (best == DENSE_SMALL && steps >= 16 && narrow <= ncu && 4 * narrow >= 3 * ncu) best = DENSE_NARROW;
   return best;
 }
 
@@ -616,7 +656,7 @@ static hipError_t dense_lds(F* kernel, int bytes, bool* set) {      // more than
 template <int EPI>
 static hipError_t dense_launch_epi(const bf16* x, const u32x4* w, int M, int N, int K, float* y, bf16* z, int ldz,
                                    const DenseRope& ra, hipStream_t st) {
-  static bool set[3] = {};
+  static bool set[4] = {};
   const int NT = N / 16, steps = K / 32, tile = dense_tile(M, NT, steps);
   hipError_t e;
   if (tile == DENSE_LARGE) {
@@ -626,10 +666,15 @@ static hipError_t dense_launch_epi(const bf16* x, const u32x4* w, int M, int N, 
     const int cx = (TN + 7) / 8, groups = (cx + 3) / 4;
     dense_gemm_kernel<EPI><<<8 * groups * TM * 4, DG_THREADS, lds_bytes, st>>>(x, w, y, z, M, N, K, ldz, NT, steps, TM, cx, ra);
   } else if (tile == DENSE_SMALL) {
-    constexpr int lds_bytes = DS_STAGES * DS_STAGE_BYTES;
-    if ((e = dense_lds(dense_small_kernel<EPI>, lds_bytes, &set[1])) != hipSuccess) return e;
+    constexpr int lds_bytes = DS_STAGES * DS_STAGE_BYTES(8);
+    if ((e = dense_lds(dense_small_kernel<EPI, 8>, lds_bytes, &set[1])) != hipSuccess) return e;
     const int TM = (M + 127) / 128, TN = (NT + 7) / 8, chunk = (TM * TN + 7) / 8;
-    dense_small_kernel<EPI><<<8 * chunk, DS_THREADS, lds_bytes, st>>>(x, w, y, z, M, N, K, ldz, NT, steps, TM, TN, chunk, steps, ra);
+    dense_small_kernel<EPI, 8><<<8 * chunk, DS_THREADS, lds_bytes, st>>>(x, w, y, z, M, N, K, ldz, NT, steps, TM, TN, chunk, steps, ra);
+  } else if (tile == DENSE_NARROW) {
+    constexpr int lds_bytes = DS_STAGES * DS_STAGE_BYTES(6);
+    if ((e = dense_lds(dense_small_kernel<EPI, 6>, lds_bytes, &set[3])) != hipSuccess) return e;
+    const int TM = (M + 127) / 128, TN = (NT + 5) / 6, chunk = (TM * TN + 7) / 8;
+    dense_small_kernel<EPI, 6><<<8 * chunk, DS_THREADS, lds_bytes, st>>>(x, w, y, z, M, N, K, ldz, NT, steps, TM, TN, chunk, steps, ra);
   } else {
     constexpr int lds_bytes = 2 * DW_X_BYTES + 3 * DW_W_BYTES;
     if ((e = dense_lds(dense_wide_kernel<EPI>, lds_bytes, &set[2])) != hipSuccess) return e;
@@ -664,14 +709,14 @@ size_t dense_slices_floats() { return (size_t)spec_num_cu() * 128 * 128; }
 // P[s][m][n] = slice s of X W^T, S = dense_slices(M, N, K) > 1 of them
 hipError_t launch_dense_slices(const bf16* x, const void* wp, int M, int N, int K, int S, float* P, hipStream_t st) {
   if ((double)M * K * 2.0 >= 4294967296.0 || S < 2) return hipErrorInvalidValue;
-  constexpr int lds_bytes = DS_STAGES * DS_STAGE_BYTES;
+  constexpr int lds_bytes = DS_STAGES * DS_STAGE_BYTES(8);
   static bool set = false;
-  hipError_t e = dense_lds(dense_small_kernel<DG_EPI_STORE>, lds_bytes, &set);
+  hipError_t e = dense_lds(dense_small_kernel<DG_EPI_STORE, 8>, lds_bytes, &set);
   if (e != hipSuccess) return e;
   const int NT = N / 16, steps = K / 32, slice = ((steps + S - 1) / S + 1) & ~1;      // whole stages
   if ((steps + slice - 1) / slice != S) return hipErrorInvalidValue;
   const int TM = (M + 127) / 128, TN = (NT + 7) / 8, chunk = (TM * TN + 7) / 8;
-  dense_small_kernel<DG_EPI_STORE><<<dim3(8 * chunk, S), DS_THREADS, lds_bytes, st>>>(x, (const u32x4*)wp, P, nullptr, M, N, K, 0, NT,
+  dense_small_kernel<DG_EPI_STORE, 8><<<dim3(8 * chunk, S), DS_THREADS, lds_bytes, st>>>(x, (const u32x4*)wp, P, nullptr, M, N, K, 0, NT,
                                                                                       steps, TM, TN, chunk, slice, DenseRope{});
   return hipGetLastError();
 }

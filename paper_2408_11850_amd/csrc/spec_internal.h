@@ -178,7 +178,7 @@ size_t attention_workspace_floats(int Hq, int Hkv, int dh, int max_seq);
 hipError_t launch_dense_gemm(const bf16* x, const void* wp, int M, int N, int K, int epi, float* y, bf16* z,
                              hipStream_t st, int ldz = 0);   // ldz: row stride of z, 0 = N / 2
 // the tile that launch_dense_gemm takes
-enum { DENSE_LARGE = 0 /* 256 x 256 */, DENSE_SMALL = 1 /* 128 x 128 */, DENSE_WIDE = 2 /* 256 x 192 */ };
+enum { DENSE_LARGE = 0 /* 256 x 256 */, DENSE_SMALL = 1 /* 128 x 128 */, DENSE_WIDE = 2 /* 256 x 192 */, DENSE_NARROW = 3 /* 128 x 96 */ };
 int dense_tile(int M, int NT, int steps);
 // K slices of a prompt projection for launch_norm to add: how many (1: none, call launch_dense_gemm), P[S][M][N], and the floats
 // that hold P for every shape

@@ -16,8 +16,8 @@
 // What bounds it is a chain of latencies: kernel start, page id, K / V, softmax, result (traced; 7B shape, M = 1, 4096
 // positions: 16.0 us for 67 MB, 4.6 the merge; 70B, M = 7: 13.2 + 5.5; with a rotation kernel in front 4.9 + 14.2 + 4.6 and
 // 4.9 + 11.2 + 5.4: the split kernel itself takes 2 us longer, every wave rotates its q, and 3 us per layer are saved).  Up to
-// 1024 positions one launch does it all (attn_short_kernel below); beyond that one CU per KV head cannot pull the cache fast
-// enough.
+// 1216 positions, with 48 KV heads and more up to 4032, one launch does it all (attn_short_kernel, short_tokens); beyond, a
+// head's few CUs cannot pull the cache fast enough.
 #include "spec_internal.h"
 
 #define NEG_BIG (-1.0e30f)
@@ -326,7 +326,6 @@ __global__ __launch_bounds__(256) void attn_split_kernel(AttnNew nw, bf16* __res
 // 854 to 863; a chunk for the eighth wave too, behind the new tokens, 36 us slower with one part.
 #define SHORT_WAVES 8
 #define SHORT_CHUNK_WAVES (SHORT_WAVES - 1)
-#define SHORT_TOKENS 1024
 #define SHORT_DEPTH 2                     // chunks of a wave in flight
 template <int DH, int DV>
 __global__ __launch_bounds__(SHORT_WAVES * 64, 2) void attn_short_kernel(AttnNew nw, bf16* __restrict__ pool,
@@ -497,6 +496,18 @@ size_t attention_workspace_floats(int Hq, int Hkv, int dh, int max_seq) {
   return (size_t)ns_max * Hkv * Rpad * (dh + 2);
 }
 
+// Most positions of room for which one launch takes the whole range.  It saves a launch and the parts' way through memory, about
+// 5 us per layer, and loses what a head's few CUs pull in more slowly than all of them do: the more heads, the later.  Where the
+// line lies depends on the heads alone, so that the rows of a window do not depend on their number (us with room for 2048,
+// split | whole range, M = 1 unless said otherwise):
+//   2 layers, 56 heads      300 in use 473.6 | 467.3   1100 479.4 | 473.2   1890 485.9 | 479.3   (M = 15: 548.0 | 528.1, 556.8 | 540.2)
+//   4 layers, 32 heads      300 373.1 | 359.7          1100 377.4 | 371.2   1890 384.8 | 381.3   (M = 8: 402.6 | 379.9, 408.8 | 399.8)
+//   12 layers, 16 heads     300 446.5 | 410.1          1100 456.3 | 440.8   1890 457.7 | 469.8
+//   8 layers, 4 of width 64 300 277.3 | 259.2          1100 279.9 | 276.5   1890 283.1 | 294.9
+// With 32 heads it stays at 1216 all the same: beside a draft model's launches its workgroups wait for whole CUs (7B / 1B shapes
+// behind 1024 tokens, step 4583 | 4610 us; with 56 heads 33B / 1B 16040 | 16054).
+static int short_tokens(int Hkv) { return Hkv < 48 ? 1216 : Hkv > 56 ? 4032 : 72 * Hkv; }
+
 // Workgroups that share the columns of a head, from the n that there are without: as many as find a CU each (us per layer against
 // one, 700 positions; 16 heads, n = 16: two -1.3, four -2.0; 56 heads, n = 56: -0.8, -1.4; n = 112: -0.8, +2.2).
 static int short_parts(int n) { return 4 * n <= spec_num_cu() ? 4 : 2 * n <= spec_num_cu() ? 2 : 1; }
@@ -510,7 +521,7 @@ hipError_t launch_attention(const float* y, const float2* tab, bf16* pool, const
   const float scale = 1.0f / sqrtf((float)dh);
   const AttnNew nw = {y, tab};
   // the kernel and the split count are chosen for the longest context, not the current one, so that the launch is replayable
-  if (split_tokens <= SHORT_TOKENS) {
+  if (split_tokens <= short_tokens(Hkv)) {
     const int parts = short_parts(Hkv * nrt);
     const dim3 grid(nrt, Hkv, parts), block(SHORT_WAVES * 64);
 #define SHORT_GO(DH, PARTS) \

@@ -206,7 +206,7 @@ __device__ __forceinline__ MaxIdx reg_load(const float* __restrict__ row, int V,
   }
   return m;
 }
-// the largest value alone; beyond V e holds -inf, which has no mass whatever the largest value is
+// the largest value alone; beyond V e holds -inf, which has no mass whatever the largest value is (mult > 0)
 template <int CH>
 __device__ __forceinline__ float reg_load_max(const float* __restrict__ row, int V, const RegGeom& g, f32x4 (&e)[CH]) {
   float m = -INFINITY;
@@ -230,6 +230,17 @@ __device__ __forceinline__ MaxIdx row_argmax(const float* logits, int V, MaxIdx*
   return block_argmax(m, shm);
 }
 
+// Clears what lies beyond V where mult leaves mass there: 0 at an infinite temperature, or a negative scale.
+template <int CH>
+__device__ __forceinline__ void reg_clear_rest(int V, float mult, const RegGeom& g, f32x4 (&e)[CH]) {
+  if (mult > 0.f) return;
+#pragma unroll
+  for (int k = 0; k < CH; ++k)
+#pragma unroll
+    for (int i = 0; i < 4; ++i)
+      if (k >= g.R || g.id(k) + i >= V) e[k][i] = 0.f;
+}
+
 // Loads the row once; returns its maximum, sum_j exp(mult l_j - zmax) and e[k] = exp(mult l - zmax) (0 outside V).  What
 // `between` loads is under way while the sum is formed.
 template <int CH, typename F>
@@ -240,11 +251,12 @@ __device__ __forceinline__ void reg_softmax(const float* __restrict__ row, int V
   const float zmax = top * mult;
   float acc = 0.f;
 #pragma unroll
-  for (int k = 0; k < CH; ++k) {
+  for (int k = 0; k < CH; ++k)
 #pragma unroll
     for (int i = 0; i < 4; ++i) e[k][i] = __expf(fmaf(e[k][i], mult, -zmax));
-    acc += (e[k][0] + e[k][1]) + (e[k][2] + e[k][3]);
-  }
+  reg_clear_rest(V, mult, g, e);
+#pragma unroll
+  for (int k = 0; k < CH; ++k) acc += (e[k][0] + e[k][1]) + (e[k][2] + e[k][3]);
   sum = (float)block_sum_d((double)acc, shd);
 }
 
@@ -754,6 +766,7 @@ __device__ __forceinline__ int accept_draw(const float* __restrict__ row, const 
           e[h * H + k][i] = qrow ? fmaxf(p - q[k][i], 0.f) : p;
         }
     }
+    reg_clear_rest(V, mult, g, e);
     double total = 0.0;
     token = reg_draw(e, g, u, 0.0, -1.0, shd, shi, &total);
     if (!qrow || total > 0.0) break;

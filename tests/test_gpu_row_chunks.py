@@ -35,3 +35,28 @@ def test_masked_ids_carry_no_mass(V):
     assert amd.sample_row(row.cuda(), 0.0, 1.0, 0.5)[1] == int(row.argmax())
     row[:] = float("-inf")
     assert amd.sample_row(row.cuda(), 0.0, 1.0, 0.5)[1] == 0
+
+
+@pytest.mark.parametrize("V", [9, 1000, 4096, 8191, 12000, 30001, 40000])
+@pytest.mark.parametrize("temp,scale", [(float("inf"), 1.0), (1.0, -1.0)])
+def test_multipliers_that_are_not_positive(V, temp, scale):
+    """Infinite temperature is the uniform distribution, a negative scale turns a row round; no mass beyond the row."""
+    amd = long_rows._amd()
+    row = synth.normal_tensor((V,), 1.0, 6, V, torch.float32)
+    z = row.double().numpy() * (0.0 if np.isinf(temp) else scale)
+    P = np.exp(z) / np.exp(z).sum()
+    for j in (0, V // 3, V - 1):
+        u = float(np.float32(P[:j].sum() + 0.5 * P[j]))      # the middle of id j's share
+        q, tok = amd.sample_row(row.cuda(), temp, scale, u)
+        np.testing.assert_allclose(q.cpu().numpy(), P, rtol=2e-5, atol=1e-12)
+        assert tok == j
+        assert amd.accept_rows(row[None].cuda(), None, [], [], temp, scale, u) == (0, j)
+    # a rejected draft: what p leaves beside a q that is all at id 1
+    one = torch.zeros(1, V)
+    one[0, 1] = 1.0
+    W = P.copy()
+    W[1] = 0.0
+    W /= W.sum()
+    j = V // 2
+    u = float(np.float32(W[:j].sum() + 0.5 * W[j]))
+    assert amd.accept_rows(row[None].cuda(), one.cuda(), [1], [0.999], temp, scale, u) == (0, j)

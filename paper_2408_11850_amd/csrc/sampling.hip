@@ -165,6 +165,12 @@ __device__ __forceinline__ RegGeom reg_geom(int V) {
 // reciprocal of the sum: relative error below 1e-5 for exponents down to -100, two orders under what the bf16
 // logits carry.  Every kernel of the register path forms p and q with this one expression.
 __device__ __forceinline__ float reg_prob(float l, float mult, float zmax, float inv) { return __expf(fmaf(l, mult, -zmax)) * inv; }
+// max(0, p - q) of the rounded p that a draft's q is compared with: fused with the product behind p, the subtraction would leave
+// the product's rounding error where p and q are the same bits, and a residual without mass would seem to have some.
+__device__ __forceinline__ float residual(float p, float q) {
+#pragma clang fp contract(off)
+  return fmaxf(p - q, 0.f);
+}
 
 // A thread's chunks of a row, `fill` beyond V.  Where no vector straddles the end the loads are unconditional (lanes
 // beyond the end read the last vector): behind branches each would be waited for before the next goes out.
@@ -727,7 +733,7 @@ __global__ __launch_bounds__(SAMP_THREADS) void accept_weights_kernel(const floa
 #pragma unroll
     for (int i = 0; i < 4; ++i) {
       const float pv = long_prob(e[k][i], mult, zmax, sum);
-      e[k][i] = g.id(k) + i < m ? (qrow ? fmaxf(pv - q[k][i], 0.f) : pv) : 0.f;
+      e[k][i] = g.id(k) + i < m ? (qrow ? residual(pv, q[k][i]) : pv) : 0.f;
     }
     store4(wbuf, g.id(k), m, e[k]);
     mine += sum4_d(e[k]);
@@ -736,7 +742,7 @@ __global__ __launch_bounds__(SAMP_THREADS) void accept_weights_kernel(const floa
   if (threadIdx.x == 0) reinterpret_cast<double*>(scratch + accept_sums_at(V))[p] = t;
 }
 
-// The draw over row n in registers: residual weights max(0, p - q) (one rounding of the exact difference), or p itself
+// The draw over row n in registers: residual weights max(0, p - q) (one rounding of the difference of rounded values), or p itself
 // (qrow == nullptr; also where the residual has no mass in floating point).
 template <int CH>
 __device__ __forceinline__ int accept_draw(const float* __restrict__ row, const float* __restrict__ qrow, int V, float mult,
@@ -763,7 +769,7 @@ __device__ __forceinline__ int accept_draw(const float* __restrict__ row, const 
 #pragma unroll
         for (int i = 0; i < 4; ++i) {
           const float p = reg_prob(e[h * H + k][i], mult, zmax, inv);
-          e[h * H + k][i] = qrow ? fmaxf(p - q[k][i], 0.f) : p;
+          e[h * H + k][i] = qrow ? residual(p, q[k][i]) : p;
         }
     }
     reg_clear_rest(V, mult, g, e);

@@ -60,3 +60,17 @@ def test_multipliers_that_are_not_positive(V, temp, scale):
     j = V // 2
     u = float(np.float32(W[:j].sum() + 0.5 * W[j]))
     assert amd.accept_rows(row[None].cuda(), one.cuda(), [1], [0.999], temp, scale, u) == (0, j)
+
+
+# 1, 2, 4 and 8 chunks in registers, and a long row
+@pytest.mark.parametrize("V", [1000, 8192, 16000, 32000, 40000])
+@pytest.mark.parametrize("temp", [1.0, 0.7])
+def test_a_residual_without_mass_falls_back_to_the_target(V, temp):
+    """q is p bit for bit but for a larger value at the draft, which is rejected: max(0, p - q) is 0 everywhere, not what a
+    product loses when it is rounded, so the corrected token is the draw from p."""
+    amd = long_rows._amd()
+    row = synth.normal_tensor((V,), 3.0, 8, V, torch.float32).cuda()
+    for u in (0.0, 0.11, 0.5, 0.83, 1.0 - 2.0 ** -24):
+        q, want = amd.sample_row(row, temp, 1.0, u)
+        q[V // 2] = 2.0
+        assert amd.accept_rows(row[None], q[None], [V // 2], [0.999], temp, 1.0, u) == (0, want)

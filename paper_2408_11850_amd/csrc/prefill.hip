@@ -314,7 +314,7 @@ __global__ __launch_bounds__(DG_THREADS, 1) void dense_gemm_kernel(const bf16* _
 // take whole lines (with a row per lane, 16 bytes of each, X took 0.23 us of a K step instead of 0.13), that loads are issued
 // between MFMAs and that every SIMD has a second wave: 1023 x 4096 x 11008 124 -> 100 us; 511 x 6144 x 2048 28 -> 23 from
 // HBM and 26.4 -> 18 to 19 from the memory-side cache.
-// PN: panels of a tile, 8 (128 outputs) or 6 (96: a wave has 32 x 96, a stage 12 KiB of W), see dense_tile.
+// PN: panels of a tile, 8 (128 outputs) or 6 (96: a wave has 32 x 96, a stage 12 KiB of W), see dense_tile, dense_epi_tile.
 #define DS_WAVES 8
 #define DS_THREADS (DS_WAVES * 64)
 #define DS_STAGES 4
@@ -635,14 +635,28 @@ int dense_tile(int M, int NT, int steps) {
     if (i == 0 || us < best_us) best = i, best_us = us;
   }
   // 128 x 96 where one round of them fills three quarters of the CUs or more and 128 x 128 would be taken (the same round with
-  // fewer, larger tiles): what a CU pulls in per K step falls by an eighth.  Not below 16 K steps, where it is all launch.
+  // fewer, larger tiles): what a CU pulls in per K step falls by an eighth, what all of them pull in together rises by a sixth.  So
+  // it gains while each CU waits for its own loads, and loses where the level they share is the limit.  Not below 16 K steps,
+  // where it is all launch.
   //   us, 128 x 128 | 128 x 96, W from HBM: 511 x 6144 x 2048  23.0 | 22.2     511 x 6144 x 4096  40.1 | 35.7    255 x 12288 x 4096  42.2 | 38.0
   //                                         1023 x 3072 x 2048 21.8 | 20.7     1023 x 3072 x 4096 38.4 | 34.3    400 x 6144 x 2048   19.6 | 19.3
+  //                                         511 x 4608 x 2048 (192 tiles) 21.9 | 20.4   511 x 5376 x 4096 (224) 40.5 | 34.8
   //   two rounds of them gain nothing:      511 x 11264 x 2048 37.0 | 38.4     2047 x 3072 x 2048 38.8 | 39.0
   // The sums are those of 128 x 128 tiles, bit for bit.
   const int narrow = (M + 127) / 128 * ((NT + 5) / 6);
   if (best == DENSE_SMALL && steps >= 16 && narrow <= ncu && 4 * narrow >= 3 * ncu) best = DENSE_NARROW;
   return best;
+}
+
+// With fp32 results 128 x 96 stays out: their stores go to the shared level too, and with operands from the memory-side cache it
+// falls behind (three sets of operands in turn, 128 x 128 | 128 x 96):
+//   fp32: 511 x 6144 x 2048 (256 tiles) 20.22 | 20.47   511 x 6144 x 4096 32.55 | 32.78   1023 x 2688 x 4096 (224) 30.84 | 31.34
+//   bf16: 511 x 6144 x 2048             18.44 | 18.42   511 x 6144 x 4096 31.31 | 31.16   1023 x 2688 x 4096       29.82 | 29.86
+// Prompt passes with them for QKV and gate/up: small pair, 511 tokens through 24 layers 2984 | 2924 us, 7B shape, 255 through 4
+// 653 | 639, 1B draft, 255 through 22 1894 | 1857; weights in that cache (small, 2 layers) 189 | 187.
+int dense_epi_tile(int M, int NT, int steps, int epi) {
+  const int t = dense_tile(M, NT, steps);
+  return t == DENSE_NARROW && (epi == DG_EPI_STORE || epi == DG_EPI_RESID) ? (int)DENSE_SMALL : t;
 }
 
 template <typename F>
@@ -657,7 +671,7 @@ template <int EPI>
 static hipError_t dense_launch_epi(const bf16* x, const u32x4* w, int M, int N, int K, float* y, bf16* z, int ldz,
                                    const DenseRope& ra, hipStream_t st) {
   static bool set[4] = {};
-  const int NT = N / 16, steps = K / 32, tile = dense_tile(M, NT, steps);
+  const int NT = N / 16, steps = K / 32, tile = dense_epi_tile(M, NT, steps, EPI);
   hipError_t e;
   if (tile == DENSE_LARGE) {
     constexpr int lds_bytes = DG_STAGES * DG_STAGE_BYTES;
@@ -671,10 +685,12 @@ static hipError_t dense_launch_epi(const bf16* x, const u32x4* w, int M, int N, 
     const int TM = (M + 127) / 128, TN = (NT + 7) / 8, chunk = (TM * TN + 7) / 8;
     dense_small_kernel<EPI, 8><<<8 * chunk, DS_THREADS, lds_bytes, st>>>(x, w, y, z, M, N, K, ldz, NT, steps, TM, TN, chunk, steps, ra);
   } else if (tile == DENSE_NARROW) {
-    constexpr int lds_bytes = DS_STAGES * DS_STAGE_BYTES(6);
-    if ((e = dense_lds(dense_small_kernel<EPI, 6>, lds_bytes, &set[3])) != hipSuccess) return e;
-    const int TM = (M + 127) / 128, TN = (NT + 5) / 6, chunk = (TM * TN + 7) / 8;
-    dense_small_kernel<EPI, 6><<<8 * chunk, DS_THREADS, lds_bytes, st>>>(x, w, y, z, M, N, K, ldz, NT, steps, TM, TN, chunk, steps, ra);
+    if constexpr (EPI != DG_EPI_STORE && EPI != DG_EPI_RESID) {
+      constexpr int lds_bytes = DS_STAGES * DS_STAGE_BYTES(6);
+      if ((e = dense_lds(dense_small_kernel<EPI, 6>, lds_bytes, &set[3])) != hipSuccess) return e;
+      const int TM = (M + 127) / 128, TN = (NT + 5) / 6, chunk = (TM * TN + 7) / 8;
+      dense_small_kernel<EPI, 6><<<8 * chunk, DS_THREADS, lds_bytes, st>>>(x, w, y, z, M, N, K, ldz, NT, steps, TM, TN, chunk, steps, ra);
+    }
   } else {
     constexpr int lds_bytes = 2 * DW_X_BYTES + 3 * DW_W_BYTES;
     if ((e = dense_lds(dense_wide_kernel<EPI>, lds_bytes, &set[2])) != hipSuccess) return e;
@@ -693,7 +709,7 @@ static hipError_t dense_launch_epi(const bf16* x, const u32x4* w, int M, int N, 
 #define DENSE_SLICES_MAX 16
 int dense_slices(int M, int N, int K) {
   const int ncu = spec_num_cu(), steps = K / 32, tiles = (M + 127) / 128 * ((N + 127) / 128);
-  if (2 * tiles > ncu || dense_tile(M, N / 16, steps) != DENSE_SMALL) return 1;
+  if (2 * tiles > ncu || dense_epi_tile(M, N / 16, steps, DG_EPI_RESID) != DENSE_SMALL) return 1;
   auto time = [&](int S, int slice) { return slice * (0.185f + 0.085f * S * tiles / ncu) + (S > 1 ? 3.f + S * (float)M * N * 4.f / 3e6f : 0.f); };
   int best = 1;
   float best_us = 0.85f * time(1, steps);

@@ -177,9 +177,10 @@ size_t attention_workspace_floats(int Hq, int Hkv, int dh, int max_seq);
 #define SPEC_PREFILL_BLOCK_MAX 4096   // most prompt tokens one dense pass takes
 hipError_t launch_dense_gemm(const bf16* x, const void* wp, int M, int N, int K, int epi, float* y, bf16* z,
                              hipStream_t st, int ldz = 0);   // ldz: row stride of z, 0 = N / 2
-// the tile that launch_dense_gemm takes
+// the tile that launch_dense_gemm takes for a shape, and with the results of an epilogue
 enum { DENSE_LARGE = 0 /* 256 x 256 */, DENSE_SMALL = 1 /* 128 x 128 */, DENSE_WIDE = 2 /* 256 x 192 */, DENSE_NARROW = 3 /* 128 x 96 */ };
 int dense_tile(int M, int NT, int steps);
+int dense_epi_tile(int M, int NT, int steps, int epi);
 // K slices of a prompt projection for launch_norm to add: how many (1: none, call launch_dense_gemm), P[S][M][N], and the floats
 // that hold P for every shape
 int dense_slices(int M, int N, int K);

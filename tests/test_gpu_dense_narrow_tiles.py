@@ -15,7 +15,7 @@ NARROW = 3
 # 256 tiles and 248, 240, 192 of them: whole tiles, one row more than a tile, N that ends two and four panels into a tile;
 # K: 16 steps of 32, odd counts, longer than the ring many times over
 @pytest.mark.parametrize("M,N,K", [(512, 6144, 512), (511, 6144, 2048), (385, 5920, 544), (500, 5888, 608), (129, 9152, 2144), (1023, 3072, 512)])
-@pytest.mark.parametrize("epilogue", [0, 1, 2])
+@pytest.mark.parametrize("epilogue", [0, 1, 2])      # 0 and 1, fp32 results, take 128 x 128 (test_prompt_tiles.py)
 def test_projection(M, N, K, epilogue):
     assert tile(M, N, K - 32 * (K // 32 - 15)) == SMALL          # 15 steps
     check_projection(M, N, K, NARROW, epilogue)

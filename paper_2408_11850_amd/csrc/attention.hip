@@ -16,8 +16,8 @@
 // What bounds it is a chain of latencies: kernel start, page id, K / V, softmax, result (traced; 7B shape, M = 1, 4096
 // positions: 16.0 us for 67 MB, 4.6 the merge; 70B, M = 7: 13.2 + 5.5; with a rotation kernel in front 4.9 + 14.2 + 4.6 and
 // 4.9 + 11.2 + 5.4: the split kernel itself takes 2 us longer, every wave rotates its q, and 3 us per layer are saved).  Up to
-// 1216 positions, with 48 KV heads and more up to 4032, one launch does it all (attn_short_kernel, short_tokens); beyond, a
-// head's few CUs cannot pull the cache fast enough.
+// 1216 positions, with 56 KV heads and more up to 3072, one launch does it all (attn_short_kernel, attention_one_launch_room);
+// beyond, a head's few CUs cannot pull the cache fast enough.
 #include "spec_internal.h"
 
 #define NEG_BIG (-1.0e30f)
@@ -498,15 +498,20 @@ size_t attention_workspace_floats(int Hq, int Hkv, int dh, int max_seq) {
 
 // Most positions of room for which one launch takes the whole range.  It saves a launch and the parts' way through memory, about
 // 5 us per layer, and loses what a head's few CUs pull in more slowly than all of them do: the more heads, the later.  Where the
-// line lies depends on the heads alone, so that the rows of a window do not depend on their number (us with room for 2048,
-// split | whole range, M = 1 unless said otherwise):
-//   2 layers, 56 heads      300 in use 473.6 | 467.3   1100 479.4 | 473.2   1890 485.9 | 479.3   (M = 15: 548.0 | 528.1, 556.8 | 540.2)
-//   4 layers, 32 heads      300 373.1 | 359.7          1100 377.4 | 371.2   1890 384.8 | 381.3   (M = 8: 402.6 | 379.9, 408.8 | 399.8)
-//   12 layers, 16 heads     300 446.5 | 410.1          1100 456.3 | 440.8   1890 457.7 | 469.8
-//   8 layers, 4 of width 64 300 277.3 | 259.2          1100 279.9 | 276.5   1890 283.1 | 294.9
-// With 32 heads it stays at 1216 all the same: beside a draft model's launches its workgroups wait for whole CUs (7B / 1B shapes
-// behind 1024 tokens, step 4583 | 4610 us; with 56 heads 33B / 1B 16040 | 16054).
-static int short_tokens(int Hkv) { return Hkv < 48 ? 1216 : Hkv > 56 ? 4032 : 72 * Hkv; }
+// line lies depends on the heads alone, so that the rows of a window do not depend on their number.  Up to 1216 it is ahead
+// wherever the context stands; from 56 heads on (224 workgroups and more with four to a head) up to 3072.  us per layer of a
+// forward with small projections, split | whole range, positions in use / new tokens:
+//   room for 1216, 16 heads of 128      300/1 24.6 | 21.9   1120/1 26.3 | 25.7   1120/8 29.9 | 28.5   1120/32 48.8 | 40.6
+//                  64 over 8 of 128     300/1 28.5 | 25.5   1120/1 29.0 | 28.2   1120/8 38.6 | 33.0   1120/32 58.9 | 45.0
+//                  8 over 1 of 64       300/1 22.9 | 20.7   1120/1 23.3 | 22.6   1120/8 26.2 | 24.9   1120/32 36.4 | 34.4
+//   room for 4032, 56 heads of 128      2000/1 39.4 | 36.1  3000/1 47.2 | 46.4   3000/17 65.1 | 63.3  3940/1 53.1 | 53.4
+//                  128 over 64 of 64    2000/1 34.7 | 32.5                       2000/32 60.9 | 59.8  3940/17 60.8 | 61.7
+//   fewer heads:   48 of 128            1700/1 36.1 | 33.6  3000/1 41.3 | 44.1   3370/1 44.5 | 47.0
+//                  52 of 128            1700/1 37.3 | 37.9                       3650/1 49.5 | 51.9
+// (12 layers, 16 heads, room for 2048, us a forward: 1100/1 456.3 | 440.8, 1890/1 457.7 | 469.8.)  32 heads, where it would be
+// ahead up to 1890 too (4 layers 384.8 | 381.3), stay at 1216: beside a draft model's launches its workgroups wait for whole CUs
+// (7B / 1B shapes behind 1024 tokens, step 4583 | 4610 us; with 56 heads 33B / 1B level, 15560 to 16190 | 15960 to 16100).
+int attention_one_launch_room(int Hkv) { return Hkv < 56 ? 1216 : 3072; }
 
 // Workgroups that share the columns of a head, from the n that there are without: as many as find a CU each (us per layer against
 // one, 700 positions; 16 heads, n = 16: two -1.3, four -2.0; 56 heads, n = 56: -0.8, -1.4; n = 112: -0.8, +2.2).
@@ -521,7 +526,7 @@ hipError_t launch_attention(const float* y, const float2* tab, bf16* pool, const
   const float scale = 1.0f / sqrtf((float)dh);
   const AttnNew nw = {y, tab};
   // the kernel and the split count are chosen for the longest context, not the current one, so that the launch is replayable
-  if (split_tokens <= short_tokens(Hkv)) {
+  if (split_tokens <= attention_one_launch_room(Hkv)) {
     const int parts = short_parts(Hkv * nrt);
     const dim3 grid(nrt, Hkv, parts), block(SHORT_WAVES * 64);
 #define SHORT_GO(DH, PARTS) \

@@ -172,6 +172,7 @@ hipError_t launch_rope_table(float2* tab, const int* len_ptr, int M, int dh, flo
 hipError_t launch_attention(const float* y, const float2* tab, bf16* pool, const int* block_table, const int* len_ptr,
                             KvGeom g, int layer, int M, int Hq, int split_tokens, float* opart, float* mlpart, bf16* out,
                             hipStream_t st);
+int attention_one_launch_room(int Hkv);   // most positions of room for which a decode attention is one launch
 size_t attention_workspace_floats(int Hq, int Hkv, int dh, int max_seq);
 // prompt-sized (matrix-core bound) kernels: epilogue 0 = store fp32, 1 = add into fp32, 2 = silu(gate)*up -> bf16
 #define SPEC_PREFILL_BLOCK_MAX 4096   // most prompt tokens one dense pass takes

@@ -1,4 +1,6 @@
 """Decode attention in one launch over more than 1216 positions, where there are KV heads enough (run with -m gpu)."""
+import ctypes as C
+
 import pytest
 
 import synth
@@ -10,12 +12,24 @@ from tests.util import gpu_available
 pytestmark = [pytest.mark.gpu, pytest.mark.skipif(not gpu_available(), reason="needs a GPU")]
 
 
-# 48 KV heads: one launch up to room for 3456 positions.  Contexts around the rounds of chunks that a workgroup has in flight (7
+def room(max_seq):
+    """Positions there is room for in the pages of a context."""
+    return (-(-max_seq // 64) + 1) * 64
+
+
+def one_launch_room(kv_heads):
+    import paper_2408_11850_amd as amd
+    amd.load_library()
+    return C.CDLL(amd.LIB_PATH)._Z25attention_one_launch_roomi(kv_heads)
+
+
+# 56 KV heads: one launch up to room for 3072 positions.  Contexts around the rounds of chunks that a workgroup has in flight (7
 # waves, two each: 448 positions), and the last ones there is room for; one part of 16-row tiles more at M = 17
 def test_long_rounds_against_the_oracle():
-    cfg = _custom(synth.ModelShape(2, 256, 48, 48, 512, 1008, head_dim=64), 1)
+    cfg = _custom(synth.ModelShape(2, 256, 56, 56, 512, 1008, head_dim=64), 1)
     cfg.n_prompt = 2100
     amd, ctx, tm, _ = _setup(cfg, gamma_max=31)
+    assert 1216 < room(2100 + 64 + 64) <= one_launch_room(56)
     ids = synth.prompt_tokens(2200, 1008, 7).tolist()
     ocm = transformer.CachedModel(tm, 2304)
     fed = 0
@@ -32,7 +46,10 @@ def test_long_rounds_against_the_oracle():
     ctx.close()
 
 
-# rows share their bits on both sides of the line: 48 heads in one launch, 32 in one (room for 1216 positions) and split (1280)
-@pytest.mark.parametrize("heads,max_seq", [(48, 2240), (32, 1152), (32, 1153)])
-def test_rows_keep_their_bits(heads, max_seq):
+# rows share their bits on both sides of the lines: 56 heads in one launch (room for 2304 and 3072 positions) and split (3136),
+# 48 and 32 in one (1216) and split (1280)
+@pytest.mark.parametrize("heads,max_seq,one", [(56, 2240, True), (56, 3008, True), (56, 3009, False), (48, 1152, True),
+                                               (48, 1153, False), (32, 1152, True), (32, 1153, False)])
+def test_rows_keep_their_bits(heads, max_seq, one):
+    assert (room(max_seq) <= one_launch_room(heads)) == one
     assert_rows_share_their_bits(synth.ModelShape(2, 256, heads, heads, 512, 1008, head_dim=64), max_seq, (300, max_seq - 20))

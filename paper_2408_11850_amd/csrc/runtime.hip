@@ -118,6 +118,35 @@ struct spec_ctx {
   ProfStamps prof;
 };
 
+// Which of two overlapped chains has its projections' waves issue first on a CU (s_setprio; no sum depends on it): the draft's by
+// default.  Beside a target whose long ranges keep a CU's memory queue full its short kernels waited for their turn at every
+// load: a draft forward inside a step took 10.5 ms (3.1 alone) and the step 42.1 ms, with priority 5.2 and 40.7 (70B / 7B shapes,
+// windows of 7).  Where the target's kernels are short too (below 200 MB a layer; 103 MB in the small pair, 405 in 7B) neither
+// starves, and it is the chain that ends later that should not wait: with r = gamma draft passes over a target pass, both
+// estimated from their bytes and five launches a layer, us per step with the draft | neither | the target in front:
+//   24 / 4 layers, gamma 4, r 0.82  1169 | 1134 | 1112     12 / 4, gamma 2, 0.78  586 | 564 | 556    16 / 1, gamma 3, 0.38  663 | 659 | 642
+//   24 / 2, gamma 8, 1.00           1286 | 1227 | 1234     24 / 3, gamma 6, 0.99  1340 | 1286 | 1288    24 / 4, gamma 5, 1.02  1257 | 1219 | 1261
+//   20 / 4, gamma 6, 1.46           1299 | 1338 | 1375     12 / 4, gamma 8, 3.1   1572 | 1610 | 1642
+//   16 / 3 of d_model 2560 (158 MB a layer), gamma 2, r 0.47  931 | 909 | 886    gamma 4, 0.94  1134 | 1084 | 1110    gamma 6, 1.42  1379 | 1403 | 1478
+//   beyond the line: 16 / 3 of 3072 (226 MB), gamma 2  1168 | 1141 | 1113    gamma 4  1451 | 1381 | 1420    gamma 6  1778 | 1761 | 1873
+//   7B / 1B, gamma 2, target the longer chain by far: 3421 | 3506 | 3504
+// A context takes the choice for its gamma_max; a PEARL loop takes the one for its window and a concurrent calibration the one
+// for the window it finds, each for as long as it runs.
+int favoured_chain(const spec_model_desc& t, const spec_model_desc& d, int gamma) {
+  auto layer_bytes = [](const spec_model_desc& d) {
+    return 2.0 * d.d_model * (2.0 * (d.n_heads + d.n_kv_heads) * d.head_dim + 3.0 * d.d_ffn);
+  };
+  auto pass_us = [&](const spec_model_desc& d) {
+    return d.n_layers * (15.0 + layer_bytes(d) / 6.5e6) + 2.0 * d.vocab * d.d_model / 6.5e6 + 15.0;
+  };
+  const double r = gamma * pass_us(d) / pass_us(t);
+  if (layer_bytes(t) >= 200e6) return SPEC_DRAFT;
+  return r < 0.95 ? SPEC_TARGET : r > 1.2 ? SPEC_DRAFT : -1;
+}
+int favoured_now(const spec_ctx* c) {
+  return c->m[SPEC_TARGET].raised ? SPEC_TARGET : c->m[SPEC_DRAFT].raised ? SPEC_DRAFT : -1;
+}
+
 namespace {
 
 inline int slot_of(const spec_ctx* c, int i /* 1-based draft index */) { return (c->ring_base + i - 1) % c->ring_n; }
@@ -272,29 +301,23 @@ int run_proj(spec_ctx* c, int which, ModelRt& m, const ProjPlan& p, ProjArgs a) 
   return SPEC_OK;
 }
 
-// Which of two overlapped chains has its projections' waves issue first on a CU (s_setprio; no sum depends on it): the draft's by
-// default.  Beside a target whose long ranges keep a CU's memory queue full its short kernels waited for their turn at every
-// load: a draft forward inside a step took 10.5 ms (3.1 alone) and the step 42.1 ms, with priority 5.2 and 40.7 (70B / 7B shapes,
-// windows of 7).  Where the target's kernels are short too (below 200 MB a layer; 103 MB in the small pair, 405 in 7B) neither
-// starves, and it is the chain that ends later that should not wait: with r = gamma draft passes over a target pass, both
-// estimated from their bytes and five launches a layer, us per step with the draft | neither | the target in front:
-//   24 / 4 layers, gamma 4, r 0.82  1169 | 1134 | 1112     12 / 4, gamma 2, 0.78  586 | 564 | 556    16 / 1, gamma 3, 0.38  663 | 659 | 642
-//   24 / 2, gamma 8, 1.00           1286 | 1227 | 1234     24 / 3, gamma 6, 0.99  1340 | 1286 | 1288    24 / 4, gamma 5, 1.02  1257 | 1219 | 1261
-//   20 / 4, gamma 6, 1.46           1299 | 1338 | 1375     12 / 4, gamma 8, 3.1   1572 | 1610 | 1642
-//   7B / 1B, gamma 2, target the longer chain by far: 3421 | 3506 | 3504
 void favour(spec_ctx* c, int gamma) {
-  auto layer_bytes = [](const spec_model_desc& d) {
-    return 2.0 * d.d_model * (2.0 * (d.n_heads + d.n_kv_heads) * d.head_dim + 3.0 * d.d_ffn);
-  };
-  auto pass_us = [&](const spec_model_desc& d) {
-    return d.n_layers * (15.0 + layer_bytes(d) / 6.5e6) + 2.0 * d.vocab * d.d_model / 6.5e6 + 15.0;
-  };
-  const spec_model_desc &t = c->m[SPEC_TARGET].d, &d = c->m[SPEC_DRAFT].d;
-  const double r = gamma * pass_us(d) / pass_us(t);
-  const bool brief = layer_bytes(t) < 200e6;
-  c->m[SPEC_TARGET].raised = brief && r < 0.95;
-  c->m[SPEC_DRAFT].raised = !brief || r > 1.2;
+  const int which = favoured_chain(c->m[SPEC_TARGET].d, c->m[SPEC_DRAFT].d, gamma);
+  c->m[SPEC_TARGET].raised = which == SPEC_TARGET;
+  c->m[SPEC_DRAFT].raised = which == SPEC_DRAFT;
 }
+
+// How forwards launch outside a loop or a calibration is put back on every way out of one, errors included.
+struct LaunchGuard {
+  spec_ctx* c;
+  int wgs;
+  bool raised[2];
+  explicit LaunchGuard(spec_ctx* c) : c(c), wgs(c->wgs), raised{c->m[0].raised, c->m[1].raised} {}
+  ~LaunchGuard() {
+    c->wgs = wgs;
+    for (int w = 0; w < 2; ++w) c->m[w].raised = raised[w];
+  }
+};
 
 // Whether the projection of the normalised residual stream (QKV, gate/up, LM head) runs in K slices.  Only where it is
 // narrower than a panel per CU and takes more than 8 tokens (three layers of d_model 8192, QKV 768, gate/up 2048, vocabulary
@@ -1051,12 +1074,7 @@ extern "C" int spec_generate(spec_ctx* c, int algo, int gamma, int n_generate, i
     FAIL(SPEC_E_STATE, "%d unverified drafts pending do not fit a window of %d", c->n_drafted, gamma);
   const int k_guess = (c->guess_opt < 0 || c->guess_opt > gamma - 1) ? gamma - 1 : c->guess_opt;
   const int g1 = gamma + 1;
-  // the launch mode is put back on every way out of the loop, errors included
-  struct WgsGuard {
-    spec_ctx* c;
-    int saved;
-    ~WgsGuard() { c->wgs = saved; }
-  } wgs_guard{c, c->wgs};
+  LaunchGuard launch_guard(c);
   // while the two streams overlap, one projection workgroup per CU and stream from gamma 6 on (long draft chains), two per CU
   // below that.  The line was measured with K-sliced projections on the 70B/7B-shape pair (42.4 ms per step of gamma 7 against
   // 44); with whole-K ones and the draft's wave priority the modes are level there: the later chain ends at 41.0 ms with one,
@@ -1234,11 +1252,7 @@ extern "C" int spec_calibrate_gamma(spec_ctx* c, int n_iter, int cap, int concur
   int nd = n_iter < c->ring_n ? n_iter : c->ring_n;
   if (nd > room_d) nd = room_d;
   if (nt < 1 || nd < 1) FAIL(SPEC_E_NOMEM, "no room in the caches for a timed forward");
-  struct WgsGuard {
-    spec_ctx* c;
-    int saved;
-    ~WgsGuard() { c->wgs = saved; }
-  } wgs_guard{c, c->wgs};
+  LaunchGuard launch_guard(c);
   if (concurrent && c->wgs_opt < 0) c->wgs = SPEC_PEARL_WGS_PER_CU;
   TokenSrc src;
   src.n = 1;
@@ -1261,9 +1275,19 @@ extern "C" int spec_calibrate_gamma(spec_ctx* c, int n_iter, int cap, int concur
     return code;
   };
   // untimed: the first forward of a shape also captures its graphs
-  if ((rc = forward(c, SPEC_TARGET, src, 1))) return fail(rc);
-  if ((rc = spec_draft_step(c, 0.5f, nullptr))) return fail(rc);
-  if ((rc = restore())) return rc;
+  auto untimed = [&]() -> int {
+    int r2;
+    if ((r2 = forward(c, SPEC_TARGET, src, 1))) return fail(r2);
+    if ((r2 = spec_draft_step(c, 0.5f, nullptr))) return fail(r2);
+    return restore();
+  };
+  if ((rc = untimed())) return rc;
+  auto window = [&](double t_target, double t_draft) {      // gamma = round(c)
+    int g = (int)((t_draft > 0 ? t_target / t_draft : (double)cap) + 0.5);
+    if (g < 1) g = 1;
+    if (g > cap) g = cap;
+    return g > c->cfg.gamma_max ? c->cfg.gamma_max : g;
+  };
   using clk = std::chrono::steady_clock;
   double tp = 0.0, tq = 0.0;
   if (!concurrent) {
@@ -1321,16 +1345,18 @@ extern "C" int spec_calibrate_gamma(spec_ctx* c, int n_iter, int cap, int concur
       A = nt < 2 ? nt : 2;
       long long want = (long long)(A * tp / (tq > 0 ? tq : 1e-9) + 0.5);
       B = (int)(want < 1 ? 1 : (want > nd ? nd : want));
+      // ... with the chain in front that a loop of this window puts there
+      const bool was[2] = {mt.raised, md.raised};
+      if (round == 0) favour(c, window(tp, tq));
+      if ((mt.raised != was[0] || md.raised != was[1]) && (rc = untimed())) {
+        destroy();
+        return rc;
+      }
     }
     destroy();
   }
   if ((rc = restore())) return rc;
-  double cc = tq > 0 ? tp / tq : (double)cap;
-  int g = (int)(cc + 0.5);
-  if (g < 1) g = 1;
-  if (g > cap) g = cap;
-  if (g > c->cfg.gamma_max) g = c->cfg.gamma_max;
-  *gamma_out = g;
+  *gamma_out = window(tp, tq);
   *t_target_s = tp;
   *t_draft_s = tq;
   return SPEC_OK;

@@ -219,4 +219,9 @@ hipError_t launch_accept(const float* logits, int V, float mult, int greedy, con
                          const int* x_direct, AcceptArgs a, float* scratch, AcceptResult* result_dev,
                          hipStream_t st, int* out2 = nullptr);
 
+// Which of two overlapped chains issues first for windows of gamma, SPEC_TARGET, SPEC_DRAFT or -1 (neither): the rule, and what
+// the next forwards of a context launch with
+int favoured_chain(const spec_model_desc& target, const spec_model_desc& draft, int gamma);
+int favoured_now(const spec_ctx* c);
+
 void spec_set_error(const char* fmt, ...);

@@ -69,7 +69,7 @@ __device__ __forceinline__ f32x4 proj_sum(const f32x4* red, int lane) {
   return t;
 }
 
-template <int MODE, int MT, int RP, int D, int EPI, int PRIO>
+template <int MODE, int MT, int RP, int D, int EPI, bool FIRST>
 __global__ __launch_bounds__(PROJ_THREADS, RP * MT > 4 ? 2 : 4) void proj_kernel(ProjArgs a) {
   static_assert(MODE == PROJ_FULL || MT == 1, "two row tiles only with one token per column");
   static_assert(MODE != PROJ_HALF || RP == (EPI == PROJ_SWIGLU ? 2 : 1), "half panels are taken one unit at a time");
@@ -80,7 +80,7 @@ __global__ __launch_bounds__(PROJ_THREADS, RP * MT > 4 ? 2 : 4) void proj_kernel
   __shared__ f32x4 red[NBUF][PROJ_WAVES][RP][MT][64];
   __shared__ float inv_sh[SPEC_MAX_TOKENS];
   // Of two overlapped chains the favoured one issues first (runtime.hip, favour), from its first instruction on.
-  if (PRIO == 1) __builtin_amdgcn_s_setprio(3);
+  if (FIRST) __builtin_amdgcn_s_setprio(3);
   const int w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), lane = threadIdx.x & 63;
   const int c = lane & 15, kb = lane >> 4;
   if (a.stamp && threadIdx.x == 0)
@@ -451,12 +451,12 @@ bool proj_plan_ok(const ProjPlan& p) {
   return false;
 }
 
-template <int EPI, int PRIO>
+template <int EPI, bool FIRST>
 static hipError_t launch_epi(const ProjPlan& p, const ProjArgs& a, hipStream_t st) {
   dim3 g(p.G), b(PROJ_THREADS);
 #define PROJ_GO(MODE, MT, RP, D)                                    \
   {                                                                 \
-    proj_kernel<MODE, MT, RP, D, EPI, PRIO><<<g, b, 0, st>>>(a);     \
+    proj_kernel<MODE, MT, RP, D, EPI, FIRST><<<g, b, 0, st>>>(a);    \
     return hipGetLastError();                                       \
   }
   constexpr int SW = EPI == PROJ_SWIGLU ? 2 : 1;
@@ -486,19 +486,16 @@ static hipError_t launch_epi(const ProjPlan& p, const ProjArgs& a, hipStream_t s
   return hipErrorInvalidValue;      // nothing was launched
 }
 
-template <int PRIO>
-static hipError_t launch_prio(const ProjPlan& p, const ProjArgs& a, hipStream_t st) {
-  if (p.epi == PROJ_STORE) return launch_epi<PROJ_STORE, PRIO>(p, a, st);
-  if (p.epi == PROJ_RESID) return launch_epi<PROJ_RESID, PRIO>(p, a, st);
-  return launch_epi<PROJ_SWIGLU, PRIO>(p, a, st);
+template <bool FIRST>
+static hipError_t launch_first(const ProjPlan& p, const ProjArgs& a, hipStream_t st) {
+  if (p.epi == PROJ_STORE) return launch_epi<PROJ_STORE, FIRST>(p, a, st);
+  if (p.epi == PROJ_RESID) return launch_epi<PROJ_RESID, FIRST>(p, a, st);
+  return launch_epi<PROJ_SWIGLU, FIRST>(p, a, st);
 }
 
-hipError_t launch_proj(const ProjPlan& p, ProjArgs a, hipStream_t st, int prio) {
+hipError_t launch_proj(const ProjPlan& p, ProjArgs a, hipStream_t st, bool first) {
   if (!proj_plan_ok(p)) return hipErrorInvalidValue;
   a.M = p.M; a.N = p.N; a.K = p.K; a.steps = p.steps;
   a.per = p.units / p.G; a.rem = p.units % p.G;
-  if (prio == 0) return launch_prio<0>(p, a, st);
-  if (prio == 1) return launch_prio<1>(p, a, st);
-  if (p.epi != PROJ_STORE) return hipErrorInvalidValue;      // stand-alone calls store
-  return launch_epi<PROJ_STORE, 2>(p, a, st);
+  return first ? launch_first<true>(p, a, st) : launch_first<false>(p, a, st);
 }

@@ -514,7 +514,9 @@ size_t attention_workspace_floats(int Hq, int Hkv, int dh, int max_seq) {
 int attention_one_launch_room(int Hkv) { return Hkv < 56 ? 1216 : 3072; }
 
 // Workgroups that share the columns of a head, from the n that there are without: as many as find a CU each (us per layer against
-// one, 700 positions; 16 heads, n = 16: two -1.3, four -2.0; 56 heads, n = 56: -0.8, -1.4; n = 112: -0.8, +2.2).
+// one, 700 positions; 16 heads, n = 16: two -1.3, four -2.0; 56 heads, n = 56: -0.8, -1.4; n = 112: -0.8, +2.2).  That is for a
+// forward that has the GPU to itself.  Beside a draft model's launches the parts of 32 heads gain nothing (7B / 1B shapes behind 600
+// tokens, windows of 4, us per step: one part 4492, four 4544, splits and their merge 4548).
 static int short_parts(int n) { return 4 * n <= spec_num_cu() ? 4 : 2 * n <= spec_num_cu() ? 2 : 1; }
 
 hipError_t launch_attention(const float* y, const float2* tab, bf16* pool, const int* block_table, const int* len_ptr,

@@ -11,7 +11,7 @@ pytestmark = [pytest.mark.gpu, pytest.mark.skipif(not gpu_available(), reason="n
 
 
 # heads, KV heads, head_dim; contexts around a chunk (32), a page (64), a round of the one-launch kernel (7 chunks); new
-# tokens around a row tile (16) and over a page boundary.  A context of room for more than 1024 tokens takes the split
+# tokens around a row tile (16) and over a page boundary.  A context of room for more than 1216 tokens takes the split
 # kernel, whatever it holds.
 @pytest.mark.parametrize("heads,kv,dh", [(4, 4, 128), (8, 2, 64), (8, 1, 128)])
 @pytest.mark.parametrize("room", [0, 1100])

@@ -25,7 +25,7 @@ def assert_rows_share_their_bits(s, max_seq, lengths):
     ctx.close()
 
 
-# the attention, behind narrow projections: room for 320 .. 1024 positions with any grouping, for more with up to 16 query rows
+# the attention, behind narrow projections: room for 320 .. 1024 positions with any grouping, for 1280 with up to 16 query rows
 # (there the split count follows the number of 16-row tiles)
 @pytest.mark.parametrize("heads,kv,dh,max_seq", [(h, k, d, n) for n in (256, 448, 900, 1200)
                                                  for h, k, d in ((2, 2, 128), (4, 2, 64), (8, 1, 128)) if n < 1024 or h <= 2 * k])

@@ -26,13 +26,15 @@ def model(s, seed, poison=None):
     return amd.pack_model(s, tensor)
 
 
-# room for 320, 512, 1024 and 1088 positions: each kernel that a context's room chooses.  Behind the poisoned token every
+# room for 320, 512, 1024, 1088 and 1280 positions: each kernel that a context's room chooses, splits in the last.  Behind the poisoned token every
 # position holds NaN; the second prompt fills whole chunks of 32 (64 positions), so that nothing stale lies among its own, or
 # none at all
-@pytest.mark.parametrize("max_seq", [256, 448, 960, 1024])
+@pytest.mark.parametrize("max_seq", [256, 448, 960, 1024, 1153])
 @pytest.mark.parametrize("heads,kv,dh", [(2, 2, 128), (8, 1, 64)])
 def test_a_poisoned_prompt_does_not_reach_the_next_one(max_seq, heads, kv, dh):
     import paper_2408_11850_amd as amd
+    from tests.test_gpu_attention_room import one_launch_room, room
+    assert (room(max_seq) > one_launch_room(kv)) == (max_seq == 1153)
     s = synth.ModelShape(2, 256, heads, kv, 512, 1008, head_dim=dh)
     m = model(s, 3, poison=5)
     ids = [i if i != 5 else 6 for i in synth.prompt_tokens(max_seq, s.vocab, 7).tolist()]

@@ -493,9 +493,10 @@ static hipError_t launch_first(const ProjPlan& p, const ProjArgs& a, hipStream_t
   return launch_epi<PROJ_SWIGLU, FIRST>(p, a, st);
 }
 
-hipError_t launch_proj(const ProjPlan& p, ProjArgs a, hipStream_t st, bool first) {
+hipError_t launch_proj(const ProjPlan& p, ProjArgs a, hipStream_t st, int prio) {
   if (!proj_plan_ok(p)) return hipErrorInvalidValue;
   a.M = p.M; a.N = p.N; a.K = p.K; a.steps = p.steps;
   a.per = p.units / p.G; a.rem = p.units % p.G;
-  return first ? launch_first<true>(p, a, st) : launch_first<false>(p, a, st);
+  if (prio == 2 && p.epi != PROJ_STORE) return hipErrorInvalidValue;      // stand-alone calls store
+  return prio == 1 ? launch_first<true>(p, a, st) : launch_first<false>(p, a, st);
 }

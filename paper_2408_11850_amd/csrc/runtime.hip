@@ -297,7 +297,7 @@ int prof_slot(spec_ctx* c, double bytes, unsigned long long** slot) {
 int run_proj(spec_ctx* c, int which, ModelRt& m, const ProjPlan& p, ProjArgs a) {
   int rc;
   if ((c->profile_flags & 1) && which == SPEC_TARGET && (rc = prof_slot(c, (double)p.weight_bytes(), &a.stamp))) return rc;
-  HIPCHK(launch_proj(p, a, m.stream, m.raised));
+  HIPCHK(launch_proj(p, a, m.stream, m.raised ? 1 : 0));
   return SPEC_OK;
 }
 
@@ -1416,7 +1416,7 @@ extern "C" int spec_gemm(float* y, const void* x, const void* w, int M, int N, i
   if (gemm_whole_k(x, w, M, N, K)) {
     ProjArgs a = {};
     a.x = (const bf16*)x; a.w = w; a.y = y;
-    HIPCHK(launch_proj(proj_plan(M, N, K, PROJ_STORE, 2), a, (hipStream_t)stream, false));
+    HIPCHK(launch_proj(proj_plan(M, N, K, PROJ_STORE, 2), a, (hipStream_t)stream, 2));
     return SPEC_OK;
   }
   if ((rc = spec_gemm_partials(x, w, M, N, K, work, stream))) return rc;

@@ -107,8 +107,8 @@ struct ProjArgs {
   int per, rem;                // ... units per workgroup; the first `rem` take one more
 };
 bool proj_plan_ok(const ProjPlan& p);     // whether a kernel is built for it
-// first: its waves issue ahead of others' on a CU
-hipError_t launch_proj(const ProjPlan& p, ProjArgs a, hipStream_t st, bool first);
+// prio: 0 = as any kernel, 1 = its waves issue ahead of others' on a CU, 2 = a stand-alone call (STORE only), as 0
+hipError_t launch_proj(const ProjPlan& p, ProjArgs a, hipStream_t st, int prio);
 
 // What a whole-K projection's STORE / SWIGLU epilogue does, from K slices: y = sum of the S slices * 1 / rms(row) with the
 // scaling of ProjArgs (ssq, ssq_w, eps; K columns), to a.y, or bf16(silu(gate) * up) to a.xo

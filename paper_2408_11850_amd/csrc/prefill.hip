@@ -638,10 +638,12 @@ int dense_tile(int M, int NT, int steps) {
   // fewer, larger tiles): what a CU pulls in per K step falls by an eighth, what all of them pull in together rises by a sixth.  So
   // it gains while each CU waits for its own loads, and loses where the level they share is the limit.  Not below 16 K steps,
   // where it is all launch.
-  //   us, 128 x 128 | 128 x 96, W from HBM: 511 x 6144 x 2048  23.0 | 22.2     511 x 6144 x 4096  40.1 | 35.7    255 x 12288 x 4096  42.2 | 38.0
-  //                                         1023 x 3072 x 2048 21.8 | 20.7     1023 x 3072 x 4096 38.4 | 34.3    400 x 6144 x 2048   19.6 | 19.3
-  //                                         511 x 4608 x 2048 (192 tiles) 21.9 | 20.4   511 x 5376 x 4096 (224) 40.5 | 34.8
-  //   two rounds of them gain nothing:      511 x 11264 x 2048 37.0 | 38.4     2047 x 3072 x 2048 38.8 | 39.0
+  //   us, 128 x 128 | 128 x 96, bf16 results, W from HBM:
+  //     256 tiles: 511 x 6144 x 2048  21.1 | 19.9   511 x 6144 x 4096  38.9 | 34.1   255 x 12288 x 4096 40.7 | 36.5
+  //                1023 x 3072 x 2048 20.2 | 19.1   1023 x 3072 x 4096 37.0 | 32.4   400 x 6144 x 2048  18.1 | 18.0
+  //     224, 192:  511 x 5376 x 2048  20.6 | 19.1   511 x 5376 x 4096  38.8 | 33.2   511 x 4608 x 2048  20.4 | 19.0
+  //   a single W in the memory-side cache: 511 x 6144 x 2048 16.8 | 17.1   511 x 6144 x 4096 28.9 | 28.3   255 x 12288 x 4096 28.7 | 29.6
+  //   two rounds of them gain nothing (fp32): 511 x 11264 x 2048 37.0 | 38.4     2047 x 3072 x 2048 38.8 | 39.0
   // The sums are those of 128 x 128 tiles, bit for bit.
   const int narrow = (M + 127) / 128 * ((NT + 5) / 6);
   if (best == DENSE_SMALL && steps >= 16 && narrow <= ncu && 4 * narrow >= 3 * ncu) best = DENSE_NARROW;

@@ -79,7 +79,7 @@ __global__ __launch_bounds__(PROJ_THREADS, RP * MT > 4 ? 2 : 4) void proj_kernel
   constexpr int NBUF = RP * MT <= 4 ? 2 : 1;            // two reduction buffers while they fit: one barrier per group
   __shared__ f32x4 red[NBUF][PROJ_WAVES][RP][MT][64];
   __shared__ float inv_sh[SPEC_MAX_TOKENS];
-  // Of two overlapped chains the favoured one issues first (runtime.hip, favour), from its first instruction on.
+  // Of two overlapped chains the favoured one issues first (runtime.hip, favoured_chain), from its first instruction on.
   if (FIRST) __builtin_amdgcn_s_setprio(3);
   const int w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), lane = threadIdx.x & 63;
   const int c = lane & 15, kb = lane >> 4;
